@@ -145,15 +145,25 @@ __device__ __forceinline__ void stage_graph(const DevGraph *g, LdsGraph &L) {
     __syncthreads();
 }
 
-// Copy the first `bytes` (a multiple of 16) of the host-built LDS image: the
-// tree kernel keeps only that prefix (kTreeLdsBytes) in LDS.
-__device__ __forceinline__ void stage_graph_prefix(const DevGraph *g, unsigned char *dst_raw, size_t bytes) {
+// Copy the first `bytes` (a multiple of 16) of the host-built LDS image.
+__device__ __forceinline__ void stage_graph_prefix(const DevGraph *g, LdsGraph &L, size_t bytes) {
     const uint4 *src = reinterpret_cast<const uint4 *>(&g->lds);
-    uint4 *dst = reinterpret_cast<uint4 *>(dst_raw);
+    uint4 *dst = reinterpret_cast<uint4 *>(&L);
     for (uint32_t i = threadIdx.x; i < bytes / 16; i += blockDim.x) dst[i] = src[i];
+}
+
+// What a tree join's level kernel reads of the image: not the neighbour
+// tables, and no selectivities beyond those of n - 1 <= 31 edges.
+__device__ __forceinline__ void stage_graph_tree(const DevGraph *g, LdsGraph &L) {
+    constexpr uint32_t kHead = (offsetof(LdsGraph, sel) + 8 * 32) / 16, kTail = offsetof(LdsGraph, ch) / 16;
+    const uint4 *src = reinterpret_cast<const uint4 *>(&g->lds);
+    uint4 *dst = reinterpret_cast<uint4 *>(&L);
+    for (uint32_t i = threadIdx.x; i < kHead + sizeof(LdsGraph) / 16 - kTail; i += blockDim.x) {
+        const uint32_t j = i < kHead ? i : i - kHead + kTail;
+        dst[j] = src[j];
+    }
     __syncthreads();
 }
-static_assert(kTreeLdsBytes % 16 == 0, "the tree prefix is copied in 16-byte units");
 
 // Memo index of T: level offset plus colex rank.
 __device__ __forceinline__ uint64_t memo_index(const LdsGraph &L, uint32_t T) {

@@ -33,7 +33,7 @@ uint64_t binom64(uint32_t a, uint32_t b) {
 }
 
 struct Layout {
-    size_t cost, card, left, op, list, heavy, parts, graph, counters, plan, root, total;
+    size_t cost, card, left, op, list, heavy, parts, arrived, tally, graph, counters, plan, root, total;
 };
 
 Layout make_layout(uint32_t n) {
@@ -46,7 +46,9 @@ Layout make_layout(uint32_t n) {
     L.op = o;       o = align_up(o + N);
     L.list = o;     o = align_up(o + 4 * binom64(n, n / 2));
     L.heavy = o;    o = align_up(o + 4 * binom64(n, n / 2));
-    L.parts = o;    o = align_up(o + sizeof(mpdp::HeavyPart) * mpdp::kHeavyGrid);
+    L.parts = o;    o = align_up(o + sizeof(mpdp::HeavyPart) * mpdp::kPairWaves);
+    L.arrived = o;  o = align_up(o + sizeof(uint32_t) * mpdp::kPairWaves);
+    L.tally = o;    o = align_up(o + 2 * sizeof(unsigned long long) * mpdp::kPairGrid);
     L.graph = o;    o = align_up(o + sizeof(DevGraph));
     L.counters = o; o = align_up(o + sizeof(Counters));
     L.plan = o;     o = align_up(o + sizeof(mpdp_plan_node) * 64);
@@ -356,6 +358,8 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     uint32_t *list = reinterpret_cast<uint32_t *>(base + L.list);
     uint32_t *heavy = reinterpret_cast<uint32_t *>(base + L.heavy);
     mpdp::HeavyPart *parts = reinterpret_cast<mpdp::HeavyPart *>(base + L.parts);
+    uint32_t *arrived = reinterpret_cast<uint32_t *>(base + L.arrived);
+    unsigned long long *tally = reinterpret_cast<unsigned long long *>(base + L.tally);
     DevGraph *dg = reinterpret_cast<DevGraph *>(base + L.graph);
     Counters *cnt = reinterpret_cast<Counters *>(base + L.counters);
     mpdp_plan_node *dplan = reinterpret_cast<mpdp_plan_node *>(base + L.plan);
@@ -376,6 +380,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     if (no_alloc && down_bytes > sizeof(down_stack)) return MPDP_ETOOLARGE;
     char *pin = no_alloc ? nullptr : pinned_staging(sizeof(DevGraph) > down_bytes ? sizeof(DevGraph) : down_bytes);
     const bool general = force_general || !q.is_tree;
+    const bool dpsub = hg->ablate != 0u;  // force_general comes with it
     // unfused-prune ablation (tree joins): room for every pair key and set
     // record of the widest level
     const bool unfused = !general && (flags & MPDP_FLAG_ABLATE_UNFUSED_PRUNE) != 0;
@@ -405,14 +410,17 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     auto enqueue = [&](hipStream_t st) -> hipError_t {
         hipError_t e = hipMemcpyAsync(dg, pin ? static_cast<const void *>(pin) : static_cast<const void *>(&q.g),
                                       sizeof(DevGraph), hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = mpdp::launch_init(dg, n, memo, cnt, st);
+        if (e == hipSuccess) e = mpdp::launch_init(dg, n, memo, general && !dpsub ? list : nullptr, arrived, tally, cnt, st);
         for (uint32_t k = 2; k <= n && e == hipSuccess; ++k) {
             const uint64_t nc = binom64(n, k);
             if (timing) e = hipEventRecord(ev.ev[4 * k - 8], st);
-            if (e == hipSuccess && general) e = mpdp::launch_filter(dg, k, nc, list, cnt, st);
+            if (e == hipSuccess && dpsub) e = mpdp::launch_filter(dg, k, nc, list, cnt, st);
             if (e == hipSuccess && timing) e = hipEventRecord(ev.ev[4 * k - 7], st);
             if (e != hipSuccess) break;
-            if (general)
+            if (general && !dpsub)  // lists of connected sets: odd levels in one buffer, even ones in the other
+                e = mpdp::launch_level_pairs(dg, q.cost_model, n, k, (k & 1u) ? heavy : list, (k & 1u) ? list : heavy,
+                                             cnt, memo, parts, arrived, tally, st);
+            else if (dpsub)
                 e = mpdp::launch_eval_general(dg, q.cost_model, k, nc, list, heavy, cnt, memo, parts, st);
             else if (unfused)  // ablation: evaluate writes every pair's key, prune reduces
                 e = mpdp::launch_level_tree_unfused(dg, q.cost_model, k, nc, q.g.flat != 0, cnt, memo, ukeys, urecs,
@@ -422,7 +430,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
                                             q.g.flat != 0, cnt, memo, st);
             if (e == hipSuccess && timing) e = hipEventRecord(ev.ev[4 * k - 6], st);
         }
-        if (e == hipSuccess) e = mpdp::launch_extract(dg, n, memo, dplan, droot, cnt, st);
+        if (e == hipSuccess) e = mpdp::launch_extract(dg, n, memo, dplan, droot, general && !dpsub ? tally : nullptr, cnt, st);
         // counters, plan and root cost are adjacent in the workspace: one copy back
         if (e == hipSuccess) e = hipMemcpyAsync(down, cnt, down_bytes, hipMemcpyDeviceToHost, st);
         return e;

@@ -15,31 +15,30 @@ constexpr int kMaxRel = 32;
 
 // Per-workgroup copy of the query information, laid out on the host exactly
 // as the kernels keep it in LDS so that staging is a plain 16-byte copy.
-// The tree kernel reads only a prefix (kTreeLdsBytes: everything before the
-// selectivity rows, plus the rows of a tree's n - 1 <= 31 edges), so the
-// selectivity rows and the neighbour tables, which only the block-based
-// kernels read in full, come last.
+// The kernels that work on lists of connected sets read only the prefix
+// before the binomials (kListLdsBytes).
 struct LdsImage {
     uint64_t loff[34];                        // memo offset of level k: sum of C(n, j), j < k
     double card[kMaxRel];
     double bcost[kMaxRel];                    // cost of scanning relation v under the model
     double csel[kMaxRel][2];                  // per v: card[v], then sel(lowest u < v adjacent to v, v) (1.0 without one)
-    uint32_t ch[4][256];                      // tree joins rooted at 0: children of a set, per byte
     uint32_t lo[kMaxRel][2];                  // per v: bit of its lowest neighbour u < v (0 without one), its other neighbours u < v
     uint32_t adj[kMaxRel];                    // bit u of adj[v]: edge (u, v)
     uint32_t pd[kMaxRel][2];                  // tree joins rooted at 0, per v: bit of its parent (0 at the root),
                                               // then the relations of the subtree rooted at v
     uint32_t selrow[kMaxRel];                 // first sel entry of relation v
-    uint32_t binom[33 * 33];                  // C(a, b) at [a * 33 + b]
-    uint32_t pad[3];
     double sel[kMaxRel * (kMaxRel - 1) / 2];  // per v: sel(u, v) of edges u < v, u ascending
     uint32_t nb[4][256];                      // neighbours of a set, one table per bitmap byte
+    uint32_t ch[4][256];                      // tree joins rooted at 0: children of a set, per byte
+    uint32_t binom[33 * 33];                  // C(a, b) at [a * 33 + b]
+    uint32_t pad[3];
 };
 static_assert(offsetof(LdsImage, csel) % 16 == 0, "(card, sel) pairs are read as 16-byte units");
 static_assert(offsetof(LdsImage, lo) % 8 == 0, "lowest-neighbour pairs are read as 8-byte units");
 static_assert(offsetof(LdsImage, pd) % 8 == 0, "(parent, subtree) pairs are read as 8-byte units");
-static_assert(offsetof(LdsImage, sel) % 16 == 0, "the tree prefix ends on a 16-byte boundary");
-constexpr size_t kTreeLdsBytes = offsetof(LdsImage, sel) + 8 * 32;  // the prefix plus 32 selectivities
+static_assert(offsetof(LdsImage, sel) % 16 == 0, "the image is copied in parts of 16-byte units");
+static_assert(offsetof(LdsImage, ch) % 16 == 0, "the list prefix ends on a 16-byte boundary");
+constexpr size_t kListLdsBytes = offsetof(LdsImage, ch);
 static_assert(sizeof(LdsImage) % 16 == 0, "LdsImage is copied in 16-byte units");
 
 // Query information as the kernels read it.  Built on the host, uploaded
@@ -64,8 +63,8 @@ struct MemoPtrs {
 
 // Device-side counters, cleared by the init kernel.
 struct Counters {
-    uint32_t level_count[34];   // connected sets found at each level (block-based path: those inducing a tree)
-    uint32_t general_count[34]; // block-based path: the other connected sets of each level
+    uint32_t level_count[34];   // connected sets found at each level (DPSUB ablation: none)
+    uint32_t general_count[34]; // DPSUB ablation: connected sets of each level
     uint32_t heavy_count[34];   // sets handed to the heavy kernel at each level
     uint32_t prune_slots[34];   // unfused-prune ablation: sets whose pair keys were written at each level
     uint32_t extract_error;     // nonzero if plan extraction met an inconsistent memo
@@ -131,7 +130,24 @@ hipError_t launch_batch(int cost_model, uint32_t workgroups, const BatchQueryDev
                         mpdp_plan_node *plans, BatchOut *out, TeamRec *teams,
                         BatchCounters *bc, hipStream_t s);
 
-hipError_t launch_init(const DevGraph *g, uint32_t n, MemoPtrs memo, Counters *cnt, hipStream_t s);
+// Waves of a level that walks lists of connected sets, which is also the
+// most parts its sets are shared out in (HeavyPart records and arrival
+// counters, zeroed by launch_init and left at zero by every level).  tally:
+// csg-cmp pairs and Alg. 3 candidates per workgroup, zeroed by launch_init,
+// summed by launch_extract (null there: not used).  list2:
+// where the connected sets of two relations go (null: no lists).
+constexpr uint32_t kPairGrid = 256;            // one workgroup per CU
+constexpr uint32_t kPairBlock = 1024;
+constexpr uint32_t kPairWaves = kPairGrid * (kPairBlock / 64);
+
+hipError_t launch_init(const DevGraph *g, uint32_t n, MemoPtrs memo, uint32_t *list2, uint32_t *arrived,
+                       unsigned long long *tally, Counters *cnt, hipStream_t s);
+// One level of the block-based path: the sets of k relations in `list`
+// (cnt->level_count[k] of them) evaluated, the sets of k + 1 into `next`.
+struct HeavyPart;
+hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,
+                              uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
+                              unsigned long long *tally, hipStream_t s);
 hipError_t launch_filter(const DevGraph *g, uint32_t k, uint64_t ncand, uint32_t *list, Counters *cnt,
                          hipStream_t s);
 constexpr uint32_t kAblateDpsub = 1u;
@@ -174,6 +190,6 @@ hipError_t launch_eval_general(const DevGraph *g, int cost_model, uint32_t k, ui
                                const uint32_t *list, uint32_t *heavy, Counters *cnt, MemoPtrs memo, HeavyPart *parts,
                                hipStream_t s);
 hipError_t launch_extract(const DevGraph *g, uint32_t n, MemoPtrs memo, mpdp_plan_node *plan,
-                          double *root_cost, Counters *cnt, hipStream_t s);
+                          double *root_cost, const unsigned long long *tally, Counters *cnt, hipStream_t s);
 
 }  // namespace mpdp

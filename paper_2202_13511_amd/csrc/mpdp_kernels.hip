@@ -24,7 +24,8 @@ namespace {
 
 // ---------------------------------------------------------------- kernels
 
-__global__ void k_init(const DevGraph *g, uint32_t n, MemoPtrs M, Counters *cnt) {
+__global__ __launch_bounds__(kBlock) void k_init(const DevGraph *g, uint32_t n, MemoPtrs M, uint32_t *list2,
+                                                 uint32_t *arrived, unsigned long long *tally, Counters *cnt) {
     const uint32_t t = threadIdx.x;
     if (t < n) {  // colex({t}) = t, level 1 starts at 1
         const uint64_t at = g->lds.loff[1] + t;
@@ -32,9 +33,18 @@ __global__ void k_init(const DevGraph *g, uint32_t n, MemoPtrs M, Counters *cnt)
         M.card[at] = g->lds.card[t];
         M.left[at] = 0;
         M.op[at] = MPDP_OP_SCAN;
+        // the connected sets of two relations: the edges, by their higher end
+        uint32_t e = 0;
+        for (uint32_t w = 0; list2 && w < t; ++w) e += (uint32_t)popc32(g->lds.adj[w] & ((1u << w) - 1u));
+        for (uint32_t U = list2 ? g->lds.adj[t] & ((1u << t) - 1u) : 0u; U; U &= U - 1) list2[e++] = (1u << t) | lowbit(U);
+    }
+    if (list2) {
+        for (uint32_t i = t; i < kPairWaves; i += blockDim.x) arrived[i] = 0u;
+        for (uint32_t i = t; i < 2 * kPairGrid; i += blockDim.x) tally[i] = 0ull;
     }
     uint32_t *words = reinterpret_cast<uint32_t *>(cnt);
-    for (uint32_t i = t; i < sizeof(Counters) / 4; i += blockDim.x) words[i] = 0;
+    for (uint32_t i = t; i < sizeof(Counters) / 4; i += blockDim.x)
+        words[i] = i == offsetof(Counters, level_count) / 4 + 2 && list2 ? g->m : 0u;
 }
 
 // The ranges of nw wave-sized pieces of a level that this wave walks (w0,
@@ -65,13 +75,10 @@ __device__ __forceinline__ void wave_ranges(uint64_t nw, uint64_t &w0, uint64_t 
 template <int CM, int kTreeChunk, bool kCompact, bool kFlat>
 __global__ __launch_bounds__(kBlock) void k_level_tree(const DevGraph *g, uint32_t k, uint64_t ncand,
                                                        Counters *cnt, MemoPtrs M) {
-    // the LDS image up to the first 32 selectivities: a tree join reads no
-    // more (n - 1 <= 31 edges, and no neighbour tables)
-    __shared__ __align__(16) unsigned char lds_tree[kTreeLdsBytes];
+    __shared__ __align__(16) LdsGraph L;
     __shared__ uint32_t ring_all[kWaves][kTreeRing];
     __shared__ uint32_t ring_bsum_all[kWaves][kTreeRing];
-    stage_graph_prefix(g, lds_tree, kTreeLdsBytes);
-    const LdsGraph &L = *reinterpret_cast<const LdsGraph *>(lds_tree);
+    stage_graph_tree(g, L);
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t per_wave = 64ull * kTreeChunk;
     uint64_t w0, ws, we;
@@ -91,11 +98,10 @@ __global__ __launch_bounds__(kBlock) void k_level_tree(const DevGraph *g, uint32
 template <int CM, int kTreeChunk>
 __global__ __launch_bounds__(kBlock) void k_level_flat(const DevGraph *g, uint32_t k, uint64_t nsets, Counters *cnt,
                                                        MemoPtrs M) {
-    __shared__ __align__(16) unsigned char lds_tree[kTreeLdsBytes];
+    __shared__ __align__(16) LdsGraph L;
     __shared__ uint32_t blk_set[kWaves][flat_block_words(kTreeChunk)];
     __shared__ uint32_t blk_bsum[kWaves][flat_block_words(kTreeChunk)];
-    stage_graph_prefix(g, lds_tree, kTreeLdsBytes);
-    const LdsGraph &L = *reinterpret_cast<const LdsGraph *>(lds_tree);
+    stage_graph_tree(g, L);
     const uint32_t lane = threadIdx.x & 63u;
     uint64_t lo = 0, len = nsets, wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6),
              waves = (uint64_t)gridDim.x * kWaves;
@@ -119,11 +125,10 @@ template <int CM, int kTreeChunk, bool kFlat>
 __global__ __launch_bounds__(kBlock) void k_level_tree_unfused(const DevGraph *g, uint32_t k, uint64_t ncand,
                                                                Counters *cnt, MemoPtrs M, PairKey *keys,
                                                                PruneRec *recs) {
-    __shared__ __align__(16) unsigned char lds_tree[kTreeLdsBytes];
+    __shared__ __align__(16) LdsGraph L;
     __shared__ uint32_t ring_all[kWaves][kTreeRing];
     __shared__ uint32_t ring_bsum_all[kWaves][kTreeRing];
-    stage_graph_prefix(g, lds_tree, kTreeLdsBytes);
-    const LdsGraph &L = *reinterpret_cast<const LdsGraph *>(lds_tree);
+    stage_graph_tree(g, L);
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t per_wave = 64ull * kTreeChunk;
     uint64_t w0, ws, we;
@@ -148,9 +153,8 @@ __global__ __launch_bounds__(kBlock) void k_prune(const DevGraph *g, uint32_t k,
 template <int CM>
 __global__ __launch_bounds__(kBlock) void k_level_tree_split(const DevGraph *g, uint32_t k, uint64_t ncand,
                                                              Counters *cnt, MemoPtrs M) {
-    __shared__ __align__(16) unsigned char lds_tree[kTreeLdsBytes];
-    stage_graph_prefix(g, lds_tree, kTreeLdsBytes);
-    const LdsGraph &L = *reinterpret_cast<const LdsGraph *>(lds_tree);
+    __shared__ __align__(16) LdsGraph L;
+    stage_graph_tree(g, L);
     const uint32_t lane = threadIdx.x & 63u;
     constexpr uint64_t per_wave = 64 / kTreeSplitLanes;
     uint64_t w0, ws, we;
@@ -282,13 +286,28 @@ __global__ __launch_bounds__(64) void k_heavy_reduce(const DevGraph *g, uint32_t
 // Rebuild the plan (Section 5: fetched recursively through left/right) in
 // post-order with one wave (see extract_plan).
 __global__ __launch_bounds__(64) void k_extract(const DevGraph *g, uint32_t n, MemoPtrs M, mpdp_plan_node *plan,
-                                                double *root_cost, Counters *cnt) {
+                                                double *root_cost, const unsigned long long *tally, Counters *cnt) {
     __shared__ uint32_t binom[33 * 33];
     __shared__ uint64_t loff[34];
     __shared__ PlanScratch P;
     for (uint32_t i = threadIdx.x; i < 33 * 33; i += blockDim.x) binom[i] = g->lds.binom[i];
     if (threadIdx.x < 34) loff[threadIdx.x] = g->lds.loff[threadIdx.x];
     __syncthreads();
+    if (tally) {
+        unsigned long long ccp = 0, evaluated = 0;
+        for (uint32_t i = threadIdx.x; i < kPairGrid; i += blockDim.x) {
+            ccp += tally[2 * i];
+            evaluated += tally[2 * i + 1];
+        }
+        for (int off = 32; off >= 1; off >>= 1) {
+            ccp += (unsigned long long)__shfl_xor((long long)ccp, off);
+            evaluated += (unsigned long long)__shfl_xor((long long)evaluated, off);
+        }
+        if (threadIdx.x == 0) {
+            cnt->ccp += ccp;
+            cnt->evaluated += evaluated;
+        }
+    }
     if (!extract_plan(binom, loff, M, n, plan, root_cost, P, threadIdx.x, blockDim.x) && threadIdx.x == 0)
         cnt->extract_error = 1;
 }
@@ -301,8 +320,9 @@ uint32_t grid_for(uint64_t items, uint64_t per_block) {
 
 }  // namespace
 
-hipError_t launch_init(const DevGraph *g, uint32_t n, MemoPtrs memo, Counters *cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_init, dim3(1), dim3(64), 0, s, g, n, memo, cnt);
+hipError_t launch_init(const DevGraph *g, uint32_t n, MemoPtrs memo, uint32_t *list2, uint32_t *arrived,
+                       unsigned long long *tally, Counters *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(k_init, dim3(1), dim3(kBlock), 0, s, g, n, memo, list2, arrived, tally, cnt);
     return hipGetLastError();
 }
 
@@ -452,8 +472,8 @@ hipError_t launch_eval_general(const DevGraph *g, int cost_model, uint32_t k, ui
 }
 
 hipError_t launch_extract(const DevGraph *g, uint32_t n, MemoPtrs memo, mpdp_plan_node *plan,
-                          double *root_cost, Counters *cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_extract, dim3(1), dim3(64), 0, s, g, n, memo, plan, root_cost, cnt);
+                          double *root_cost, const unsigned long long *tally, Counters *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(k_extract, dim3(1), dim3(64), 0, s, g, n, memo, plan, root_cost, tally, cnt);
     return hipGetLastError();
 }
 

@@ -1,0 +1,531 @@
+// Levels as lists of connected sets: the next level's list is grown from
+// this one's (expand_sets), and a set's csg-cmp pairs are enumerated
+// directly (eval_pairs: one search step per pair, whatever the block
+// structure of the set), instead of unranking every k-subset and testing
+// every subset of every block.  Shared by the per-level kernels and the
+// batched kernel.  Internal; every function is inlined into its kernels.
+#pragma once
+
+#include "mpdp_device.h"
+
+namespace mpdp {
+namespace {
+
+// ---------------------------------------------------------------- colex ranks by table
+
+// Colex rank of a set from its six-bit digits: digit j holds relations
+// 6j .. 6j + 5 and contributes sum C(6j + b, c + i + 1) over its set bits b
+// (i-th from below), where c members of the set lie below the digit.  That
+// depends on (j, c, digit) alone: 4284 words for all 32 relations, six
+// lookups a set (four up to 24 relations) with no loop over the members.
+// (Eight-bit digits would take four lookups but 53 KB of LDS.)
+constexpr int kRankAt[6] = {0, 64, 512, 1344, 2560, 4160};
+constexpr int kRankWords = 4160 + 31 * 4;
+constexpr int kRankWords24 = 2560;  // the first four digits: up to 24 relations
+
+struct RankTable {
+    uint32_t v[kRankWords];
+};
+
+constexpr RankTable make_rank_table() {
+    uint32_t binom[33][34] = {};
+    for (int a = 0; a <= 32; ++a) {
+        binom[a][0] = 1;
+        for (int b = 1; b <= a; ++b) binom[a][b] = binom[a - 1][b - 1] + (b <= a - 1 ? binom[a - 1][b] : 0u);
+    }
+    RankTable t{};
+    for (int j = 0; j < 6; ++j) {
+        const int bits = j < 5 ? 6 : 2;
+        for (int c = 0; c <= 6 * j; ++c)
+            for (int d = 0; d < (1 << bits); ++d) {
+                uint32_t r = 0;
+                int i = c;
+                for (int b = 0; b < bits; ++b)
+                    if ((d >> b) & 1) {
+                        ++i;
+                        r += binom[6 * j + b][i];
+                    }
+                t.v[kRankAt[j] + (c << bits) + d] = r;
+            }
+    }
+    return t;
+}
+
+__device__ const RankTable kRankTable = make_rank_table();
+
+// Copy the digits that n relations need into LDS.
+__device__ __forceinline__ void stage_ranks(uint32_t *dst, uint32_t n) {
+    const uint32_t words = n <= 24 ? kRankWords24 : kRankWords;
+    const uint4 *src = reinterpret_cast<const uint4 *>(kRankTable.v);
+    for (uint32_t i = threadIdx.x; i < words / 4; i += blockDim.x) reinterpret_cast<uint4 *>(dst)[i] = src[i];
+}
+static_assert(kRankWords % 4 == 0 && kRankWords24 % 4 == 0, "the rank table is copied in 16-byte units");
+
+__device__ __forceinline__ uint32_t colex_rank(const uint32_t *T, uint32_t X, bool wide) {
+    uint32_t r = T[X & 63u];
+    r += T[64 + (popc32(X & 0x3fu) << 6) + ((X >> 6) & 63u)];
+    r += T[512 + (popc32(X & 0xfffu) << 6) + ((X >> 12) & 63u)];
+    r += T[1344 + (popc32(X & 0x3ffffu) << 6) + ((X >> 18) & 63u)];
+    if (wide) {  // uniform: more than 24 relations
+        r += T[2560 + (popc32(X & 0xffffffu) << 6) + ((X >> 24) & 63u)];
+        r += T[4160 + (popc32(X & 0x3fffffffu) << 2) + (X >> 30)];
+    }
+    return r;
+}
+
+// ---------------------------------------------------------------- buffers
+
+// One wave's LDS.  The pool is the stack of search states (eval_pairs):
+// kPool entries are shared by all lanes, kPoolReserve more are for the one
+// lane that goes on alone when the pool is full.  Sets with hundreds of
+// pairs fill 512 entries now and then; at 192 some waves spent most of
+// their time stalled (28 relations, 10 chords: 8.0 -> 12.3 ms).
+constexpr uint32_t kPool = 448, kPoolReserve = 64;
+
+struct PairBuf {
+    uint32_t p0[kPool + kPoolReserve], p1[kPool + kPoolReserve], p2[kPool + kPoolReserve];
+    unsigned long long bc[64];  // best key of each set: cost bits,
+    double card[64];            // card(S)
+    uint32_t bl[64], bop[64];   // left set, operator
+    uint32_t claim[64];
+    uint8_t slot[kPool + kPoolReserve];
+};
+
+// ---------------------------------------------------------------- Alg. 3's counter
+
+// Sum over the blocks of G[S] (S connected) of 2^b - 2, Alg. 3's
+// EvaluatedCounter: relations of degree one are bridges (2 each) and are
+// stripped; in what remains every cut vertex that a block hangs on has three
+// or more neighbours, so only those are tested, by whether one neighbour
+// reaches the others without it; a cut splits the rest in two pieces that
+// share the vertex.  One lane per set; `todo` holds the pieces put aside
+// (16 per lane, stride 64; a piece put aside has two or more relations that
+// the others lack, so 32 relations leave at most 15).
+__device__ __forceinline__ unsigned long long block_candidates(const LdsGraph &L, uint32_t S, uint32_t *todo) {
+    unsigned long long sum = 0;
+    uint32_t sp = 0, K = S;
+    for (;;) {
+        for (uint32_t U = K; U; U &= U - 1) {
+            uint32_t v = lowbit(U);
+            while (K & v) {  // strip v, then its neighbour if that leaves it with one edge
+                const uint32_t nv = L.adj[ctz32(v)] & K;
+                if (nv == 0 || (nv & (nv - 1))) break;
+                sum += 2;
+                K ^= v;
+                v = nv;
+            }
+        }
+        bool cut = false;
+        if (K & (K - 1)) {
+            for (uint32_t U = K; U && !cut; U &= U - 1) {
+                const uint32_t v = lowbit(U), nv = L.adj[ctz32(v)] & K;
+                if (popc32(nv) < 3) continue;
+                const uint32_t R = K ^ v;
+                uint32_t seen = lowbit(nv), fr = seen;
+                while (fr && (nv & ~seen)) {
+                    fr = nbrs(L.nb, fr) & R & ~seen;
+                    seen |= fr;
+                }
+                if (nv & ~seen) {
+                    todo[sp * 64] = K & ~seen;
+                    ++sp;
+                    K = seen | v;
+                    cut = true;
+                }
+            }
+            if (cut) continue;
+            sum += (1ull << popc32(K)) - 2ull;
+        }
+        if (sp == 0) return sum;
+        --sp;
+        K = todo[sp * 64];
+    }
+}
+
+// ---------------------------------------------------------------- csg-cmp pairs of any connected set
+
+// All csg-cmp pairs of the sets list[0 .. count), Alg. 3's result without
+// its candidate subsets.  For one set S with lowest relation r, a search
+// state (A, X), A holding r, stands for every pair whose left side contains
+// A and none of X; S - A is connected, so (A, S - A) itself is one of them.
+// The others take some neighbour of A into the left side, and are divided by
+// the first one they take: for v the lowest neighbour of A in S - A - X,
+// v joins A, or v joins X and the next neighbour is tried.  When v joins A,
+// the component of S - A - v that holds X (or, while X is empty, each
+// component in turn) becomes the right side and everything else the left,
+// which is again connected; if v separates X there is no such pair.  So
+// every state but those dead ends yields one pair: 1.2 to 1.5 steps per
+// pair on cycles with chords (n = 24), 1.0 on cliques, where the walk over
+// all subsets of a block tests up to 632 candidates per pair.
+//
+// A wave takes `per` sets at a time; their states share one LDS stack, from
+// which idle lanes pop and onto which a lane pushes the state it leaves
+// behind.  A full stack stalls the lanes that would push, all but the first
+// active one, which goes on depth first into the reserve (a search path
+// pushes less than two states per relation, so 64 entries suffice) until
+// there is room.  The memo reads of a pair are issued one step before they
+// are used, and a lane keeps the best key of the set it is on to itself
+// until it comes to another set.
+//
+// With parts > 1 (levels of few sets) `parts` waves share one set: each runs
+// the same first steps until there are at least two states per part, keeps
+// every parts-th state, and leaves its key in `rec`; the last one to arrive
+// reduces them.
+//
+// A lane's state: A, C = S - A, X and F, the neighbours of A in C - X still
+// to try.  F = 0 with C != 0 marks components still to place: the right
+// sides are the components of C, and A = S - C.  C = 0: idle.  When v joins
+// A, the relations that become its neighbours are those of v alone (the
+// components that go left with it touch nothing of the one that stays).
+// A stack entry is three bit planes (A: 1 0 0, C alone: 0 1 0, X: 1 1 0,
+// F: 0 0 1) and the set's slot.
+struct PairState {
+    uint32_t A, C, X, F, slot;
+};
+
+__device__ __forceinline__ void push_state(PairBuf &B, uint32_t at, uint32_t A, uint32_t C, uint32_t X, uint32_t F,
+                                           uint32_t slot) {
+    B.p0[at] = A | X;
+    B.p1[at] = C & ~F;
+    B.p2[at] = F;
+    B.slot[at] = (uint8_t)slot;
+}
+
+template <int CM>
+struct PairLoad {
+    double cA, cB, kA, kB;
+    uint32_t A, B, slot;
+    bool on;
+};
+
+// A lane's best key of the set in `slot`, not yet in the set's LDS entry.
+struct PairBest {
+    unsigned long long c;
+    uint32_t l, op, slot;
+    double card;
+};
+
+__device__ __forceinline__ bool key_before(unsigned long long c, uint32_t l, uint32_t op, unsigned long long bc,
+                                           uint32_t bl, uint32_t bop) {
+    return (c < bc) | ((c == bc) & ((l < bl) | ((l == bl) & (op < bop))));
+}
+
+// The keys of the lanes in `on` into their sets' entries (LDS, this wave's
+// alone); lanes that improve the same set take turns.
+__device__ __forceinline__ void flush_best(PairBuf &B, const PairBest &b, bool on, uint32_t lane) {
+    bool better = on && key_before(b.c, b.l, b.op, B.bc[b.slot], B.bl[b.slot], B.bop[b.slot]);
+    while (__ballot(better) != 0ull) {
+        if (better) B.claim[b.slot] = lane;
+        wave_sync_lds();
+        if (better && B.claim[b.slot] == lane) {
+            B.bc[b.slot] = b.c;
+            B.bl[b.slot] = b.l;
+            B.bop[b.slot] = b.op;
+            better = false;
+        }
+        wave_sync_lds();
+        better = better && key_before(b.c, b.l, b.op, B.bc[b.slot], B.bl[b.slot], B.bop[b.slot]);
+    }
+}
+
+// The pair whose memo values have arrived into its lane's best key.
+template <int CM>
+__device__ __forceinline__ void settle_pair(PairBuf &B, const PairLoad<CM> &p, PairBest &b, uint32_t lane) {
+    const bool moved = p.on && p.slot != b.slot;
+    if (__ballot(moved) != 0ull) {
+        flush_best(B, b, moved, lane);
+        if (moved) {
+            b.c = ~0ull;
+            b.l = b.op = ~0u;
+            b.slot = p.slot;
+            b.card = B.card[p.slot];
+        }
+    }
+    if (!p.on) return;
+    unsigned long long c;
+    uint32_t l, op;
+    const double base = p.cA + p.cB, cS = b.card;
+    if (CM == MPDP_COST_COUT) {
+        c = (unsigned long long)__double_as_longlong(base + cS);
+        l = p.A < p.B ? p.A : p.B;
+        op = MPDP_OP_JOIN;
+    } else {
+        const double out = 0.01 * cS;
+        const double hjA = ((base + 0.0125 * p.kB) + 0.0025 * p.kA) + out;  // A outer, B hashed
+        const double nlA = (base + (0.0025 * p.kA) * p.kB) + out;
+        const double hjB = ((base + 0.0125 * p.kA) + 0.0025 * p.kB) + out;  // B outer, A hashed
+        const double nlB = (base + (0.0025 * p.kB) * p.kA) + out;
+        const bool hA = hjA <= nlA, hB = hjB <= nlB;
+        const unsigned long long ca = (unsigned long long)__double_as_longlong(hA ? hjA : nlA);
+        const unsigned long long cb = (unsigned long long)__double_as_longlong(hB ? hjB : nlB);
+        const bool first = (ca < cb) | ((ca == cb) & (p.A < p.B));
+        c = first ? ca : cb;
+        l = first ? p.A : p.B;
+        op = (first ? hA : hB) ? MPDP_OP_HASH : MPDP_OP_NESTLOOP;
+    }
+    if (key_before(c, l, op, b.c, b.l, b.op)) {
+        b.c = c;
+        b.l = l;
+        b.op = op;
+    }
+}
+
+struct PairParts {
+    HeavyPart *rec;
+    uint32_t *arrived;  // per set, zero between uses
+};
+
+template <int CM>
+__device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, const MemoPtrs &M, const uint32_t *list,
+                           uint32_t count, uint32_t k, uint32_t w, uint32_t nw, uint32_t per, uint32_t parts,
+                           PairBuf &B, PairParts pp, uint32_t lane, unsigned long long &ccp,
+                           unsigned long long &evaluated) {
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const uint32_t items = parts > 1 ? count * parts : (count + per - 1) / per;
+    for (uint32_t item = w; item < items; item += nw) {
+        const uint32_t s0 = parts > 1 ? item / parts : item * per, part = parts > 1 ? item - s0 * parts : 0u;
+        const uint32_t ns = parts > 1 ? 1u : min(per, count - s0);
+        bool quiet = part != 0;       // the first steps of a shared set count for its first part alone
+        bool shared = parts > 1;      // not split yet
+        uint32_t myset = 0;
+        double mycard = 0.0;
+        PairBest best{~0ull, ~0u, ~0u, lane, 0.0};
+        if (lane < ns) {
+            myset = list[s0 + lane];
+            if (part == 0) evaluated += block_candidates(L, myset, B.p0 + lane);
+            mycard = card_of(L, myset);
+            B.card[lane] = mycard;
+            B.bc[lane] = ~0ull;
+            B.bl[lane] = B.bop[lane] = ~0u;
+        }
+        // the first right sides are the components of S without its lowest
+        // relation: every lane starts with its set
+        PairState s{lowbit(myset), myset & (myset - 1u), 0u, 0u, lane};
+        best.card = mycard;
+        if (shared) best.card = rdlane_f64(mycard, 0);
+        uint32_t top = 0;
+        PairLoad<CM> ld;
+        ld.on = false;
+        ld.slot = 0;
+        ld.A = ld.B = 0;
+        ld.cA = ld.cB = ld.kA = ld.kB = 0.0;
+        wave_sync_lds();
+        for (;;) {
+            if (top != 0u) {  // idle lanes take states from the stack
+                const unsigned long long im = __ballot(s.C == 0u);
+                const uint32_t r = (uint32_t)__popcll(im & below);
+                if (s.C == 0u && r < top) {
+                    const uint32_t e = top - 1u - r;
+                    const uint32_t e0 = B.p0[e], e1 = B.p1[e], e2 = B.p2[e];
+                    s.slot = B.slot[e];
+                    s.A = e0 & ~e1;
+                    s.X = e0 & e1;
+                    s.C = e1 | e2;
+                    s.F = e2;
+                }
+                const uint32_t ni = (uint32_t)__popcll(im);
+                top = top > ni ? top - ni : 0u;
+            }
+            const unsigned long long am = __ballot(s.C != 0u);
+            if (am == 0ull) break;
+            if (shared && top + (uint32_t)__popcll(am) >= 2u * parts) {
+                // every parts-th state is this part's
+                shared = quiet = false;
+                if (lane % parts != part) s.C = 0u;
+                const uint32_t keep = top > part ? (top - part + parts - 1u) / parts : 0u;
+                for (uint32_t i0 = 0; i0 < keep; i0 += 64u) {
+                    const uint32_t i = i0 + lane;
+                    const uint32_t from = part + i * parts;
+                    uint32_t e0 = 0, e1 = 0, e2 = 0;
+                    if (i < keep) { e0 = B.p0[from]; e1 = B.p1[from]; e2 = B.p2[from]; }
+                    wave_sync_lds();
+                    if (i < keep) { B.p0[i] = e0; B.p1[i] = e1; B.p2[i] = e2; B.slot[i] = 0; }
+                    wave_sync_lds();
+                }
+                top = keep;
+                continue;
+            }
+            // one step of every active lane
+            const bool act = s.C != 0u, place = s.F == 0u;  // place: the next component of C
+            const uint32_t v = lowbit(s.F), rest = s.F ^ v, C1 = s.C ^ v;
+            const uint32_t av = L.adj[ctz32(v | 0x80000000u)];
+            const uint32_t nv = place ? C1 : av & C1;
+            uint32_t comp = C1;
+            if ((nv & (nv - 1u)) != 0u) {
+                // C was connected, so C1 is once one neighbour of v reaches the others
+                uint32_t seen = lowbit(nv), fr = seen;
+                while (fr != 0u && (nv & ~seen) != 0u) {
+                    fr = nbrs(L.nb, fr) & C1 & ~seen;
+                    seen |= fr;
+                }
+                if ((nv & ~seen) != 0u) {
+                    if (s.X != 0u && (s.X & seen) == 0u) {  // the component of X is the one that stays
+                        seen = lowbit(s.X);
+                        fr = seen;
+                        while (fr != 0u) {
+                            fr = nbrs(L.nb, fr) & C1 & ~seen;
+                            seen |= fr;
+                        }
+                    }
+                    comp = seen;
+                }
+            }
+            const bool ok = act && C1 != 0u && (s.X & ~comp) == 0u;
+            const uint32_t left = s.X == 0u ? C1 & ~comp : 0u;  // other components, each a right side of its own
+            const bool push_rest = ok && rest != 0u, push_left = ok && left != 0u;
+            const unsigned long long mr = __ballot(push_rest), ml = __ballot(push_left);
+            uint32_t at = top + (uint32_t)__popcll(mr & below) + (uint32_t)__popcll(ml & below);
+            uint32_t total = (uint32_t)__popcll(mr) + (uint32_t)__popcll(ml);
+            bool go = act;
+            if (top + total > kPool) {  // uniform, rare
+                const uint32_t need = (push_rest ? 1u : 0u) + (push_left ? 1u : 0u);
+                go = act && (need == 0u || at + need <= kPool || (am & below) == 0ull);
+                total = (uint32_t)__popcll(__ballot(go && push_rest)) + (uint32_t)__popcll(__ballot(go && push_left));
+            }
+            top += total;
+            settle_pair<CM>(B, ld, best, lane);
+            ld.on = go && ok && !quiet;
+            if (go && ok) {
+                const uint32_t S = s.A | s.C, A1 = S & ~comp;
+                if (push_rest) push_state(B, at++, s.A, s.C, s.X | v, rest, s.slot);
+                if (push_left) push_state(B, at, S & ~left, left, 0u, 0u, s.slot);
+                if (!quiet) {
+                    const uint32_t ka = (uint32_t)popc32(A1);
+                    const uint64_t ia = L.loff[ka] + colex_rank(T, A1, wide);
+                    const uint64_t ib = L.loff[k - ka] + colex_rank(T, comp, wide);
+                    ld.A = A1;
+                    ld.B = comp;
+                    ld.slot = s.slot;
+                    ld.cA = M.cost[ia];
+                    ld.cB = M.cost[ib];
+                    if (CM != MPDP_COST_COUT) {
+                        ld.kA = M.card[ia];
+                        ld.kB = M.card[ib];
+                    }
+                    ++ccp;
+                }
+                s.F = ((place ? nbrs(L.nb, s.A) : av) | rest) & comp & ~s.X;
+                s.A = A1;
+                s.C = s.F != 0u ? comp : 0u;
+            } else if (go) {  // no pair takes v to the left
+                s.X |= v;
+                s.F = rest;
+                s.C = rest != 0u ? s.C : 0u;
+            }
+            wave_sync_lds();
+        }
+        settle_pair<CM>(B, ld, best, lane);
+        flush_best(B, best, true, lane);
+        wave_sync_lds();
+        if (parts == 1) {
+            if (lane < ns) {
+                const uint64_t at = L.loff[k] + colex_rank(T, myset, wide);
+                store_best(M, at, Key{B.bc[lane], B.bl[lane], B.bop[lane]}, mycard);
+            }
+        } else {
+            // the part's key, then the last part to arrive takes the least
+            // (a part of which no state was left keeps the worst key)
+            const uint32_t S0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)myset);
+            HeavyPart *rec = pp.rec + (size_t)s0 * parts;
+            uint32_t n_here = 0;
+            if (lane == 0) {
+                unsigned long long *r64 = reinterpret_cast<unsigned long long *>(&rec[part]);
+                __hip_atomic_store(&r64[0], B.bc[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&r64[1], ((unsigned long long)B.bop[0] << 32) | B.bl[0], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                n_here = __hip_atomic_fetch_add(&pp.arrived[s0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            n_here = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_here);
+            if (n_here == parts - 1u) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                Key best = worst_key();
+                for (uint32_t p = lane; p < parts; p += 64u) {
+                    unsigned long long *r64 = reinterpret_cast<unsigned long long *>(&rec[p]);
+                    const unsigned long long c =
+                        __hip_atomic_load(&r64[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const unsigned long long lo =
+                        __hip_atomic_load(&r64[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const Key o{c, (uint32_t)lo, (uint32_t)(lo >> 32)};
+                    if (key_less(o, best)) best = o;
+                }
+                best = wave_min(best);
+                if (lane == 0) {
+                    store_best(M, L.loff[k] + colex_rank(T, S0, wide), best, mycard);
+                    __hip_atomic_store(&pp.arrived[s0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+        }
+        wave_sync_lds();
+    }
+}
+
+// ---------------------------------------------------------------- the next level's sets
+
+// The connected sets of k + 1 relations from the `count` of k relations in
+// `list`: S + v for every neighbour v of S.  Such a set arises once per
+// relation whose removal leaves it connected; it is kept where v is the
+// highest relation of the last round of a breadth-first search from its
+// lowest relation (which can always be removed), so that every set is listed
+// once.  One search per neighbour, against C(n, k + 1) subsets to unrank and
+// search; `group` lanes (a power of two) divide the neighbours of one set.
+// The waves of a workgroup collect their sets in LDS (`buf`, `cap` words) and
+// append them with one atomic on the list's end: some 30 ns each when all workgroups add to one word, an atomic per 64
+// sets or per wave made that word the bound of the smaller levels.  Starts
+// and ends with the workgroup in step.
+struct ExpandEnds {
+    uint32_t fill, end, start;  // words taken, first word not used, place in the list
+};
+
+__device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t count, uint32_t *out, uint32_t *out_count,
+                            uint32_t w, uint32_t nw, uint32_t group, uint32_t *buf, uint32_t cap, ExpandEnds &ends,
+                            uint32_t lane) {
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const uint32_t each = 64u / group, sub = lane & (group - 1u);
+    if (threadIdx.x == 0) ends = ExpandEnds{0u, cap, 0u};
+    __syncthreads();
+    for (uint32_t base = w * each; base < count; base += nw * each) {
+        const uint32_t i = base + lane / group;
+        const uint32_t S = i < count ? list[i] : 0u;
+        uint32_t N = nbrs(L.nb, S) & ~S;
+        for (uint32_t j = 0; j < sub; ++j) N &= N - 1u;
+        while (__ballot(N != 0u) != 0ull) {
+            const uint32_t v = lowbit(N), S1 = S | v;
+            for (uint32_t j = 0; j < group; ++j) N &= N - 1u;
+            bool keep = false;
+            if (v != 0u) {
+                uint32_t seen = lowbit(S1), fr = seen;
+                while (seen != S1) {  // S1 is connected
+                    fr = nbrs(L.nb, fr) & S1 & ~seen;
+                    seen |= fr;
+                }
+                keep = (v & fr) != 0u && (fr & ~(v | (v - 1u))) == 0u;
+            }
+            const unsigned long long m = __ballot(keep);
+            const uint32_t add = (uint32_t)__popcll(m);
+            if (add == 0u) continue;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&ends.fill, add);
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+            if (at + add <= cap) {
+                if (keep) buf[at + (uint32_t)__popcll(m & below)] = S1;
+            } else {  // the buffer is full: straight to the list
+                if (lane == 0) {
+                    atomicMin(&ends.end, at);
+                    at = atomicAdd(out_count, add);
+                }
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+                if (keep) out[at + (uint32_t)__popcll(m & below)] = S1;
+            }
+        }
+    }
+    __syncthreads();
+    const uint32_t have = min(ends.fill, ends.end);
+    if (threadIdx.x == 0 && have != 0u) ends.start = atomicAdd(out_count, have);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < have; i += blockDim.x) out[ends.start + i] = buf[i];
+    __syncthreads();
+}
+
+}  // namespace
+}  // namespace mpdp

@@ -1,0 +1,98 @@
+"""Levels walked as lists of connected sets, against the CPU oracle (every memo
+entry, the plan and the counters, bit for bit) where they can go wrong: block
+structures that split many times (triangles around one relation, cliques
+joined by a path, cycles sharing relations), sets whose search states
+overflow a wave's pool (dense graphs), sets shared between waves (the top
+levels), and more than 24 relations (the last digits of the rank table)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2202_13511_amd import mpdp, workloads as W
+
+from test_gpu_parity import CMS, check_memo, check_plan, check_stats, run_ws
+
+pytestmark = pytest.mark.gpu
+
+
+def friendship(k):
+    """k triangles around relation 0."""
+    return 2 * k + 1, [e for i in range(k) for e in ([0, 2 * i + 1], [0, 2 * i + 2], [2 * i + 1, 2 * i + 2])]
+
+
+def barbell(a, path, b):
+    """Cliques of a and b relations joined by a path."""
+    n = a + path + b
+    edges = [[i, j] for i in range(a) for j in range(i)] + [[i, i + 1] for i in range(a - 1, a + path)]
+    return n, edges + [[a + path + i, a + path + j] for i in range(b) for j in range(i)]
+
+
+def necklace(k):
+    """k squares in a row, neighbours sharing a relation."""
+    edges = []
+    for i in range(k):
+        c = 3 * i
+        edges += [[c, c + 1], [c + 1, c + 3], [c + 3, c + 2], [c + 2, c]]
+    return 3 * k + 1, edges
+
+
+@pytest.mark.parametrize("cm", CMS)
+@pytest.mark.parametrize("n,edges", [friendship(7), barbell(5, 3, 6), barbell(3, 0, 3), necklace(4)])
+def test_block_structures(n, edges, cm):
+    q = W.from_edges(n, edges, n, f"blocks{n}")
+    res, gm = run_ws(q, cm)
+    ref = oracle.mpdp(q, cm)
+    check_memo(q, gm, ref)
+    check_plan(q, res, ref)
+    check_stats(q, res, ref, general=True)
+
+
+@pytest.mark.parametrize("cm", CMS)
+@pytest.mark.parametrize("q", [W.random_connected(15, 2, 0.6), W.clique(13, 3), W.cycle_chords(5, n=17, chords=6)],
+                         ids=lambda q: q.name)
+def test_full_pools_and_shared_sets(q, cm):
+    res, gm = run_ws(q, cm)
+    ref = oracle.mpdp(q, cm)
+    check_memo(q, gm, ref)
+    check_plan(q, res, ref)
+    check_stats(q, res, ref, general=True)
+
+
+@pytest.mark.parametrize("n", [24, 25, 31, 32])
+def test_cycle_ranks(n):
+    """A cycle's counts in closed form, and its optimum: the best of the chains
+    that its last join leaves (every plan joins two arcs at the root)."""
+    q = W.cycle(n, n)
+    if n > 30:
+        import torch
+        if torch.cuda.mem_get_info()[0] < 1.1 * mpdp.mpdp_workspace_bytes(n):
+            pytest.skip("not enough device memory")
+    ws = mpdp.workspace(n, mpdp.MPDP_COST_COUT)
+    res = mpdp.mpdp_optimize_ws(q, mpdp.MPDP_COST_COUT, ws)
+    assert res.stats["connected_sets"] == n * (n - 1) + 1 - n
+    assert res.stats["ccp_pairs"] == (n ** 3 - 2 * n ** 2 + n) // 2
+    # arcs of k < n relations have k - 1 bridges, the whole cycle is one block
+    assert res.stats["evaluated_pairs"] == n * sum(2 * (k - 1) for k in range(2, n)) + 2 ** n - 2
+    # interval DP over arcs (start, length), C_out
+    sel = {(min(u, v), max(u, v)): s for (u, v), s in zip(q.edges.tolist(), q.sel.tolist())}
+
+    def card(members):
+        c = 1.0
+        have = set()
+        for v in sorted(members):
+            c = c * float(q.card[v])
+            for u in sorted(have):
+                if (u, v) in sel:
+                    c = c * sel[(u, v)]
+            have.add(v)
+        return 1.0 if c < 1.0 else c
+
+    best = {(s, 1): 0.0 for s in range(n)}
+    for k in range(2, n + 1):
+        for s in range(n if k < n else 1):
+            c = card([(s + i) % n for i in range(k)])
+            if k < n:
+                best[(s, k)] = min((best[(s, j)] + best[((s + j) % n, k - j)]) + c for j in range(1, k))
+            else:
+                root = min((best[(t, j)] + best[((t + j) % n, n - j)]) + c for t in range(n) for j in range(1, n))
+    assert np.float64(res.cost).view(np.uint64) == np.float64(root).view(np.uint64)
