@@ -340,6 +340,57 @@ struct EventPool {
     }
 };
 
+// run() for a query of at most kSmallMaxRel relations without flags: one
+// launch, no upload, and the plan written straight to pinned memory (without
+// pinned memory, or no_alloc, it is copied back from the workspace).
+mpdp_status run_small(const Query &q, const Layout &L, char *base, hipStream_t s, mpdp_plan_node *plan_out,
+                      double *cost_out, mpdp_stats *stats_out, double t0, bool no_alloc) {
+    const uint32_t n = q.n;
+    const mpdp::LdsImage &I = q.g.lds;
+    mpdp::SmallQuery sq{};
+    sq.n = n;
+    sq.is_tree = q.is_tree ? 1u : 0u;
+    for (uint32_t v = 0; v < n; ++v) {
+        sq.adj[v] = I.adj[v];
+        sq.pd[v][0] = I.pd[v][0];
+        sq.pd[v][1] = I.pd[v][1];
+        sq.card[v] = I.card[v];
+        sq.bcost[v] = I.bcost[v];
+    }
+    for (uint32_t v = 1; v < n; ++v) {
+        if (q.is_tree) sq.kids[__builtin_ctz(I.pd[v][0])] |= 1u << v;
+        for (uint32_t u = 0; u < v; ++u)
+            sq.sel[v * (v - 1) / 2 + u] = (I.adj[v] >> u) & 1u ? q.sel_full[u * 32 + v] : 1.0;
+    }
+    for (uint32_t k = 0; k < 16; ++k) sq.loff[k] = (uint32_t)I.loff[k];
+    MemoPtrs memo{reinterpret_cast<double *>(base + L.cost), reinterpret_cast<double *>(base + L.card),
+                  reinterpret_cast<uint32_t *>(base + L.left), reinterpret_cast<uint8_t *>(base + L.op)};
+    if (no_alloc) memo = MemoPtrs{nullptr, nullptr, nullptr, nullptr};  // nobody can read it
+    mpdp::SmallOut *pin = no_alloc ? nullptr : reinterpret_cast<mpdp::SmallOut *>(pinned_staging(sizeof(DevGraph)));
+    // (the parts region is free here: the result on its way back)
+    mpdp::SmallOut *dev = reinterpret_cast<mpdp::SmallOut *>(base + L.parts);
+    mpdp::SmallOut host;
+    HIPCHK(mpdp::launch_small(sq, q.cost_model, memo, pin ? pin : dev, s));
+    if (!pin) HIPCHK(hipMemcpyAsync(&host, dev, sizeof(host), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    const mpdp::SmallOut &r = pin ? *pin : host;
+    if (r.error) return MPDP_EDEVICE;
+    std::memcpy(plan_out, r.plan, sizeof(mpdp_plan_node) * (2 * n - 1));
+    *cost_out = r.root;
+    if (stats_out) {
+        mpdp_stats st{};
+        for (uint32_t k = 2; k <= n; ++k) st.candidates += binom64(n, k);
+        st.connected_sets = r.connected;
+        st.ccp_pairs = r.ccp;
+        st.evaluated_pairs = r.evaluated;
+        st.levels = n - 1;
+        st.eval_launches = 1;
+        st.ms_total = now_ms() - t0;
+        *stats_out = st;
+    }
+    return MPDP_OK;
+}
+
 // One exact optimization in the workspace d_ws on stream s.  With
 // no_alloc, nothing is allocated on the host or the device: the query
 // information goes up and the plan comes back through pageable memory (the
@@ -353,6 +404,8 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     if (ws_bytes < L.total) return MPDP_ENOMEM;
     if (reinterpret_cast<uintptr_t>(d_ws) % kAlign) return MPDP_EINVAL;
     char *base = static_cast<char *>(d_ws);
+    if (flags == 0 && !force_general && n <= mpdp::kSmallMaxRel)
+        return run_small(q, L, base, s, plan_out, cost_out, stats_out, t0, no_alloc);
     MemoPtrs memo{reinterpret_cast<double *>(base + L.cost), reinterpret_cast<double *>(base + L.card),
                   reinterpret_cast<uint32_t *>(base + L.left), reinterpret_cast<uint8_t *>(base + L.op)};
     uint32_t *list = reinterpret_cast<uint32_t *>(base + L.list);

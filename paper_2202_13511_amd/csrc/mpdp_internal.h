@@ -73,6 +73,30 @@ struct Counters {
     unsigned long long ccp;       // unordered csg-cmp pairs (general path)
 };
 
+// Small queries (mpdp_small.hip): one launch for the whole query.  The query
+// travels in the kernel's arguments; sel(u, v), u < v, at v (v - 1) / 2 + u,
+// 1.0 without an edge.  out: pinned host memory, or device
+// memory that is copied back.  memo.cost null: the memo is not kept.
+constexpr uint32_t kSmallMaxRel = 12;  // 2^12 entries of 23 bytes fit in LDS, 2^13 do not
+
+struct SmallQuery {
+    uint32_t n, is_tree;
+    uint32_t adj[kSmallMaxRel], kids[kSmallMaxRel];  // kids: a tree join's children, rooted at 0
+    uint32_t pd[kSmallMaxRel][2];
+    uint32_t loff[16];
+    double card[kSmallMaxRel], bcost[kSmallMaxRel];
+    double sel[kSmallMaxRel * (kSmallMaxRel - 1) / 2];
+};
+
+struct SmallOut {
+    unsigned long long connected, ccp, evaluated;
+    double root;
+    uint32_t error, pad;
+    mpdp_plan_node plan[2 * kSmallMaxRel - 1];
+};
+
+hipError_t launch_small(const SmallQuery &q, int cost_model, MemoPtrs memo, SmallOut *out, hipStream_t s);
+
 // Batched path (mpdp_batch.hip): one queue entry per workgroup at a time.
 // A query is one entry, or, if it is large and cyclic, kTeamSize entries in
 // a row: a team of workgroups that share its levels.
