@@ -2,7 +2,10 @@
 // ReLU) with BF16 weights and activations and FP32 accumulation.  The two
 // wide layers and their gradients run on the matrix cores
 // (v_mfma_f32_32x32x16_bf16); the 256 -> 1 head, the loss, the bias sums
-// and the Adam update are plain FP32 vector code.  It scores candidate
+// and the Adam update are plain FP32 vector code.  A training step is two
+// launches: everything that is local to a block of 32 batch rows (forward,
+// loss, the gradients of the activations), then everything summed over the
+// batch (the weights' gradients, each with its Adam update).  It scores candidate
 // unions of UnionDP's partition phase (Section 4.2) and is trained on plans
 // the exact DP produces (mpdp_scorer.h).
 #include <hip/hip_runtime.h>
@@ -87,7 +90,7 @@ Params params_at(void *base) {
 // Work buffer of one batch: activations and their gradients.
 struct Work {
     uint16_t *h1, *h2, *dz2, *dz1;  // batch x 256 bf16
-    float *logit, *dlogit;          // batch
+    float *row_loss, *dlogit;       // batch
     float *loss;                    // 1 (sum over the batch)
 };
 
@@ -103,160 +106,343 @@ Work work_at(void *base, uint32_t batch) {
     w.h2 = reinterpret_cast<uint16_t *>(b + a);
     w.dz2 = reinterpret_cast<uint16_t *>(b + 2 * a);
     w.dz1 = reinterpret_cast<uint16_t *>(b + 3 * a);
-    w.logit = reinterpret_cast<float *>(b + 4 * a);
+    w.row_loss = reinterpret_cast<float *>(b + 4 * a);
     w.dlogit = reinterpret_cast<float *>(b + 4 * a + f);
     w.loss = reinterpret_cast<float *>(b + 4 * a + 2 * f);
     return w;
 }
 
-// ---------------------------------------------------------------- MFMA GEMM
+// ---------------------------------------------------------------- matrix cores
 //
-// C (M x N) = A (M x K) * B (K x N), BF16 in, FP32 accumulate.  A(i, k) is
-// at A[i * lda + k] (TA = 0) or A[k * lda + i] (TA = 1); B(k, j) is at
-// B[k * ldb + j] (TB = 0) or B[j * ldb + k] (TB = 1).  One wave computes one
-// 32 x 32 tile of C with v_mfma_f32_32x32x16_bf16: lane l supplies A(i, k)
-// for i = l % 32 and k = 8 (l / 32) + 0..7 of each 16-wide K step, and
-// B(k, j) for j = l % 32 and the same k; it receives C(i, j) for j = l % 32
-// and i = 8 (r / 4) + 4 (l / 32) + r % 4, r = 0..15.  Out-of-range rows,
-// columns and K positions load as zero and are not stored.  A workgroup of
-// four waves covers a 64 x 64 block.
-enum { kEpiBiasReluBf16 = 0, kEpiStoreF32 = 1, kEpiReluMaskBf16 = 2 };
+// v_mfma_f32_32x32x16_bf16, C (32 x 32) += A (32 x 16) B (16 x 32): lane l
+// supplies A(i, k) for i = l % 32 and k = 8 (l / 32) + 0..7, and B(k, j) for
+// j = l % 32 and the same k; it holds C(i, j) for j = l % 32 and
+// i = 8 (r / 4) + 4 (l / 32) + r % 4, r = 0..15.
 
-template <int TA, int TB, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, int lda,
-                                              const uint16_t *__restrict__ B, int ldb, int M, int N, int K,
-                                              const float *__restrict__ bias,      // EPI 0: per column
-                                              const uint16_t *__restrict__ mask,   // EPI 2: keep where mask > 0
-                                              int ldm, float *__restrict__ Cf, uint16_t *__restrict__ Ch, int ldc) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i0 = blockIdx.y * 64 + (wave >> 1) * 32;
-    const int j0 = blockIdx.x * 64 + (wave & 1) * 32;
-    const int ai = i0 + (lane & 31), bj = j0 + (lane & 31), kq = 8 * (lane >> 5);
-    floatx16 acc = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        u16x8 a, b;
+__device__ __forceinline__ floatx16 mfma(const u16x8 &a, const u16x8 &b, const floatx16 &c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+}
+
+__device__ __forceinline__ int c_row(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+
+// Eight values M(k, j), k = k0 .. k0 + 7, of a row-major matrix: one column.
+__device__ __forceinline__ u16x8 column8(const uint16_t *__restrict__ m, int ld, int k0, int j) {
+    u16x8 v;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int k = k0 + kq + t;
-            uint16_t av = 0, bv = 0;
-            if (ai < M && k < K) av = TA ? A[(size_t)k * lda + ai] : A[(size_t)ai * lda + k];
-            if (bj < N && k < K) bv = TB ? B[(size_t)bj * ldb + k] : B[(size_t)k * ldb + bj];
-            a[t] = av;
-            b[t] = bv;
-        }
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
-                                                      acc, 0, 0, 0);
+    for (int t = 0; t < 8; ++t) v[t] = m[(size_t)(k0 + t) * ld + j];
+    return v;
+}
+
+// The same where rows from `rows` on count as zero.
+__device__ __forceinline__ u16x8 column8_below(const uint16_t *__restrict__ m, int ld, uint32_t k0, int j,
+                                               uint32_t rows) {
+    u16x8 v;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = k0 + (uint32_t)t < rows ? m[(size_t)(k0 + t) * ld + j] : (uint16_t)0;
+    return v;
+}
+
+// Eight consecutive values, as one 16-byte access where the caller's buffers
+// are aligned for it (`vec`, uniform), else one by one.
+__device__ __forceinline__ u16x8 load8(const uint16_t *__restrict__ p, bool vec) {
+    if (vec) return *reinterpret_cast<const u16x8 *>(p);
+    u16x8 v;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = p[t];
+    return v;
+}
+
+__device__ __forceinline__ void store8(uint16_t *__restrict__ p, const u16x8 &v, bool vec) {
+    if (vec) {
+        *reinterpret_cast<u16x8 *>(p) = v;
+    } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) p[t] = v[t];
     }
+}
+
+// ---------------------------------------------------------------- rows
+
+constexpr int kRowBlock = 32;                 // batch rows of a workgroup
+constexpr int kRowThreads = 512;              // eight waves, 32 of the 256 columns each
+constexpr int kLd = kHid + 8;                 // LDS row stride: 16-byte reads of 32 rows spread over the banks
+constexpr int kMfmaK = 16;
+
+// Everything of a batch row but the weights' gradients, 32 rows to a
+// workgroup, so that the activations pass from layer to layer through LDS:
+// h1, h2, the logits (j ascending, FP32, then b3) and, for training, the
+// loss of each row (max(l, 0) - l y + log1p(exp(-|l|))), dlogit =
+// (sigmoid(l) - y) / batch, dz2 = bf16(h2 > 0 ? dlogit w3 : 0) and
+// dz1 = bf16(h1 > 0 ? dz2 w2^T : 0).  The K steps of every product run in
+// ascending order in one accumulator, whatever the batch.  Bound by latency:
+// 512 rows occupy 16 CUs (16.7 us); each wave reads its 32 columns of w2 (16
+// KB) once for each direction.
+template <bool kTrain>
+__global__ __launch_bounds__(kRowThreads) void k_rows(const uint16_t *__restrict__ x, const float *__restrict__ y,
+                                                      uint32_t batch, const uint16_t *__restrict__ w1h,
+                                                      const float *__restrict__ b1, const uint16_t *__restrict__ w2h,
+                                                      const float *__restrict__ b2, const uint16_t *__restrict__ w3h,
+                                                      const float *__restrict__ b3, float *__restrict__ logits,
+                                                      Work w, bool vec) {
+    __shared__ __align__(16) uint16_t h1[kRowBlock][kLd];
+    __shared__ __align__(16) uint16_t h2[kRowBlock][kLd];
+    __shared__ __align__(16) uint16_t dz[kRowBlock][kLd];
+    __shared__ float w3[kHid], dl[kRowBlock];
+    const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int i = lane & 31, kq = 8 * (lane >> 5), j = 32 * wave + (lane & 31);
+    const uint32_t row0 = blockIdx.x * kRowBlock;
+    const bool have = row0 + (uint32_t)i < batch;
+    if (t < kHid) w3[t] = bf2f(w3h[t]);
+
+    floatx16 acc = {};
+#pragma unroll
+    for (int k0 = 0; k0 < kIn; k0 += kMfmaK) {
+        u16x8 a = {};
+        if (have) a = load8(x + (size_t)(row0 + i) * kIn + k0 + kq, vec);
+        acc = mfma(a, column8(w1h, kHid, k0 + kq, j), acc);
+    }
+    {
+        const float bias = b1[j];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float z = acc[r] + bias;
+            h1[c_row(lane, r)][j] = f2bf(z > 0.f ? z : 0.f);
+        }
+    }
+    __syncthreads();
+
+    acc = floatx16{};
+#pragma unroll 8
+    for (int k0 = 0; k0 < kHid; k0 += kMfmaK)
+        acc = mfma(*reinterpret_cast<const u16x8 *>(&h1[i][k0 + kq]), column8(w2h, kHid, k0 + kq, j), acc);
+    {
+        const float bias = b2[j];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float z = acc[r] + bias;
+            h2[c_row(lane, r)][j] = f2bf(z > 0.f ? z : 0.f);
+        }
+    }
+    __syncthreads();
+
+    if (t < kRowBlock) {
+        float sum = 0.f;
+#pragma unroll 4
+        for (int c = 0; c < kHid; c += 8) {
+            const u16x8 h = *reinterpret_cast<const u16x8 *>(&h2[t][c]);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += bf2f(h[u]) * w3[c + u];
+        }
+        const float l = sum + b3[0];
+        const uint32_t row = row0 + (uint32_t)t;
+        float d = 0.f;
+        if (row < batch) {
+            if (!kTrain) {
+                logits[row] = l;
+            } else {
+                const float label = y[row];
+                const float p = 1.f / (1.f + expf(-l));
+                d = (p - label) / (float)batch;
+                w.dlogit[row] = d;
+                w.row_loss[row] = fmaxf(l, 0.f) - l * label + log1pf(expf(-fabsf(l)));
+            }
+        }
+        dl[t] = d;
+    }
+    if (!kTrain) return;
+    __syncthreads();
+
+    // dz2, and the rows' activations out to memory for the sums over the
+    // batch: thread t, 16 columns of row t / 16
+    {
+        const int r = t >> 4, c0 = (t & 15) * 16;
+        const uint32_t row = row0 + (uint32_t)r;
+        const float d = dl[r];
+#pragma unroll
+        for (int c = c0; c < c0 + 16; c += 8) {
+            const u16x8 a1 = *reinterpret_cast<const u16x8 *>(&h1[r][c]), a2 = *reinterpret_cast<const u16x8 *>(&h2[r][c]);
+            u16x8 z;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) z[u] = a2[u] != 0 ? f2bf(d * w3[c + u]) : (uint16_t)0;
+            *reinterpret_cast<u16x8 *>(&dz[r][c]) = z;
+            if (row < batch) {
+                store8(w.h1 + (size_t)row * kHid + c, a1, vec);
+                store8(w.h2 + (size_t)row * kHid + c, a2, vec);
+                store8(w.dz2 + (size_t)row * kHid + c, z, vec);
+            }
+        }
+    }
+    __syncthreads();
+
+    acc = floatx16{};
+#pragma unroll 8
+    for (int k0 = 0; k0 < kHid; k0 += kMfmaK)
+        acc = mfma(*reinterpret_cast<const u16x8 *>(&dz[i][k0 + kq]),
+                   *reinterpret_cast<const u16x8 *>(w2h + (size_t)j * kHid + k0 + kq), acc);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int i = i0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int j = bj;
-        if (i >= M || j >= N) continue;
-        const float c = acc[r];
-        if (EPI == kEpiBiasReluBf16) {
-            const float z = c + bias[j];
-            Ch[(size_t)i * ldc + j] = f2bf(z > 0.f ? z : 0.f);
-        } else if (EPI == kEpiStoreF32) {
-            Cf[(size_t)i * ldc + j] = c;
-        } else {
-            Ch[(size_t)i * ldc + j] = mask[(size_t)i * ldm + j] != 0 ? f2bf(c) : (uint16_t)0;
-        }
+        const int row = c_row(lane, r);
+        if (row0 + (uint32_t)row < batch)
+            w.dz1[(size_t)(row0 + row) * kHid + j] = h1[row][j] != 0 ? f2bf(acc[r]) : (uint16_t)0;
     }
 }
 
-template <int TA, int TB, int EPI>
-hipError_t gemm(hipStream_t s, const uint16_t *A, int lda, const uint16_t *B, int ldb, int M, int N, int K,
-                const float *bias, const uint16_t *mask, int ldm, float *Cf, uint16_t *Ch, int ldc) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    const dim3 grid((N + 63) / 64, (M + 63) / 64);
-    hipLaunchKernelGGL((k_gemm<TA, TB, EPI>), grid, dim3(256), 0, s, A, lda, B, ldb, M, N, K, bias, mask, ldm, Cf, Ch,
-                       ldc);
-    return hipGetLastError();
+// ---------------------------------------------------------------- sums over the batch
+
+// Adam (Kingma & Ba): m = b1 m + (1 - b1) g; v = b2 v + (1 - b2) g^2;
+// w -= lr * (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps); then the BF16 copy.
+struct AdamStep {
+    float *w, *m, *v;   // master values and moments, in parameter order
+    uint16_t *wh;       // BF16 copies (w1, w2, w3)
+    float lr, c1, c2;
+};
+
+__device__ __forceinline__ void adam(const AdamStep &s, size_t at, float g, long bf_at) {
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    const float mi = b1 * s.m[at] + (1.f - b1) * g;
+    const float vi = b2 * s.v[at] + (1.f - b2) * g * g;
+    s.m[at] = mi;
+    s.v[at] = vi;
+    const float w = s.w[at] - s.lr * (mi / s.c1) / (sqrtf(vi / s.c2) + eps);
+    s.w[at] = w;
+    if (bf_at >= 0) s.wh[bf_at] = f2bf(w);
 }
 
-// ---------------------------------------------------------------- vector kernels
+constexpr int kSumThreads = 512;
+constexpr int kSumWaves = kSumThreads / 64;
+constexpr int kTiles2 = (kHid / 32) * (kHid / 32), kTiles1 = kHid / 32;
+constexpr int kSumBlocks = kTiles2 + kTiles1 + kHid / 32;
+constexpr int kStepsEach = 4;                        // MFMA steps whose operands a wave fetches at a time
+constexpr int kStepsAll = kStepsEach * kSumWaves;    // of the workgroup: 512 batch rows
+constexpr int kSumRows = 256;                        // batch rows of a column sum fetched at a time
 
-__global__ void k_zero1(float *x) { x[0] = 0.f; }
+struct SumTile {
+    u16x8 a[kStepsAll][64], b[kStepsAll][64];        // operands as the lanes take them
+};
+struct SumColumns {
+    uint16_t v[3][kSumRows][32];                     // dz1, dz2, h2
+    float d[kSumRows];
+};
+
+// Gradients of the parameters: a 32 x 32 tile of dW2 = h1^T dz2 or
+// dW1 = x^T dz1 per workgroup, or 32 columns of db1, db2 and dw3.  Every sum
+// over the batch runs in ascending row order in one accumulator, so the
+// gradients do not depend on how the work is laid out; what the eight waves
+// share is the fetching: operands go to LDS 512 rows at a time, the next
+// ones on their way while one wave multiplies.  kAdam: the update of each
+// parameter follows at once.  512 rows: 25 us a tile product and 110 us a
+// column sum when each step waited for its own reads, 13.6 us for all of them
+// here; a step of training took 449 us in 18 launches and takes 30.
+template <bool kAdam>
+__global__ __launch_bounds__(kSumThreads) void k_sums(const uint16_t *__restrict__ x, uint32_t batch, Work w,
+                                                      float *__restrict__ grad, AdamStep step) {
+    __shared__ __align__(16) unsigned char lds[sizeof(SumTile) > sizeof(SumColumns) ? sizeof(SumTile)
+                                                                                     : sizeof(SumColumns)];
+    const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6, b = (int)blockIdx.x;
+    constexpr size_t oB1 = kN1, oW2 = oB1 + kHid, oB2 = oW2 + kN2, oW3 = oB2 + kHid, oB3 = oW3 + kN3;
+    if (b < kTiles2 + kTiles1) {
+        SumTile &T = *reinterpret_cast<SumTile *>(lds);
+        const bool second = b < kTiles2;
+        const int i0 = second ? 32 * (b >> 3) : 0, j0 = second ? 32 * (b & 7) : 32 * (b - kTiles2);
+        const uint16_t *A = second ? w.h1 : x, *B = second ? w.dz2 : w.dz1;
+        const int lda = second ? kHid : kIn, c = lane & 31;
+        const uint32_t kq = 8u * (uint32_t)(lane >> 5);
+        const uint32_t steps = batch / kMfmaK + (batch % kMfmaK != 0 ? 1u : 0u);
+        u16x8 ra[kStepsEach], rb[kStepsEach];
+        auto fetch = [&](uint32_t s0) {
+#pragma unroll
+            for (int u = 0; u < kStepsEach; ++u) {
+                const uint32_t k0 = (s0 + (uint32_t)(wave * kStepsEach + u)) * kMfmaK + kq;
+                ra[u] = column8_below(A, lda, k0, i0 + c, batch);
+                rb[u] = column8_below(B, kHid, k0, j0 + c, batch);
+            }
+        };
+        floatx16 acc = {};
+        fetch(0);
+        for (uint32_t s0 = 0; s0 < steps; s0 += kStepsAll) {
+#pragma unroll
+            for (int u = 0; u < kStepsEach; ++u) {
+                T.a[wave * kStepsEach + u][lane] = ra[u];
+                T.b[wave * kStepsEach + u][lane] = rb[u];
+            }
+            __syncthreads();
+            if (s0 + kStepsAll < steps) fetch(s0 + kStepsAll);
+            if (wave == 0) {
+                const uint32_t ns = steps - s0 < (uint32_t)kStepsAll ? steps - s0 : (uint32_t)kStepsAll;
+#pragma unroll 4
+                for (uint32_t u = 0; u < ns; ++u) acc = mfma(T.a[u][lane], T.b[u][lane], acc);
+            }
+            __syncthreads();
+        }
+        float *out = reinterpret_cast<float *>(lds);
+        if (wave == 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) out[c_row(lane, r) * 32 + c] = acc[r];
+        }
+        __syncthreads();
+        for (int e = t; e < 32 * 32; e += kSumThreads) {
+            const float g = out[e];
+            const size_t in = (size_t)(i0 + e / 32) * kHid + j0 + e % 32;
+            const size_t at = (second ? oW2 : 0) + in;
+            grad[at] = g;
+            if (kAdam) adam(step, at, g, (long)((second ? kN1 : 0) + in));
+        }
+        return;
+    }
+    // 32 columns: waves 0, 1, 2 sum dz1, dz2 and h2 dlogit, wave 3 (of the
+    // first such workgroup) dlogit; wave 4 the losses
+    SumColumns &C = *reinterpret_cast<SumColumns *>(lds);
+    const int cg = b - kTiles2 - kTiles1, c = t & 31, j = 32 * cg + c;
+    const uint16_t *src[3] = {w.dz1, w.dz2, w.h2};
+    constexpr int kEach = 3 * kSumRows * 32 / kSumThreads;
+    uint16_t rv[kEach];
+    float rd = 0.f;
+    auto fetch = [&](uint32_t r0) {
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+            const uint32_t row = r0 + (uint32_t)((u % (kEach / 3)) * (kSumThreads / 32) + (t >> 5));
+            rv[u] = row < batch ? src[u / (kEach / 3)][(size_t)row * kHid + j] : (uint16_t)0;
+        }
+        if (t < kSumRows) rd = r0 + (uint32_t)t < batch ? w.dlogit[r0 + (uint32_t)t] : 0.f;
+    };
+    float g = 0.f;
+    fetch(0);
+    for (uint32_t r0 = 0; r0 < batch; r0 += kSumRows) {
+#pragma unroll
+        for (int u = 0; u < kEach; ++u)
+            C.v[u / (kEach / 3)][(u % (kEach / 3)) * (kSumThreads / 32) + (t >> 5)][c] = rv[u];
+        if (t < kSumRows) C.d[t] = rd;
+        __syncthreads();
+        if (batch - r0 > (uint32_t)kSumRows) fetch(r0 + kSumRows);
+        const int rows = batch - r0 < (uint32_t)kSumRows ? (int)(batch - r0) : kSumRows;
+        if (wave < 2) {
+#pragma unroll 16
+            for (int i = 0; i < rows; ++i) g += bf2f(C.v[wave][i][c]);
+        } else if (wave == 2) {
+#pragma unroll 16
+            for (int i = 0; i < rows; ++i) g += bf2f(C.v[2][i][c]) * C.d[i];
+        } else if (wave == 3) {
+#pragma unroll 16
+            for (int i = 0; i < rows; ++i) g += C.d[i];
+        }
+        __syncthreads();
+    }
+    if (wave == 4 && cg == 0) {
+        float l = 0.f;
+        for (uint32_t i = (uint32_t)lane; i < batch; i += 64u) l += w.row_loss[i];
+        for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off);
+        if (lane == 0) w.loss[0] = l;
+    }
+    if (wave > 3 || lane >= 32 || (wave == 3 && (cg != 0 || c != 0))) return;
+    const size_t at = wave == 0 ? oB1 + j : wave == 1 ? oB2 + j : wave == 2 ? oW3 + j : oB3;
+    grad[at] = g;
+    if (kAdam) adam(step, at, g, wave == 2 ? (long)(kN1 + kN2 + j) : -1l);
+}
 
 __global__ void k_to_bf16(const float *__restrict__ x, uint16_t *__restrict__ y, size_t n) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         y[i] = f2bf(x[i]);
-}
-
-// logit_i = sum_j h2[i][j] * w3[j] (j ascending, FP32) + b3
-__global__ void k_head(const uint16_t *__restrict__ h2, const uint16_t *__restrict__ w3h, const float *__restrict__ b3,
-                       float *__restrict__ logit, uint32_t batch) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= batch) return;
-    float acc = 0.f;
-    for (int j = 0; j < kHid; ++j) acc += bf2f(h2[(size_t)i * kHid + j]) * bf2f(w3h[j]);
-    logit[i] = acc + b3[0];
-}
-
-// Mean binary cross-entropy with logits: dlogit_i = (sigmoid(logit_i) - y_i) / batch;
-// loss accumulates max(l, 0) - l y + log1p(exp(-|l|)) over the batch.
-__global__ void k_loss(const float *__restrict__ logit, const float *__restrict__ y, float *__restrict__ dlogit,
-                       float *__restrict__ loss, uint32_t batch) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    float li = 0.f;
-    if (i < batch) {
-        const float l = logit[i], t = y[i];
-        const float p = 1.f / (1.f + expf(-l));
-        dlogit[i] = (p - t) / (float)batch;
-        li = fmaxf(l, 0.f) - l * t + log1pf(expf(-fabsf(l)));
-    }
-    for (int off = 32; off >= 1; off >>= 1) li += __shfl_xor(li, off);
-    if ((threadIdx.x & 63) == 0) atomicAdd(loss, li);
-}
-
-// dz2[i][j] = bf16(h2[i][j] > 0 ? dlogit_i * w3[j] : 0)
-__global__ void k_dz2(const uint16_t *__restrict__ h2, const float *__restrict__ dlogit,
-                      const uint16_t *__restrict__ w3h, uint16_t *__restrict__ dz2, uint32_t batch) {
-    const size_t n = (size_t)batch * kHid;
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x) {
-        const size_t i = t / kHid;
-        const int j = (int)(t % kHid);
-        dz2[t] = h2[t] != 0 ? f2bf(dlogit[i] * bf2f(w3h[j])) : (uint16_t)0;
-    }
-}
-
-// Column sums over the batch (i ascending, FP32): bias gradients, and the
-// head's weight gradient dw3[j] = sum_i h2[i][j] dlogit_i, db3 = sum_i dlogit_i.
-__global__ void k_colsum(const uint16_t *__restrict__ d, uint32_t batch, float *__restrict__ out) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= kHid) return;
-    float acc = 0.f;
-    for (uint32_t i = 0; i < batch; ++i) acc += bf2f(d[(size_t)i * kHid + j]);
-    out[j] = acc;
-}
-
-__global__ void k_head_grad(const uint16_t *__restrict__ h2, const float *__restrict__ dlogit, uint32_t batch,
-                            float *__restrict__ dw3, float *__restrict__ db3) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < kHid) {
-        float acc = 0.f;
-        for (uint32_t i = 0; i < batch; ++i) acc += bf2f(h2[(size_t)i * kHid + j]) * dlogit[i];
-        dw3[j] = acc;
-    } else if (j == kHid) {
-        float acc = 0.f;
-        for (uint32_t i = 0; i < batch; ++i) acc += dlogit[i];
-        db3[0] = acc;
-    }
-}
-
-// Adam (Kingma & Ba): m = b1 m + (1 - b1) g; v = b2 v + (1 - b2) g^2;
-// w -= lr * (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps); then the BF16 copies.
-__global__ void k_adam(float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m, float *__restrict__ v,
-                       size_t n, float lr, float c1, float c2) {
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = b1 * m[i] + (1.f - b1) * gi;
-        const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    }
 }
 
 #define HIPCHK(expr)                                   \
@@ -271,41 +457,30 @@ hipError_t refresh_bf16(const Params &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t forward(const Params &p, const uint16_t *x, uint32_t batch, const Work &w, float *logits, hipStream_t s) {
-    hipError_t e = gemm<0, 0, kEpiBiasReluBf16>(s, x, kIn, p.w1h, kHid, (int)batch, kHid, kIn, p.b1, nullptr, 0,
-                                                nullptr, w.h1, kHid);
-    if (e != hipSuccess) return e;
-    e = gemm<0, 0, kEpiBiasReluBf16>(s, w.h1, kHid, p.w2h, kHid, (int)batch, kHid, kHid, p.b2, nullptr, 0, nullptr,
-                                     w.h2, kHid);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_head, dim3((batch + 255) / 256), dim3(256), 0, s, w.h2, p.w3h, p.b3, logits, batch);
+template <bool kTrain>
+hipError_t rows(const Params &p, const uint16_t *x, const float *y, uint32_t batch, const Work &w, float *logits,
+                hipStream_t s) {
+    const bool vec = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w.h1)) & 15u) == 0;
+    const uint32_t blocks = batch / kRowBlock + (batch % kRowBlock != 0 ? 1u : 0u);
+    hipLaunchKernelGGL(k_rows<kTrain>, dim3(blocks), dim3(kRowThreads), 0, s, x, y, batch, p.w1h, p.b1, p.w2h, p.b2,
+                       p.w3h, p.b3, logits, w, vec);
     return hipGetLastError();
 }
 
-// Loss and all gradients into p.g (same order as the master values).
-hipError_t backward(const Params &p, const uint16_t *x, const float *y, uint32_t batch, const Work &w, hipStream_t s) {
-    float *g1 = p.g, *gb1 = g1 + kN1, *g2 = gb1 + kHid, *gb2 = g2 + kN2, *g3 = gb2 + kHid, *gb3 = g3 + kN3;
-    hipLaunchKernelGGL(k_zero1, dim3(1), dim3(1), 0, s, w.loss);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_loss, dim3((batch + 255) / 256), dim3(256), 0, s, w.logit, y, w.dlogit, w.loss, batch);
-    hipLaunchKernelGGL(k_head_grad, dim3((kHid + 1 + 255) / 256), dim3(256), 0, s, w.h2, w.dlogit, batch, g3, gb3);
-    hipLaunchKernelGGL(k_dz2, dim3(256), dim3(256), 0, s, w.h2, w.dlogit, p.w3h, w.dz2, batch);
-    // dW2 = H1^T dZ2 (256 x 256, K = batch); db2 = column sums of dZ2
-    e = gemm<1, 0, kEpiStoreF32>(s, w.h1, kHid, w.dz2, kHid, kHid, kHid, (int)batch, nullptr, nullptr, 0, g2,
-                                 nullptr, kHid);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum, dim3(1), dim3(kHid), 0, s, w.dz2, batch, gb2);
-    // dZ1 = (dZ2 W2^T) masked by H1 > 0
-    e = gemm<0, 1, kEpiReluMaskBf16>(s, w.dz2, kHid, p.w2h, kHid, (int)batch, kHid, kHid, nullptr, w.h1, kHid,
-                                     nullptr, w.dz1, kHid);
-    if (e != hipSuccess) return e;
-    // dW1 = X^T dZ1 (kIn x 256, K = batch); db1
-    e = gemm<1, 0, kEpiStoreF32>(s, x, kIn, w.dz1, kHid, kIn, kHid, (int)batch, nullptr, nullptr, 0, g1, nullptr,
-                                 kHid);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum, dim3(1), dim3(kHid), 0, s, w.dz1, batch, gb1);
+template <bool kAdam>
+hipError_t sums(const Params &p, const uint16_t *x, uint32_t batch, const Work &w, const AdamStep &step,
+                hipStream_t s) {
+    hipLaunchKernelGGL(k_sums<kAdam>, dim3(kSumBlocks), dim3(kSumThreads), 0, s, x, batch, w, p.g, step);
     return hipGetLastError();
+}
+
+// Mean loss of the last batch (waits for the stream).
+mpdp_status read_loss(const Work &w, uint32_t batch, hipStream_t s, float *loss_out) {
+    float l = 0.f;
+    HIPCHK(hipMemcpyAsync(&l, w.loss, sizeof(float), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    *loss_out = l / (float)batch;
+    return MPDP_OK;
 }
 
 }  // namespace
@@ -358,7 +533,7 @@ mpdp_status mpdp_scorer_forward(const void *d_params, const uint16_t *d_x, uint3
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const Params p = params_at(const_cast<void *>(d_params));
     const Work w = work_at(d_work, batch);
-    HIPCHK(forward(p, d_x, batch, w, d_logits, s));
+    HIPCHK(rows<false>(p, d_x, nullptr, batch, w, d_logits, s));
     return MPDP_OK;
 }
 
@@ -369,29 +544,23 @@ mpdp_status mpdp_scorer_grad(void *d_params, const uint16_t *d_x, const float *d
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const Params p = params_at(d_params);
     const Work w = work_at(d_work, batch);
-    HIPCHK(forward(p, d_x, batch, w, w.logit, s));
-    HIPCHK(backward(p, d_x, d_y, batch, w, s));
-    if (loss_out) {
-        float l = 0.f;
-        HIPCHK(hipMemcpyAsync(&l, w.loss, sizeof(float), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        *loss_out = l / (float)batch;
-    }
-    return MPDP_OK;
+    HIPCHK(rows<true>(p, d_x, d_y, batch, w, nullptr, s));
+    HIPCHK(sums<false>(p, d_x, batch, w, AdamStep{}, s));
+    return loss_out ? read_loss(w, batch, s, loss_out) : MPDP_OK;
 }
 
 mpdp_status mpdp_scorer_train_step(void *d_params, const uint16_t *d_x, const float *d_y, uint32_t batch, float lr,
                                    uint32_t step, void *d_work, size_t work_size, void *hip_stream, float *loss_out) {
     if (step == 0 || !(lr > 0.f)) return MPDP_EINVAL;
-    mpdp_status st = mpdp_scorer_grad(d_params, d_x, d_y, batch, d_work, work_size, hip_stream, loss_out);
-    if (st != MPDP_OK) return st;
+    if (!d_params || !d_x || !d_y || !d_work || batch == 0) return MPDP_EINVAL;
+    if (work_size < work_bytes(batch)) return MPDP_ENOMEM;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const Params p = params_at(d_params);
-    const float c1 = 1.f - powf(0.9f, (float)step), c2 = 1.f - powf(0.999f, (float)step);
-    hipLaunchKernelGGL(k_adam, dim3(512), dim3(256), 0, s, p.w1, p.g, p.m, p.v, kNParams, lr, c1, c2);
-    HIPCHK(hipGetLastError());
-    HIPCHK(refresh_bf16(p, s));
-    return MPDP_OK;
+    const Work w = work_at(d_work, batch);
+    const AdamStep adam{p.w1, p.m, p.v, p.w1h, lr, 1.f - powf(0.9f, (float)step), 1.f - powf(0.999f, (float)step)};
+    HIPCHK(rows<true>(p, d_x, d_y, batch, w, nullptr, s));
+    HIPCHK(sums<true>(p, d_x, batch, w, adam, s));
+    return loss_out ? read_loss(w, batch, s, loss_out) : MPDP_OK;
 }
 
 }  // extern "C"
