@@ -152,6 +152,19 @@ __device__ __forceinline__ void stage_graph_prefix(const DevGraph *g, LdsGraph &
     for (uint32_t i = threadIdx.x; i < bytes / 16; i += blockDim.x) dst[i] = src[i];
 }
 
+// The query from pinned host memory (src) into g and LDS, or, without src,
+// from g into LDS.
+__device__ __forceinline__ void bring_graph(const DevGraph *src, DevGraph *g, DevGraph &G) {
+    const uint4 *from = reinterpret_cast<const uint4 *>(src ? src : g);
+    uint4 *to = reinterpret_cast<uint4 *>(g), *lds = reinterpret_cast<uint4 *>(&G);
+    for (uint32_t i = threadIdx.x; i < sizeof(DevGraph) / 16; i += blockDim.x) {
+        const uint4 v = from[i];
+        lds[i] = v;
+        if (src) to[i] = v;
+    }
+}
+static_assert(sizeof(DevGraph) % 16 == 0, "DevGraph is copied in 16-byte units");
+
 // What a tree join's level kernel reads of the image: not the neighbour
 // tables, and no selectivities beyond those of n - 1 <= 31 edges.
 __device__ __forceinline__ void stage_graph_tree(const DevGraph *g, LdsGraph &L) {
@@ -163,6 +176,17 @@ __device__ __forceinline__ void stage_graph_tree(const DevGraph *g, LdsGraph &L)
         dst[j] = src[j];
     }
     __syncthreads();
+}
+
+// What a tree join's list kernels read: the same, and the preorder tables.
+__device__ __forceinline__ void stage_graph_preorder(const DevGraph *g, LdsGraph &L) {
+    constexpr uint32_t kHead = (offsetof(LdsGraph, sel) + 8 * 32) / 16, kTail = offsetof(LdsGraph, pch) / 16;
+    const uint4 *src = reinterpret_cast<const uint4 *>(&g->lds);
+    uint4 *dst = reinterpret_cast<uint4 *>(&L);
+    for (uint32_t i = threadIdx.x; i < kHead + offsetof(LdsGraph, ch) / 16 - kTail; i += blockDim.x) {
+        const uint32_t j = i < kHead ? i : i - kHead + kTail;
+        dst[j] = src[j];
+    }
 }
 
 // Memo index of T: level offset plus colex rank.

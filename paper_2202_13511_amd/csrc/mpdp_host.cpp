@@ -58,6 +58,7 @@ Layout make_layout(uint32_t n) {
 }
 
 struct Query {
+    uint64_t sets[33];  // tree joins: connected sets by size
     uint32_t n, m;
     int cost_model;
     bool is_tree;
@@ -155,6 +156,48 @@ mpdp_status validate(uint32_t n, uint32_t m, const mpdp_edge *edges, const doubl
         }
         for (int i = tail - 1; i > 0; --i) L.pd[parent[order[i]]][1] |= L.pd[order[i]][1];
         g.flat = (n >= 2 && (L.adj[0] & full) == (full & ~1u)) ? 1u : 0u;
+        // preorder numbers, and in them the children and the own numbers of
+        // every byte's sets
+        uint32_t own[32], num[32], kids[32] = {0};
+        for (int v = 0, at = 0, up[32]; at < (int)n; ++at) {
+            own[at] = (uint32_t)v;
+            num[v] = (uint32_t)at;
+            if (at > 0) kids[num[parent[v]]] |= 1u << at;
+            up[v] = 0;
+            while (at + 1 < (int)n) {  // the next child of v, or of the nearest ancestor that has one left
+                uint32_t down = L.adj[v] & ~L.pd[v][0];
+                for (int i = 0; i < up[v]; ++i) down &= down - 1;
+                if (down) { ++up[v]; v = __builtin_ctz(down); break; }
+                v = parent[v];
+            }
+        }
+        for (int b = 0; b < 4; ++b)
+            for (uint32_t x = 1; x < 256; ++x) {
+                const uint32_t u = 8u * b + (uint32_t)__builtin_ctz(x);
+                L.pch[b][x] = L.pch[b][x & (x - 1)] | (u < n ? kids[u] : 0u);
+                L.perm[b][x] = L.perm[b][x & (x - 1)] | (u < n ? 1u << own[u] : 0u);
+            }
+        // connected sets by size: those with top relation v are v and, for
+        // each child, nothing or a set with that child on top
+        uint64_t of[32][33];
+        for (int i = tail - 1; i >= 0; --i) {
+            const int v = order[i];
+            uint64_t f[33] = {0, 1};
+            uint32_t size = 1;
+            for (uint32_t t = L.adj[v]; t; t &= t - 1) {
+                const int c = __builtin_ctz(t);
+                if (c == parent[v]) continue;
+                const uint32_t more = (uint32_t)__builtin_popcount(L.pd[c][1]);
+                uint64_t h[33] = {0};
+                for (uint32_t a = 1; a <= size; ++a)
+                    for (uint32_t b = 0; b <= more; ++b) h[a + b] += f[a] * of[c][b];
+                size += more;
+                std::memcpy(f, h, sizeof(f));
+            }
+            std::memcpy(of[v], f, sizeof(f));
+            of[v][0] = 1;
+            for (uint32_t k = 1; k <= size; ++k) q.sets[k] += f[k];
+        }
     }
     // selectivities of the edges (u, v), u < v, grouped by v, u ascending
     uint32_t at = 0;
@@ -265,9 +308,10 @@ struct GraphKey {
     void *ws, *pin;
     uint32_t n, cost_model;
     bool general, flat;  // the level kernels recorded depend on both
+    uint64_t sets[33];   // tree joins: and their grids on the levels' sizes
     bool operator==(const GraphKey &o) const {
         return ws == o.ws && pin == o.pin && n == o.n && cost_model == o.cost_model && general == o.general &&
-               flat == o.flat;
+               flat == o.flat && std::memcmp(sets, o.sets, sizeof(sets)) == 0;
     }
 };
 
@@ -391,6 +435,16 @@ mpdp_status run_small(const Query &q, const Layout &L, char *base, hipStream_t s
     return MPDP_OK;
 }
 
+// Runs of tree levels of up to kSpanLevelPairs pairs each go to one
+// workgroup: there a level takes some 5 us and 2 ns a pair, a launch of its
+// own 7 to 8 us (random tree of 21, PG-like, and snowflake 25, C_out: 2500
+// pairs 198 / 235 us, 1000 pairs 191 / 234, 400 pairs 191 / 234).
+#ifndef MPDP_SPAN_LEVEL_PAIRS
+#define MPDP_SPAN_LEVEL_PAIRS 1000
+#endif
+constexpr uint64_t kSpanLevelPairs = MPDP_SPAN_LEVEL_PAIRS;
+constexpr uint32_t kFlatListMaxRel = 14;
+
 // One exact optimization in the workspace d_ws on stream s.  With
 // no_alloc, nothing is allocated on the host or the device: the query
 // information goes up and the plan comes back through pageable memory (the
@@ -415,8 +469,6 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     unsigned long long *tally = reinterpret_cast<unsigned long long *>(base + L.tally);
     DevGraph *dg = reinterpret_cast<DevGraph *>(base + L.graph);
     Counters *cnt = reinterpret_cast<Counters *>(base + L.counters);
-    mpdp_plan_node *dplan = reinterpret_cast<mpdp_plan_node *>(base + L.plan);
-    double *droot = reinterpret_cast<double *>(base + L.root);
 
     const bool timing = (flags & MPDP_FLAG_TIMING) != 0;
     if (timing && no_alloc) return MPDP_EINVAL;
@@ -425,9 +477,9 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
 
     DevGraph *hg = const_cast<DevGraph *>(&q.g);
     hg->ablate = (flags & MPDP_FLAG_ABLATE_DPSUB) ? mpdp::kAblateDpsub : 0u;
-    // upload and readback go through this thread's pinned staging buffer
-    // (plain DMA, no runtime-side staging copy); the call waits for its
-    // stream before returning, so the buffer is free again by the next call
+    // the query and the results pass through this thread's pinned staging
+    // buffer; the call waits for its stream before returning, so the buffer is
+    // free again by the next call
     const size_t down_bytes = L.root + sizeof(double) - L.counters;
     alignas(16) char down_stack[kNoAllocDownBytes];
     if (no_alloc && down_bytes > sizeof(down_stack)) return MPDP_ETOOLARGE;
@@ -459,11 +511,49 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     }
     std::vector<char> down_pageable((pin || no_alloc) ? 0 : down_bytes);
     char *down = pin ? pin : (no_alloc ? down_stack : down_pageable.data());
+    // tree joins: lists of connected sets, but for stars around relation 0
+    // (every set that holds it is connected) and the ablations
+    const bool tree_lists = !general && !unfused && (flags & MPDP_FLAG_ABLATE_NO_COMPACTION) == 0 &&
+                            (q.g.flat == 0 || n <= kFlatListMaxRel);
+    auto in_span = [&](uint32_t k) { return (k - 1) * q.sets[k] <= kSpanLevelPairs; };
     // the whole call on one stream: upload, init, every level, plan, readback
     auto enqueue = [&](hipStream_t st) -> hipError_t {
-        hipError_t e = hipMemcpyAsync(dg, pin ? static_cast<const void *>(pin) : static_cast<const void *>(&q.g),
-                                      sizeof(DevGraph), hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = mpdp::launch_init(dg, n, memo, general && !dpsub ? list : nullptr, arrived, tally, cnt, st);
+        // pinned staging: the first kernel fetches the query from it and the
+        // last one leaves the results in it
+        hipError_t e = pin ? hipSuccess : hipMemcpyAsync(dg, &q.g, sizeof(DevGraph), hipMemcpyHostToDevice, st);
+        const DevGraph *src = reinterpret_cast<const DevGraph *>(pin);
+        char *to = pin ? pin : reinterpret_cast<char *>(cnt);
+        const mpdp::Results res{reinterpret_cast<Counters *>(to),
+                                reinterpret_cast<mpdp_plan_node *>(to + (L.plan - L.counters)),
+                                reinterpret_cast<double *>(to + (L.root - L.counters))};
+        auto finish = [&](const unsigned long long *sums) -> hipError_t {
+            hipError_t f = mpdp::launch_extract(dg, n, memo, res, sums, cnt, st);
+            // counters, plan and root cost are adjacent in the workspace: one copy back
+            if (f == hipSuccess && !pin) f = hipMemcpyAsync(down, cnt, down_bytes, hipMemcpyDeviceToHost, st);
+            return f;
+        };
+        if (tree_lists) {
+            // runs of small levels by one workgroup, the others one launch each
+            for (uint32_t k = 2; k <= n && e == hipSuccess;) {
+                uint32_t k1 = k;
+                while (!timing && k1 <= n && in_span(k1)) ++k1;
+                if (k1 > k) {
+                    e = mpdp::launch_tree_span(src, dg, q.cost_model, n, k, k1 - 1, list, heavy, cnt, memo, st);
+                    k = k1;
+                    continue;
+                }
+                if (k == 2) e = mpdp::launch_init(src, dg, n, memo, list, arrived, tally, true, cnt, st);
+                if (timing && e == hipSuccess) e = hipEventRecord(ev.ev[4 * k - 8], st);
+                if (timing && e == hipSuccess) e = hipEventRecord(ev.ev[4 * k - 7], st);
+                if (e == hipSuccess)
+                    e = mpdp::launch_tree_level(dg, q.cost_model, n, k, q.sets[k], (k & 1u) ? heavy : list,
+                                                (k & 1u) ? list : heavy, cnt, memo, st);
+                if (timing && e == hipSuccess) e = hipEventRecord(ev.ev[4 * k - 6], st);
+                ++k;
+            }
+            return e == hipSuccess ? finish(nullptr) : e;
+        }
+        if (e == hipSuccess) e = mpdp::launch_init(src, dg, n, memo, general && !dpsub ? list : nullptr, arrived, tally, false, cnt, st);
         for (uint32_t k = 2; k <= n && e == hipSuccess; ++k) {
             const uint64_t nc = binom64(n, k);
             if (timing) e = hipEventRecord(ev.ev[4 * k - 8], st);
@@ -483,10 +573,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
                                             q.g.flat != 0, cnt, memo, st);
             if (e == hipSuccess && timing) e = hipEventRecord(ev.ev[4 * k - 6], st);
         }
-        if (e == hipSuccess) e = mpdp::launch_extract(dg, n, memo, dplan, droot, general && !dpsub ? tally : nullptr, cnt, st);
-        // counters, plan and root cost are adjacent in the workspace: one copy back
-        if (e == hipSuccess) e = hipMemcpyAsync(down, cnt, down_bytes, hipMemcpyDeviceToHost, st);
-        return e;
+        return e == hipSuccess ? finish(general && !dpsub ? tally : nullptr) : e;
     };
     if (pin) std::memcpy(pin, &q.g, sizeof(DevGraph));
     const bool graphed = pin && !timing && flags == 0 && n <= kGraphMaxRel;
@@ -494,7 +581,9 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
         // replay the sequence recorded once for this workspace, staging
         // buffer and shape (the upload reads the staging buffer at replay)
         hipGraphExec_t exec = nullptr;
-        HIPCHK(cached_graph(GraphKey{d_ws, pin, n, (uint32_t)q.cost_model, general, q.g.flat != 0}, enqueue, exec));
+        GraphKey key{d_ws, pin, n, (uint32_t)q.cost_model, general, q.g.flat != 0, {0}};
+        if (tree_lists) std::memcpy(key.sets, q.sets, sizeof(key.sets));
+        HIPCHK(cached_graph(key, enqueue, exec));
         HIPCHK(hipGraphLaunch(exec, s));
     } else {
         HIPCHK(enqueue(s));

@@ -16,7 +16,7 @@ constexpr int kMaxRel = 32;
 // Per-workgroup copy of the query information, laid out on the host exactly
 // as the kernels keep it in LDS so that staging is a plain 16-byte copy.
 // The kernels that work on lists of connected sets read only the prefix
-// before the binomials (kListLdsBytes).
+// before the preorder tables (kListLdsBytes).
 struct LdsImage {
     uint64_t loff[34];                        // memo offset of level k: sum of C(n, j), j < k
     double card[kMaxRel];
@@ -29,6 +29,9 @@ struct LdsImage {
     uint32_t selrow[kMaxRel];                 // first sel entry of relation v
     double sel[kMaxRel * (kMaxRel - 1) / 2];  // per v: sel(u, v) of edges u < v, u ascending
     uint32_t nb[4][256];                      // neighbours of a set, one table per bitmap byte
+    uint32_t pch[4][256];                     // tree joins, relations numbered in preorder from relation 0: children of
+                                              // a set, per byte
+    uint32_t perm[4][256];                    // and the set in the query's own numbers, per byte
     uint32_t ch[4][256];                      // tree joins rooted at 0: children of a set, per byte
     uint32_t binom[33 * 33];                  // C(a, b) at [a * 33 + b]
     uint32_t pad[3];
@@ -37,8 +40,9 @@ static_assert(offsetof(LdsImage, csel) % 16 == 0, "(card, sel) pairs are read as
 static_assert(offsetof(LdsImage, lo) % 8 == 0, "lowest-neighbour pairs are read as 8-byte units");
 static_assert(offsetof(LdsImage, pd) % 8 == 0, "(parent, subtree) pairs are read as 8-byte units");
 static_assert(offsetof(LdsImage, sel) % 16 == 0, "the image is copied in parts of 16-byte units");
-static_assert(offsetof(LdsImage, ch) % 16 == 0, "the list prefix ends on a 16-byte boundary");
-constexpr size_t kListLdsBytes = offsetof(LdsImage, ch);
+static_assert(offsetof(LdsImage, pch) % 16 == 0 && offsetof(LdsImage, ch) % 16 == 0,
+              "the image is copied in parts of 16-byte units");
+constexpr size_t kListLdsBytes = offsetof(LdsImage, pch);
 static_assert(sizeof(LdsImage) % 16 == 0, "LdsImage is copied in 16-byte units");
 
 // Query information as the kernels read it.  Built on the host, uploaded
@@ -96,6 +100,14 @@ struct SmallOut {
 };
 
 hipError_t launch_small(const SmallQuery &q, int cost_model, MemoPtrs memo, SmallOut *out, hipStream_t s);
+
+// Where a query's results go: pinned host memory, or the device region they
+// are copied back from.
+struct Results {
+    Counters *cnt;
+    mpdp_plan_node *plan;
+    double *root;
+};
 
 // Batched path (mpdp_batch.hip): one queue entry per workgroup at a time.
 // A query is one entry, or, if it is large and cyclic, kTeamSize entries in
@@ -159,16 +171,27 @@ hipError_t launch_batch(int cost_model, uint32_t workgroups, const BatchQueryDev
 // counters, zeroed by launch_init and left at zero by every level).  tally:
 // csg-cmp pairs and Alg. 3 candidates per workgroup, zeroed by launch_init,
 // summed by launch_extract (null there: not used).  list2:
-// where the connected sets of two relations go (null: no lists).
+// where the connected sets of two relations go (null: no lists; `preorder`:
+// those of a tree join, in preorder numbers).
 constexpr uint32_t kPairGrid = 256;            // one workgroup per CU
 constexpr uint32_t kPairBlock = 1024;
 constexpr uint32_t kPairWaves = kPairGrid * (kPairBlock / 64);
 
-hipError_t launch_init(const DevGraph *g, uint32_t n, MemoPtrs memo, uint32_t *list2, uint32_t *arrived,
-                       unsigned long long *tally, Counters *cnt, hipStream_t s);
+// src: the query in pinned host memory, brought to g on the way (null: g holds
+// it already).
+hipError_t launch_init(const DevGraph *src, DevGraph *g, uint32_t n, MemoPtrs memo, uint32_t *list2,
+                       uint32_t *arrived, unsigned long long *tally, bool preorder, Counters *cnt, hipStream_t s);
 // One level of the block-based path: the sets of k relations in `list`
 // (cnt->level_count[k] of them) evaluated, the sets of k + 1 into `next`.
 struct HeavyPart;
+// One level of a tree join, or levels k0 .. k1 by one workgroup (with k0 = 2
+// in place of launch_init).  even, odd: the lists of even and odd levels, in
+// preorder numbers; count: the sets of level k.
+constexpr uint32_t kTreeListGrid = 1024;
+hipError_t launch_tree_level(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, uint64_t count,
+                             const uint32_t *list, uint32_t *next, Counters *cnt, MemoPtrs memo, hipStream_t s);
+hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, uint32_t n, uint32_t k0, uint32_t k1,
+                            uint32_t *even, uint32_t *odd, Counters *cnt, MemoPtrs memo, hipStream_t s);
 hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,
                               uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
                               unsigned long long *tally, hipStream_t s);
@@ -213,7 +236,7 @@ __host__ __device__ inline uint32_t heavy_parts(uint32_t count, uint32_t grid) {
 hipError_t launch_eval_general(const DevGraph *g, int cost_model, uint32_t k, uint64_t ncand,
                                const uint32_t *list, uint32_t *heavy, Counters *cnt, MemoPtrs memo, HeavyPart *parts,
                                hipStream_t s);
-hipError_t launch_extract(const DevGraph *g, uint32_t n, MemoPtrs memo, mpdp_plan_node *plan,
-                          double *root_cost, const unsigned long long *tally, Counters *cnt, hipStream_t s);
+hipError_t launch_extract(const DevGraph *g, uint32_t n, MemoPtrs memo, Results down,
+                          const unsigned long long *tally, Counters *cnt, hipStream_t s);
 
 }  // namespace mpdp

@@ -24,27 +24,42 @@ namespace {
 
 // ---------------------------------------------------------------- kernels
 
-__global__ __launch_bounds__(kBlock) void k_init(const DevGraph *g, uint32_t n, MemoPtrs M, uint32_t *list2,
-                                                 uint32_t *arrived, unsigned long long *tally, Counters *cnt) {
+// Base relations, counters and level 2's list.  src: the query in pinned host
+// memory, which this kernel then also brings to g (one dispatch less than an
+// upload of its own), or null where g already holds it.
+constexpr int kInitBlock = 1024;
+
+__global__ __launch_bounds__(kInitBlock) void k_init(const DevGraph *src, DevGraph *g, uint32_t n, MemoPtrs M,
+                                                     uint32_t *list2, uint32_t *arrived, unsigned long long *tally,
+                                                     bool preorder, Counters *cnt) {
+    __shared__ __align__(16) DevGraph G;
     const uint32_t t = threadIdx.x;
+    bring_graph(src, g, G);
+    __syncthreads();
     if (t < n) {  // colex({t}) = t, level 1 starts at 1
-        const uint64_t at = g->lds.loff[1] + t;
-        M.cost[at] = g->lds.bcost[t];
-        M.card[at] = g->lds.card[t];
+        const uint64_t at = G.lds.loff[1] + t;
+        M.cost[at] = G.lds.bcost[t];
+        M.card[at] = G.lds.card[t];
         M.left[at] = 0;
         M.op[at] = MPDP_OP_SCAN;
-        // the connected sets of two relations: the edges, by their higher end
-        uint32_t e = 0;
-        for (uint32_t w = 0; list2 && w < t; ++w) e += (uint32_t)popc32(g->lds.adj[w] & ((1u << w) - 1u));
-        for (uint32_t U = list2 ? g->lds.adj[t] & ((1u << t) - 1u) : 0u; U; U &= U - 1) list2[e++] = (1u << t) | lowbit(U);
+        // the connected sets of two relations: the edges (tree joins: as the
+        // preorder numbers have them), by their higher end
+        if (list2 && preorder) {
+            for (uint32_t C = G.lds.pch[t >> 3][1u << (t & 7u)]; C; C &= C - 1u)
+                list2[ctz32(C) - 1] = (1u << t) | lowbit(C);
+        } else if (list2) {
+            uint32_t e = 0;
+            for (uint32_t w = 0; w < t; ++w) e += (uint32_t)popc32(G.lds.adj[w] & ((1u << w) - 1u));
+            for (uint32_t U = G.lds.adj[t] & ((1u << t) - 1u); U; U &= U - 1) list2[e++] = (1u << t) | lowbit(U);
+        }
     }
-    if (list2) {
+    if (list2 && !preorder) {
         for (uint32_t i = t; i < kPairWaves; i += blockDim.x) arrived[i] = 0u;
         for (uint32_t i = t; i < 2 * kPairGrid; i += blockDim.x) tally[i] = 0ull;
     }
     uint32_t *words = reinterpret_cast<uint32_t *>(cnt);
     for (uint32_t i = t; i < sizeof(Counters) / 4; i += blockDim.x)
-        words[i] = i == offsetof(Counters, level_count) / 4 + 2 && list2 ? g->m : 0u;
+        words[i] = i == offsetof(Counters, level_count) / 4 + 2 && list2 ? G.m : 0u;
 }
 
 // The ranges of nw wave-sized pieces of a level that this wave walks (w0,
@@ -284,17 +299,18 @@ __global__ __launch_bounds__(64) void k_heavy_reduce(const DevGraph *g, uint32_t
 }
 
 // Rebuild the plan (Section 5: fetched recursively through left/right) in
-// post-order with one wave (see extract_plan).
-__global__ __launch_bounds__(64) void k_extract(const DevGraph *g, uint32_t n, MemoPtrs M, mpdp_plan_node *plan,
-                                                double *root_cost, const unsigned long long *tally, Counters *cnt) {
+// post-order with one wave (see extract_plan), and the counters: into `down`,
+// the caller's pinned memory or the place they are copied back from.
+__global__ __launch_bounds__(64) void k_extract(const DevGraph *g, uint32_t n, MemoPtrs M, Results down,
+                                                const unsigned long long *tally, Counters *cnt) {
     __shared__ uint32_t binom[33 * 33];
     __shared__ uint64_t loff[34];
     __shared__ PlanScratch P;
     for (uint32_t i = threadIdx.x; i < 33 * 33; i += blockDim.x) binom[i] = g->lds.binom[i];
     if (threadIdx.x < 34) loff[threadIdx.x] = g->lds.loff[threadIdx.x];
     __syncthreads();
+    unsigned long long ccp = 0, evaluated = 0;
     if (tally) {
-        unsigned long long ccp = 0, evaluated = 0;
         for (uint32_t i = threadIdx.x; i < kPairGrid; i += blockDim.x) {
             ccp += tally[2 * i];
             evaluated += tally[2 * i + 1];
@@ -303,13 +319,16 @@ __global__ __launch_bounds__(64) void k_extract(const DevGraph *g, uint32_t n, M
             ccp += (unsigned long long)__shfl_xor((long long)ccp, off);
             evaluated += (unsigned long long)__shfl_xor((long long)evaluated, off);
         }
-        if (threadIdx.x == 0) {
-            cnt->ccp += ccp;
-            cnt->evaluated += evaluated;
-        }
     }
-    if (!extract_plan(binom, loff, M, n, plan, root_cost, P, threadIdx.x, blockDim.x) && threadIdx.x == 0)
-        cnt->extract_error = 1;
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(cnt);
+    for (uint32_t i = threadIdx.x; i < offsetof(Counters, extract_error) / 4; i += blockDim.x)
+        reinterpret_cast<uint32_t *>(down.cnt)[i] = words[i];
+    if (threadIdx.x == 0) {
+        down.cnt->ccp = cnt->ccp + ccp;
+        down.cnt->evaluated = cnt->evaluated + evaluated;
+    }
+    const bool ok = extract_plan(binom, loff, M, n, down.plan, down.root, P, threadIdx.x, blockDim.x);
+    if (threadIdx.x == 0) down.cnt->extract_error = ok ? 0u : 1u;
 }
 
 uint32_t grid_for(uint64_t items, uint64_t per_block) {
@@ -320,9 +339,9 @@ uint32_t grid_for(uint64_t items, uint64_t per_block) {
 
 }  // namespace
 
-hipError_t launch_init(const DevGraph *g, uint32_t n, MemoPtrs memo, uint32_t *list2, uint32_t *arrived,
-                       unsigned long long *tally, Counters *cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_init, dim3(1), dim3(kBlock), 0, s, g, n, memo, list2, arrived, tally, cnt);
+hipError_t launch_init(const DevGraph *src, DevGraph *g, uint32_t n, MemoPtrs memo, uint32_t *list2,
+                       uint32_t *arrived, unsigned long long *tally, bool preorder, Counters *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(k_init, dim3(1), dim3(kInitBlock), 0, s, src, g, n, memo, list2, arrived, tally, preorder, cnt);
     return hipGetLastError();
 }
 
@@ -471,9 +490,9 @@ hipError_t launch_eval_general(const DevGraph *g, int cost_model, uint32_t k, ui
     return hipGetLastError();
 }
 
-hipError_t launch_extract(const DevGraph *g, uint32_t n, MemoPtrs memo, mpdp_plan_node *plan,
-                          double *root_cost, const unsigned long long *tally, Counters *cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_extract, dim3(1), dim3(64), 0, s, g, n, memo, plan, root_cost, tally, cnt);
+hipError_t launch_extract(const DevGraph *g, uint32_t n, MemoPtrs memo, Results down,
+                          const unsigned long long *tally, Counters *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(k_extract, dim3(1), dim3(64), 0, s, g, n, memo, down, tally, cnt);
     return hipGetLastError();
 }
 

@@ -469,6 +469,9 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
 // lowest relation (which can always be removed), so that every set is listed
 // once.  One search per neighbour, against C(n, k + 1) subsets to unrank and
 // search; `group` lanes (a power of two) divide the neighbours of one set.
+// kTree: sets of a tree join in preorder numbers, for which the sets that
+// add a child numbered above every member are all there is to list (a set's
+// last relation in preorder has no child in it), without any search.
 // The waves of a workgroup collect their sets in LDS (`buf`, `cap` words) and
 // append them with one atomic on the list's end: some 30 ns each when all workgroups add to one word, an atomic per 64
 // sets or per wave made that word the bound of the smaller levels.  Starts
@@ -477,6 +480,7 @@ struct ExpandEnds {
     uint32_t fill, end, start;  // words taken, first word not used, place in the list
 };
 
+template <bool kTree>
 __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t count, uint32_t *out, uint32_t *out_count,
                             uint32_t w, uint32_t nw, uint32_t group, uint32_t *buf, uint32_t cap, ExpandEnds &ends,
                             uint32_t lane) {
@@ -487,13 +491,13 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
     for (uint32_t base = w * each; base < count; base += nw * each) {
         const uint32_t i = base + lane / group;
         const uint32_t S = i < count ? list[i] : 0u;
-        uint32_t N = nbrs(L.nb, S) & ~S;
+        uint32_t N = kTree ? nbrs(L.pch, S) & ~(0xffffffffu >> __builtin_clz(S | 1u)) : nbrs(L.nb, S) & ~S;
         for (uint32_t j = 0; j < sub; ++j) N &= N - 1u;
         while (__ballot(N != 0u) != 0ull) {
             const uint32_t v = lowbit(N), S1 = S | v;
             for (uint32_t j = 0; j < group; ++j) N &= N - 1u;
-            bool keep = false;
-            if (v != 0u) {
+            bool keep = kTree && v != 0u;
+            if (!kTree && v != 0u) {
                 uint32_t seen = lowbit(S1), fr = seen;
                 while (seen != S1) {  // S1 is connected
                     fr = nbrs(L.nb, fr) & S1 & ~seen;
@@ -525,6 +529,115 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < have; i += blockDim.x) out[ends.start + i] = buf[i];
     __syncthreads();
+}
+
+// ---------------------------------------------------------------- tree joins
+
+// Alg. 2 for the sets list[0 .. count) of a tree join (in preorder numbers),
+// 2^lgP lanes a set:
+// with the tree rooted at relation 0, the edge (parent(c), c) of G[S] gives
+// the pair (S and c's subtree, the rest) for every member c whose parent is
+// a member.  The lanes of a group take every 2^lgP-th member, four at a time
+// with all their reads in flight; a member without a pair (the topmost, or
+// past the end) reads entry 0 and offers nothing.  `thread` of `threads`
+// (groups of lanes never straddle waves).
+template <int CM>
+__device__ void eval_tree_list(const LdsGraph &L, const uint32_t *T, bool wide, const MemoPtrs &M,
+                               const uint32_t *list, uint32_t count, uint32_t k, uint32_t lgP, uint32_t thread,
+                               uint32_t threads) {
+    const uint32_t P = 1u << lgP, sub = thread & (P - 1u);
+    for (uint32_t i = thread >> lgP; i < count; i += threads >> lgP) {
+        const uint32_t S = nbrs(L.perm, list[i]);
+        double cS;
+        tree_card_n<1>(L, &S, k, &cS);
+        double bc = __builtin_inf();
+        uint32_t bl = ~0u, bop = ~0u, U = S;
+        for (uint32_t j = 0; j < sub; ++j) U &= U - 1u;
+        while (U) {
+            uint32_t A[4];
+            uint64_t ia[4], ib[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t c = (uint32_t)ctz32(U | 0x80000000u);
+                const uint2 pd = *reinterpret_cast<const uint2 *>(L.pd[c]);  // parent bit, subtree
+                A[u] = U != 0u && (S & pd.x) != 0u ? pd.y & S : 0u;
+                for (uint32_t j = 0; j < P; ++j) U &= U - 1u;
+                const uint32_t ka = (uint32_t)popc32(A[u]);
+                ia[u] = A[u] ? L.loff[ka] + colex_rank(T, A[u], wide) : 0ull;
+                ib[u] = A[u] ? L.loff[k - ka] + colex_rank(T, S ^ A[u], wide) : 0ull;
+            }
+            double cA[4], cB[4], kA[4], kB[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                cA[u] = M.cost[ia[u]];
+                cB[u] = M.cost[ib[u]];
+                kA[u] = CM == MPDP_COST_COUT ? 0.0 : M.card[ia[u]];
+                kB[u] = CM == MPDP_COST_COUT ? 0.0 : M.card[ib[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t B = S ^ A[u];
+                const double base = cA[u] + cB[u];
+                double c;
+                uint32_t l, op;
+                if (CM == MPDP_COST_COUT) {
+                    c = base + cS;
+                    l = A[u] < B ? A[u] : B;
+                    op = MPDP_OP_JOIN;
+                } else {
+                    const double out = 0.01 * cS;
+                    const double hjA = ((base + 0.0125 * kB[u]) + 0.0025 * kA[u]) + out;  // A outer, B hashed
+                    const double nlA = (base + (0.0025 * kA[u]) * kB[u]) + out;
+                    const double hjB = ((base + 0.0125 * kA[u]) + 0.0025 * kB[u]) + out;  // B outer, A hashed
+                    const double nlB = (base + (0.0025 * kB[u]) * kA[u]) + out;
+                    const bool hA = hjA <= nlA, hB = hjB <= nlB;
+                    const double ca = hA ? hjA : nlA, cb = hB ? hjB : nlB;
+                    const bool first = (ca < cb) | ((ca == cb) & (A[u] < B));
+                    c = first ? ca : cb;
+                    l = first ? A[u] : B;
+                    op = (first ? hA : hB) ? MPDP_OP_HASH : MPDP_OP_NESTLOOP;
+                }
+                // a set's offers all have different left sets, so cost and
+                // left set order them
+                const bool take = A[u] != 0u && ((c < bc) | ((c == bc) & (l < bl)));
+                bc = take ? c : bc;
+                bl = take ? l : bl;
+                bop = take ? op : bop;
+            }
+        }
+        for (uint32_t d = 1; d < P; d <<= 1) {
+            const double oc = __shfl_xor(bc, (int)d, 64);
+            const uint32_t ol = (uint32_t)__shfl_xor((int)bl, (int)d, 64), oo = (uint32_t)__shfl_xor((int)bop, (int)d, 64);
+            const bool take = (oc < bc) | ((oc == bc) & (ol < bl));
+            bc = take ? oc : bc;
+            bl = take ? ol : bl;
+            bop = take ? oo : bop;
+        }
+        if (sub == 0u)
+            store_best(M, L.loff[k] + colex_rank(T, S, wide),
+                       Key{(unsigned long long)__double_as_longlong(bc), bl, bop}, cS);
+    }
+}
+
+// Relation u's share of the list of two-relation sets of a tree join: in
+// preorder numbers, u and each of its children.  A relation's edge to its
+// parent sits at the relation's number less one.
+__device__ __forceinline__ void first_tree_list(const LdsGraph &L, uint32_t u, uint32_t *list2) {
+    for (uint32_t C = nbrs(L.pch, 1u << u); C; C &= C - 1u) list2[ctz32(C) - 1] = (1u << u) | lowbit(C);
+}
+
+// Lanes per set (2^0 .. 2^3): as many as `threads` lanes leave the level.
+__device__ __forceinline__ uint32_t tree_group(uint32_t count, uint32_t threads) {
+    uint32_t lgP = 0;
+    while (lgP < 3u && (2u * count << lgP) <= threads) ++lgP;
+    return lgP;
+}
+
+// Lanes that grow one set's successors (expand_sets).
+__device__ __forceinline__ uint32_t expand_group(uint32_t count, uint32_t threads) {
+    uint32_t group = 1;
+    while (group < 16u && 2u * count * group <= threads) group <<= 1;
+    return group;
 }
 
 }  // namespace

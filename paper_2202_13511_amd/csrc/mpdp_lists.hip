@@ -3,6 +3,8 @@
 // the next level's list.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "mpdp_internal.h"
 #include "mpdp_lists.h"
 
@@ -35,8 +37,7 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
     // another round for the last few sets
     const uint32_t rounds = (count + 64u * nw - 1u) / (64u * nw);
     const uint32_t per = (count + rounds * nw - 1u) / (rounds * nw);
-    uint32_t group = 1u;  // lanes that grow one set's successors
-    while (group < 16u && count * group < 32u * nw) group <<= 1;
+    const uint32_t group = expand_group(count, 64u * nw);
     const uint32_t parts = k >= kShareMinK && 2u * count <= nw ? min(64u, nw / count) : 1u;
     // neighbouring items to different CUs, so that few items still fill the chip
     const uint32_t lane = threadIdx.x & 63u, w = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
@@ -48,7 +49,7 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
     if (threadIdx.x < 2) sums[threadIdx.x] = 0ull;
     __syncthreads();
     if (k < n)
-        expand_sets(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, reinterpret_cast<uint32_t *>(buf),
+        expand_sets<false>(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, reinterpret_cast<uint32_t *>(buf),
                     sizeof(buf) / 4, ends, lane);
     unsigned long long ccp = 0, evaluated = 0;
     eval_pairs<CM>(L, ranks, n > 24u, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6],
@@ -65,6 +66,79 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
     if (threadIdx.x < 2) tally[2 * blockIdx.x + threadIdx.x] += sums[threadIdx.x];
 }
 
+// One level of a tree join: the first `eval` workgroups cost the level's
+// sets, the others grow the next level's list, so that neither waits for the
+// other's reads.
+constexpr int kTreeBlock = 256;
+constexpr uint32_t kTreeExpand = 4096;  // words of the expansion's LDS buffer
+
+template <int CM>
+__global__ __launch_bounds__(kTreeBlock) void k_tree_level(const DevGraph *g, uint32_t n, uint32_t k, uint32_t eval,
+                                                           const uint32_t *list, uint32_t *next, Counters *cnt,
+                                                           MemoPtrs M) {
+    __shared__ __align__(16) LdsGraph L;
+    __shared__ __align__(16) uint32_t ranks[kRankWords > kTreeExpand ? kRankWords : kTreeExpand];
+    __shared__ ExpandEnds ends;
+    const uint32_t count = cnt->level_count[k], lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    stage_graph_preorder(g, L);
+    if (blockIdx.x < eval) {
+        stage_ranks(ranks, n);
+        __syncthreads();
+        const uint32_t threads = eval * kTreeBlock;
+        eval_tree_list<CM>(L, ranks, n > 24u, M, list, count, k, tree_group(count, threads),
+                           (wave * eval + blockIdx.x) * 64u + lane, threads);
+    } else {
+        const uint32_t blocks = gridDim.x - eval, threads = blocks * kTreeBlock;
+        expand_sets<true>(L, list, count, next, &cnt->level_count[k + 1], wave * blocks + blockIdx.x - eval,
+                          threads / 64, 1u, ranks, kTreeExpand, ends, lane);
+    }
+}
+
+// Levels k0 .. k1 of a tree join by one workgroup, barriers between them:
+// levels of a few thousand pairs take less time than a launch.  The span that
+// starts at level 2 also fills the base relations and level 2's list (and
+// needs no k_init).
+constexpr int kSpanBlock = 1024;
+constexpr uint32_t kSpanExpand = 16384;
+
+template <int CM>
+__global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, DevGraph *g, uint32_t n, uint32_t k0,
+                                                          uint32_t k1, uint32_t *even, uint32_t *odd, Counters *cnt,
+                                                          MemoPtrs M) {
+    __shared__ __align__(16) DevGraph G;
+    __shared__ __align__(16) uint32_t ranks[kRankWords];
+    __shared__ uint32_t buf[kSpanExpand];
+    __shared__ ExpandEnds ends;
+    const uint32_t t = threadIdx.x;
+    const LdsGraph &L = G.lds;
+    bring_graph(k0 == 2u ? src : nullptr, g, G);
+    stage_ranks(ranks, n);
+    if (k0 == 2u) {
+        uint32_t *words = reinterpret_cast<uint32_t *>(cnt);
+        for (uint32_t i = t; i < sizeof(Counters) / 4; i += blockDim.x)
+            words[i] = i == offsetof(Counters, level_count) / 4 + 2 ? n - 1u : 0u;
+    }
+    __syncthreads();
+    if (k0 == 2u && t < n) {
+        const uint64_t at = L.loff[1] + t;
+        M.cost[at] = L.bcost[t];
+        M.card[at] = L.card[t];
+        M.left[at] = 0;
+        M.op[at] = MPDP_OP_SCAN;
+    }
+    if (k0 == 2u && t >= 64u && t - 64u < n) first_tree_list(L, t - 64u, even);
+    __syncthreads();
+    for (uint32_t k = k0; k <= k1; ++k) {
+        const uint32_t *list = (k & 1u) ? odd : even;
+        const uint32_t count = __hip_atomic_load(&cnt->level_count[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (k < n)
+            expand_sets<true>(L, list, count, (k & 1u) ? even : odd, &cnt->level_count[k + 1], t >> 6,
+                              kSpanBlock / 64, 1u, buf, kSpanExpand, ends, t & 63u);
+        eval_tree_list<CM>(L, ranks, n > 24u, M, list, count, k, tree_group(count, kSpanBlock), t, kSpanBlock);
+        __syncthreads();
+    }
+}
+
 }  // namespace
 
 hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,
@@ -76,6 +150,32 @@ hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uin
     else
         hipLaunchKernelGGL(k_level_pairs<MPDP_COST_PGLIKE>, dim3(kPairGrid), dim3(kPairBlock), 0, s, g, n, k, list,
                            next, cnt, memo, rec, arrived, tally);
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_level(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, uint64_t count,
+                             const uint32_t *list, uint32_t *next, Counters *cnt, MemoPtrs memo, hipStream_t s) {
+    // eight lanes a set, up to four workgroups per CU; one lane a set to grow
+    // the list, up to one workgroup per CU
+    const uint32_t eval = (uint32_t)std::min<uint64_t>((count * 8 + kTreeBlock - 1) / kTreeBlock, kTreeListGrid);
+    const uint32_t grid = eval + (k < n ? (uint32_t)std::min<uint64_t>((count + kTreeBlock - 1) / kTreeBlock, 256) : 0u);
+    if (cost_model == MPDP_COST_COUT)
+        hipLaunchKernelGGL(k_tree_level<MPDP_COST_COUT>, dim3(grid), dim3(kTreeBlock), 0, s, g, n, k, eval, list, next,
+                           cnt, memo);
+    else
+        hipLaunchKernelGGL(k_tree_level<MPDP_COST_PGLIKE>, dim3(grid), dim3(kTreeBlock), 0, s, g, n, k, eval, list,
+                           next, cnt, memo);
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, uint32_t n, uint32_t k0, uint32_t k1,
+                            uint32_t *even, uint32_t *odd, Counters *cnt, MemoPtrs memo, hipStream_t s) {
+    if (cost_model == MPDP_COST_COUT)
+        hipLaunchKernelGGL(k_tree_span<MPDP_COST_COUT>, dim3(1), dim3(kSpanBlock), 0, s, src, g, n, k0, k1, even, odd,
+                           cnt, memo);
+    else
+        hipLaunchKernelGGL(k_tree_span<MPDP_COST_PGLIKE>, dim3(1), dim3(kSpanBlock), 0, s, src, g, n, k0, k1, even,
+                           odd, cnt, memo);
     return hipGetLastError();
 }
 

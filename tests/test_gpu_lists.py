@@ -58,6 +58,30 @@ def test_full_pools_and_shared_sets(q, cm):
     check_stats(q, res, ref, general=True)
 
 
+def hub_tree(n, hub):
+    """A star around another relation than 0, one leaf of it a chain of two."""
+    others = [v for v in range(n) if v != hub]
+    return [[hub, v] for v in others[:-1]] + [[others[0], others[-1]]]
+
+
+@pytest.mark.parametrize("cm", CMS)
+@pytest.mark.parametrize("q", [W.random_tree(13, 1), W.random_tree(17, 2), W.random_tree(18, 3), W.chain(17, 4),
+                               W.snowflake(18, 5), W.from_edges(15, hub_tree(15, 9), 6, "hub15"),
+                               W.from_edges(16, hub_tree(16, 15), 7, "hub16")], ids=lambda q: q.name)
+def test_tree_lists(q, cm):
+    """Tree joins of every shape (levels in one workgroup, levels of their
+    own, one to eight lanes a set), numbered at random."""
+    res, gm = run_ws(q, cm)
+    ref = oracle.mpdp(q, cm)
+    check_memo(q, gm, ref)
+    check_plan(q, res, ref)
+    check_stats(q, res, ref, general=False)
+    res, gm = run_ws(q, cm, flags=mpdp.MPDP_FLAG_TIMING)
+    check_memo(q, gm, ref)
+    check_plan(q, res, ref)
+    assert res.stats["ms_eval"] > 0
+
+
 @pytest.mark.parametrize("n", [24, 25, 31, 32])
 def test_cycle_ranks(n):
     """A cycle's counts in closed form, and its optimum: the best of the chains

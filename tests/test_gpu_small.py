@@ -1,8 +1,8 @@
 """Queries that run as one launch of one workgroup, against the CPU oracle
 (every memo entry, plan and counters, bit for bit) over the sizes of its
 parts: two relations, the last size below one wave and one workgroup of
-subsets, the largest, the first beyond; and costs that overflow to infinity,
-where only the left set decides."""
+subsets, the largest, the first beyond; and costs that overflow to infinity
+(there and on the larger queries' paths), where only the left set decides."""
 import numpy as np
 import pytest
 
@@ -43,7 +43,7 @@ def test_sizes(n, cm):
 @pytest.mark.parametrize("cm", CMS)
 @pytest.mark.parametrize("make", [W.star, W.random_tree, W.cycle, lambda n, s: W.random_connected(n, s, 0.3)],
                          ids=["star", "tree", "cycle", "random"])
-@pytest.mark.parametrize("n", [8, 12])
+@pytest.mark.parametrize("n", [8, 12, 14])
 def test_infinite_costs(n, make, cm):
     q = make(n, 3)
     q.card = np.where(np.arange(n) % 3 == 1, 1e308, 10.0)
