@@ -251,17 +251,19 @@ typedef struct {
 /* Device workspace bytes for mpdp_optimize_batch (0 if a query is invalid in
  * size: n = 0 or n > 20).  It grows with the total input and output sizes
  * and with at most 512 memo slots of 2^max_n entries, not with nq itself
- * (plus a few hundred bytes per cyclic query of 17 or more relations, which
- * may be shared by a team of workgroups). */
+ * (plus a few hundred bytes per cyclic query of 17 or more relations, as room
+ * for teams of workgroups that share a query). */
 size_t mpdp_batch_workspace_bytes(uint32_t nq, const mpdp_batch_query *queries);
 
 /*
  * Optimize nq queries in one persistent launch on hip_stream: every
  * workgroup takes the next query, runs all its DP levels with workgroup
- * barriers between levels, and writes its plan.  A cyclic query of 17 or
- * more relations that is predicted to be slow is taken by a team of 4 or 8
- * workgroups, which split every level and meet at device-wide barriers
- * (each wait bounded; a team that times out reports MPDP_EDEVICE).
+ * barriers between levels, and writes its plan.  A query of 17 or more
+ * relations that is predicted to take a large part of the batch's time is
+ * taken by a team of 2, 4 or 8 workgroups, which split every level and meet
+ * at device-wide barriers (each wait bounded; a team that times out reports
+ * MPDP_EDEVICE); there are at most as many teams as cyclic queries of 17 or
+ * more relations.
  * Results equal those of mpdp_optimize on each query alone.
  *   plans_out      host, sum over q of (2 n_q - 1) nodes; query q's plan
  *                  (layout of mpdp_plan_node) starts after those of 0..q-1
@@ -289,11 +291,13 @@ mpdp_status mpdp_optimize_batch(uint32_t nq, const mpdp_batch_query *queries, co
 /*
  * Schedule of one query in the batched kernel (defaults in brackets, which
  * mpdp_optimize_batch uses):
- *   tree_chunk    acyclic queries: consecutive colex ranks per lane in each
- *                 level's fused unrank, filter and evaluate pass: 1, 2 or 4 [4]
- *   heavy_chunks  cyclic queries: a set whose Alg. 3 candidates fill more
- *                 than this many chunks of 16 is evaluated by the whole
- *                 workgroup, a smaller one by one wave: 1 .. 65535 [256]
+ *   tree_chunk    stars around relation 0: consecutive colex ranks per lane
+ *                 in each level's fused unrank and evaluate pass: 1, 2 or 4
+ *                 [4]; no effect on other acyclic queries
+ *   heavy_chunks  cyclic queries: sets whose 2^k subsets fill at least this
+ *                 many chunks of 16 are shared by several waves on levels
+ *                 with fewer sets than waves, smaller ones go to one wave
+ *                 each: 1 .. 65535 [256]
  * Every schedule gives the same plans and costs; only the time differs.
  */
 typedef struct { uint32_t tree_chunk, heavy_chunks; } mpdp_batch_schedule;

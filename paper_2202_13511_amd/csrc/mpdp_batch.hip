@@ -4,31 +4,29 @@
 // whole level loop of Alg. 5 for it, with workgroup barriers between levels
 // instead of kernel launches: it builds the query's LDS image from the raw
 // edges, cardinalities and selectivities, fills the base relations, runs
-// levels 2..n (Alg. 2 for tree joins, Alg. 3 otherwise: filter, one wave per
-// light set, the whole workgroup per heavy set), rebuilds the plan and
-// records the device wall clock at the query's start and end.  Memo and
+// levels 2..n, rebuilds the plan and records the device wall clock at the
+// query's start and end.  A level is its list of connected sets, grown from
+// the level before (see mpdp_lists.h): tree joins cost their edges (Alg. 2),
+// the others search their csg-cmp pairs; of a star around relation 0 every
+// set of relation 0 and others is connected, so it needs no lists.  Memo and
 // scratch live in a per-workgroup slot that is reused from query to query,
-// so the workspace does not grow with the batch.  A large cyclic query is
+// so the workspace does not grow with the batch.  A large query may be
 // taken by a team of workgroups (consecutive queue entries): they split the
-// candidates and sets of every level and meet at device-wide barriers, in
-// the slot of the team's first member.  Entries are taken in queue order,
-// so a member waiting at a barrier waits only for workgroups that have
-// already taken their entries, or for ones that will take them next.
+// sets of every level and meet at device-wide barriers, in the slot of the
+// team's first member.  Entries are taken in queue order, so a member
+// waiting at a barrier waits only for workgroups that have already taken
+// their entries, or for ones that will take them next.
 #include <hip/hip_runtime.h>
 
 #include "mpdp_device.h"
 #include "mpdp_internal.h"
+#include "mpdp_lists.h"
 
 namespace mpdp {
 namespace {
 
 constexpr int kBatchBlock = 512;
 constexpr int kBW = kBatchBlock / 64;
-// members per gather batch of a tree set: three keeps the kernel (every
-// path of a query inlined, 128 registers per lane) from spilling far more
-constexpr int kBatchPairBatch = 3;
-// (for the same reason Alg. 3's candidate chunks take the plain subset walk
-// here, without the per-chunk neighbourhood tables)
 constexpr unsigned long long kTeamWaitTicks = 200000000ull;  // 2 s of the 100 MHz device clock
 
 // The workgroups of a team meet here for the `phase`-th time.  Every wave
@@ -69,11 +67,27 @@ __device__ __forceinline__ uint32_t load_shared_count(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Workgroups' LDS, two per CU: 160 KB / 2 less the image and rank table.
+// A search path leaves less than two states per relation behind.
+using BatchBuf = PairBufN<240, 2 * kBatchMaxRel>;
+static_assert(3 * (240 + 2 * kBatchMaxRel) >= 64 * (kBatchMaxRel / 2), "block_candidates' pieces");
+
+// What the waves keep while a level runs; the plan is rebuilt in its place.
+union BatchScratch {
+    BatchBuf pairs[kBW];
+    struct {
+        uint32_t set[kBW][flat_block_words(kTreeChunkMax)], bsum[kBW][flat_block_words(kTreeChunkMax)];
+    } flat;
+    uint32_t grow[sizeof(BatchBuf) * kBW / 4];  // expand_sets
+    PlanScratch plan;
+};
+
 // Build the LDS image of one query inside the workgroup (everything except
-// the binomials, which are staged once per workgroup).
+// the binomials, which are staged once per workgroup; no children table).
+// num, kids: scratch, a tree join's preorder numbers and children in them.
 __device__ void build_image(LdsGraph &L, const BatchQueryDev &Q, const uint32_t *edges, const double *cards,
-                            const double *sels, const double *bcosts) {
-    const uint32_t t = threadIdx.x, n = Q.n, m = Q.m;
+                            const double *sels, const double *bcosts, uint32_t *num, uint32_t *kids) {
+    const uint32_t t = threadIdx.x, n = Q.n, m = Q.m, full = (1u << n) - 1u;
     const uint32_t *E = edges + 2ull * Q.edge_off;
     const double *C = cards + Q.card_off;
     const double *SL = sels + Q.edge_off;
@@ -89,6 +103,11 @@ __device__ void build_image(LdsGraph &L, const BatchQueryDev &Q, const uint32_t 
         if (t >= n) L.bcost[t] = 0.0;
         else if (bcosts) L.bcost[t] = bcosts[Q.card_off + t];  // planned intermediate results
         else L.bcost[t] = Q.cost_model == MPDP_COST_PGLIKE ? 0.01 * C[t] : 0.0;
+    } else if (t >= 64u && t < 98u) {
+        const uint32_t k = t - 64u;
+        uint64_t off = 0;
+        for (uint32_t j = 0; j < k && j <= n; ++j) off += L.binom[n * 33 + j];
+        L.loff[k] = off;
     }
     __syncthreads();
     for (uint32_t e = t; e < m; e += blockDim.x) {
@@ -97,64 +116,93 @@ __device__ void build_image(LdsGraph &L, const BatchQueryDev &Q, const uint32_t 
         atomicOr(&L.adj[v], 1u << u);
     }
     __syncthreads();
-    if (t < n) {  // selectivities of edges (u, v), u < v, grouped by v, u ascending
-        const uint32_t lower = L.adj[t] & ((1u << t) - 1u);
+    if (t < 64u) {  // wave 0
+        // selectivities of edges (u, v), u < v, grouped by v, u ascending
+        const uint32_t lower = t < n ? L.adj[t] & ((1u << t) - 1u) : 0u;
         uint32_t start = 0;
-        for (uint32_t w = 0; w < t; ++w) start += (uint32_t)popc32(L.adj[w] & ((1u << w) - 1u));
-        L.selrow[t] = start;
-        for (uint32_t e = 0; e < m; ++e) {
+        for (uint32_t w = 0; w < n; ++w) start += w < t ? (uint32_t)popc32(L.adj[w] & ((1u << w) - 1u)) : 0u;
+        if (t < n) {
+            L.selrow[t] = start;
+            L.lo[t][0] = lowbit(lower);
+            L.lo[t][1] = lower & ~lowbit(lower);
+        }
+        wave_sync_lds();
+        for (uint32_t e = t; e < m; e += 64u) {
             const uint32_t a = E[2 * e], b = E[2 * e + 1];
             const uint32_t hi = a > b ? a : b, lo = a > b ? b : a;
-            if (hi == t) L.sel[start + (uint32_t)popc32(lower & ((1u << lo) - 1u))] = SL[e];
+            L.sel[L.selrow[hi] + (uint32_t)popc32(L.adj[hi] & ((1u << lo) - 1u))] = SL[e];
         }
-        L.lo[t][0] = lower & (0u - lower);
-        L.lo[t][1] = lower & ~(lower & (0u - lower));
-        L.csel[t][1] = lower ? L.sel[start] : 1.0;  // written by this thread above
+        wave_sync_lds();
+        if (lower) L.csel[t][1] = L.sel[start];
+    } else if (t < 128u && Q.is_tree) {  // wave 1, relation v = lane
+        // rooted at relation 0: parents by breadth-first rounds, subtrees from
+        // the last round up, preorder numbers from the first down
+        const uint32_t v = t - 64u, av = v < n ? L.adj[v] : 0u;
+        uint32_t fr = 1u, seen = 1u, depth = 0, round = 0, par = 0;
+        while (seen != full) {
+            ++round;
+            const bool in = (av & fr) != 0u && ((seen >> (v & 31u)) & 1u) == 0u;
+            if (in) {
+                par = av & fr;
+                depth = round;
+            }
+            fr = (uint32_t)__ballot(in);
+            if (fr == 0u) break;
+            seen |= fr;
+        }
+        const uint32_t last = round, up = par ? (uint32_t)ctz32(par) : 0u;
+        if (v < n) L.pd[v][0] = par;
+        for (uint32_t d = last; d >= 1u; --d) {
+            wave_sync_lds();
+            if (depth == d && par) atomicOr(&L.pd[up][1], L.pd[v][1]);
+        }
+        wave_sync_lds();
+        if (v < n) kids[v] = 0;
+        uint32_t before = 1;  // relations between the parent and v in preorder, and the parent
+        if (par)
+            for (uint32_t U = L.adj[up] & ~L.pd[up][0] & ((1u << v) - 1u); U; U &= U - 1u)
+                before += (uint32_t)popc32(L.pd[ctz32(U)][1]);
+        if (v == 0u) num[0] = 0;
+        for (uint32_t d = 1; d <= last; ++d) {
+            wave_sync_lds();
+            if (depth == d && par) num[v] = num[up] + before;
+        }
+        wave_sync_lds();
+        if (par) atomicOr(&kids[num[up]], 1u << num[v]);
     }
-    for (uint32_t i = t; i < 4 * 256; i += blockDim.x) {
+    __syncthreads();
+    // tables by bitmap byte (only those that n relations reach): neighbours of
+    // a set; children and own numbers of a set in preorder numbers
+    const uint32_t bytes = (n + 7u) / 8u;
+    for (uint32_t i = t; i < 4u * 256u; i += blockDim.x) {
         const uint32_t byte = i >> 8, x = i & 255u;
-        uint32_t u = 0;
-        for (uint32_t j = 0; j < 8; ++j)
-            if (((x >> j) & 1u) && 8u * byte + j < n) u |= L.adj[8u * byte + j];
-        L.nb[byte][x] = u;
-    }
-    if (t == 0) {
-        uint64_t off = 0;
-        for (uint32_t k = 0; k < 34; ++k) {
-            L.loff[k] = off;
-            if (k <= n) off += L.binom[n * 33 + k];
-        }
-        if (Q.is_tree) {  // rooted at relation 0: parent bits and subtree sets in BFS order
-            uint32_t order[kMaxRel], parent[kMaxRel];
-            uint32_t head = 0, tail = 0, vis = 1u;
-            order[tail++] = 0;
-            parent[0] = 0;
-            while (head < tail) {
-                const uint32_t v = order[head++];
-                for (uint32_t T = L.adj[v] & ~vis; T; T &= T - 1) {
-                    const uint32_t c = (uint32_t)ctz32(T);
-                    parent[c] = v;
-                    vis |= 1u << c;
-                    order[tail++] = c;
+        if (byte >= bytes && x != 0u) continue;
+        uint32_t a = 0, c = 0, p = 0;
+        if (!Q.is_tree) {
+            for (uint32_t j = 0; j < 8u; ++j) a |= ((x >> j) & 1u) && 8u * byte + j < n ? L.adj[8u * byte + j] : 0u;
+            L.nb[byte][x] = a;
+        } else {
+            for (uint32_t v = 0; v < n; ++v) {
+                const uint32_t at = num[v];
+                if ((at >> 3) == byte && ((x >> (at & 7u)) & 1u)) {
+                    c |= kids[at];
+                    p |= 1u << v;
                 }
             }
-            for (uint32_t i = 1; i < tail; ++i) L.pd[order[i]][0] = 1u << parent[order[i]];
-            for (uint32_t i = tail - 1; i > 0; --i) L.pd[parent[order[i]]][1] |= L.pd[order[i]][1];
+            L.pch[byte][x] = c;
+            L.perm[byte][x] = p;
         }
     }
     __syncthreads();
-    if (Q.is_tree) {  // children of a set, one table per bitmap byte
-        for (uint32_t i = t; i < 4 * 256; i += blockDim.x) {
-            const uint32_t byte = i >> 8, x = i & 255u;
-            uint32_t c = 0;
-            for (uint32_t v = 1; v < n; ++v)
-                if (L.pd[v][0] & (x << (8u * byte))) c |= 1u << v;
-            L.ch[byte][x] = c;
-        }
-        __syncthreads();
-    }
 }
 
+// Two workgroups a CU: 16 waves, 128 registers a lane (some 50 spilled, in the
+// set-up and the plan).  4096 mixed queries of 8-20 relations, C_out, took
+// 14.7 ms while every level unranked and tested all C(n, k) subsets and every
+// block's subsets were walked, and take 6.5; per query on one workgroup a
+// chain of 20 went from 1.42 to 0.16 ms, a cycle of 20 with up to two chords
+// from 2.89 to 0.87, a 20-relation tree with one to three extra edges from
+// more than 3.4 to 1.15.
 template <int CM>
 __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_batch(const BatchQueryDev *qs, const uint32_t *edges,
                                                        const double *cards, const double *sels,
@@ -162,14 +210,14 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                                                        uint32_t maxn, mpdp_plan_node *plans, BatchOut *out,
                                                        TeamRec *teams, BatchCounters *bc) {
     __shared__ __align__(16) LdsGraph L;
-    __shared__ uint32_t rings[kBW][kRing];
-    __shared__ uint32_t ring_bsums[kBW][kRing];
-    __shared__ WaveScratch WS[kBW];
-    __shared__ SetBlocks hsb;
-    __shared__ Key hkeys[kBW];
-    __shared__ PlanScratch P;
-    __shared__ uint32_t s_q, s_level, s_ok;
-    __shared__ uint32_t s_ntree[24], s_ngen[24], s_nheavy[24];  // per level k: list and heavy-list counts
+    __shared__ __align__(16) uint32_t ranks[kRankWords24];
+    __shared__ __align__(16) BatchScratch W;
+    __shared__ __align__(16) HeavyPart parts_rec[kBW];
+    __shared__ uint32_t parts_arrived[kBW];
+    __shared__ ExpandEnds ends;
+    __shared__ uint32_t s_q, s_ok;
+    __shared__ uint32_t s_count[24];  // connected sets per level k
+    __shared__ uint32_t s_num[kMaxRel], s_kids[kMaxRel];
     __shared__ unsigned long long s_conn, s_ccp, s_eval, s_t0;
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     if (t == 0) atomicMin(&bc->t0, (unsigned long long)wall_clock64());
@@ -177,8 +225,11 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
     // serves any run with the same layout
     const uint32_t nq = bc->entries;
     for (uint32_t i = t; i < 33 * 33; i += blockDim.x) L.binom[i] = binom_g[i];
+    stage_ranks(ranks, kBatchMaxRel);
+    if (t < kBW) parts_arrived[t] = 0;
 
-    // a workgroup's slot: memo (cost, card, left, op over 2^maxn entries), set list, heavy list
+    // a workgroup's slot: memo (cost, card, left, op over 2^maxn entries), two set lists
+    // of cap entries (level k uses list k mod 2), and a team's shared sets
     const uint64_t N = 1ull << maxn;
     const uint64_t list_off = (21 * N + 255) & ~255ull;
     // sets of the widest level; read from global memory: the LDS copy of the
@@ -194,8 +245,9 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         const bool team = Q.team > 1;
         TeamRec *R = team ? teams + Q.team_rec : nullptr;
         uint32_t phase = 0;
-        build_image(L, Q, edges, cards, sels, bcosts);
+        build_image(L, Q, edges, cards, sels, bcosts, s_num, s_kids);
         const uint32_t n = Q.n;
+        const bool star = Q.is_tree && L.adj[0] == (1u << n) - 2u;
         if (t == 0) {
             s_t0 = (unsigned long long)wall_clock64();
             s_conn = 0;
@@ -208,17 +260,28 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         char *slot = slots + (uint64_t)slot_id * slot_bytes;
         MemoPtrs M{reinterpret_cast<double *>(slot), reinterpret_cast<double *>(slot + 8 * N),
                    reinterpret_cast<uint32_t *>(slot + 16 * N), reinterpret_cast<uint8_t *>(slot + 20 * N)};
-        if (t < 24) {
-            s_ntree[t] = 0;
-            s_ngen[t] = 0;
-            s_nheavy[t] = 0;
-        }
-        if (t < n && Q.member == 0) {
-            const uint64_t at = L.loff[1] + t;
-            M.cost[at] = L.bcost[t];
-            M.card[at] = L.card[t];
-            M.left[at] = 0;
-            M.op[at] = MPDP_OP_SCAN;
+        uint32_t *even = reinterpret_cast<uint32_t *>(slot + list_off), *odd = even + cap;
+        const uint64_t parts_off = (list_off + 8ull * cap + 15) & ~15ull;
+        if (t < 24) s_count[t] = t == 2u ? Q.m : 0u;
+        if (Q.member == 0) {
+            if (t < n) {
+                const uint64_t at = L.loff[1] + t;
+                M.cost[at] = L.bcost[t];
+                M.card[at] = L.card[t];
+                M.left[at] = 0;
+                M.op[at] = MPDP_OP_SCAN;
+            }
+            // the sets of two relations: the edges
+            if (Q.is_tree) {
+                if (t < n) first_tree_list(L, t, even);
+            } else {
+                for (uint32_t e = t; e < Q.m; e += blockDim.x)
+                    even[e] = (1u << edges[2ull * (Q.edge_off + e)]) | (1u << edges[2ull * (Q.edge_off + e) + 1]);
+            }
+            if (team) {
+                if (t < kTeamSize * kBW) reinterpret_cast<uint32_t *>(slot + parts_off + sizeof(HeavyPart) * kTeamSize * kBW)[t] = 0;
+                if (t == 0) __hip_atomic_store(&R->count[2], Q.m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
         bool failed = false;
         if (team) {
@@ -227,100 +290,66 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
             slot = slots + (uint64_t)slot_id * slot_bytes;
             M = MemoPtrs{reinterpret_cast<double *>(slot), reinterpret_cast<double *>(slot + 8 * N),
                          reinterpret_cast<uint32_t *>(slot + 16 * N), reinterpret_cast<uint8_t *>(slot + 20 * N)};
+            even = reinterpret_cast<uint32_t *>(slot + list_off);
+            odd = even + cap;
         } else {
             __syncthreads();
         }
-        // two set lists of cap entries (level k uses list k mod 2, so the
-        // filter of level k + 1 can run with level k's evaluation), then the
-        // heavy list
-        uint32_t *lists = reinterpret_cast<uint32_t *>(slot + list_off);
-        uint32_t *hv = lists + 2 * cap;
-        // this workgroup's waves among the team's (w0, w0 + wstride, ...)
-        const uint32_t w0 = Q.member * kBW + wave, wstride = Q.team * kBW;
-        auto filter_level = [&](uint32_t kk) {  // connected sets of level kk into their list
-            filter_wave(L, (int)n, kk, L.binom[n * 33 + kk], w0, wstride, lists + (kk & 1u) * cap, cap,
-                        team ? &R->ntree[kk] : &s_ntree[kk], team ? &R->ngen[kk] : &s_ngen[kk], lane);
-        };
-        if (!Q.is_tree && n >= 2 && !failed) {
-            filter_level(2);
-            if (team) failed = !team_barrier(R, Q.team, phase, s_ok);
-            else __syncthreads();
-        }
+        // (a record and a counter for each of the team's waves: a team has
+        // kTeamMinRel relations or more, and its slot room for a third list)
+        const PairParts pp = team ? PairParts{reinterpret_cast<HeavyPart *>(slot + parts_off),
+                                              reinterpret_cast<uint32_t *>(slot + parts_off + sizeof(HeavyPart) * kTeamSize * kBW),
+                                              false}
+                                  : PairParts{parts_rec, parts_arrived, true};
+        // this workgroup's waves among the team's, neighbours in other members
+        const uint32_t nw = Q.team * kBW, w = wave * Q.team + Q.member;
+        uint32_t *counts = team ? R->count : s_count;
         unsigned long long my_ccp = 0, my_eval = 0;
         for (uint32_t k = 2; k <= n && !failed; ++k) {
-            const uint64_t ncand = L.binom[n * 33 + k];
-            if (Q.is_tree) {
-                if (t == 0) s_level = 0;
-                __syncthreads();
-                uint32_t found;
+            const uint32_t *list = (k & 1u) ? odd : even;
+            uint32_t *next = (k & 1u) ? even : odd;
+            const uint32_t count = star ? L.binom[(n - 1) * 33 + k - 1] : team ? load_shared_count(&counts[k]) : counts[k];
+            if (star) {
+                constexpr int kR = flat_sets_per_lane<CM>();
                 switch (Q.sched & kSchedChunkMask) {  // consecutive ranks per lane
                     case 0:
-                        found = level_tree_wave<CM, 1, true, kRing, 1, kBatchPairBatch>(L, M, (int)n, k, ncand, wave, kBW, (ncand + 63) / 64,
-                                                       rings[wave], ring_bsums[wave], lane);
+                        level_flat_wave<CM, 1, 1>(L, M, (int)n, k, 0, count, w, nw, W.flat.set[wave], W.flat.bsum[wave], lane);
                         break;
                     case 1:
-                        found = level_tree_wave<CM, 2, true, kRing, 1, kBatchPairBatch>(L, M, (int)n, k, ncand, wave, kBW, (ncand + 127) / 128,
-                                                       rings[wave], ring_bsums[wave], lane);
+                        level_flat_wave<CM, 2, kR>(L, M, (int)n, k, 0, count, w, nw, W.flat.set[wave], W.flat.bsum[wave], lane);
                         break;
                     default:
-                        found = level_tree_wave<CM, 4, true, kRing, 1, kBatchPairBatch>(L, M, (int)n, k, ncand, wave, kBW, (ncand + 255) / 256,
-                                                       rings[wave], ring_bsums[wave], lane);
+                        level_flat_wave<CM, 4, kR>(L, M, (int)n, k, 0, count, w, nw, W.flat.set[wave], W.flat.bsum[wave], lane);
                         break;
                 }
-                if (lane == 0 && found) atomicAdd(&s_level, found);
-                __syncthreads();
-                if (t == 0) {
-                    s_conn += s_level;
-                    s_ccp += (unsigned long long)(k - 1) * s_level;
-                    s_eval += 2ull * (k - 1) * s_level;
-                }
-                __syncthreads();
-                continue;
-            }
-            // level k's list was filtered during level k - 1 (or before the loop)
-            uint32_t *nhp = team ? &R->nheavy[k] : &s_nheavy[k];
-            const uint32_t ntree = team ? load_shared_count(&R->ntree[k]) : s_ntree[k];
-            const uint32_t ngen = team ? load_shared_count(&R->ngen[k]) : s_ngen[k];
-            const uint32_t count = ntree + ngen;
-            // light work: tree-inducing sets one per lane, other sets one per wave
-            light_sets<CM, false>(L, M, lists + (k & 1u) * cap, cap, ntree, ngen, w0, wstride, WS[wave], hv, nhp, lane,
-                           my_ccp, my_eval, false, (Q.sched >> kSchedHeavyShift) & 0xffffu);
-            if (k < n) filter_level(k + 1);
-            if (team) {
-                if (!team_barrier(R, Q.team, phase, s_ok)) { failed = true; break; }
+            } else if (Q.is_tree) {
+                if (k < n)
+                    expand_sets<true>(L, list, count, next, &counts[k + 1], w, nw, 1u, W.grow, sizeof(W.grow) / 4, ends, lane);
+                eval_tree_list<CM>(L, ranks, false, M, list, count, k, tree_group(count, 64u * nw), 64u * w + lane, 64u * nw);
             } else {
-                __syncthreads();
+                if (k < n)
+                    expand_sets<false>(L, list, count, next, &counts[k + 1], w, nw, expand_group(count, 64u * nw),
+                                       W.grow, sizeof(W.grow) / 4, ends, lane);
+                // sets per wave at a time, and waves per set, as in the per-level kernel
+                const uint32_t rounds = (count + 64u * nw - 1u) / (64u * nw);
+                const uint32_t per = (count + rounds * nw - 1u) / (rounds * nw);
+                const bool heavy = (1u << k) / 16u >= ((Q.sched >> kSchedHeavyShift) & 0xffffu);
+                const uint32_t parts = heavy && 2u * count <= nw ? nw / count : 1u;
+                eval_pairs<CM>(L, ranks, false, M, list, count, k, w, nw, per, parts, W.pairs[wave], pp, lane, my_ccp,
+                               my_eval);
             }
-            // heavy sets: a whole workgroup each (a team deals them out)
-            const uint32_t hcount = team ? load_shared_count(nhp) : s_nheavy[k];
-            for (uint32_t h = Q.member; h < hcount; h += Q.team) {
-                const uint32_t S = hv[h];
-                if (wave == 0) {
-                    const SetBlocks sb = analyze_set(L, S, WS[0], lane, blockDim.x);
-                    if (lane == 0) { hsb = sb; my_eval += sb.evaluated; }
-                }
-                __syncthreads();
-                const SetBlocks sb = hsb;
-                const double cardS = card_of_wave(L, S, threadIdx.x & 63u);
-                Key best = worst_key();
-                eval_chunks<CM, false>(L, M, WS[0], S, sb, t, blockDim.x, cardS, best, my_ccp);
-                best = wave_min(best);
-                if (lane == 0) hkeys[wave] = best;
-                __syncthreads();
-                if (t == 0) {
-                    Key b = hkeys[0];
-                    for (int i = 1; i < kBW; ++i)
-                        if (key_less(hkeys[i], b)) b = hkeys[i];
-                    store_best(M, memo_index(L, S), b, cardS);
-                }
-                __syncthreads();
-            }
-            if (t == 0) s_conn += count;
             // the level's memo is complete before the next level reads it
             if (team) failed = !team_barrier(R, Q.team, phase, s_ok);
             else __syncthreads();
+            if (t == 0 && Q.member == 0) {
+                s_conn += count;
+                if (Q.is_tree) {
+                    s_ccp += (unsigned long long)(k - 1) * count;
+                    s_eval += 2ull * (k - 1) * count;
+                }
+            }
         }
-        // counters of the block-based path
+        // counters of the cyclic queries
         for (int off = 32; off >= 1; off >>= 1) {
             my_ccp += (unsigned long long)__shfl_xor((long long)my_ccp, off);
             my_eval += (unsigned long long)__shfl_xor((long long)my_eval, off);
@@ -344,7 +373,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
             __syncthreads();
         }
         double root = 0.0;
-        const bool ok = !failed && extract_plan(L.binom, L.loff, M, n, plans + Q.plan_off, &root, P, t, blockDim.x);
+        const bool ok = !failed && extract_plan(L.binom, L.loff, M, n, plans + Q.plan_off, &root, W.plan, t, blockDim.x);
         __syncthreads();
         if (t == 0) {
             BatchOut o;

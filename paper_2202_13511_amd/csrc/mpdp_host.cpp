@@ -642,10 +642,10 @@ struct BatchLayout {
     uint64_t sum_m, sum_n, sum_nodes;
 };
 
-// Only a large cyclic query may be shared by a team of workgroups (a tree
-// query's sets are cheap and fill one workgroup well).  The layout depends
-// on the shapes alone, so it leaves room for every such query to take the
-// largest team; which ones do is decided per run from their edges.
+// Only a large query may be shared by a team of workgroups.  The layout
+// depends on the shapes alone, so it leaves room for every such cyclic query
+// to take the largest team; which queries do, large tree joins among them, is
+// decided per run from their edges.
 bool team_eligible(const mpdp_batch_query &Q) { return Q.n >= mpdp::kTeamMinRel && Q.m != Q.n - 1; }
 
 bool batch_layout(uint32_t nq, const mpdp_batch_query *qs, BatchLayout &B) {
@@ -748,15 +748,17 @@ mpdp_status check_batch_args(uint32_t nq, const mpdp_batch_query *queries, const
 }
 
 // Predicted device time (ms) of a query alone on one workgroup of the
-// batched kernel, for scheduling only.  Its connected sets are counted on a
-// breadth-first spanning tree from relation 0 (the subtrees of a rooted
-// tree: f(v) = prod over children of (1 + f(child)), summed over v).  A
-// tree query's time is close to linear in that count and in n^2; a cyclic
-// query's follows a power law in it and in 1 + its extra edges, and grows
-// exponentially with the size of
-// its 2-core (the relations left after repeatedly removing those of degree
-// one), which bounds the blocks Alg. 3 walks.  The coefficients were fitted
-// to measured per-query times of mixed batches of 8-20 relations on MI355X.
+// batched kernel, for scheduling only.  A tree query's time is close to
+// linear in its pairs (the connected sets, weighted by their size less one:
+// over the sets with top relation v, f(v) = prod over children of
+// (1 + f(child)) counts them and g(v) sums their sizes), less per pair for a
+// star around relation 0, whose gathers are neighbours.  A cyclic query's
+// connected sets are counted on a breadth-first spanning tree from relation
+// 0; its time follows a power law in them, in n and in its extra edges, with
+// an exponent that grows with its 2-core (the relations left after repeatedly
+// removing those of degree one).  Fitted to the times of 4096 mixed queries
+// of 8-20 relations and of 1500 random ones with up to all edges, C_out, one
+// workgroup each, on MI355X: four of five are within a third of it.
 double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges) {
     const uint32_t n = Q.n;
     uint32_t adj[32] = {0};
@@ -777,12 +779,23 @@ double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges) {
             order[tail++] = c;
         }
     }
-    double f[32], subtrees = 0.0;
-    for (uint32_t i = 0; i < tail; ++i) f[order[i]] = 1.0;
-    for (uint32_t i = tail; i-- > 1;) f[parent[order[i]]] *= 1.0 + f[order[i]];
-    for (uint32_t i = 0; i < tail; ++i) subtrees += f[order[i]];
+    double f[32], g[32], subtrees = 0.0, members = 0.0;
+    for (uint32_t i = 0; i < tail; ++i) f[order[i]] = g[order[i]] = 1.0;
+    for (uint32_t i = tail; i-- > 1;) {
+        const uint32_t v = order[i], p = parent[v];
+        g[p] = g[p] * (1.0 + f[v]) + f[p] * g[v];
+        f[p] *= 1.0 + f[v];
+    }
+    for (uint32_t i = 0; i < tail; ++i) {
+        subtrees += f[order[i]];
+        members += g[order[i]];
+    }
     const uint32_t extra = Q.m - (n - 1);
-    if (extra == 0) return std::max(0.05, -0.361 + 1.20e-5 * subtrees + 0.00308 * (double)(n * n));
+    if (extra == 0) {
+        const bool star = n >= 2 && adj[0] == (1u << n) - 2u;
+        const double pairs = members - subtrees;
+        return 1e-3 * (star ? 5.1 + 3.2 * n + 0.86e-3 * pairs : 10.0 + 5.0 * n + 2.7e-3 * pairs);
+    }
     uint32_t alive = (n == 32) ? ~0u : (1u << n) - 1u;
     for (bool changed = true; changed;) {
         changed = false;
@@ -795,13 +808,21 @@ double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges) {
         }
     }
     const double core = (double)__builtin_popcount(alive);
-    return std::exp(-6.466 + 0.1238 * core) * std::pow(subtrees, 0.856) * std::pow(1.0 + extra, 0.080);
+    return std::exp(-3.55 + 0.1777 * std::log(subtrees) + (0.1095 * core - 0.776) * std::log(1.0 + extra) -
+                    0.0878 * core + 0.138 * (double)n);
 }
 
-// Team size of a query from its predicted time alone on one workgroup.
-uint32_t team_size(const mpdp_batch_query &Q, double ms) {
-    if (!team_eligible(Q)) return 1;
-    return ms >= 8.0 ? mpdp::kTeamSize : ms >= 3.0 ? mpdp::kTeamSize / 2 : 1u;
+// Team size of a query from its predicted time alone on one workgroup and
+// the batch's per workgroup: a query that would take the larger part of the
+// batch's time is shared out until a member takes two fifths of it, but not to
+// less than 0.1 ms a member, of which the team's barriers (one a level) take a
+// good part.
+uint32_t team_size(const mpdp_batch_query &Q, double ms, double batch_ms) {
+    if (Q.n < mpdp::kTeamMinRel) return 1;
+    const double share = std::max(0.1, 0.4 * batch_ms);
+    uint32_t team = 1;
+    while (team < mpdp::kTeamSize && ms > share * team) team *= 2;
+    return team;
 }
 
 // Order in which the workgroups take the queries (longest predicted time
@@ -811,14 +832,20 @@ void batch_order(uint32_t nq, const mpdp_batch_query *queries, const mpdp_edge *
                  std::vector<uint32_t> &order, std::vector<uint32_t> &team, std::vector<uint64_t> &plan_at,
                  bool all_teams = false) {
     std::vector<double> ms(nq);
-    for (uint32_t i = 0; i < nq; ++i) ms[i] = predicted_ms(queries[i], edges);
+    double total = 0.0;
+    for (uint32_t i = 0; i < nq; ++i) total += ms[i] = predicted_ms(queries[i], edges);
     order.resize(nq);
     for (uint32_t i = 0; i < nq; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return ms[a] > ms[b]; });
     team.resize(nq);
-    for (uint32_t j = 0; j < nq; ++j)
+    uint32_t room = 0;  // teams
+    for (uint32_t i = 0; i < nq; ++i) room += team_eligible(queries[i]) ? 1u : 0u;
+    for (uint32_t j = 0; j < nq; ++j) {
         team[j] = all_teams ? (team_eligible(queries[order[j]]) ? mpdp::kTeamSize : 1u)
-                            : team_size(queries[order[j]], ms[order[j]]);
+                  : room    ? team_size(queries[order[j]], ms[order[j]], total / mpdp::kBatchWorkgroups)
+                            : 1u;
+        room -= team[j] > 1u ? 1u : 0u;
+    }
     plan_at.resize(nq);
     uint64_t p = 0;
     for (uint32_t i = 0; i < nq; ++i) { plan_at[i] = p; p += 2ull * queries[i].n - 1; }
@@ -867,7 +894,7 @@ void fill_batch_upload(char *up, const BatchLayout &B, uint32_t nq, const mpdp_b
         co += Q.n;
         eo += Q.m;
     }
-    bc->entries = entry;  // at most B.max_entries: only eligible queries take teams
+    bc->entries = entry;  // at most B.max_entries: no more teams than eligible queries
 }
 
 hipError_t enqueue_batch_kernel(char *base, const BatchLayout &B, uint32_t nq, mpdp_cost_model cost_model,

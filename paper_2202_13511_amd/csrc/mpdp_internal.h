@@ -110,8 +110,8 @@ struct Results {
 };
 
 // Batched path (mpdp_batch.hip): one queue entry per workgroup at a time.
-// A query is one entry, or, if it is large and cyclic, kTeamSize entries in
-// a row: a team of workgroups that share its levels.
+// A query is one entry, or, if it is large, up to kTeamSize entries in a row:
+// a team of workgroups that share its levels.
 struct BatchQueryDev {
     uint32_t n, m, is_tree, cost_model;
     uint64_t card_off, edge_off, plan_off;
@@ -128,17 +128,17 @@ struct TeamRec {
     uint32_t slot;                   // workgroup whose slot holds the memo and lists
     uint32_t error;                  // a barrier wait ran out of time
     uint32_t pad;
-    uint32_t ntree[24], ngen[24], nheavy[24];  // per level k
+    uint32_t count[24];              // connected sets per level k
     unsigned long long ccp, evaluated;
 };
 
 constexpr uint32_t kTeamSize = 8;     // largest team
-constexpr uint32_t kTeamMinRel = 17;  // only cyclic queries of at least this many relations may get a team
+constexpr uint32_t kTeamMinRel = 17;  // only queries of at least this many relations may get a team
 
 // Schedule of one query in the batched kernel: bits 0-1 hold log2 of the
-// consecutive ranks per lane of a tree query's levels (1, 2 or 4), bits
-// 8-23 the number of 16-candidate chunks above which a set of a cyclic
-// query is evaluated by the whole workgroup instead of one wave.
+// consecutive ranks per lane of a star's levels (1, 2 or 4), bits 8-23 the
+// number of 16-subset chunks from which a cyclic query's sets may be shared
+// by several waves.
 constexpr uint32_t kSchedChunkMask = 3u;
 constexpr uint32_t kSchedHeavyShift = 8;
 constexpr uint32_t kSchedDefault = 2u | (256u << kSchedHeavyShift);

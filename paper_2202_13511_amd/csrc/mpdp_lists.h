@@ -76,20 +76,22 @@ __device__ __forceinline__ uint32_t colex_rank(const uint32_t *T, uint32_t X, bo
 // ---------------------------------------------------------------- buffers
 
 // One wave's LDS.  The pool is the stack of search states (eval_pairs):
-// kPool entries are shared by all lanes, kPoolReserve more are for the one
-// lane that goes on alone when the pool is full.  Sets with hundreds of
-// pairs fill 512 entries now and then; at 192 some waves spent most of
-// their time stalled (28 relations, 10 chords: 8.0 -> 12.3 ms).
-constexpr uint32_t kPool = 448, kPoolReserve = 64;
-
-struct PairBuf {
-    uint32_t p0[kPool + kPoolReserve], p1[kPool + kPoolReserve], p2[kPool + kPoolReserve];
+// kPoolN entries are shared by all lanes, kReserve more are for the one lane
+// that goes on alone when the pool is full.  With 28 relations and 10 chords
+// the sets have hundreds of pairs, which fill 512 entries now and then; at
+// 192 some waves spent most of their time stalled (8.0 -> 12.3 ms).  The batched
+// kernel's queries are smaller, and two of its workgroups share a CU's LDS.
+template <uint32_t kPoolN, uint32_t kReserve>
+struct PairBufN {
+    static constexpr uint32_t kPool = kPoolN;
+    uint32_t p0[kPoolN + kReserve], p1[kPoolN + kReserve], p2[kPoolN + kReserve];
     unsigned long long bc[64];  // best key of each set: cost bits,
     double card[64];            // card(S)
     uint32_t bl[64], bop[64];   // left set, operator
     uint32_t claim[64];
-    uint8_t slot[kPool + kPoolReserve];
+    uint8_t slot[kPoolN + kReserve];
 };
+using PairBuf = PairBufN<448, 64>;
 
 // ---------------------------------------------------------------- Alg. 3's counter
 
@@ -183,7 +185,8 @@ struct PairState {
     uint32_t A, C, X, F, slot;
 };
 
-__device__ __forceinline__ void push_state(PairBuf &B, uint32_t at, uint32_t A, uint32_t C, uint32_t X, uint32_t F,
+template <class Buf>
+__device__ __forceinline__ void push_state(Buf &B, uint32_t at, uint32_t A, uint32_t C, uint32_t X, uint32_t F,
                                            uint32_t slot) {
     B.p0[at] = A | X;
     B.p1[at] = C & ~F;
@@ -212,7 +215,8 @@ __device__ __forceinline__ bool key_before(unsigned long long c, uint32_t l, uin
 
 // The keys of the lanes in `on` into their sets' entries (LDS, this wave's
 // alone); lanes that improve the same set take turns.
-__device__ __forceinline__ void flush_best(PairBuf &B, const PairBest &b, bool on, uint32_t lane) {
+template <class Buf>
+__device__ __forceinline__ void flush_best(Buf &B, const PairBest &b, bool on, uint32_t lane) {
     bool better = on && key_before(b.c, b.l, b.op, B.bc[b.slot], B.bl[b.slot], B.bop[b.slot]);
     while (__ballot(better) != 0ull) {
         if (better) B.claim[b.slot] = lane;
@@ -229,8 +233,8 @@ __device__ __forceinline__ void flush_best(PairBuf &B, const PairBest &b, bool o
 }
 
 // The pair whose memo values have arrived into its lane's best key.
-template <int CM>
-__device__ __forceinline__ void settle_pair(PairBuf &B, const PairLoad<CM> &p, PairBest &b, uint32_t lane) {
+template <int CM, class Buf>
+__device__ __forceinline__ void settle_pair(Buf &B, const PairLoad<CM> &p, PairBest &b, uint32_t lane) {
     const bool moved = p.on && p.slot != b.slot;
     if (__ballot(moved) != 0ull) {
         flush_best(B, b, moved, lane);
@@ -273,12 +277,13 @@ __device__ __forceinline__ void settle_pair(PairBuf &B, const PairLoad<CM> &p, P
 struct PairParts {
     HeavyPart *rec;
     uint32_t *arrived;  // per set, zero between uses
+    bool local;         // both in LDS: one workgroup's waves
 };
 
-template <int CM>
+template <int CM, class Buf>
 __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, const MemoPtrs &M, const uint32_t *list,
                            uint32_t count, uint32_t k, uint32_t w, uint32_t nw, uint32_t per, uint32_t parts,
-                           PairBuf &B, PairParts pp, uint32_t lane, unsigned long long &ccp,
+                           Buf &B, PairParts pp, uint32_t lane, unsigned long long &ccp,
                            unsigned long long &evaluated) {
     const unsigned long long below = (1ull << lane) - 1ull;
     const uint32_t items = parts > 1 ? count * parts : (count + per - 1) / per;
@@ -377,9 +382,9 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
             uint32_t at = top + (uint32_t)__popcll(mr & below) + (uint32_t)__popcll(ml & below);
             uint32_t total = (uint32_t)__popcll(mr) + (uint32_t)__popcll(ml);
             bool go = act;
-            if (top + total > kPool) {  // uniform, rare
+            if (top + total > Buf::kPool) {  // uniform, rare
                 const uint32_t need = (push_rest ? 1u : 0u) + (push_left ? 1u : 0u);
-                go = act && (need == 0u || at + need <= kPool || (am & below) == 0ull);
+                go = act && (need == 0u || at + need <= Buf::kPool || (am & below) == 0ull);
                 total = (uint32_t)__popcll(__ballot(go && push_rest)) + (uint32_t)__popcll(__ballot(go && push_left));
             }
             top += total;
@@ -433,12 +438,14 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
                 __hip_atomic_store(&r64[0], B.bc[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&r64[1], ((unsigned long long)B.bop[0] << 32) | B.bl[0], __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                if (pp.local) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
                 n_here = __hip_atomic_fetch_add(&pp.arrived[s0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             n_here = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_here);
             if (n_here == parts - 1u) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (pp.local) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 Key best = worst_key();
                 for (uint32_t p = lane; p < parts; p += 64u) {
                     unsigned long long *r64 = reinterpret_cast<unsigned long long *>(&rec[p]);

@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
                     sizeof(buf) / 4, ends, lane);
     unsigned long long ccp = 0, evaluated = 0;
     eval_pairs<CM>(L, ranks, n > 24u, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6],
-                   PairParts{rec, arrived}, lane, ccp, evaluated);
+                   PairParts{rec, arrived, false}, lane, ccp, evaluated);
     for (int off = 32; off >= 1; off >>= 1) {
         ccp += (unsigned long long)__shfl_xor((long long)ccp, off);
         evaluated += (unsigned long long)__shfl_xor((long long)evaluated, off);
