@@ -12,10 +12,10 @@
 // scratch live in a per-workgroup slot that is reused from query to query,
 // so the workspace does not grow with the batch.  A large query may be
 // taken by a team of workgroups (consecutive queue entries): they split the
-// sets of every level and meet at device-wide barriers, in the slot of the
-// team's first member.  Entries are taken in queue order, so a member
-// waiting at a barrier waits only for workgroups that have already taken
-// their entries, or for ones that will take them next.
+// sets of every level and meet at barriers, in the slot of the team's first
+// member.  Entries are taken in queue order within their share, so of each
+// share at most one team waits for members, and those come: every workgroup
+// that does not wait takes entries, of all shares in the end.
 #include <hip/hip_runtime.h>
 
 #include "mpdp_device.h"
@@ -29,21 +29,27 @@ constexpr int kBatchBlock = 512;
 constexpr int kBW = kBatchBlock / 64;
 constexpr unsigned long long kTeamWaitTicks = 200000000ull;  // 2 s of the 100 MHz device clock
 
+__device__ __forceinline__ uint32_t load_shared_count(const uint32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The workgroups of a team meet here for the `phase`-th time.  Every wave
 // first waits until its own stores (memo, lists) have reached the L2; then
-// one thread per workgroup writes the L2 back (agent-scope release) and
-// arrives, and after the wait drops the lines other members may have
-// written from this CU's and this XCD's caches (agent-scope acquire), once
-// for all its waves.  The wait is bounded by the device clock: past
-// kTeamWaitTicks the team is marked failed, and every later wait of that
-// team returns at once.  Returns false once the team has failed; its
-// members then leave the query (its lists may be incomplete), and the
-// query reports an error.
-__device__ bool team_barrier(TeamRec *R, uint32_t team, uint32_t &phase, uint32_t &s_ok) {
+// one thread per workgroup arrives, and after the wait drops the lines other
+// members may have written from this CU's cache (agent-scope acquire), once
+// for all its waves.  `spread`: the members run on several XCDs, so the
+// thread writes the L2 back before it arrives (agent-scope release).  That
+// takes some 40 us with hundreds of workgroups at work, and members of one
+// XCD, which share its L2, don't need it.  The
+// wait is bounded by the device clock: past kTeamWaitTicks the team is marked
+// failed, and every later wait of that team returns at once.  Returns false
+// once the team has failed; its members then leave the query (its lists may
+// be incomplete), and the query reports an error.
+__device__ bool team_barrier(TeamRec *R, uint32_t team, bool spread, uint32_t &phase, uint32_t &s_ok) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (spread) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __hip_atomic_fetch_add(&R->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t target = team * (phase + 1u);
         const unsigned long long start = wall_clock64();
@@ -63,14 +69,34 @@ __device__ bool team_barrier(TeamRec *R, uint32_t team, uint32_t &phase, uint32_
     return s_ok != 0u;
 }
 
-__device__ __forceinline__ uint32_t load_shared_count(const uint32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// The XCD this workgroup runs on (hardware register XCC_ID).
+__device__ __forceinline__ uint32_t xcd_id() { return (uint32_t)__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 7u; }
+
+// The next queue entry: of the XCD's own share, of the common rest, of the
+// other shares; bc->entries when there is none.  One thread.
+__device__ uint32_t take_entry(BatchCounters *bc, uint32_t xcd, bool &own) {
+    for (uint32_t y = 0; y < 9u; ++y) {
+        if (y == 1u) {  // after the own share
+            own = false;
+            const uint32_t i = atomicAdd(&bc->next, 1u);
+            if (i < bc->entries) return i;
+        }
+        if (y == 0u && !own) continue;
+        const uint32_t x = (xcd + y) & 7u;
+        const uint32_t first = x ? bc->share_end[x - 1u] : 0u, end = bc->share_end[x];
+        if (load_shared_count(&bc->share_taken[x]) >= end - first) continue;
+        const uint32_t i = first + atomicAdd(&bc->share_taken[x], 1u);
+        if (i < end) return i;
+    }
+    return bc->entries;
 }
 
-// Workgroups' LDS, two per CU: 160 KB / 2 less the image and rank table.
-// A search path leaves less than two states per relation behind.
-using BatchBuf = PairBufN<240, 2 * kBatchMaxRel>;
-static_assert(3 * (240 + 2 * kBatchMaxRel) >= 64 * (kBatchMaxRel / 2), "block_candidates' pieces");
+
+// Workgroups' LDS, two per CU: 160 KB / 2 less the image.  A search path
+// leaves less than two states per relation behind.
+constexpr uint32_t kBatchPool = 240;
+using BatchBuf = PairBufN<kBatchPool, 2 * kBatchMaxRel>;
+static_assert(3 * (kBatchPool + 2 * kBatchMaxRel) >= 64 * (kBatchMaxRel / 2), "block_candidates' pieces");
 
 // What the waves keep while a level runs; the plan is rebuilt in its place.
 union BatchScratch {
@@ -196,10 +222,15 @@ __device__ void build_image(LdsGraph &L, const BatchQueryDev &Q, const uint32_t 
     __syncthreads();
 }
 
+// Least sets that a wave takes at a time on a cyclic query's level: a wave of
+// fewer has too few search states, while other queries wait for the CU
+// (4096 queries: 7.78 ms with 1, 7.64 with 16, 7.70 with 32).
+constexpr uint32_t kBatchPer = 16;
+
 // Two workgroups a CU: 16 waves, 128 registers a lane (some 50 spilled, in the
 // set-up and the plan).  4096 mixed queries of 8-20 relations, C_out, took
 // 14.7 ms while every level unranked and tested all C(n, k) subsets and every
-// block's subsets were walked, and take 6.5; per query on one workgroup a
+// block's subsets were walked, and take 5.1; per query on one workgroup a
 // chain of 20 went from 1.42 to 0.16 ms, a cycle of 20 with up to two chords
 // from 2.89 to 0.87, a 20-relation tree with one to three extra edges from
 // more than 3.4 to 1.15.
@@ -228,7 +259,9 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
     stage_ranks(ranks, kBatchMaxRel);
     if (t < kBW) parts_arrived[t] = 0;
 
-    // a workgroup's slot: memo (cost, card, left, op over 2^maxn entries), two set lists
+    // a workgroup's slot: memo (cost, card, left, op over 2^maxn entries, a
+    // set's entry at the set itself, or, of a tree join, whose many sets are
+    // then neighbours, at its level and rank), two set lists
     // of cap entries (level k uses list k mod 2), and a team's shared sets
     const uint64_t N = 1ull << maxn;
     const uint64_t list_off = (21 * N + 255) & ~255ull;
@@ -236,8 +269,10 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
     // table is complete only after the first barrier below
     const uint32_t cap = binom_g[maxn * 33 + maxn / 2];
 
+    const uint32_t xcd = xcd_id();
+    bool own = true;
     for (;;) {
-        if (t == 0) s_q = atomicAdd(&bc->next, 1u);
+        if (t == 0) s_q = take_entry(bc, xcd, own);
         __syncthreads();
         const uint32_t q = s_q;
         if (q >= nq) break;
@@ -256,7 +291,10 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         }
         // a team works in its first member's slot, published through the team record
         uint32_t slot_id = blockIdx.x;
-        if (team && Q.member == 0 && t == 0) __hip_atomic_store(&R->slot, slot_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (team && t == 0) {
+            if (Q.member == 0) __hip_atomic_store(&R->slot, slot_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_or(&R->xcds, 1u << xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         char *slot = slots + (uint64_t)slot_id * slot_bytes;
         MemoPtrs M{reinterpret_cast<double *>(slot), reinterpret_cast<double *>(slot + 8 * N),
                    reinterpret_cast<uint32_t *>(slot + 16 * N), reinterpret_cast<uint8_t *>(slot + 20 * N)};
@@ -265,7 +303,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         if (t < 24) s_count[t] = t == 2u ? Q.m : 0u;
         if (Q.member == 0) {
             if (t < n) {
-                const uint64_t at = L.loff[1] + t;
+                const uint64_t at = Q.is_tree ? L.loff[1] + t : 1u << t;
                 M.cost[at] = L.bcost[t];
                 M.card[at] = L.card[t];
                 M.left[at] = 0;
@@ -283,9 +321,14 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 if (t == 0) __hip_atomic_store(&R->count[2], Q.m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-        bool failed = false;
+        bool failed = false, spread = false;
         if (team) {
-            failed = !team_barrier(R, Q.team, phase, s_ok);
+            // the first meeting is for the record alone, unless it shows that
+            // the first member's stores have yet to leave its XCD
+            failed = !team_barrier(R, Q.team, false, phase, s_ok);
+            const uint32_t xcds = load_shared_count(&R->xcds);
+            spread = (xcds & (xcds - 1u)) != 0u;
+            if (spread && !failed) failed = !team_barrier(R, Q.team, true, phase, s_ok);
             slot_id = load_shared_count(&R->slot);
             slot = slots + (uint64_t)slot_id * slot_bytes;
             M = MemoPtrs{reinterpret_cast<double *>(slot), reinterpret_cast<double *>(slot + 8 * N),
@@ -298,9 +341,8 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         // (a record and a counter for each of the team's waves: a team has
         // kTeamMinRel relations or more, and its slot room for a third list)
         const PairParts pp = team ? PairParts{reinterpret_cast<HeavyPart *>(slot + parts_off),
-                                              reinterpret_cast<uint32_t *>(slot + parts_off + sizeof(HeavyPart) * kTeamSize * kBW),
-                                              false}
-                                  : PairParts{parts_rec, parts_arrived, true};
+                                              reinterpret_cast<uint32_t *>(slot + parts_off + sizeof(HeavyPart) * kTeamSize * kBW)}
+                                  : PairParts{parts_rec, parts_arrived};
         // this workgroup's waves among the team's, neighbours in other members
         const uint32_t nw = Q.team * kBW, w = wave * Q.team + Q.member;
         uint32_t *counts = team ? R->count : s_count;
@@ -324,22 +366,21 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 }
             } else if (Q.is_tree) {
                 if (k < n)
-                    expand_sets<true>(L, list, count, next, &counts[k + 1], w, nw, 1u, W.grow, sizeof(W.grow) / 4, ends, lane);
-                eval_tree_list<CM>(L, ranks, false, M, list, count, k, tree_group(count, 64u * nw), 64u * w + lane, 64u * nw);
+                    expand_sets<true, false>(L, list, count, next, &counts[k + 1], w, nw, 1u, W.grow, sizeof(W.grow) / 4, ends, lane);
+                eval_tree_list<CM>(L, ColexMemo{ranks, L.loff, false}, M, list, count, k, tree_group(count, 64u * nw), 64u * w + lane, 64u * nw);
             } else {
                 if (k < n)
-                    expand_sets<false>(L, list, count, next, &counts[k + 1], w, nw, expand_group(count, 64u * nw),
+                    expand_sets<false, false>(L, list, count, next, &counts[k + 1], w, nw, expand_group(count, 64u * nw),
                                        W.grow, sizeof(W.grow) / 4, ends, lane);
                 // sets per wave at a time, and waves per set, as in the per-level kernel
-                const uint32_t rounds = (count + 64u * nw - 1u) / (64u * nw);
-                const uint32_t per = (count + rounds * nw - 1u) / (rounds * nw);
+                const uint32_t per = max(pair_sets(count, nw), min(count, kBatchPer));
                 const bool heavy = (1u << k) / 16u >= ((Q.sched >> kSchedHeavyShift) & 0xffffu);
                 const uint32_t parts = heavy && 2u * count <= nw ? nw / count : 1u;
-                eval_pairs<CM>(L, ranks, false, M, list, count, k, w, nw, per, parts, W.pairs[wave], pp, lane, my_ccp,
+                eval_pairs<CM, false>(L, BitMemo{}, M, list, count, k, w, nw, per, parts, W.pairs[wave], pp, lane, my_ccp,
                                my_eval);
             }
             // the level's memo is complete before the next level reads it
-            if (team) failed = !team_barrier(R, Q.team, phase, s_ok);
+            if (team) failed = !team_barrier(R, Q.team, spread, phase, s_ok);
             else __syncthreads();
             if (t == 0 && Q.member == 0) {
                 s_conn += count;
@@ -364,7 +405,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 __hip_atomic_fetch_add(&R->ccp, s_ccp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_fetch_add(&R->evaluated, s_eval, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (!failed) failed = !team_barrier(R, Q.team, phase, s_ok);
+            if (!failed) failed = !team_barrier(R, Q.team, spread, phase, s_ok);
             if (Q.member != 0) continue;
             if (t == 0) {
                 s_ccp = __hip_atomic_load(&R->ccp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -373,7 +414,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
             __syncthreads();
         }
         double root = 0.0;
-        const bool ok = !failed && extract_plan(L.binom, L.loff, M, n, plans + Q.plan_off, &root, W.plan, t, blockDim.x);
+        const bool ok = !failed && extract_plan(L.binom, L.loff, !Q.is_tree, M, n, plans + Q.plan_off, &root, W.plan, t, blockDim.x);
         __syncthreads();
         if (t == 0) {
             BatchOut o;

@@ -1987,6 +1987,7 @@ __device__ void light_sets(const LdsGraph &L, const MemoPtrs &M, const uint32_t 
 // chain is the tree's depth); then all `nthreads` threads fill cost, card
 // and operator of every node.  Memo indices are summed by the wave, one
 // member per lane, one frontier set at a time, and kept for the fill.
+// by_set: a set's entry is at the set itself (a memo of the kernel's own).
 // Returns false if the memo is inconsistent.
 struct PlanScratch {
     uint64_t node_at[64];
@@ -2006,7 +2007,7 @@ __device__ __forceinline__ uint64_t memo_index_wave_t(const uint32_t *binom, con
     return loff[popc32(S)] + wave_sum32(term);
 }
 
-__device__ bool extract_plan(const uint32_t *binom, const uint64_t *loff, const MemoPtrs &M, uint32_t n,
+__device__ bool extract_plan(const uint32_t *binom, const uint64_t *loff, bool by_set, const MemoPtrs &M, uint32_t n,
                              mpdp_plan_node *plan, double *root_cost, PlanScratch &P, uint32_t t,
                              uint32_t nthreads) {
     const uint32_t full = (n == 32) ? 0xffffffffu : ((1u << n) - 1u);
@@ -2020,14 +2021,15 @@ __device__ bool extract_plan(const uint32_t *binom, const uint64_t *loff, const 
         }
         wave_sync_lds();
         // the root's cost is read while the walk goes on
-        const uint64_t root_at = memo_index_wave_t(binom, loff, full, lane);
+        const uint64_t root_at = by_set ? full : memo_index_wave_t(binom, loff, full, lane);
         const double root_c = lane == 0 ? M.cost[root_at] : 0.0;
         int cur = 0;
         uint32_t nfr = n > 1 ? 1u : 0u;  // frontier size, uniform; at most 31 join nodes per depth
         bool bad = false;
         for (uint32_t depth = 0; nfr != 0 && depth < n; ++depth) {
             uint64_t my_at = 0;  // lane j: index of frontier set j
-            for (uint32_t j = 0; j < nfr; ++j) {
+            if (by_set) my_at = lane < nfr ? P.fr_set[cur][lane] : 0u;
+            else for (uint32_t j = 0; j < nfr; ++j) {
                 const uint64_t at = memo_index_wave_t(binom, loff, P.fr_set[cur][j], lane);
                 if (lane == j) my_at = at;
             }
@@ -2080,7 +2082,7 @@ __device__ bool extract_plan(const uint32_t *binom, const uint64_t *loff, const 
     __syncthreads();
     if (P.error) return false;
     for (uint32_t v = t; v < n; v += nthreads) {
-        const uint64_t at = loff[1] + v;
+        const uint64_t at = by_set ? 1ull << v : loff[1] + v;
         plan[v] = mpdp_plan_node{-1, -1, 1u << v, MPDP_OP_SCAN, M.cost[at], M.card[at]};
     }
     for (uint32_t j = n + t; j + 1 < 2 * n; j += nthreads) {

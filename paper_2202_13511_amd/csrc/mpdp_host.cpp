@@ -813,13 +813,15 @@ double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges) {
 }
 
 // Team size of a query from its predicted time alone on one workgroup and
-// the batch's per workgroup: a query that would take the larger part of the
-// batch's time is shared out until a member takes two fifths of it, but not to
-// less than 0.1 ms a member, of which the team's barriers (one a level) take a
-// good part.
+// the batch's per workgroup: shared out until a member takes a fifth of the
+// batch's time, so that none of the longest ends after all others and fewer
+// memos compete for an XCD's cache, but not to less than 0.3 ms a member.
+// (4096 queries of 8-20 relations / 1000 of 10-18, C_out: 5.1 / 1.18 ms; a
+// tenth and 0.4 ms 5.6 / 1.19, two fifths 5.6 / 1.19, a fifth with 0.1 ms
+// 5.1 / 1.51, without teams 7.0 / 2.8.)
 uint32_t team_size(const mpdp_batch_query &Q, double ms, double batch_ms) {
     if (Q.n < mpdp::kTeamMinRel) return 1;
-    const double share = std::max(0.1, 0.4 * batch_ms);
+    const double share = std::max(0.3, 0.2 * batch_ms);
     uint32_t team = 1;
     while (team < mpdp::kTeamSize && ms > share * team) team *= 2;
     return team;
@@ -829,9 +831,9 @@ uint32_t team_size(const mpdp_batch_query &Q, double ms, double batch_ms) {
 // first, ties in input order), each query's team size in that order, and
 // each query's first plan node in input order.
 void batch_order(uint32_t nq, const mpdp_batch_query *queries, const mpdp_edge *edges,
-                 std::vector<uint32_t> &order, std::vector<uint32_t> &team, std::vector<uint64_t> &plan_at,
-                 bool all_teams = false) {
-    std::vector<double> ms(nq);
+                 std::vector<uint32_t> &order, std::vector<uint32_t> &team, std::vector<double> &ms,
+                 std::vector<uint64_t> &plan_at, bool all_teams = false) {
+    ms.resize(nq);
     double total = 0.0;
     for (uint32_t i = 0; i < nq; ++i) total += ms[i] = predicted_ms(queries[i], edges);
     order.resize(nq);
@@ -841,10 +843,12 @@ void batch_order(uint32_t nq, const mpdp_batch_query *queries, const mpdp_edge *
     uint32_t room = 0;  // teams
     for (uint32_t i = 0; i < nq; ++i) room += team_eligible(queries[i]) ? 1u : 0u;
     for (uint32_t j = 0; j < nq; ++j) {
-        team[j] = all_teams ? (team_eligible(queries[order[j]]) ? mpdp::kTeamSize : 1u)
-                  : room    ? team_size(queries[order[j]], ms[order[j]], total / mpdp::kBatchWorkgroups)
-                            : 1u;
-        room -= team[j] > 1u ? 1u : 0u;
+        const mpdp_batch_query &Q = queries[order[j]];
+        uint32_t size = 1;
+        if (all_teams) size = team_eligible(Q) ? mpdp::kTeamSize : 1u;
+        else if (room) size = team_size(Q, ms[order[j]], total / mpdp::kBatchWorkgroups);
+        room -= size > 1u ? 1u : 0u;
+        team[j] = size;
     }
     plan_at.resize(nq);
     uint64_t p = 0;
@@ -855,22 +859,49 @@ void batch_order(uint32_t nq, const mpdp_batch_query *queries, const mpdp_edge *
 // uploaded to the workspace in one copy.
 void fill_batch_upload(char *up, const BatchLayout &B, uint32_t nq, const mpdp_batch_query *queries,
                        const std::vector<uint32_t> &order, const std::vector<uint32_t> &team_of,
+                       const std::vector<double> &ms,
                        const std::vector<uint64_t> &plan_at,
                        const mpdp_edge *edges, const double *cardinalities, const double *selectivities,
                        const double *base_costs, mpdp_cost_model cost_model, const mpdp_batch_schedule *sched) {
     std::memset(up, 0, B.plans);
     std::memcpy(up + B.binom, binom_table(), 33 * 33 * sizeof(uint32_t));
     auto *bc = reinterpret_cast<mpdp::BatchCounters *>(up + B.counters);
-    bc->next = 0;
-    bc->entries = 0;
     bc->t0 = ~0ull;
+    // entries: first a share of the teams for each XCD, each team to the share
+    // with the least predicted time so far, then the others
+    std::vector<uint32_t> share[8], rest;  // places in `order`
+    double load[8] = {0.0};
+    for (uint32_t j = 0; j < nq; ++j) {
+        if (team_of[j] == 1u) {
+            rest.push_back(j);
+            continue;
+        }
+        const uint32_t to = (uint32_t)(std::min_element(load, load + 8) - load);
+        share[to].push_back(j);
+        load[to] += ms[order[j]];
+    }
+    std::vector<uint32_t> entry_of(nq);
+    uint32_t entries = 0;
+    for (uint32_t x = 0; x < 8; ++x) {
+        for (uint32_t j : share[x]) {
+            entry_of[j] = entries;
+            entries += team_of[j];
+        }
+        bc->share_end[x] = entries;
+    }
+    bc->next = entries;
+    for (uint32_t j : rest) {
+        entry_of[j] = entries;
+        entries += team_of[j];
+    }
+    bc->entries = entries;  // at most B.max_entries: no more teams than eligible queries
     auto *dq = reinterpret_cast<mpdp::BatchQueryDev *>(up + B.queries);
     uint32_t *de = reinterpret_cast<uint32_t *>(up + B.edges);
     double *dc = reinterpret_cast<double *>(up + B.cards);
     double *ds = reinterpret_cast<double *>(up + B.sels);
     double *db = reinterpret_cast<double *>(up + B.bcosts);
     uint64_t eo = 0, co = 0;
-    uint32_t entry = 0, team_rec = 0;
+    uint32_t team_rec = 0;
     for (uint32_t j = 0; j < nq; ++j) {
         const uint32_t i = order[j];
         const mpdp_batch_query &Q = queries[i];
@@ -878,7 +909,7 @@ void fill_batch_upload(char *up, const BatchLayout &B, uint32_t nq, const mpdp_b
         if (sched) (void)encode_schedule(sched[i], packed);  // checked by check_batch_args
         const uint32_t team = team_of[j];
         for (uint32_t member = 0; member < team; ++member)
-            dq[entry++] = mpdp::BatchQueryDev{Q.n, Q.m, Q.m == Q.n - 1 ? 1u : 0u, (uint32_t)cost_model,
+            dq[entry_of[j] + member] = mpdp::BatchQueryDev{Q.n, Q.m, Q.m == Q.n - 1 ? 1u : 0u, (uint32_t)cost_model,
                                               co, eo, plan_at[i], packed, j, team, member,
                                               team > 1 ? team_rec : 0u, 0u};
         if (team > 1) ++team_rec;
@@ -894,7 +925,6 @@ void fill_batch_upload(char *up, const BatchLayout &B, uint32_t nq, const mpdp_b
         co += Q.n;
         eo += Q.m;
     }
-    bc->entries = entry;  // at most B.max_entries: no more teams than eligible queries
 }
 
 hipError_t enqueue_batch_kernel(char *base, const BatchLayout &B, uint32_t nq, mpdp_cost_model cost_model,
@@ -957,9 +987,10 @@ mpdp_status batch_core(uint32_t nq, const mpdp_batch_query *queries, const mpdp_
     char *base = static_cast<char *>(d_workspace);
     std::vector<uint32_t> order, team;
     std::vector<uint64_t> plan_at;
-    batch_order(nq, queries, edges, order, team, plan_at, (flags & kFlagBatchAllTeams) != 0);
+    std::vector<double> ms;
+    batch_order(nq, queries, edges, order, team, ms, plan_at, (flags & kFlagBatchAllTeams) != 0);
     std::vector<char> up(B.plans);
-    fill_batch_upload(up.data(), B, nq, queries, order, team, plan_at, edges, cardinalities, selectivities, base_costs,
+    fill_batch_upload(up.data(), B, nq, queries, order, team, ms, plan_at, edges, cardinalities, selectivities, base_costs,
                       cost_model, sched);
     const int rate_khz = wall_clock_khz();
     const bool timing = (flags & MPDP_FLAG_TIMING) != 0;
@@ -1094,6 +1125,7 @@ struct mpdp_batch_graph {
     std::vector<mpdp_batch_query> shape;  // n and m per query, offsets as given at creation
     BatchLayout B{};
     std::vector<uint32_t> order, team;    // queue order and team sizes of the current run
+    std::vector<double> ms;               // predicted times, by query
     std::vector<uint64_t> plan_at;
     char *base = nullptr;                 // device workspace
     char *h_up = nullptr;                 // pinned: the upload image (B.plans bytes)
@@ -1305,8 +1337,8 @@ mpdp_status mpdp_batch_graph_run(mpdp_batch_graph *g, const mpdp_batch_query *qu
     if (st0 != MPDP_OK) return st0;
     // order and teams follow this run's edges; the layout, fixed by the
     // shapes, has room for any choice of teams
-    batch_order(g->nq, queries, edges, g->order, g->team, g->plan_at);
-    fill_batch_upload(g->h_up, g->B, g->nq, queries, g->order, g->team, g->plan_at, edges, cardinalities, selectivities,
+    batch_order(g->nq, queries, edges, g->order, g->team, g->ms, g->plan_at);
+    fill_batch_upload(g->h_up, g->B, g->nq, queries, g->order, g->team, g->ms, g->plan_at, edges, cardinalities, selectivities,
                       nullptr, g->cm, schedules);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     HIPCHK(hipGraphLaunch(g->exec, s));

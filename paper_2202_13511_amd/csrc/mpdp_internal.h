@@ -127,7 +127,7 @@ struct TeamRec {
     uint32_t arrive;                 // barrier arrivals so far
     uint32_t slot;                   // workgroup whose slot holds the memo and lists
     uint32_t error;                  // a barrier wait ran out of time
-    uint32_t pad;
+    uint32_t xcds;                   // bit x: a member runs on XCD x
     uint32_t count[24];              // connected sets per level k
     unsigned long long ccp, evaluated;
 };
@@ -150,10 +150,15 @@ struct BatchOut {
     uint32_t error, pad;
 };
 
+// The queue: the teams in a share for each XCD, entries share_end[x - 1] ..
+// share_end[x] - 1 (from 0 for the first), then the others for all.  The
+// workgroups of an XCD start with its share, so that a team's members,
+// neighbours there, run on one XCD.
 struct BatchCounters {
-    uint32_t next;           // next queue entry to take
+    uint32_t next;           // next entry to take after the shares
     uint32_t entries;        // queue entries of this launch
     unsigned long long t0;   // earliest workgroup start (device wall clock)
+    uint32_t share_taken[8], share_end[8];
 };
 
 constexpr uint32_t kBatchMaxRel = 20;      // largest query the batched path takes

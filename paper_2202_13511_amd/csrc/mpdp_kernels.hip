@@ -327,7 +327,7 @@ __global__ __launch_bounds__(64) void k_extract(const DevGraph *g, uint32_t n, M
         down.cnt->ccp = cnt->ccp + ccp;
         down.cnt->evaluated = cnt->evaluated + evaluated;
     }
-    const bool ok = extract_plan(binom, loff, M, n, down.plan, down.root, P, threadIdx.x, blockDim.x);
+    const bool ok = extract_plan(binom, loff, false, M, n, down.plan, down.root, P, threadIdx.x, blockDim.x);
     if (threadIdx.x == 0) down.cnt->extract_error = ok ? 0u : 1u;
 }
 

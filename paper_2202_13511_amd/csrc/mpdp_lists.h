@@ -73,6 +73,28 @@ __device__ __forceinline__ uint32_t colex_rank(const uint32_t *T, uint32_t X, bo
     return r;
 }
 
+// nbrs of a set of up to 24 relations: three lookups.
+template <bool kWide>
+__device__ __forceinline__ uint32_t nbrs_of(const uint32_t (*nb)[256], uint32_t V) {
+    const uint32_t r = nb[0][V & 255u] | nb[1][(V >> 8) & 255u] | nb[2][(V >> 16) & 255u];
+    return kWide ? r | nb[3][V >> 24] : r;
+}
+
+// Where a set's memo entry is.  ColexMemo: the level's offset plus the colex
+// rank, the layout that callers see.  BitMemo: the set itself, for a memo of
+// the kernel's own, with no lookup at all.
+struct ColexMemo {
+    const uint32_t *T;
+    const uint64_t *loff;
+    bool wide;  // more than 24 relations (T holds the last digits only then)
+    __device__ __forceinline__ uint64_t operator()(uint32_t X, uint32_t k) const {
+        return loff[k] + colex_rank(T, X, wide);
+    }
+};
+struct BitMemo {
+    __device__ __forceinline__ uint64_t operator()(uint32_t X, uint32_t) const { return X; }
+};
+
 // ---------------------------------------------------------------- buffers
 
 // One wave's LDS.  The pool is the stack of search states (eval_pairs):
@@ -275,30 +297,31 @@ __device__ __forceinline__ void settle_pair(Buf &B, const PairLoad<CM> &p, PairB
 }
 
 struct PairParts {
-    HeavyPart *rec;
+    HeavyPart *rec;     // (global memory, or LDS where one workgroup's waves share)
     uint32_t *arrived;  // per set, zero between uses
-    bool local;         // both in LDS: one workgroup's waves
 };
 
-template <int CM, class Buf>
-__device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, const MemoPtrs &M, const uint32_t *list,
+template <int CM, bool kWide, class At, class Buf>
+__device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M, const uint32_t *list,
                            uint32_t count, uint32_t k, uint32_t w, uint32_t nw, uint32_t per, uint32_t parts,
                            Buf &B, PairParts pp, uint32_t lane, unsigned long long &ccp,
                            unsigned long long &evaluated) {
     const unsigned long long below = (1ull << lane) - 1ull;
-    const uint32_t items = parts > 1 ? count * parts : (count + per - 1) / per;
+    const uint32_t chunks = (count + per - 1) / per, items = parts > 1 ? count * parts : chunks;
     for (uint32_t item = w; item < items; item += nw) {
-        const uint32_t s0 = parts > 1 ? item / parts : item * per, part = parts > 1 ? item - s0 * parts : 0u;
-        const uint32_t ns = parts > 1 ? 1u : min(per, count - s0);
+        // sets s0, s0 + chunks, ..: neighbours in the list have much the same
+        // number of pairs, and no wave should get the largest ones alone
+        const uint32_t s0 = parts > 1 ? item / parts : item, part = parts > 1 ? item - s0 * parts : 0u;
+        const uint32_t ns = parts > 1 ? 1u : (count - s0 + chunks - 1u) / chunks;
         bool quiet = part != 0;       // the first steps of a shared set count for its first part alone
         bool shared = parts > 1;      // not split yet
         uint32_t myset = 0;
         double mycard = 0.0;
         PairBest best{~0ull, ~0u, ~0u, lane, 0.0};
         if (lane < ns) {
-            myset = list[s0 + lane];
+            myset = list[s0 + lane * chunks];
             if (part == 0) evaluated += block_candidates(L, myset, B.p0 + lane);
-            mycard = card_of(L, myset);
+            tree_card_n<1>(L, &myset, k, &mycard);
             B.card[lane] = mycard;
             B.bc[lane] = ~0ull;
             B.bl[lane] = B.bop[lane] = ~0u;
@@ -357,19 +380,42 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
             const uint32_t nv = place ? C1 : av & C1;
             uint32_t comp = C1;
             if ((nv & (nv - 1u)) != 0u) {
-                // C was connected, so C1 is once one neighbour of v reaches the others
-                uint32_t seen = lowbit(nv), fr = seen;
+                // C was connected, so C1 is once one neighbour of v reaches the
+                // others, and every component of C1 holds one.  Two neighbours
+                // search towards each other: they meet in half as many rounds
+                // as one would need, and apart, the smaller component ends it.
+                const uint32_t b = 31u - (uint32_t)__builtin_clz(nv);
+                uint32_t sa = lowbit(nv), sb = 1u << b;
+                uint32_t fa = L.adj[ctz32(sa)] & C1, fb = L.adj[b] & C1;
+                sa |= fa;
+                sb |= fb;
+                while ((sa & sb) == 0u && fa != 0u && fb != 0u) {
+                    fa = nbrs_of<kWide>(L.nb, fa) & C1 & ~sa;
+                    fb = nbrs_of<kWide>(L.nb, fb) & C1 & ~sb;
+                    sa |= fa;
+                    sb |= fb;
+                }
+                const bool met = (sa & sb) != 0u;
+                // met: one component, which may lack others; apart: that of
+                // the side that ended
+                uint32_t seen = met ? sa | sb : fa == 0u ? sa : sb;
+                uint32_t fr = met ? fa | fb : 0u;
                 while (fr != 0u && (nv & ~seen) != 0u) {
-                    fr = nbrs(L.nb, fr) & C1 & ~seen;
+                    fr = nbrs_of<kWide>(L.nb, fr) & C1 & ~seen;
                     seen |= fr;
                 }
                 if ((nv & ~seen) != 0u) {
                     if (s.X != 0u && (s.X & seen) == 0u) {  // the component of X is the one that stays
-                        seen = lowbit(s.X);
-                        fr = seen;
-                        while (fr != 0u) {
-                            fr = nbrs(L.nb, fr) & C1 & ~seen;
-                            seen |= fr;
+                        const uint32_t others = nv & ~seen;
+                        if ((others & (others - 1u)) == 0u) {
+                            seen = C1 & ~seen;
+                        } else {
+                            seen = lowbit(s.X);
+                            fr = seen;
+                            while (fr != 0u) {
+                                fr = nbrs_of<kWide>(L.nb, fr) & C1 & ~seen;
+                                seen |= fr;
+                            }
                         }
                     }
                     comp = seen;
@@ -396,8 +442,8 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
                 if (push_left) push_state(B, at, S & ~left, left, 0u, 0u, s.slot);
                 if (!quiet) {
                     const uint32_t ka = (uint32_t)popc32(A1);
-                    const uint64_t ia = L.loff[ka] + colex_rank(T, A1, wide);
-                    const uint64_t ib = L.loff[k - ka] + colex_rank(T, comp, wide);
+                    const uint64_t ia = at_of(A1, ka);
+                    const uint64_t ib = at_of(comp, k - ka);
                     ld.A = A1;
                     ld.B = comp;
                     ld.slot = s.slot;
@@ -409,7 +455,7 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
                     }
                     ++ccp;
                 }
-                s.F = ((place ? nbrs(L.nb, s.A) : av) | rest) & comp & ~s.X;
+                s.F = ((place ? nbrs_of<kWide>(L.nb, s.A) : av) | rest) & comp & ~s.X;
                 s.A = A1;
                 s.C = s.F != 0u ? comp : 0u;
             } else if (go) {  // no pair takes v to the left
@@ -424,7 +470,7 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
         wave_sync_lds();
         if (parts == 1) {
             if (lane < ns) {
-                const uint64_t at = L.loff[k] + colex_rank(T, myset, wide);
+                const uint64_t at = at_of(myset, k);
                 store_best(M, at, Key{B.bc[lane], B.bl[lane], B.bop[lane]}, mycard);
             }
         } else {
@@ -438,14 +484,17 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
                 __hip_atomic_store(&r64[0], B.bc[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&r64[1], ((unsigned long long)B.bop[0] << 32) | B.bl[0], __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-                if (pp.local) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                // the record is all that others read, and its stores are
+                // device-wide themselves: once they are complete, the
+                // arrival may follow (an agent-scope release would write
+                // the whole L2 back first, in every part's wave)
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_s_waitcnt(0);
                 n_here = __hip_atomic_fetch_add(&pp.arrived[s0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             n_here = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_here);
             if (n_here == parts - 1u) {
-                if (pp.local) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // (device-wide loads follow)
                 Key best = worst_key();
                 for (uint32_t p = lane; p < parts; p += 64u) {
                     unsigned long long *r64 = reinterpret_cast<unsigned long long *>(&rec[p]);
@@ -458,7 +507,7 @@ __device__ void eval_pairs(const LdsGraph &L, const uint32_t *T, bool wide, cons
                 }
                 best = wave_min(best);
                 if (lane == 0) {
-                    store_best(M, L.loff[k] + colex_rank(T, S0, wide), best, mycard);
+                    store_best(M, at_of(S0, k), best, mycard);
                     __hip_atomic_store(&pp.arrived[s0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
@@ -487,7 +536,7 @@ struct ExpandEnds {
     uint32_t fill, end, start;  // words taken, first word not used, place in the list
 };
 
-template <bool kTree>
+template <bool kTree, bool kWide>
 __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t count, uint32_t *out, uint32_t *out_count,
                             uint32_t w, uint32_t nw, uint32_t group, uint32_t *buf, uint32_t cap, ExpandEnds &ends,
                             uint32_t lane) {
@@ -498,7 +547,7 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
     for (uint32_t base = w * each; base < count; base += nw * each) {
         const uint32_t i = base + lane / group;
         const uint32_t S = i < count ? list[i] : 0u;
-        uint32_t N = kTree ? nbrs(L.pch, S) & ~(0xffffffffu >> __builtin_clz(S | 1u)) : nbrs(L.nb, S) & ~S;
+        uint32_t N = kTree ? nbrs_of<kWide>(L.pch, S) & ~(0xffffffffu >> __builtin_clz(S | 1u)) : nbrs_of<kWide>(L.nb, S) & ~S;
         for (uint32_t j = 0; j < sub; ++j) N &= N - 1u;
         while (__ballot(N != 0u) != 0ull) {
             const uint32_t v = lowbit(N), S1 = S | v;
@@ -507,7 +556,7 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
             if (!kTree && v != 0u) {
                 uint32_t seen = lowbit(S1), fr = seen;
                 while (seen != S1) {  // S1 is connected
-                    fr = nbrs(L.nb, fr) & S1 & ~seen;
+                    fr = nbrs_of<kWide>(L.nb, fr) & S1 & ~seen;
                     seen |= fr;
                 }
                 keep = (v & fr) != 0u && (fr & ~(v | (v - 1u))) == 0u;
@@ -548,8 +597,8 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
 // with all their reads in flight; a member without a pair (the topmost, or
 // past the end) reads entry 0 and offers nothing.  `thread` of `threads`
 // (groups of lanes never straddle waves).
-template <int CM>
-__device__ void eval_tree_list(const LdsGraph &L, const uint32_t *T, bool wide, const MemoPtrs &M,
+template <int CM, class At>
+__device__ void eval_tree_list(const LdsGraph &L, const At &at_of, const MemoPtrs &M,
                                const uint32_t *list, uint32_t count, uint32_t k, uint32_t lgP, uint32_t thread,
                                uint32_t threads) {
     const uint32_t P = 1u << lgP, sub = thread & (P - 1u);
@@ -570,8 +619,8 @@ __device__ void eval_tree_list(const LdsGraph &L, const uint32_t *T, bool wide, 
                 A[u] = U != 0u && (S & pd.x) != 0u ? pd.y & S : 0u;
                 for (uint32_t j = 0; j < P; ++j) U &= U - 1u;
                 const uint32_t ka = (uint32_t)popc32(A[u]);
-                ia[u] = A[u] ? L.loff[ka] + colex_rank(T, A[u], wide) : 0ull;
-                ib[u] = A[u] ? L.loff[k - ka] + colex_rank(T, S ^ A[u], wide) : 0ull;
+                ia[u] = A[u] ? at_of(A[u], ka) : 0ull;
+                ib[u] = A[u] ? at_of(S ^ A[u], k - ka) : 0ull;
             }
             double cA[4], cB[4], kA[4], kB[4];
 #pragma unroll
@@ -621,7 +670,7 @@ __device__ void eval_tree_list(const LdsGraph &L, const uint32_t *T, bool wide, 
             bop = take ? oo : bop;
         }
         if (sub == 0u)
-            store_best(M, L.loff[k] + colex_rank(T, S, wide),
+            store_best(M, at_of(S, k),
                        Key{(unsigned long long)__double_as_longlong(bc), bl, bop}, cS);
     }
 }
@@ -638,6 +687,15 @@ __device__ __forceinline__ uint32_t tree_group(uint32_t count, uint32_t threads)
     uint32_t lgP = 0;
     while (lgP < 3u && (2u * count << lgP) <= threads) ++lgP;
     return lgP;
+}
+
+// Sets that a wave of eval_pairs takes at a time, of a level of `count` sets
+// and nw waves: the same for all waves, so that none goes another round for
+// the last few sets.  (A step's latency bounds a level, not its lanes: half
+// as many waves with twice the sets took cycles with chords 10 % longer.)
+__device__ __forceinline__ uint32_t pair_sets(uint32_t count, uint32_t nw) {
+    const uint32_t rounds = (count + 64u * nw - 1u) / (64u * nw);
+    return (count + rounds * nw - 1u) / (rounds * nw);
 }
 
 // Lanes that grow one set's successors (expand_sets).

@@ -21,7 +21,7 @@ constexpr uint32_t kShareMinK = 10;
 // workgroup does in step, then each wave its own sets.  `tally` holds two
 // sums per workgroup (pairs, Alg. 3 candidates): adding them to one counter
 // per wave took longer than most levels.
-template <int CM>
+template <int CM, bool kWide>
 __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, uint32_t n, uint32_t k,
                                                             const uint32_t *list, uint32_t *next, Counters *cnt,
                                                             MemoPtrs M, HeavyPart *rec, uint32_t *arrived,
@@ -33,10 +33,7 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
     __shared__ unsigned long long sums[2];
     const uint32_t count = cnt->level_count[k];
     const uint32_t nw = gridDim.x * (kPairBlock / 64);
-    // sets per wave at a time: the same for all waves, so that none goes
-    // another round for the last few sets
-    const uint32_t rounds = (count + 64u * nw - 1u) / (64u * nw);
-    const uint32_t per = (count + rounds * nw - 1u) / (rounds * nw);
+    const uint32_t per = pair_sets(count, nw);
     const uint32_t group = expand_group(count, 64u * nw);
     const uint32_t parts = k >= kShareMinK && 2u * count <= nw ? min(64u, nw / count) : 1u;
     // neighbouring items to different CUs, so that few items still fill the chip
@@ -49,11 +46,11 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
     if (threadIdx.x < 2) sums[threadIdx.x] = 0ull;
     __syncthreads();
     if (k < n)
-        expand_sets<false>(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, reinterpret_cast<uint32_t *>(buf),
+        expand_sets<false, kWide>(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, reinterpret_cast<uint32_t *>(buf),
                     sizeof(buf) / 4, ends, lane);
     unsigned long long ccp = 0, evaluated = 0;
-    eval_pairs<CM>(L, ranks, n > 24u, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6],
-                   PairParts{rec, arrived, false}, lane, ccp, evaluated);
+    eval_pairs<CM, kWide>(L, ColexMemo{ranks, L.loff, kWide}, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6],
+                   PairParts{rec, arrived}, lane, ccp, evaluated);
     for (int off = 32; off >= 1; off >>= 1) {
         ccp += (unsigned long long)__shfl_xor((long long)ccp, off);
         evaluated += (unsigned long long)__shfl_xor((long long)evaluated, off);
@@ -85,11 +82,11 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_level(const DevGraph *g, ui
         stage_ranks(ranks, n);
         __syncthreads();
         const uint32_t threads = eval * kTreeBlock;
-        eval_tree_list<CM>(L, ranks, n > 24u, M, list, count, k, tree_group(count, threads),
+        eval_tree_list<CM>(L, ColexMemo{ranks, L.loff, n > 24u}, M, list, count, k, tree_group(count, threads),
                            (wave * eval + blockIdx.x) * 64u + lane, threads);
     } else {
         const uint32_t blocks = gridDim.x - eval, threads = blocks * kTreeBlock;
-        expand_sets<true>(L, list, count, next, &cnt->level_count[k + 1], wave * blocks + blockIdx.x - eval,
+        expand_sets<true, true>(L, list, count, next, &cnt->level_count[k + 1], wave * blocks + blockIdx.x - eval,
                           threads / 64, 1u, ranks, kTreeExpand, ends, lane);
     }
 }
@@ -132,9 +129,9 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
         const uint32_t *list = (k & 1u) ? odd : even;
         const uint32_t count = __hip_atomic_load(&cnt->level_count[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (k < n)
-            expand_sets<true>(L, list, count, (k & 1u) ? even : odd, &cnt->level_count[k + 1], t >> 6,
+            expand_sets<true, true>(L, list, count, (k & 1u) ? even : odd, &cnt->level_count[k + 1], t >> 6,
                               kSpanBlock / 64, 1u, buf, kSpanExpand, ends, t & 63u);
-        eval_tree_list<CM>(L, ranks, n > 24u, M, list, count, k, tree_group(count, kSpanBlock), t, kSpanBlock);
+        eval_tree_list<CM>(L, ColexMemo{ranks, L.loff, n > 24u}, M, list, count, k, tree_group(count, kSpanBlock), t, kSpanBlock);
         __syncthreads();
     }
 }
@@ -144,12 +141,14 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
 hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,
                               uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
                               unsigned long long *tally, hipStream_t s) {
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(kPairGrid), dim3(kPairBlock), 0, s, g, n, k, list, next, cnt, memo, rec,
+                           arrived, tally);
+    };
     if (cost_model == MPDP_COST_COUT)
-        hipLaunchKernelGGL(k_level_pairs<MPDP_COST_COUT>, dim3(kPairGrid), dim3(kPairBlock), 0, s, g, n, k, list, next,
-                           cnt, memo, rec, arrived, tally);
+        n > 24 ? go(k_level_pairs<MPDP_COST_COUT, true>) : go(k_level_pairs<MPDP_COST_COUT, false>);
     else
-        hipLaunchKernelGGL(k_level_pairs<MPDP_COST_PGLIKE>, dim3(kPairGrid), dim3(kPairBlock), 0, s, g, n, k, list,
-                           next, cnt, memo, rec, arrived, tally);
+        n > 24 ? go(k_level_pairs<MPDP_COST_PGLIKE, true>) : go(k_level_pairs<MPDP_COST_PGLIKE, false>);
     return hipGetLastError();
 }
 
