@@ -33,7 +33,7 @@ uint64_t binom64(uint32_t a, uint32_t b) {
 }
 
 struct Layout {
-    size_t cost, card, left, op, list, heavy, parts, arrived, tally, graph, counters, plan, root, total;
+    size_t cost, card, left, op, list, heavy, parts, arrived, tally, bits, graph, counters, plan, root, total;
 };
 
 Layout make_layout(uint32_t n) {
@@ -49,6 +49,7 @@ Layout make_layout(uint32_t n) {
     L.parts = o;    o = align_up(o + sizeof(mpdp::HeavyPart) * mpdp::kPairWaves);
     L.arrived = o;  o = align_up(o + sizeof(uint32_t) * mpdp::kPairWaves);
     L.tally = o;    o = align_up(o + 2 * sizeof(unsigned long long) * mpdp::kPairGrid);
+    L.bits = o;     o = n <= mpdp::kBitsMaxRel ? align_up(o + 24 * N + (N < 128 ? 16 : N / 8)) : o;
     L.graph = o;    o = align_up(o + sizeof(DevGraph));
     L.counters = o; o = align_up(o + sizeof(Counters));
     L.plan = o;     o = align_up(o + sizeof(mpdp_plan_node) * 64);
@@ -511,6 +512,14 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     }
     std::vector<char> down_pageable((pin || no_alloc) ? 0 : down_bytes);
     char *down = pin ? pin : (no_alloc ? down_stack : down_pageable.data());
+    const bool bits = general && !dpsub && n <= mpdp::kBitsMaxRel;
+    const size_t N = size_t(1) << n;
+    char *const bat = base + L.bits;
+    const bool cout_model = q.cost_model == MPDP_COST_COUT;
+    const mpdp::BitsSpace space{reinterpret_cast<uint32_t *>(bat + 24 * N), reinterpret_cast<double *>(bat),
+                                reinterpret_cast<double *>(bat + (cout_model ? 8 * N : 8)), cout_model ? 1u : 2u,
+                                reinterpret_cast<uint32_t *>(bat + 16 * N),
+                                reinterpret_cast<uint32_t *>(bat + 20 * N)};
     // tree joins: lists of connected sets, but for stars around relation 0
     // (every set that holds it is connected) and the ablations
     const bool tree_lists = !general && !unfused && (flags & MPDP_FLAG_ABLATE_NO_COMPACTION) == 0 &&
@@ -542,7 +551,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
                     k = k1;
                     continue;
                 }
-                if (k == 2) e = mpdp::launch_init(src, dg, n, memo, list, arrived, tally, true, cnt, st);
+                if (k == 2) e = mpdp::launch_init(src, dg, n, memo, list, nullptr, nullptr, true, cnt, st);
                 if (timing && e == hipSuccess) e = hipEventRecord(ev.ev[4 * k - 8], st);
                 if (timing && e == hipSuccess) e = hipEventRecord(ev.ev[4 * k - 7], st);
                 if (e == hipSuccess)
@@ -553,14 +562,20 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
             }
             return e == hipSuccess ? finish(nullptr) : e;
         }
-        if (e == hipSuccess) e = mpdp::launch_init(src, dg, n, memo, general && !dpsub ? list : nullptr, arrived, tally, false, cnt, st);
+        const bool counted = general && !dpsub;  // per workgroup
+        if (e == hipSuccess)
+            e = mpdp::launch_init(src, dg, n, memo, counted && !bits ? list : nullptr, counted ? arrived : nullptr, tally,
+                                  false, cnt, st);
         for (uint32_t k = 2; k <= n && e == hipSuccess; ++k) {
             const uint64_t nc = binom64(n, k);
             if (timing) e = hipEventRecord(ev.ev[4 * k - 8], st);
             if (e == hipSuccess && dpsub) e = mpdp::launch_filter(dg, k, nc, list, cnt, st);
+            if (e == hipSuccess && bits && k == 2) e = mpdp::launch_bits_init(dg, n, cnt, space, st);
             if (e == hipSuccess && timing) e = hipEventRecord(ev.ev[4 * k - 7], st);
             if (e != hipSuccess) break;
-            if (general && !dpsub)  // lists of connected sets: odd levels in one buffer, even ones in the other
+            if (bits)
+                e = mpdp::launch_bits_level(dg, q.cost_model, n, k, nc, cnt, space, memo, parts, arrived, tally, st);
+            else if (counted)  // lists of connected sets: odd levels in one buffer, even ones in the other
                 e = mpdp::launch_level_pairs(dg, q.cost_model, n, k, (k & 1u) ? heavy : list, (k & 1u) ? list : heavy,
                                              cnt, memo, parts, arrived, tally, st);
             else if (dpsub)
@@ -573,7 +588,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
                                             q.g.flat != 0, cnt, memo, st);
             if (e == hipSuccess && timing) e = hipEventRecord(ev.ev[4 * k - 6], st);
         }
-        return e == hipSuccess ? finish(general && !dpsub ? tally : nullptr) : e;
+        return e == hipSuccess ? finish(counted ? tally : nullptr) : e;
     };
     if (pin) std::memcpy(pin, &q.g, sizeof(DevGraph));
     const bool graphed = pin && !timing && flags == 0 && n <= kGraphMaxRel;

@@ -186,9 +186,26 @@ constexpr uint32_t kPairWaves = kPairGrid * (kPairBlock / 64);
 // it already).
 hipError_t launch_init(const DevGraph *src, DevGraph *g, uint32_t n, MemoPtrs memo, uint32_t *list2,
                        uint32_t *arrived, unsigned long long *tally, bool preorder, Counters *cnt, hipStream_t s);
-// One level of the block-based path: the sets of k relations in `list`
-// (cnt->level_count[k] of them) evaluated, the sets of k + 1 into `next`.
 struct HeavyPart;
+// Cyclic queries of up to kBitsMaxRel relations: launch_bits_init (after
+// launch_init) fills conn, list, card and the single relations' cost; one
+// launch_bits_level a level.  sets: C(n, k), the most the level can have.
+// At 18 relations, C_out, a clique takes 1074 us here and 1742 with lists and
+// pair search, a cycle with 4 chords 331 and 530; each relation more triples
+// the candidates.
+constexpr uint32_t kBitsMaxRel = 18;
+struct BitsSpace {
+    uint32_t *conn;       // bit S: S is connected
+    double *cost, *card;  // of a connected set S, at S * stride: two arrays, or (PG-like) pairs
+    uint32_t stride;
+    uint32_t *cand;       // its Alg. 3 candidates (sum over its blocks of 2^b - 2)
+    uint32_t *list;       // connected sets, level k from loff[k] on
+};
+hipError_t launch_bits_init(const DevGraph *g, uint32_t n, Counters *cnt, const BitsSpace &b, hipStream_t s);
+hipError_t launch_bits_level(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, uint64_t sets,
+                             const Counters *cnt, const BitsSpace &b, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
+                             unsigned long long *tally, hipStream_t s);
+
 // One level of a tree join, or levels k0 .. k1 by one workgroup (with k0 = 2
 // in place of launch_init).  even, odd: the lists of even and odd levels, in
 // preorder numbers; count: the sets of level k.
@@ -197,6 +214,8 @@ hipError_t launch_tree_level(const DevGraph *g, int cost_model, uint32_t n, uint
                              const uint32_t *list, uint32_t *next, Counters *cnt, MemoPtrs memo, hipStream_t s);
 hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, uint32_t n, uint32_t k0, uint32_t k1,
                             uint32_t *even, uint32_t *odd, Counters *cnt, MemoPtrs memo, hipStream_t s);
+// One level of the block-based path: the sets of k relations in `list`
+// (cnt->level_count[k] of them) evaluated, the sets of k + 1 into `next`.
 hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,
                               uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
                               unsigned long long *tally, hipStream_t s);

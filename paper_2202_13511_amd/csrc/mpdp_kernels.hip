@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kInitBlock) void k_init(const DevGraph *src, DevGra
             for (uint32_t U = G.lds.adj[t] & ((1u << t) - 1u); U; U &= U - 1) list2[e++] = (1u << t) | lowbit(U);
         }
     }
-    if (list2 && !preorder) {
+    if (arrived) {
         for (uint32_t i = t; i < kPairWaves; i += blockDim.x) arrived[i] = 0u;
         for (uint32_t i = t; i < 2 * kPairGrid; i += blockDim.x) tally[i] = 0ull;
     }

@@ -587,6 +587,77 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
     __syncthreads();
 }
 
+// ---------------------------------------------------------------- best keys of lane groups
+
+// A set's best key so far: the smallest cost (+inf before the first offer;
+// every connected set has a finite one or offers +inf itself), then the
+// smallest left set, which names the offer and its operator (a set's offers
+// all have different left sets).
+struct SetBest {
+    double c;
+    uint32_t l, op;
+};
+
+__device__ __forceinline__ void take_best(SetBest &b, const SetBest &o) {
+    const bool take = (o.c < b.c) | ((o.c == b.c) & (o.l < b.l));
+    b.c = take ? o.c : b.c;
+    b.l = take ? o.l : b.l;
+    b.op = take ? o.op : b.op;
+}
+
+template <int kCtrl>
+__device__ __forceinline__ void merge_best(SetBest &b) {
+    const unsigned long long c = (unsigned long long)__double_as_longlong(b.c);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)c, kCtrl, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(c >> 32), kCtrl, 0xf, 0xf, true);
+    SetBest o;
+    o.c = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    o.l = (uint32_t)__builtin_amdgcn_mov_dpp((int)b.l, kCtrl, 0xf, 0xf, true);
+    o.op = (uint32_t)__builtin_amdgcn_mov_dpp((int)b.op, kCtrl, 0xf, 0xf, true);
+    take_best(b, o);
+}
+
+// The best of 2^lgP neighbouring lanes, in all of them.
+__device__ __forceinline__ void group_best(SetBest &b, uint32_t P) {
+    if (P >= 2u) merge_best<0xB1>(b);   // lanes ^ 1 (quad_perm 1 0 3 2)
+    if (P >= 4u) merge_best<0x4E>(b);   // ^ 2 (quad_perm 2 3 0 1)
+    if (P >= 8u) merge_best<0x141>(b);  // ^ 4: quads agree, so mirroring eight lanes swaps them
+    if (P >= 16u) merge_best<0x140>(b); // ^ 8, mirroring a row
+    for (uint32_t d = 16; d < P; d <<= 1) {
+        SetBest o;
+        o.c = __shfl_xor(b.c, (int)d, 64);
+        o.l = (uint32_t)__shfl_xor((int)b.l, (int)d, 64);
+        o.op = (uint32_t)__shfl_xor((int)b.op, (int)d, 64);
+        take_best(b, o);
+    }
+}
+
+// Both offers of the pair (A, B) under PG-like, or its one under C_out.
+template <int CM>
+__device__ __forceinline__ SetBest pair_best(uint32_t A, uint32_t B, double cA, double cB, double kA, double kB,
+                                             double cS) {
+    const double base = cA + cB;
+    SetBest o;
+    if (CM == MPDP_COST_COUT) {
+        o.c = base + cS;
+        o.l = A < B ? A : B;
+        o.op = MPDP_OP_JOIN;
+    } else {
+        const double out = 0.01 * cS;
+        const double hjA = ((base + 0.0125 * kB) + 0.0025 * kA) + out;  // A outer, B hashed
+        const double nlA = (base + (0.0025 * kA) * kB) + out;
+        const double hjB = ((base + 0.0125 * kA) + 0.0025 * kB) + out;  // B outer, A hashed
+        const double nlB = (base + (0.0025 * kB) * kA) + out;
+        const bool hA = hjA <= nlA, hB = hjB <= nlB;
+        o.c = hA ? hjA : nlA;
+        o.l = A;
+        o.op = hA ? MPDP_OP_HASH : MPDP_OP_NESTLOOP;
+        const SetBest o2{hB ? hjB : nlB, B, hB ? MPDP_OP_HASH : MPDP_OP_NESTLOOP};
+        take_best(o, o2);
+    }
+    return o;
+}
+
 // ---------------------------------------------------------------- tree joins
 
 // Alg. 2 for the sets list[0 .. count) of a tree join (in preorder numbers),

@@ -55,38 +55,10 @@ __device__ __forceinline__ uint32_t small_candidates(const SmallLds &D, uint32_t
     return (uint32_t)D.cand[part | v] + D.cand[S ^ part];
 }
 
-// A set's best key so far: the smallest cost (+inf before the first offer;
-// every connected set has a finite one or offers +inf itself), then the
-// smallest left set, which names the offer and its operator (a set's offers
-// all have different left sets).
-struct SmallBest {
-    double c;
-    uint32_t l, op;
-};
-
-__device__ __forceinline__ void small_take(SmallBest &b, const SmallBest &o) {
-    const bool take = (o.c < b.c) | ((o.c == b.c) & (o.l < b.l));
-    b.c = take ? o.c : b.c;
-    b.l = take ? o.l : b.l;
-    b.op = take ? o.op : b.op;
-}
-
-template <int kCtrl>
-__device__ __forceinline__ void small_merge(SmallBest &b) {
-    const unsigned long long c = (unsigned long long)__double_as_longlong(b.c);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)c, kCtrl, 0xf, 0xf, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(c >> 32), kCtrl, 0xf, 0xf, true);
-    SmallBest o;
-    o.c = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-    o.l = (uint32_t)__builtin_amdgcn_mov_dpp((int)b.l, kCtrl, 0xf, 0xf, true);
-    o.op = (uint32_t)__builtin_amdgcn_mov_dpp((int)b.op, kCtrl, 0xf, 0xf, true);
-    small_take(b, o);
-}
-
 // The pairs (A[j], S - A[j]) with on[j], both orientations, without branches.
 template <int CM, int R>
 __device__ __forceinline__ void small_offers(const SmallLds &D, uint32_t S, const uint32_t *A, const bool *on,
-                                             double cS, SmallBest &best) {
+                                             double cS, SetBest &best) {
     double cA[R], cB[R], kA[R], kB[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
@@ -97,29 +69,10 @@ __device__ __forceinline__ void small_offers(const SmallLds &D, uint32_t S, cons
     }
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const uint32_t B = S ^ A[j];
-        const double base = cA[j] + cB[j];
-        SmallBest o;
-        if (CM == MPDP_COST_COUT) {
-            o.c = base + cS;
-            o.l = A[j] < B ? A[j] : B;
-            o.op = MPDP_OP_JOIN;
-        } else {
-            const double out = 0.01 * cS;
-            const double hjA = ((base + 0.0125 * kB[j]) + 0.0025 * kA[j]) + out;  // A outer, B hashed
-            const double nlA = (base + (0.0025 * kA[j]) * kB[j]) + out;
-            const double hjB = ((base + 0.0125 * kA[j]) + 0.0025 * kB[j]) + out;  // B outer, A hashed
-            const double nlB = (base + (0.0025 * kB[j]) * kA[j]) + out;
-            const bool hA = hjA <= nlA, hB = hjB <= nlB;
-            o.c = hA ? hjA : nlA;
-            o.l = A[j];
-            o.op = hA ? MPDP_OP_HASH : MPDP_OP_NESTLOOP;
-            const SmallBest o2{hB ? hjB : nlB, B, hB ? MPDP_OP_HASH : MPDP_OP_NESTLOOP};
-            small_take(o, o2);
-        }
+        SetBest o = pair_best<CM>(A[j], S ^ A[j], cA[j], cB[j], kA[j], kB[j], cS);
         o.l = on[j] ? o.l : ~0u;
         o.c = on[j] ? o.c : __builtin_inf();
-        small_take(best, o);
+        take_best(best, o);
     }
 }
 
@@ -247,7 +200,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(SmallQuery Q, MemoPtrs M,
         for (uint32_t i = t >> lgP; i < count; i += threads >> lgP) {
             const uint32_t S = D.list[D.loff[k] + i];
             const double cS = D.card[S];
-            SmallBest best{__builtin_inf(), ~0u, ~0u};
+            SetBest best{__builtin_inf(), ~0u, ~0u};
             if (Q.is_tree) {
                 for (uint32_t v0 = sub; v0 < n; v0 += 4u << lgP) {
                     // four members' pairs, their reads in flight together (a
@@ -284,17 +237,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(SmallQuery Q, MemoPtrs M,
                     if (on[0] | on[1]) small_offers<CM, 2>(D, S, A, on, cS, best);
                 }
             }
-            if (P >= 2u) small_merge<0xB1>(best);   // lanes ^ 1 (quad_perm 1 0 3 2)
-            if (P >= 4u) small_merge<0x4E>(best);   // ^ 2 (quad_perm 2 3 0 1)
-            if (P >= 8u) small_merge<0x141>(best);  // ^ 4: quads agree, so mirroring eight lanes swaps them
-            if (P >= 16u) small_merge<0x140>(best); // ^ 8, mirroring a row
-            for (uint32_t d = 16; d < P; d <<= 1) {
-                SmallBest o;
-                o.c = __shfl_xor(best.c, (int)d, 64);
-                o.l = (uint32_t)__shfl_xor((int)best.l, (int)d, 64);
-                o.op = (uint32_t)__shfl_xor((int)best.op, (int)d, 64);
-                small_take(best, o);
-            }
+            group_best(best, P);
             if (sub == 0u) {
                 D.cost[S] = best.c;
                 D.left[S] = (uint16_t)best.l;
