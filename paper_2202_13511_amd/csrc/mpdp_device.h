@@ -710,18 +710,19 @@ __device__ __forceinline__ void eval_tree_set(const LdsGraph &L, const MemoPtrs 
 // card(S) is tree_card_n's product with its conditions settled: each member
 // ascending multiplies its card, then its selectivity to relation 0 (1.0
 // for relation 0 itself), and no member has another smaller neighbour.
-// A batch's keys are reduced without per-offer branches: the smallest cost
-// of the batch and the running best first, then the smallest left set among
-// the offers that reach it, which is key_less's order (a connected set has
-// at least one pair, so the running best's +inf start never survives; under
-// PG-like the operator follows from the left set, see flat_batch).  Pairs go
-// in batches of kPairBatch (members 1 .. k - 1); only the last batch of a
-// set has slots past its last member, and they take no part (skipped under
-// C_out, +inf offers under PG-like).
+// A set's offers are taken in the order of their members m.  Under C_out the
+// pair's left set is the smaller side, {m}, but S - {m} for the last member,
+// which is larger than all others' (or, with two relations, the only one): the
+// left sets ascend, so that an offer is taken only where it is cheaper, and
+// just the member is kept.  Under PG-like a pair's two left sets, {m} and
+// S - {m}, are compared; all left sets of a set differ, so that cost and left
+// set order the offers.  Pairs go in batches of kPairBatch (members 1 ..
+// k - 1); only the last batch of a set has slots past its last member, and
+// they take no part.
 struct FlatBest {
-    double c;     // running smallest cost (+inf before the first pair)
-    uint32_t l;   // smallest left set at that cost
-    uint32_t op;  // its operator (PG-like)
+    double c;     // smallest cost (+inf before the first pair)
+    uint32_t l;   // C_out: its member; PG-like: the smallest left set at it
+    bool hash;    // PG-like: its operator is the hash join
 };
 
 template <int CM, int R, int kPairBatch, bool kFull, bool kUnfused>
@@ -762,28 +763,23 @@ __device__ __forceinline__ void flat_batch(const LdsGraph &L, const uint32_t *S,
         }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        double c[kPairBatch];
-        uint32_t l[kPairBatch];
-        double pc[2 * kPairBatch];  // PG-like offers: cost, left set, operator
-        uint32_t pl[2 * kPairBatch], po[2 * kPairBatch];
-        double mn = best[r].c;
 #pragma unroll
         for (int u = 0; u < kPairBatch; ++u) {
-            const bool live = kFull || p0 + (uint32_t)u < np;
+            const bool live = kFull || p0 + (uint32_t)u < np;  // uniform
+            if (!live) continue;
             const int m = mv[r][u] & 31;
-            const uint32_t A = 1u << m, B = S[r] ^ A;
-            const double cA = L.bcost[m];
-            const double base = cA + cB[r][u];
-            if (CM == MPDP_COST_COUT) {
-                c[u] = base + cardS[r];
-                l[u] = A < B ? A : B;
-                if (kUnfused) {
-                    if (live)
-                        sink.keys[(uint64_t)sink.slot[r] * k + p0 + (uint32_t)u + 1u] =
-                            PairKey{(unsigned long long)__double_as_longlong(c[u]), l[u], MPDP_OP_JOIN};
-                } else if (live) {
-                    mn = __builtin_fmin(mn, c[u]);
-                }
+            const uint32_t A = 1u << m;
+            const double base = L.bcost[m] + cB[r][u];
+            if (kUnfused) {
+                const uint32_t B = S[r] ^ A;
+                Key one = worst_key();
+                eval_vals<CM>(A, B, L.bcost[m], cB[r][u], L.card[m], kB[r][u], cardS[r], one);
+                sink.keys[(uint64_t)sink.slot[r] * k + p0 + (uint32_t)u + 1u] = PairKey{one.c, one.l, one.op};
+            } else if (CM == MPDP_COST_COUT) {
+                const double c = base + cardS[r];
+                const bool take = c < best[r].c;
+                best[r].c = take ? c : best[r].c;
+                best[r].l = take ? A : best[r].l;
             } else {
                 const double kA = L.card[m];
                 const double out = 0.01 * cardS[r];
@@ -791,49 +787,16 @@ __device__ __forceinline__ void flat_batch(const LdsGraph &L, const uint32_t *S,
                 const double nlA = (base + (0.0025 * kA) * kB[r][u]) + out;
                 const double hjB = ((base + 0.0125 * kA) + 0.0025 * kB[r][u]) + out;  // B outer, A hashed
                 const double nlB = (base + (0.0025 * kB[r][u]) * kA) + out;
-                const bool hA = hjA <= nlA, hB = hjB <= nlB;
-                if (kUnfused) {
-                    Key one = worst_key();
-                    offer_if<CM>(true, one, hA ? hjA : nlA, A, hA ? MPDP_OP_HASH : MPDP_OP_NESTLOOP);
-                    offer_if<CM>(true, one, hB ? hjB : nlB, B, hB ? MPDP_OP_HASH : MPDP_OP_NESTLOOP);
-                    if (live) sink.keys[(uint64_t)sink.slot[r] * k + p0 + (uint32_t)u + 1u] = PairKey{one.c, one.l, one.op};
-                } else {
-                    // both orientations; a slot past the last member offers +inf
-                    pc[2 * u] = live ? (hA ? hjA : nlA) : __builtin_inf();
-                    pl[2 * u] = A;
-                    po[2 * u] = hA ? MPDP_OP_HASH : MPDP_OP_NESTLOOP;
-                    pc[2 * u + 1] = live ? (hB ? hjB : nlB) : __builtin_inf();
-                    pl[2 * u + 1] = B;
-                    po[2 * u + 1] = hB ? MPDP_OP_HASH : MPDP_OP_NESTLOOP;
-                    mn = __builtin_fmin(mn, __builtin_fmin(pc[2 * u], pc[2 * u + 1]));
-                }
+                const double xA = hjA <= nlA ? hjA : nlA, xB = hjB <= nlB ? hjB : nlB;
+                const uint32_t B = S[r] ^ A;
+                const bool first = (xA < xB) | ((xA == xB) & (A < B));
+                const double x = first ? xA : xB;
+                const uint32_t l = first ? A : B;
+                const bool take = (x < best[r].c) | ((x == best[r].c) & (l < best[r].l));
+                best[r].c = take ? x : best[r].c;
+                best[r].l = take ? l : best[r].l;
+                best[r].hash = take ? (first ? hjA : hjB) == x : best[r].hash;
             }
-        }
-        if (CM == MPDP_COST_COUT && !kUnfused) {
-            uint32_t nl = best[r].c == mn ? best[r].l : ~0u;
-#pragma unroll
-            for (int u = 0; u < kPairBatch; ++u) {
-                const bool live = kFull || p0 + (uint32_t)u < np;
-                if (live) nl = min(nl, c[u] == mn ? l[u] : ~0u);
-            }
-            best[r].c = mn;
-            best[r].l = nl;
-        }
-        if (CM != MPDP_COST_COUT && !kUnfused) {
-            // PG-like: the smallest cost, then the smallest left set at it;
-            // the left sets of a set's offers all differ (one relation, or
-            // all but one, and both only for two relations, which have one
-            // pair), so that left set names one offer, whose operator is
-            // taken: the key order (cost, left set, operator)
-            uint32_t nl = best[r].c == mn ? best[r].l : ~0u;
-#pragma unroll
-            for (int o = 0; o < 2 * kPairBatch; ++o) nl = min(nl, pc[o] == mn ? pl[o] : ~0u);
-            uint32_t nop = (best[r].c == mn && best[r].l == nl) ? best[r].op : ~0u;
-#pragma unroll
-            for (int o = 0; o < 2 * kPairBatch; ++o) nop = min(nop, (pc[o] == mn && pl[o] == nl) ? po[o] : ~0u);
-            best[r].c = mn;
-            best[r].l = nl;
-            best[r].op = nop;
         }
     }
 }
@@ -882,8 +845,8 @@ __device__ __forceinline__ void eval_flat_sets(const LdsGraph &L, const MemoPtrs
         pb[r] = 1;
         T[r] = S[r] & ~1u;
         best[r].c = __builtin_inf();
-        best[r].l = ~0u;
-        best[r].op = ~0u;
+        best[r].l = CM == MPDP_COST_COUT ? lowbit(T[r]) : ~0u;  // (the first at +inf, too)
+        best[r].hash = false;
         if (kUnfused) sink.keys[(uint64_t)sink.slot[r] * k] = PairKey{~0ull, ~0u, ~0u};  // member 0 has no pair
     }
     const uint32_t np = k - 1;
@@ -899,11 +862,12 @@ __device__ __forceinline__ void eval_flat_sets(const LdsGraph &L, const MemoPtrs
         if (kUnfused) {
             sink.recs[sink.slot[r]] = PruneRec{pa[r], S[r], cardS[r]};
         } else if (CM == MPDP_COST_COUT) {
-            store_best(M, off_k + pa[r], Key{(unsigned long long)__double_as_longlong(best[r].c), best[r].l,
-                                             MPDP_OP_JOIN}, cardS[r]);
+            store_best(M, off_k + pa[r], Key{(unsigned long long)__double_as_longlong(best[r].c),
+                                             min(best[r].l, S[r] ^ best[r].l), MPDP_OP_JOIN}, cardS[r]);
         } else {
             store_best(M, off_k + pa[r], Key{(unsigned long long)__double_as_longlong(best[r].c), best[r].l,
-                                             best[r].op}, cardS[r]);
+                                             best[r].hash ? (uint32_t)MPDP_OP_HASH : (uint32_t)MPDP_OP_NESTLOOP},
+                       cardS[r]);
         }
     }
 }
@@ -1696,7 +1660,7 @@ __device__ void level_flat_wave(const LdsGraph &L, const MemoPtrs &M, int n, uin
         }
         wave_sync_lds();
         const uint64_t left = r_end - base;  // elements of this block in range (uniform)
-#pragma unroll
+#pragma unroll 1
         for (int j = 0; j < kTreeChunk; j += R) {
             if ((uint64_t)(j + R) * 64u <= left) {  // the whole group, on every lane
                 uint32_t s[R], b[R];
@@ -1708,7 +1672,7 @@ __device__ void level_flat_wave(const LdsGraph &L, const MemoPtrs &M, int n, uin
                 }
                 eval_flat_sets<CM, R>(L, M, s, b, k, off_k, cost_km1, card_km1);
             } else if ((uint64_t)j * 64u < left) {  // the group that straddles the end
-#pragma unroll
+#pragma unroll 1
                 for (int r = 0; r < R; ++r) {
                     const uint32_t e = (uint32_t)(j + r) * 64u + lane;
                     if (e < left) {
@@ -1988,6 +1952,10 @@ __device__ void light_sets(const LdsGraph &L, const MemoPtrs &M, const uint32_t 
 // and operator of every node.  Memo indices are summed by the wave, one
 // member per lane, one frontier set at a time, and kept for the fill.
 // by_set: a set's entry is at the set itself (a memo of the kernel's own).
+// While the frontier is a single set S (a plan that joins one relation at a
+// time has no other), the left sets of all S - {v} are read along with S's
+// own, so that a round covers two depths where S splits off one relation: the
+// plan of a 25-relation star took 24 rounds of some 0.9 us.
 // Returns false if the memo is inconsistent.
 struct PlanScratch {
     uint64_t node_at[64];
@@ -2005,6 +1973,44 @@ __device__ __forceinline__ uint64_t memo_index_wave_t(const uint32_t *binom, con
     uint32_t term = 0;
     if (lane < 32 && ((S >> lane) & 1u)) term = binom[lane * 33 + popc32(S & ((1u << lane) - 1u)) + 1];
     return loff[popc32(S)] + wave_sum32(term);
+}
+
+// Sums of x over this lane's and all lower lanes, of lanes 0 .. 31.
+__device__ __forceinline__ uint32_t scan32(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row 0's sum to row 1
+    return x;
+}
+
+// Node S of the plan (uniform), whose left set is Lft: recorded by lane 0;
+// its joined inputs are c[0 .. pushes), their starts st[].  False if Lft is
+// no proper subset of S.
+__device__ __forceinline__ bool plan_node(PlanScratch &P, uint32_t n, uint32_t S, int start, uint64_t at, uint32_t Lft,
+                                          uint32_t lane, uint32_t &pushes, uint32_t *c, int *st) {
+    pushes = 0;
+    if (Lft == 0 || (Lft & ~S) != 0 || Lft == S) return false;
+    const uint32_t Rgt = S & ~Lft;
+    const int nl = popc32(Lft), nr = popc32(Rgt), rst = start + nl - 1, idx = (int)n + start + popc32(S) - 2;
+    if (lane == 0) {
+        P.node_set[idx] = S;
+        P.node_at[idx] = at;
+        P.node_l[idx] = nl >= 2 ? (int)n + start + nl - 2 : ctz32(Lft);
+        P.node_r[idx] = nr >= 2 ? (int)n + rst + nr - 2 : ctz32(Rgt);
+    }
+    if (nl >= 2) {
+        c[0] = Lft;
+        st[0] = start;
+        pushes = 1;
+    }
+    if (nr >= 2) {
+        c[pushes] = Rgt;
+        st[pushes] = rst;
+        ++pushes;
+    }
+    return true;
 }
 
 __device__ bool extract_plan(const uint32_t *binom, const uint64_t *loff, bool by_set, const MemoPtrs &M, uint32_t n,
@@ -2027,6 +2033,43 @@ __device__ bool extract_plan(const uint32_t *binom, const uint64_t *loff, bool b
         uint32_t nfr = n > 1 ? 1u : 0u;  // frontier size, uniform; at most 31 join nodes per depth
         bool bad = false;
         for (uint32_t depth = 0; nfr != 0 && depth < n; ++depth) {
+            if (nfr == 1u) {
+                const uint32_t S = (uint32_t)__builtin_amdgcn_readfirstlane((int)P.fr_set[cur][0]), k = (uint32_t)popc32(S);
+                const int start = __builtin_amdgcn_readfirstlane(P.fr_start[cur][0]);
+                const bool in = lane < 32u && ((S >> (lane & 31u)) & 1u);
+                uint64_t at = S, my_at = S ^ (1u << (lane & 31u));  // of S, of S without this lane's relation
+                if (!by_set) {
+                    const uint32_t i = (uint32_t)popc32(S & ((1u << (lane & 31u)) - 1u));
+                    const uint32_t up = in ? binom[lane * 33 + i + 1u] : 0u, down = in ? binom[lane * 33 + i] : 0u;
+                    const uint32_t ups = scan32(up), downs = scan32(down);
+                    at = loff[k] + (uint32_t)__builtin_amdgcn_readlane((int)ups, 31);
+                    my_at = loff[k - 1u] + (ups - up) + ((uint32_t)__builtin_amdgcn_readlane((int)downs, 31) - downs);
+                }
+                const uint32_t mine = in && k >= 3u ? M.left[my_at] : 0u;
+                const uint32_t Lft = (uint32_t)__builtin_amdgcn_readfirstlane((int)M.left[at]);
+                uint32_t pushes, c[2];
+                int st[2];
+                bool ok = plan_node(P, n, S, start, at, Lft, lane, pushes, c, st);
+                if (ok && pushes == 1u && (uint32_t)popc32(c[0]) == k - 1u) {
+                    const int v = ctz32(S ^ c[0]);
+                    const uint32_t S1 = c[0];
+                    const uint64_t at1 = ((uint64_t)rdlane((uint32_t)(my_at >> 32), v) << 32) | rdlane((uint32_t)my_at, v);
+                    ok = plan_node(P, n, S1, st[0], at1, rdlane(mine, v), lane, pushes, c, st);
+                }
+                if (!ok) {
+                    bad = true;
+                    nfr = 0;
+                    break;
+                }
+                cur ^= 1;
+                if (lane < pushes) {
+                    P.fr_set[cur][lane] = lane ? c[1] : c[0];
+                    P.fr_start[cur][lane] = lane ? st[1] : st[0];
+                }
+                nfr = pushes;
+                wave_sync_lds();
+                continue;
+            }
             uint64_t my_at = 0;  // lane j: index of frontier set j
             if (by_set) my_at = lane < nfr ? P.fr_set[cur][lane] : 0u;
             else for (uint32_t j = 0; j < nfr; ++j) {

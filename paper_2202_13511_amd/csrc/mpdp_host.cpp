@@ -524,6 +524,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     // (every set that holds it is connected) and the ablations
     const bool tree_lists = !general && !unfused && (flags & MPDP_FLAG_ABLATE_NO_COMPACTION) == 0 &&
                             (q.g.flat == 0 || n <= kFlatListMaxRel);
+    const bool star = !general && !unfused && (flags & MPDP_FLAG_ABLATE_NO_COMPACTION) == 0 && !tree_lists;
     auto in_span = [&](uint32_t k) { return (k - 1) * q.sets[k] <= kSpanLevelPairs; };
     // the whole call on one stream: upload, init, every level, plan, readback
     auto enqueue = [&](hipStream_t st) -> hipError_t {
@@ -541,20 +542,22 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
             if (f == hipSuccess && !pin) f = hipMemcpyAsync(down, cnt, down_bytes, hipMemcpyDeviceToHost, st);
             return f;
         };
-        if (tree_lists) {
+        if (tree_lists || star) {
             // runs of small levels by one workgroup, the others one launch each
             for (uint32_t k = 2; k <= n && e == hipSuccess;) {
                 uint32_t k1 = k;
                 while (!timing && k1 <= n && in_span(k1)) ++k1;
                 if (k1 > k) {
-                    e = mpdp::launch_tree_span(src, dg, q.cost_model, n, k, k1 - 1, list, heavy, cnt, memo, st);
+                    e = mpdp::launch_tree_span(src, dg, q.cost_model, star, n, k, k1 - 1, list, heavy, cnt, memo, st);
                     k = k1;
                     continue;
                 }
-                if (k == 2) e = mpdp::launch_init(src, dg, n, memo, list, nullptr, nullptr, true, cnt, st);
+                if (k == 2) e = mpdp::launch_init(src, dg, n, memo, star ? nullptr : list, nullptr, nullptr, true, cnt, st);
                 if (timing && e == hipSuccess) e = hipEventRecord(ev.ev[4 * k - 8], st);
                 if (timing && e == hipSuccess) e = hipEventRecord(ev.ev[4 * k - 7], st);
-                if (e == hipSuccess)
+                if (e == hipSuccess && star)
+                    e = mpdp::launch_level_tree(dg, q.cost_model, n, k, binom64(n, k), true, true, cnt, memo, st);
+                else if (e == hipSuccess)
                     e = mpdp::launch_tree_level(dg, q.cost_model, n, k, q.sets[k], (k & 1u) ? heavy : list,
                                                 (k & 1u) ? list : heavy, cnt, memo, st);
                 if (timing && e == hipSuccess) e = hipEventRecord(ev.ev[4 * k - 6], st);

@@ -212,8 +212,8 @@ hipError_t launch_bits_level(const DevGraph *g, int cost_model, uint32_t n, uint
 constexpr uint32_t kTreeListGrid = 1024;
 hipError_t launch_tree_level(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, uint64_t count,
                              const uint32_t *list, uint32_t *next, Counters *cnt, MemoPtrs memo, hipStream_t s);
-hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, uint32_t n, uint32_t k0, uint32_t k1,
-                            uint32_t *even, uint32_t *odd, Counters *cnt, MemoPtrs memo, hipStream_t s);
+hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, bool star, uint32_t n, uint32_t k0,
+                            uint32_t k1, uint32_t *even, uint32_t *odd, Counters *cnt, MemoPtrs memo, hipStream_t s);
 // One level of the block-based path: the sets of k relations in `list`
 // (cnt->level_count[k] of them) evaluated, the sets of k + 1 into `next`.
 hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,

@@ -94,11 +94,13 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_level(const DevGraph *g, ui
 // Levels k0 .. k1 of a tree join by one workgroup, barriers between them:
 // levels of a few thousand pairs take less time than a launch.  The span that
 // starts at level 2 also fills the base relations and level 2's list (and
-// needs no k_init).
+// needs no k_init).  kStar: a star around relation 0, of which every set that
+// holds it is connected; each level's list is unranked, so that the span
+// needs none from the level before.
 constexpr int kSpanBlock = 1024;
 constexpr uint32_t kSpanExpand = 16384;
 
-template <int CM>
+template <int CM, bool kStar>
 __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, DevGraph *g, uint32_t n, uint32_t k0,
                                                           uint32_t k1, uint32_t *even, uint32_t *odd, Counters *cnt,
                                                           MemoPtrs M) {
@@ -123,12 +125,18 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
         M.left[at] = 0;
         M.op[at] = MPDP_OP_SCAN;
     }
-    if (k0 == 2u && t >= 64u && t - 64u < n) first_tree_list(L, t - 64u, even);
+    if (!kStar && k0 == 2u && t >= 64u && t - 64u < n) first_tree_list(L, t - 64u, even);
     __syncthreads();
     for (uint32_t k = k0; k <= k1; ++k) {
-        const uint32_t *list = (k & 1u) ? odd : even;
-        const uint32_t count = __hip_atomic_load(&cnt->level_count[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (k < n)
+        uint32_t *list = (k & 1u) ? odd : even;
+        const uint32_t count = kStar ? L.binom[(n - 1u) * 33u + k - 1u]
+                                     : __hip_atomic_load(&cnt->level_count[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (kStar) {
+            if (t == 0) cnt->level_count[k] = count;
+            for (uint32_t i = t; i < count; i += kSpanBlock)
+                list[i] = (colex_unrank(L.binom, (int)n - 1, (int)k - 1, i) << 1) | 1u;
+            __syncthreads();
+        } else if (k < n)
             expand_sets<true, true>(L, list, count, (k & 1u) ? even : odd, &cnt->level_count[k + 1], t >> 6,
                               kSpanBlock / 64, 1u, buf, kSpanExpand, ends, t & 63u);
         eval_tree_list<CM>(L, ColexMemo{ranks, L.loff, n > 24u}, M, list, count, k, tree_group(count, kSpanBlock), t, kSpanBlock);
@@ -167,14 +175,15 @@ hipError_t launch_tree_level(const DevGraph *g, int cost_model, uint32_t n, uint
     return hipGetLastError();
 }
 
-hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, uint32_t n, uint32_t k0, uint32_t k1,
-                            uint32_t *even, uint32_t *odd, Counters *cnt, MemoPtrs memo, hipStream_t s) {
+hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, bool star, uint32_t n, uint32_t k0,
+                            uint32_t k1, uint32_t *even, uint32_t *odd, Counters *cnt, MemoPtrs memo, hipStream_t s) {
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kSpanBlock), 0, s, src, g, n, k0, k1, even, odd, cnt, memo);
+    };
     if (cost_model == MPDP_COST_COUT)
-        hipLaunchKernelGGL(k_tree_span<MPDP_COST_COUT>, dim3(1), dim3(kSpanBlock), 0, s, src, g, n, k0, k1, even, odd,
-                           cnt, memo);
+        star ? go(k_tree_span<MPDP_COST_COUT, true>) : go(k_tree_span<MPDP_COST_COUT, false>);
     else
-        hipLaunchKernelGGL(k_tree_span<MPDP_COST_PGLIKE>, dim3(1), dim3(kSpanBlock), 0, s, src, g, n, k0, k1, even,
-                           odd, cnt, memo);
+        star ? go(k_tree_span<MPDP_COST_PGLIKE, true>) : go(k_tree_span<MPDP_COST_PGLIKE, false>);
     return hipGetLastError();
 }
 
