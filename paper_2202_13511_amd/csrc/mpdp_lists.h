@@ -120,49 +120,72 @@ using PairBuf = PairBufN<448, 64>;
 // Sum over the blocks of G[S] (S connected) of 2^b - 2, Alg. 3's
 // EvaluatedCounter: relations of degree one are bridges (2 each) and are
 // stripped; in what remains every cut vertex that a block hangs on has three
-// or more neighbours, so only those are tested, by whether one neighbour
-// reaches the others without it; a cut splits the rest in two pieces that
-// share the vertex.  One lane per set; `todo` holds the pieces put aside
-// (16 per lane, stride 64; a piece put aside has two or more relations that
-// the others lack, so 32 relations leave at most 15).
+// or more neighbours, so only those are tested, by whether their neighbours
+// reach each other without them; a cut splits the rest in two pieces that
+// share the vertex.  A relation that is no cut of a piece is none of the
+// pieces that come of it, so each is tested once, and the one cut at again in
+// the piece that may hold more of its components.  One lane per set; `todo` holds the pieces put aside (16 per lane, stride 64; a
+// piece put aside has two or more relations that the others lack, so 32
+// relations leave at most 15).  (28 relations, 10 chords: 21 % of the level
+// kernels' time with a test of every relation of every piece.)
+template <bool kWide>
 __device__ __forceinline__ unsigned long long block_candidates(const LdsGraph &L, uint32_t S, uint32_t *todo) {
     unsigned long long sum = 0;
-    uint32_t sp = 0, K = S;
+    uint32_t sp = 0, K = S, untested = S;
+    // relations of degree one from v on: v, its neighbour if that leaves it
+    // with one edge, ..
+    const auto strip = [&](uint32_t &P, uint32_t v) {
+        while (P & v) {
+            const uint32_t nv = L.adj[ctz32(v)] & P;
+            if (nv == 0 || (nv & (nv - 1))) break;
+            sum += 2;
+            P ^= v;
+            v = nv;
+        }
+    };
+    for (uint32_t U = K; U; U &= U - 1) strip(K, lowbit(U));
     for (;;) {
-        for (uint32_t U = K; U; U &= U - 1) {
-            uint32_t v = lowbit(U);
-            while (K & v) {  // strip v, then its neighbour if that leaves it with one edge
-                const uint32_t nv = L.adj[ctz32(v)] & K;
-                if (nv == 0 || (nv & (nv - 1))) break;
-                sum += 2;
-                K ^= v;
-                v = nv;
-            }
+        uint32_t cur = 0, nv = 0;
+        for (uint32_t U = untested & K; U != 0u; U &= U - 1u) {
+            cur = lowbit(U);
+            nv = L.adj[ctz32(cur)] & K;
+            if (popc32(nv) >= 3) break;
+            untested ^= cur;
+            cur = 0;
         }
-        bool cut = false;
-        if (K & (K - 1)) {
-            for (uint32_t U = K; U && !cut; U &= U - 1) {
-                const uint32_t v = lowbit(U), nv = L.adj[ctz32(v)] & K;
-                if (popc32(nv) < 3) continue;
-                const uint32_t R = K ^ v;
-                uint32_t seen = lowbit(nv), fr = seen;
-                while (fr && (nv & ~seen)) {
-                    fr = nbrs(L.nb, fr) & R & ~seen;
-                    seen |= fr;
-                }
-                if (nv & ~seen) {
-                    todo[sp * 64] = K & ~seen;
-                    ++sp;
-                    K = seen | v;
-                    cut = true;
-                }
-            }
-            if (cut) continue;
-            sum += (1ull << popc32(K)) - 2ull;
+        if (cur == 0u) {
+            if (K & (K - 1)) sum += (1ull << popc32(K)) - 2ull;
+            if (sp == 0) return sum;
+            --sp;
+            K = todo[sp * 64];
+            continue;
         }
-        if (sp == 0) return sum;
-        --sp;
-        K = todo[sp * 64];
+        const uint32_t b = 31u - (uint32_t)__builtin_clz(nv), C = K ^ cur;
+        uint32_t fa = L.adj[ctz32(nv)] & C, fb = L.adj[b] & C, sa = lowbit(nv) | fa, sb = (1u << b) | fb;
+        while ((sa & sb) == 0u && fa != 0u && fb != 0u) {
+            fa = nbrs_of<kWide>(L.nb, fa) & C & ~sa;
+            fb = nbrs_of<kWide>(L.nb, fb) & C & ~sb;
+            sa |= fa;
+            sb |= fb;
+        }
+        const bool met = (sa & sb) != 0u;
+        uint32_t seen = met ? sa | sb : fa == 0u ? sa : sb, fr = met ? fa | fb : 0u;
+        while (fr != 0u && (nv & ~seen) != 0u) {
+            fr = nbrs_of<kWide>(L.nb, fr) & C & ~seen;
+            seen |= fr;
+        }
+        if ((nv & ~seen) == 0u) {
+            untested ^= cur;
+            continue;
+        }
+        uint32_t piece = seen | cur;  // seen: a component without cur
+        K &= ~seen;
+        strip(piece, cur);
+        strip(K, cur);
+        if (piece & (piece - 1)) {
+            todo[sp * 64] = piece;
+            ++sp;
+        }
     }
 }
 
@@ -320,7 +343,7 @@ __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M
         PairBest best{~0ull, ~0u, ~0u, lane, 0.0};
         if (lane < ns) {
             myset = list[s0 + lane * chunks];
-            if (part == 0) evaluated += block_candidates(L, myset, B.p0 + lane);
+            if (part == 0) evaluated += block_candidates<kWide>(L, myset, B.p0 + lane);
             tree_card_n<1>(L, &myset, k, &mycard);
             B.card[lane] = mycard;
             B.bc[lane] = ~0ull;
