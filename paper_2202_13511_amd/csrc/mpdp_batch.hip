@@ -376,7 +376,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 const uint32_t per = max(pair_sets(count, nw), min(count, kBatchPer));
                 const bool heavy = (1u << k) / 16u >= ((Q.sched >> kSchedHeavyShift) & 0xffffu);
                 const uint32_t parts = heavy && 2u * count <= nw ? nw / count : 1u;
-                eval_pairs<CM, false>(L, BitMemo{}, M, list, count, k, w, nw, per, parts, W.pairs[wave], pp, lane, my_ccp,
+                eval_pairs<CM, false, false>(L, BitMemo{}, M, list, count, k, w, nw, per, parts, W.pairs[wave], pp, lane, my_ccp,
                                my_eval);
             }
             // the level's memo is complete before the next level reads it

@@ -308,11 +308,11 @@ constexpr size_t kGraphCacheSize = 32;  // recorded graphs kept per thread
 struct GraphKey {
     void *ws, *pin;
     uint32_t n, cost_model;
-    bool general, flat;  // the level kernels recorded depend on both
+    bool general, flat, lazy;  // the level kernels recorded depend on them
     uint64_t sets[33];   // tree joins: and their grids on the levels' sizes
     bool operator==(const GraphKey &o) const {
         return ws == o.ws && pin == o.pin && n == o.n && cost_model == o.cost_model && general == o.general &&
-               flat == o.flat && std::memcmp(sets, o.sets, sizeof(sets)) == 0;
+               flat == o.flat && lazy == o.lazy && std::memcmp(sets, o.sets, sizeof(sets)) == 0;
     }
 };
 
@@ -513,6 +513,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     std::vector<char> down_pageable((pin || no_alloc) ? 0 : down_bytes);
     char *down = pin ? pin : (no_alloc ? down_stack : down_pageable.data());
     const bool bits = general && !dpsub && n <= mpdp::kBitsMaxRel;
+    const bool lazy = general && mpdp::lazy_cards((uint32_t)q.cost_model, n, q.m);
     const size_t N = size_t(1) << n;
     char *const bat = base + L.bits;
     const bool cout_model = q.cost_model == MPDP_COST_COUT;
@@ -579,7 +580,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
             if (bits)
                 e = mpdp::launch_bits_level(dg, q.cost_model, n, k, nc, cnt, space, memo, parts, arrived, tally, st);
             else if (counted)  // lists of connected sets: odd levels in one buffer, even ones in the other
-                e = mpdp::launch_level_pairs(dg, q.cost_model, n, k, (k & 1u) ? heavy : list, (k & 1u) ? list : heavy,
+                e = mpdp::launch_level_pairs(dg, q.cost_model, lazy, n, k, (k & 1u) ? heavy : list, (k & 1u) ? list : heavy,
                                              cnt, memo, parts, arrived, tally, st);
             else if (dpsub)
                 e = mpdp::launch_eval_general(dg, q.cost_model, k, nc, list, heavy, cnt, memo, parts, st);
@@ -599,7 +600,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
         // replay the sequence recorded once for this workspace, staging
         // buffer and shape (the upload reads the staging buffer at replay)
         hipGraphExec_t exec = nullptr;
-        GraphKey key{d_ws, pin, n, (uint32_t)q.cost_model, general, q.g.flat != 0, {0}};
+        GraphKey key{d_ws, pin, n, (uint32_t)q.cost_model, general, q.g.flat != 0, lazy, {0}};
         if (tree_lists) std::memcpy(key.sets, q.sets, sizeof(key.sets));
         HIPCHK(cached_graph(key, enqueue, exec));
         HIPCHK(hipGraphLaunch(exec, s));

@@ -211,7 +211,7 @@ __device__ __forceinline__ unsigned long long block_candidates(const LdsGraph &L
 // active one, which goes on depth first into the reserve (a search path
 // pushes less than two states per relation, so 64 entries suffice) until
 // there is room.  The memo reads of a pair are issued one step before they
-// are used, and a lane keeps the best key of the set it is on to itself
+// are used (with kLazy, PG-like, its costs first, its cards if still needed), and a lane keeps the best key of the set it is on to itself
 // until it comes to another set.
 //
 // With parts > 1 (levels of few sets) `parts` waves share one set: each runs
@@ -242,6 +242,7 @@ __device__ __forceinline__ void push_state(Buf &B, uint32_t at, uint32_t A, uint
 template <int CM>
 struct PairLoad {
     double cA, cB, kA, kB;
+    uint64_t ia, ib;  // entries of A and B
     uint32_t A, B, slot;
     bool on;
 };
@@ -319,12 +320,37 @@ __device__ __forceinline__ void settle_pair(Buf &B, const PairLoad<CM> &p, PairB
     }
 }
 
+// kLazy, PG-like: a pair whose costs have arrived in `p` goes on to `q`, which reads
+// its cards, unless its cost alone is too high: every offer adds terms of
+// zero or more to cA + cB, then card(S)'s, and rounding keeps the order, so
+// (cA + cB) + 0.01 card(S) bounds them all from below.  Most pairs end here,
+// which leaves out half of their gathers, for a step more of latency.
+template <int CM, class Buf>
+__device__ __forceinline__ void pass_pair(const Buf &B, const MemoPtrs &M, const PairLoad<CM> &p, PairLoad<CM> &q,
+                                          const PairBest &b) {
+    q.on = p.on;
+    if (!p.on) return;
+    const unsigned long long least =
+        (unsigned long long)__double_as_longlong((p.cA + p.cB) + 0.01 * B.card[p.slot]);
+    unsigned long long bound = B.bc[p.slot];
+    if (p.slot == b.slot && b.c < bound) bound = b.c;
+    q.on = least <= bound;
+    if (!q.on) return;
+    q.cA = p.cA;
+    q.cB = p.cB;
+    q.A = p.A;
+    q.B = p.B;
+    q.slot = p.slot;
+    q.kA = M.card[p.ia];
+    q.kB = M.card[p.ib];
+}
+
 struct PairParts {
     HeavyPart *rec;     // (global memory, or LDS where one workgroup's waves share)
     uint32_t *arrived;  // per set, zero between uses
 };
 
-template <int CM, bool kWide, class At, class Buf>
+template <int CM, bool kWide, bool kLazy, class At, class Buf>
 __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M, const uint32_t *list,
                            uint32_t count, uint32_t k, uint32_t w, uint32_t nw, uint32_t per, uint32_t parts,
                            Buf &B, PairParts pp, uint32_t lane, unsigned long long &ccp,
@@ -360,6 +386,8 @@ __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M
         ld.slot = 0;
         ld.A = ld.B = 0;
         ld.cA = ld.cB = ld.kA = ld.kB = 0.0;
+        ld.ia = ld.ib = 0;
+        PairLoad<CM> ld2 = ld;  // (kLazy) the pair whose cards are on the way
         wave_sync_lds();
         for (;;) {
             if (top != 0u) {  // idle lanes take states from the stack
@@ -457,7 +485,12 @@ __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M
                 total = (uint32_t)__popcll(__ballot(go && push_rest)) + (uint32_t)__popcll(__ballot(go && push_left));
             }
             top += total;
-            settle_pair<CM>(B, ld, best, lane);
+            if (!kLazy) {
+                settle_pair<CM>(B, ld, best, lane);
+            } else {
+                settle_pair<CM>(B, ld2, best, lane);
+                pass_pair<CM>(B, M, ld, ld2, best);
+            }
             ld.on = go && ok && !quiet;
             if (go && ok) {
                 const uint32_t S = s.A | s.C, A1 = S & ~comp;
@@ -472,7 +505,10 @@ __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M
                     ld.slot = s.slot;
                     ld.cA = M.cost[ia];
                     ld.cB = M.cost[ib];
-                    if (CM != MPDP_COST_COUT) {
+                    if (kLazy) {
+                        ld.ia = ia;
+                        ld.ib = ib;
+                    } else if (CM != MPDP_COST_COUT) {
                         ld.kA = M.card[ia];
                         ld.kB = M.card[ib];
                     }
@@ -487,6 +523,11 @@ __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M
                 s.C = rest != 0u ? s.C : 0u;
             }
             wave_sync_lds();
+        }
+        if (kLazy) {
+            settle_pair<CM>(B, ld2, best, lane);
+            pass_pair<CM>(B, M, ld, ld2, best);
+            ld = ld2;
         }
         settle_pair<CM>(B, ld, best, lane);
         flush_best(B, best, true, lane);

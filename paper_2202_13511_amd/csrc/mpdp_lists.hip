@@ -21,7 +21,7 @@ constexpr uint32_t kShareMinK = 10;
 // workgroup does in step, then each wave its own sets.  `tally` holds two
 // sums per workgroup (pairs, Alg. 3 candidates): adding them to one counter
 // per wave took longer than most levels.
-template <int CM, bool kWide>
+template <int CM, bool kWide, bool kLazy>
 __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, uint32_t n, uint32_t k,
                                                             const uint32_t *list, uint32_t *next, Counters *cnt,
                                                             MemoPtrs M, HeavyPart *rec, uint32_t *arrived,
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
         expand_sets<false, kWide>(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, reinterpret_cast<uint32_t *>(buf),
                     sizeof(buf) / 4, ends, lane);
     unsigned long long ccp = 0, evaluated = 0;
-    eval_pairs<CM, kWide>(L, ColexMemo{ranks, L.loff, kWide}, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6],
+    eval_pairs<CM, kWide, kLazy>(L, ColexMemo{ranks, L.loff, kWide}, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6],
                    PairParts{rec, arrived}, lane, ccp, evaluated);
     for (int off = 32; off >= 1; off >>= 1) {
         ccp += (unsigned long long)__shfl_xor((long long)ccp, off);
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
 
 }  // namespace
 
-hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,
+hipError_t launch_level_pairs(const DevGraph *g, int cost_model, bool lazy, uint32_t n, uint32_t k, const uint32_t *list,
                               uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
                               unsigned long long *tally, hipStream_t s) {
     const auto go = [&](auto kernel) {
@@ -154,9 +154,11 @@ hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uin
                            arrived, tally);
     };
     if (cost_model == MPDP_COST_COUT)
-        n > 24 ? go(k_level_pairs<MPDP_COST_COUT, true>) : go(k_level_pairs<MPDP_COST_COUT, false>);
+        n > 24 ? go(k_level_pairs<MPDP_COST_COUT, true, false>) : go(k_level_pairs<MPDP_COST_COUT, false, false>);
+    else if (lazy)
+        go(k_level_pairs<MPDP_COST_PGLIKE, true, true>);
     else
-        n > 24 ? go(k_level_pairs<MPDP_COST_PGLIKE, true>) : go(k_level_pairs<MPDP_COST_PGLIKE, false>);
+        n > 24 ? go(k_level_pairs<MPDP_COST_PGLIKE, true, false>) : go(k_level_pairs<MPDP_COST_PGLIKE, false, false>);
     return hipGetLastError();
 }
 

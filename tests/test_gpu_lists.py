@@ -120,3 +120,36 @@ def test_cycle_ranks(n):
             else:
                 root = min((best[(t, j)] + best[((t + j) % n, n - j)]) + c for t in range(n) for j in range(1, n))
     assert np.float64(res.cost).view(np.uint64) == np.float64(root).view(np.uint64)
+
+
+def chain_and_clique(length, size, card=None, sel=None):
+    """A chain that ends in a clique: many extra edges, few connected sets."""
+    n = length + size
+    edges = [(i, i + 1) for i in range(length)]
+    edges += [(a, b) for a in range(length, n) for b in range(a + 1, n)]
+    q = W.from_edges(n, edges, n, f"chain{length}clique{size}")
+    if card is not None:
+        q.card[:] = card
+        q.sel[:] = sel
+    return q
+
+
+LAZY = [chain_and_clique(18, 7), chain_and_clique(22, 6), chain_and_clique(20, 8), chain_and_clique(19, 7, 1000.0, 0.001),
+        chain_and_clique(18, 7, 1e308, 1.0)]
+
+
+@pytest.mark.parametrize("q", LAZY, ids=lambda q: f"{q.name}-{q.card[0]:.0e}")
+def test_cards_read_only_where_needed(q):
+    """PG-like, more than 24 relations and many extra edges: a pair whose costs
+    alone are too high has its cards left out.  With ties and with costs
+    beyond the largest double as well, bit for bit against the oracle."""
+    assert q.n > 24 and q.m + 1 >= 38
+    cm = mpdp.MPDP_COST_PGLIKE
+    ref = oracle.mpdp(q, cm)
+    got = mpdp.mpdp_optimize_ws(q, cm, mpdp.workspace(q.n, cm))
+    assert np.float64(got.cost).view(np.uint64) == np.float64(ref.root_cost).view(np.uint64)
+    want = oracle.plan_from_memo(ref)
+    assert [(p["relset"], p["left"], p["right"], p["op"]) for p in got.plan] == \
+           [(p["relset"], p["left"], p["right"], p["op"]) for p in want]
+    assert (got.stats["connected_sets"], got.stats["ccp_pairs"], got.stats["evaluated_pairs"]) == \
+           (ref.connected_sets, ref.ccp_ordered // 2, ref.evaluated)
