@@ -18,7 +18,6 @@ constexpr int kFilterChunk = 16;    // consecutive ranks per lane in k_filter (<
 // consecutive ranks per lane in k_level_tree: 1, 2 or 4, and 8 on the
 // largest levels under C_out (one unrank per eight candidates)
 constexpr int kTreeChunkMax = 8;
-constexpr int kRing = 384;          // per-wave ring of the batched kernel (chunks up to 4, one set per lane)
 constexpr uint32_t kPersistGrid = 1024;  // workgroups that keep the whole chip busy (4 per CU)
 // Tree levels under C_out gather one word per pair: three workgroups per CU
 // leave fewer gathers in flight and lose fewer of them from the caches
@@ -42,22 +41,12 @@ constexpr int kHeavyBlock = 512;         // threads per heavy set
 constexpr uint32_t kMaxGrid = 8192; // workgroups per launch (grid-stride beyond)
 constexpr uint32_t kGeneralGrid = 1024;  // workgroups of a block-based level's light sets
 
-// Sets a lane evaluates at once in k_level_tree (independent chains,
-// interleaved): two under C_out, one under PG-like, whose gathers and
-// costs of two sets at once need more registers than pay off.
-#ifndef MPDP_TREE_SETS_PER_LANE_COUT
-#define MPDP_TREE_SETS_PER_LANE_COUT 2
-#endif
-constexpr int kTreeSetsMax = MPDP_TREE_SETS_PER_LANE_COUT;
-template <int CM>
-constexpr int tree_sets_per_lane() { return CM == MPDP_COST_COUT ? MPDP_TREE_SETS_PER_LANE_COUT : 1; }
-// per-wave ring of k_level_tree: room for the sets a drain leaves (fewer
-// than 64 per lane) and one pass of appends (at most 64 * chunk)
+// per-wave ring of the ablations: room for the sets a drain leaves (fewer
+// than 64) and one pass of appends (at most 64 * chunk)
 constexpr int kTreeRing = 640;
-static_assert(kTreeRing >= 64 * kTreeSetsMax - 1 + 64 * kTreeChunkMax, "ring too small");
-// members per batch of the tree pair loop (gathers in flight per lane; the
-// batched kernel, which keeps much more state live, takes three) and of the
-// card(S) pass (LDS reads in flight)
+static_assert(kTreeRing >= 63 + 64 * kTreeChunkMax, "ring too small");
+// members per batch of the tree pair loop (gathers in flight per lane) and of
+// the card(S) pass (LDS reads in flight)
 // depth-one tree levels (k_level_flat): sets per lane and grid caps.  On
 // a 25-relation star (ms per query) the C_out cap of 256 / 384 / 512 / 768 /
 // 1024 workgroups gave 0.84 / 0.78 / 0.78 / 0.83 / 0.87, and the PG-like
@@ -480,7 +469,7 @@ struct TreeSink {
     uint32_t slot[2] = {0, 0};
 };
 
-template <int CM, int R, int kPairBatch = MPDP_TREE_PAIR_BATCH, bool kUnfused = false, bool kBatchKeys = false>
+template <int CM, int R, int kPairBatch = MPDP_TREE_PAIR_BATCH, bool kUnfused = false>
 __device__ __forceinline__ void eval_tree_sets(const LdsGraph &L, const MemoPtrs &M, const uint32_t *S,
                                                const uint32_t *bsum, uint32_t k, uint64_t off_k,
                                                const double *__restrict__ cost_km1,
@@ -493,12 +482,10 @@ __device__ __forceinline__ void eval_tree_sets(const LdsGraph &L, const MemoPtrs
     // C_out offers carry one operator, so the running best starts with it
     // and the operator never decides
     Key best[R];
-    double bc[R];  // kBatchKeys (C_out): running smallest cost, +inf before the first pair
     uint32_t pa[R], pb[R], T[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         best[r] = worst_key();
-        bc[r] = __builtin_inf();
         if (CM == MPDP_COST_COUT) best[r].op = MPDP_OP_JOIN;
         pa[r] = pb[r] = 0;
         T[r] = S[r];
@@ -595,31 +582,6 @@ __device__ __forceinline__ void eval_tree_sets(const LdsGraph &L, const MemoPtrs
                     if (CM != MPDP_COST_COUT) kA[r][u] = single ? L.card[m] : hA[r][u];
                 }
         }
-        if (CM == MPDP_COST_COUT && kBatchKeys && !kUnfused) {
-            // the batch's keys without per-pair branches: the smallest cost
-            // of the batch and the running best, then the smallest left set
-            // among the pairs that reach it (the key order); a slot without
-            // a pair costs +inf, and a connected set has at least one pair
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                double c[kPairBatch];
-                uint32_t l[kPairBatch];
-                double mn = bc[r];
-#pragma unroll
-                for (int u = 0; u < kPairBatch; ++u) {
-                    const uint32_t A = Av[r][u], B = S[r] ^ A;
-                    c[u] = A != 0 ? (cA[r][u] + cB[r][u]) + cardS[r] : __builtin_inf();
-                    l[u] = A < B ? A : B;
-                    mn = __builtin_fmin(mn, c[u]);
-                }
-                uint32_t nl = bc[r] == mn ? best[r].l : ~0u;
-#pragma unroll
-                for (int u = 0; u < kPairBatch; ++u) nl = min(nl, c[u] == mn ? l[u] : ~0u);
-                bc[r] = mn;
-                best[r].l = nl;
-            }
-            continue;
-        }
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -663,7 +625,6 @@ __device__ __forceinline__ void eval_tree_sets(const LdsGraph &L, const MemoPtrs
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (CM == MPDP_COST_COUT && kBatchKeys && !kUnfused) best[r].c = (unsigned long long)__double_as_longlong(bc[r]);
         if (kUnfused) sink.recs[sink.slot[r]] = PruneRec{pa[r], S[r], cardS[r]};
         else store_best(M, off_k + pa[r], best[r], cardS[r]);
     }
@@ -1056,39 +1017,24 @@ __device__ __forceinline__ uint32_t rdlane(uint32_t v, int lane) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
+// The candidates of one set S as chunks of 2^shift: `blk` and the prefix of
+// chunks are lists of blocks, of which DPSUB has one, S itself.
 struct WaveScratch {
-    uint32_t blk[32];    // blocks of G[S]
-    uint32_t full[32];   // 1 if the block's induced subgraph is complete
-    uint32_t cpre[33];   // prefix of candidate chunks per block
+    uint32_t blk[32];
+    uint32_t cpre[33];
 };
 
 struct SetBlocks {
-    uint32_t A;             // cut vertices of G[S]
-    uint32_t total_chunks;  // candidate chunks over all blocks, 2^shift candidates each
+    uint32_t total_chunks;  // candidate chunks, 2^shift candidates each
     uint32_t shift;
-    uint32_t chunks16;      // chunks at 16 candidates each (decides light or heavy in the batched kernel)
-    uint32_t work16;        // the same with a sparse block's chunks weighted 1/16: most of its
-                            // candidates fall to the per-chunk neighbourhood test (per-level kernels)
-    unsigned long long evaluated;  // Alg. 3 candidates of S: sum over blocks of 2^b - 2
+    uint32_t chunks16;      // chunks at 16 candidates each (decides light or heavy)
+    unsigned long long evaluated;  // 2^k - 2
 };
 
-// Blocks of G[S] for one connected S, computed by one wave:
-//  1. a depth-first search from the lowest relation, uniform across the wave:
-//     the adjacency of the current relation comes from its lane by readlane,
-//     lane v records its parent and, on the way back, its subtree D(v);
-//  2. non-tree edges of a depth-first tree join a relation to an ancestor,
-//     so the parent p of v separates D(v) from the rest of S exactly when
-//     every neighbour of D(v) outside it is p (the lowpoint test); such a v
-//     is the top of one block;
-//  3. the block of top v is p plus D(v) without the subtrees of the tops
-//     below v; the cut vertices are the parents of tops, the root only when
-//     it has two or more children.
-// The block list, completeness flags and candidate-chunk prefix go to W.
-// The half of a block's candidates that hold its lowest relation is cut into
+// The half of S's candidates that hold its lowest relation is cut into
 // chunks of 2^shift, with the smallest shift (up to 4) that leaves at most
 // `budget` chunks, so that the candidates of a small set still spread over
 // all the lanes that take part.
-// DPSUB's enumeration (ablation): S itself is the only block, no cut vertex.
 __device__ SetBlocks whole_set(uint32_t S, WaveScratch &W, int lane, uint32_t budget) {
     const int k = popc32(S);
     const uint32_t half = (1u << (k - 1)) - 1u;
@@ -1098,110 +1044,10 @@ __device__ SetBlocks whole_set(uint32_t S, WaveScratch &W, int lane, uint32_t bu
     const uint32_t chunks = (half + (1u << shift) - 1u) >> shift;
     if (lane == 0) {
         W.blk[0] = S;
-        W.full[0] = 0;
         W.cpre[0] = 0;
         W.cpre[1] = chunks;
     }
-    return SetBlocks{0u, chunks, shift, (half + 15u) >> 4, (half + 15u) >> 4, (1ull << k) - 2ull};
-}
-
-__device__ SetBlocks analyze_set(const LdsGraph &L, uint32_t S, WaveScratch &W, int lane, uint32_t budget) {
-    const bool mine = lane < 32 && ((S >> lane) & 1u);
-    const uint32_t adjS = mine ? (L.adj[lane] & S) : 0u;
-
-    // 0. a complete G[S] (every set of a clique) is one complete block with
-    // no cut vertex: what the search below finds, without its serial steps
-    if (__ballot(mine && (adjS | (1u << lane)) != S) == 0ull) {
-        const int k = popc32(S);
-        const uint32_t half = (1u << (k - 1)) - 1u;
-        const uint32_t c[5] = {half, (half + 1u) >> 1, (half + 3u) >> 2, (half + 7u) >> 3, (half + 15u) >> 4};
-        const uint32_t shift = c[0] <= budget ? 0u : c[1] <= budget ? 1u : c[2] <= budget ? 2u : c[3] <= budget ? 3u : 4u;
-        if (lane == 0) {
-            W.blk[0] = S;
-            W.full[0] = 1u;
-            W.cpre[0] = 0u;
-            W.cpre[1] = c[shift];
-        }
-        return SetBlocks{0u, c[shift], shift, c[4], c[4], (1ull << k) - 2ull};
-    }
-
-    // 1. depth-first search: k - 1 steps down, k - 1 back up, one final test
-    const uint32_t root = (uint32_t)ctz32(S);
-    uint32_t par = 0, desc = mine ? (1u << lane) : 0u;
-    uint32_t cur = root, seen = 1u << root;
-    for (int step = 0; step < 2 * kMaxRel; ++step) {
-        const uint32_t next = rdlane(adjS, (int)cur) & ~seen;
-        if (next) {
-            const uint32_t c = (uint32_t)ctz32(next);
-            if (lane == (int)c) par = cur;
-            seen |= 1u << c;
-            cur = c;
-        } else {
-            if (cur == root) break;
-            const uint32_t p = rdlane(par, (int)cur);
-            const uint32_t d = rdlane(desc, (int)cur);
-            if (lane == (int)p) desc |= d;
-            cur = p;
-        }
-    }
-
-    // 2. lowpoint test, one neighbourhood lookup per lane
-    const bool child = mine && lane != (int)root;
-    const uint32_t outside = child ? (nbrs(L.nb, desc) & S & ~desc) : 0u;
-    const bool top = child && outside == (1u << par);
-    const uint32_t T = (uint32_t)__ballot(top);
-    const uint32_t rootkids = (uint32_t)__popcll(__ballot(child && par == root));
-
-    // 3. blocks and cut vertices
-    uint32_t A = 0, inner = 0;
-    for (uint32_t U = T; U; U &= U - 1) {
-        const uint32_t t = (uint32_t)ctz32(U);
-        A |= 1u << rdlane(par, (int)t);
-        const uint32_t dt = rdlane(desc, (int)t);
-        if (lane != (int)t && ((desc >> t) & 1u)) inner |= dt;
-    }
-    if (rootkids < 2) A &= ~(1u << root);
-    const uint32_t myblk = top ? ((desc & ~inner) | (1u << par)) : 0u;
-
-    // per-block candidates with the lowest relation (a top lane owns its block)
-    uint32_t half = 0, complete = 0;
-    if (top) {
-        const int bs = popc32(myblk);
-        half = (1u << (bs - 1)) - 1u;
-        complete = bs <= 3;  // a bridge or a triangle
-    }
-    {   // larger blocks: complete iff every member is adjacent to all the others
-        uint32_t d2 = 0;
-        for (uint32_t U = S; U; U &= U - 1) {
-            const int v = ctz32(U);
-            const uint32_t a = rdlane(adjS, v);
-            if ((myblk >> v) & 1u) d2 += (uint32_t)popc32(a & myblk);
-        }
-        const int bs = popc32(myblk);
-        if (top && bs > 3) complete = d2 == (uint32_t)(bs * (bs - 1));
-    }
-    uint32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0, c4 = 0, w4 = 0;
-    for (uint32_t U = T; U; U &= U - 1) {
-        const uint32_t h = rdlane(half, ctz32(U));
-        c0 += h;
-        c1 += (h + 1u) >> 1;
-        c2 += (h + 3u) >> 2;
-        c3 += (h + 7u) >> 3;
-        c4 += (h + 15u) >> 4;
-        w4 += rdlane(complete, ctz32(U)) ? (h + 15u) >> 4 : (h + 255u) >> 8;
-    }
-    const uint32_t shift = c0 <= budget ? 0u : c1 <= budget ? 1u : c2 <= budget ? 2u : c3 <= budget ? 3u : 4u;
-    const uint32_t round = (1u << shift) - 1u;
-    uint32_t acc = 0, idx = 0;
-    unsigned long long evaluated = 0;
-    for (uint32_t U = T; U; U &= U - 1, ++idx) {
-        const int t = ctz32(U);
-        if (lane == t) { W.blk[idx] = myblk; W.full[idx] = complete; W.cpre[idx] = acc; }
-        acc += (rdlane(half, t) + round) >> shift;
-        evaluated += (1ull << popc32(rdlane(myblk, t))) - 2ull;
-    }
-    if (lane == 0) W.cpre[idx] = acc;
-    return SetBlocks{A, acc, shift, c4, w4, evaluated};
+    return SetBlocks{chunks, shift, (half + 15u) >> 4, (1ull << k) - 2ull};
 }
 
 // Colex ranks of Sl and of S - Sl in one pass over the members of S.
@@ -1232,19 +1078,16 @@ __device__ __forceinline__ void split_ranks(const LdsGraph &L, uint32_t S, uint3
     rr = b;
 }
 
-// The pair of S from one Alg. 3 candidate whose two sides are connected:
-// S_left = grow(lb, S - rb) (lb when the block has no cut vertex of S), and
-// S_right = S - S_left, costed in both orientations.
+// The pair (lb, rb) of S = lb + rb, both connected, in both orientations.
 template <int CM>
-__device__ __forceinline__ void eval_lb(const LdsGraph &L, const MemoPtrs &M, uint32_t S, uint32_t A, int k,
+__device__ __forceinline__ void eval_lb(const LdsGraph &L, const MemoPtrs &M, uint32_t S, int k,
                                         uint32_t lb, uint32_t rb, double cardS, Key &best,
                                         unsigned long long &ccp) {
     ++ccp;
-    const uint32_t Sl = (lb & A) ? grow(L.nb, lb, S & ~rb) : lb;
     uint32_t rl, rr;
-    split_ranks(L, S, Sl, rl, rr);
-    const int kl = popc32(Sl);
-    eval_pair<CM>(M, Sl, S ^ Sl, L.loff[kl] + rl, L.loff[k - kl] + rr, cardS, best);
+    split_ranks(L, S, lb, rl, rr);
+    const int kl = popc32(lb);
+    eval_pair<CM>(M, lb, rb, L.loff[kl] + rl, L.loff[k - kl] + rr, cardS, best);
 }
 
 // The CCP check of a candidate (lb, rb) of a block: G[lb] and G[rb]
@@ -1262,7 +1105,7 @@ constexpr uint32_t kSurvCap = 128;
 // wave's buffer of valid pairs `vb` (vfill < 64 entries there, uniform);
 // 64 of them are costed together once there are.
 template <int CM>
-__device__ __forceinline__ void push_valid(const LdsGraph &L, const MemoPtrs &M, uint32_t S, uint32_t A, int k,
+__device__ __forceinline__ void push_valid(const LdsGraph &L, const MemoPtrs &M, uint32_t S, int k,
                                            uint2 e, bool ok, uint2 *vb, uint32_t &vfill, uint32_t lane,
                                            unsigned long long below_me, double cardS, Key &best,
                                            unsigned long long &ccp) {
@@ -1274,7 +1117,7 @@ __device__ __forceinline__ void push_valid(const LdsGraph &L, const MemoPtrs &M,
         const uint2 v = vb[vfill - 64u + lane];
         vfill -= 64u;
         wave_sync_lds();
-        eval_lb<CM>(L, M, S, A, k, v.x, v.y, cardS, best, ccp);
+        eval_lb<CM>(L, M, S, k, v.x, v.y, cardS, best, ccp);
     }
 }
 
@@ -1345,7 +1188,7 @@ __device__ __forceinline__ void chunk_pass1(const LdsGraph &L, const WaveScratch
 // (as many as fit), then 64 at a time out of it through the CCP check, until
 // every lane has placed its own.
 template <int CM>
-__device__ __forceinline__ void place_survivors(const LdsGraph &L, const MemoPtrs &M, uint32_t S, uint32_t A, int k,
+__device__ __forceinline__ void place_survivors(const LdsGraph &L, const MemoPtrs &M, uint32_t S, int k,
                                                 uint32_t pend, uint32_t H, uint32_t RH, uint32_t low4, uint4 edges,
                                                 uint2 *sv, uint32_t &fill, uint32_t &vfill, uint32_t lane,
                                                 unsigned long long below_me, double cardS, Key &best,
@@ -1397,41 +1240,38 @@ __device__ __forceinline__ void place_survivors(const LdsGraph &L, const MemoPtr
             const uint2 e = sv[fill - 64u + lane];
             fill -= 64u;
             wave_sync_lds();
-            push_valid<CM>(L, M, S, A, k, e, ccp_lb(L, e.x, e.y), sv + kSurvCap, vfill, lane, below_me, cardS, best,
+            push_valid<CM>(L, M, S, k, e, ccp_lb(L, e.x, e.y), sv + kSurvCap, vfill, lane, below_me, cardS, best,
                            ccp);
         }
     }
 }
 
-// Alg. 3 candidates of S over the chunks ch = first, first + stride, ... of
-// its blocks: for each block-local lb holding the block's lowest relation
-// (lb != block, so each unordered pair is met once and both orientations
-// are costed) the CCP check, then S_left and S_right (eval_lb).  A thread's
+// DPSUB's candidates of S over the chunks ch = first, first + stride, ...:
+// for each lb holding the lowest relation (lb != S, so each unordered pair is
+// met once and both orientations are costed) the CCP check, then the pair
+// (eval_lb).  A thread's
 // next chunk in the same block is `stride` chunks on, so its first
 // candidate's deposit over the block's members follows by one masked add
 // (the holes filled with ones carry through); only a new block needs the
 // bit-by-bit deposit.
 //
-// With chunk tables (the per-level kernels; `first - lane` and `stride`
-// multiples of 64, so every wave walks its chunks together, and `sv` the
-// wave's survivor buffer): the candidates of a sparse block's chunk that
+// `first - lane` and `stride` are multiples of 64, so every wave walks its
+// chunks together, and `sv` is the wave's buffers: the candidates of a chunk that
 // pass the neighbourhood tests go to the buffer, and whenever 64 are there
 // the wave checks and costs them with every lane busy, instead of each
 // lane walking its own few while the others wait.
-template <int CM, bool kChunkTables = true>
+template <int CM>
 __device__ __forceinline__ void eval_chunks(const LdsGraph &L, const MemoPtrs &M, const WaveScratch &W, uint32_t S,
                                             const SetBlocks &sb, uint32_t first, uint32_t stride, double cardS,
-                                            Key &best, unsigned long long &ccp, uint2 *sv = nullptr) {
+                                            Key &best, unsigned long long &ccp, uint2 *sv) {
     const int k = popc32(S);
-    const uint32_t A = sb.A;
     const uint32_t lane = first & 63u;
     const unsigned long long below_me = (1ull << lane) - 1ull;
     int bi = -1;
     uint32_t j0 = 0, hi0 = 0, dstep = 0, fill = 0, vfill = 0, cfill = 0;
     uint2 *cb = sv + 2u * kSurvCap;
-    const uint32_t base0 = kChunkTables ? first - lane : first, lane_off = kChunkTables ? lane : 0u;
-    for (uint32_t base = base0; base < sb.total_chunks; base += stride) {
-        const uint32_t ch = base + lane_off;
+    for (uint32_t base = first - lane; base < sb.total_chunks; base += stride) {
+        const uint32_t ch = base + lane;
         bool alive = false;
         uint2 centry = make_uint2(0u, 0u);
         if (ch < sb.total_chunks) {
@@ -1441,7 +1281,6 @@ __device__ __forceinline__ void eval_chunks(const LdsGraph &L, const MemoPtrs &M
                 while (W.cpre[bi + 1] <= ch) ++bi;
             }
             const uint32_t b = W.blk[bi];
-            const bool full = W.full[bi] != 0;
             const uint32_t lo = lowbit(b), rest = b ^ lo;
             const uint32_t hb = (1u << (popc32(b) - 1)) - 1u;
             if (fresh) {
@@ -1455,7 +1294,7 @@ __device__ __forceinline__ void eval_chunks(const LdsGraph &L, const MemoPtrs &M
                 hi0 = ((hi0 | ~rest) + dstep) & rest;
             }
             const uint32_t j1 = min(j0 + (1u << sb.shift), hb);
-            if (kChunkTables && !full && sb.shift == 4 && popc32(rest) >= 5) {
+            if (sb.shift == 4 && popc32(rest) >= 5) {
                 // 16 candidates share the members of rest above its lowest
                 // four (`hi` in lb, the others of that part in rb) and differ
                 // in which of those four (low4) they take.  The chunk is dead
@@ -1477,21 +1316,18 @@ __device__ __forceinline__ void eval_chunks(const LdsGraph &L, const MemoPtrs &M
                 for (uint32_t j = j0; j < j1; ++j) {
                     const uint32_t lb = lo | sub, rb = b ^ lb;
                     sub = (sub - rest) & rest;
-                    if (!full) {
-                        // a connected side of two or more relations has no
-                        // member without a neighbour on its side: four table
-                        // lookups reject most disconnected candidates of a
-                        // sparse block before the breadth-first check
-                        if ((lb & (lb - 1)) && (lb & ~nbrs(L.nb, lb))) continue;
-                        if ((rb & (rb - 1)) && (rb & ~nbrs(L.nb, rb))) continue;
-                        if (grow(L.nb, lo, lb) != lb) continue;
-                        if (grow(L.nb, lowbit(rb), rb) != rb) continue;
-                    }
-                    eval_lb<CM>(L, M, S, A, k, lb, rb, cardS, best, ccp);
+                    // a connected side of two or more relations has no
+                    // member without a neighbour on its side: four table
+                    // lookups reject most disconnected candidates before
+                    // the breadth-first check
+                    if ((lb & (lb - 1)) && (lb & ~nbrs(L.nb, lb))) continue;
+                    if ((rb & (rb - 1)) && (rb & ~nbrs(L.nb, rb))) continue;
+                    if (grow(L.nb, lo, lb) != lb) continue;
+                    if (grow(L.nb, lowbit(rb), rb) != rb) continue;
+                    eval_lb<CM>(L, M, S, k, lb, rb, cardS, best, ccp);
                 }
             }
         }
-        if (!kChunkTables) continue;
         // this round's live chunks into the wave's chunk buffer; once 64
         // are there, each lane tests the 16 candidates of one of them and
         // the survivors go on to the survivor buffer
@@ -1506,97 +1342,30 @@ __device__ __forceinline__ void eval_chunks(const LdsGraph &L, const MemoPtrs &M
             uint32_t pend, H, RH, low4;
             uint4 edges;
             chunk_pass1(L, W, ce, pend, H, RH, low4, edges);
-            place_survivors<CM>(L, M, S, A, k, pend, H, RH, low4, edges, sv, fill, vfill, lane, below_me, cardS, best,
+            place_survivors<CM>(L, M, S, k, pend, H, RH, low4, edges, sv, fill, vfill, lane, below_me, cardS, best,
                                 ccp);
         }
     }
-    if (kChunkTables) {
-        if (cfill != 0u) {
-            const uint2 ce = lane < cfill ? cb[lane] : make_uint2(0u, 1u);  // an empty chunk: no candidate
-            wave_sync_lds();
-            uint32_t pend = 0, H = 0, RH = 0, low4 = 0;
-            uint4 edges = make_uint4(0u, 0u, 0u, 0u);
-            if (lane < cfill) chunk_pass1(L, W, ce, pend, H, RH, low4, edges);
-            place_survivors<CM>(L, M, S, A, k, pend, H, RH, low4, edges, sv, fill, vfill, lane, below_me, cardS, best,
-                                ccp);
-        }
-        if (fill != 0u) {
-            const uint2 e = lane < fill ? sv[lane] : make_uint2(0u, 0u);
-            wave_sync_lds();
-            push_valid<CM>(L, M, S, A, k, e, lane < fill && ccp_lb(L, e.x, e.y), sv + kSurvCap, vfill, lane,
-                           below_me, cardS, best, ccp);
-        }
-        if (vfill != 0u) {
-            const uint2 e = lane < vfill ? sv[kSurvCap + lane] : make_uint2(0u, 0u);
-            wave_sync_lds();
-            if (lane < vfill) eval_lb<CM>(L, M, S, A, k, e.x, e.y, cardS, best, ccp);
-        }
+    if (cfill != 0u) {
+        const uint2 ce = lane < cfill ? cb[lane] : make_uint2(0u, 1u);  // an empty chunk: no candidate
+        wave_sync_lds();
+        uint32_t pend = 0, H = 0, RH = 0, low4 = 0;
+        uint4 edges = make_uint4(0u, 0u, 0u, 0u);
+        if (lane < cfill) chunk_pass1(L, W, ce, pend, H, RH, low4, edges);
+        place_survivors<CM>(L, M, S, k, pend, H, RH, low4, edges, sv, fill, vfill, lane, below_me, cardS, best,
+                            ccp);
     }
-}
-
-
-// True if the connected set S induces a tree (|S| - 1 edges).
-__device__ __forceinline__ bool induces_tree(const LdsGraph &L, uint32_t S) {
-    uint32_t e2 = 0;
-    for (uint32_t T = S; T; T &= T - 1) e2 += (uint32_t)popc32(L.adj[ctz32(T)] & S);
-    return e2 == 2u * (uint32_t)(popc32(S) - 1);
-}
-
-// Alg. 2 on one connected S whose induced subgraph is a tree, one lane per
-// set: every edge (u, v) of G[S] with u < v gives the pair
-// (grow({u}, S - {v}), the rest), both orientations costed.  The memo
-// gathers of kB pairs are issued before any of them is used.
-template <int CM>
-__device__ __forceinline__ void eval_treelike_set(const LdsGraph &L, const MemoPtrs &M, uint32_t S,
-                                                  unsigned long long &ccp) {
-    constexpr int kB = 4;
-    const int k = popc32(S);
-    const double cardS = card_of(L, S);
-    Key best = worst_key();
-    uint32_t V = S, U = 0, vbit = 0;
-    while (V | U) {
-        uint32_t Av[kB];
-        uint64_t ia[kB], ib[kB];
-#pragma unroll
-        for (int b = 0; b < kB; ++b) {
-            Av[b] = 0;
-            ia[b] = 0;
-            ib[b] = 0;
-            while (!U && V) {
-                vbit = lowbit(V);
-                V ^= vbit;
-                U = L.adj[ctz32(vbit)] & S & (vbit - 1u);
-            }
-            if (U) {
-                const uint32_t ubit = lowbit(U);
-                U ^= ubit;
-                const uint32_t A = grow(L.nb, ubit, S & ~vbit);
-                uint32_t ra, rb;
-                split_ranks(L, S, A, ra, rb);
-                const int ka = popc32(A);
-                Av[b] = A;
-                ia[b] = L.loff[ka] + ra;
-                ib[b] = L.loff[k - ka] + rb;
-            }
-        }
-        double cA[kB], cB[kB], kA[kB], kB2[kB];
-#pragma unroll
-        for (int b = 0; b < kB; ++b) {
-            cA[b] = cB[b] = kA[b] = kB2[b] = 0.0;
-            if (!Av[b]) continue;
-            cA[b] = M.cost[ia[b]];
-            cB[b] = M.cost[ib[b]];
-            if (CM != MPDP_COST_COUT) {
-                kA[b] = M.card[ia[b]];
-                kB2[b] = M.card[ib[b]];
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < kB; ++b)
-            if (Av[b]) eval_vals<CM>(Av[b], S ^ Av[b], cA[b], cB[b], kA[b], kB2[b], cardS, best);
+    if (fill != 0u) {
+        const uint2 e = lane < fill ? sv[lane] : make_uint2(0u, 0u);
+        wave_sync_lds();
+        push_valid<CM>(L, M, S, k, e, lane < fill && ccp_lb(L, e.x, e.y), sv + kSurvCap, vfill, lane,
+                       below_me, cardS, best, ccp);
     }
-    ccp += (unsigned long long)(k - 1);
-    store_best(M, memo_index(L, S), best, cardS);
+    if (vfill != 0u) {
+        const uint2 e = lane < vfill ? sv[kSurvCap + lane] : make_uint2(0u, 0u);
+        wave_sync_lds();
+        if (lane < vfill) eval_lb<CM>(L, M, S, k, e.x, e.y, cardS, best, ccp);
+    }
 }
 
 
@@ -1690,9 +1459,9 @@ __device__ void level_flat_wave(const LdsGraph &L, const MemoPtrs &M, int n, uin
 // scatter fused): it walks the ranges w0, w0 + wstride, ... (below wend) of
 // 64 * kTreeChunk colex ranks (kTreeChunk consecutive ranks per lane: unrank the
 // first, then the same-popcount successor), appends the connected sets to
-// its LDS ring (kRingN entries) in rank order, each with its sum of
-// C(s_i, i), and evaluates 64 * kTreeSetsPerLane of them at a time,
-// kTreeSetsPerLane per lane, so no lane idles on a disconnected candidate.
+// its LDS ring (kTreeRing entries) in rank order, each with its sum of
+// C(s_i, i), and evaluates 64 of them at a time, so no lane idles on a
+// disconnected candidate; without kCompact each lane evaluates its own.
 // Returns the number of connected sets it found (uniform across the wave).
 // Outputs of the unfused-prune ablation (see TreeSink): the pair keys, the
 // set records and the counter that hands out their slots.
@@ -1709,15 +1478,13 @@ __device__ __forceinline__ uint32_t take_slots(uint32_t *slots, uint32_t count, 
     return (uint32_t)__shfl((int)base, 0) + lane;
 }
 
-template <int CM, int kTreeChunk, bool kCompact = true, int kRingN = kRing, int kTreeSetsPerLane = 1,
-          int kPairBatch = MPDP_TREE_PAIR_BATCH, bool kUnfused = false, bool kFlat = false,
-          bool kBatchKeys = false>
+template <int CM, int kTreeChunk, bool kCompact, bool kUnfused, bool kFlat>
 __device__ uint32_t level_tree_wave(const LdsGraph &L, const MemoPtrs &M, int n, uint32_t k, uint64_t ncand,
                                     uint64_t w0, uint64_t wstride, uint64_t wend, uint32_t *ring,
                                     uint32_t *ring_bsum, uint32_t lane,
                                     UnfusedOut uo = UnfusedOut{nullptr, nullptr, nullptr}) {
-    static_assert(kRingN >= 64 * kTreeSetsPerLane - 1 + 64 * kTreeChunk, "ring too small");
-    static_assert(!kUnfused || (kCompact && kTreeSetsPerLane == 1), "the unfused ablation is one set per lane");
+    constexpr int kPairBatch = MPDP_TREE_PAIR_BATCH;
+    static_assert(!kUnfused || kCompact, "the unfused ablation takes the sets from the ring");
     TreeSink sink;
     sink.keys = uo.keys;
     sink.recs = uo.recs;
@@ -1772,48 +1539,31 @@ __device__ uint32_t level_tree_wave(const LdsGraph &L, const MemoPtrs &M, int n,
 #pragma unroll
         for (int j = 0; j < kTreeChunk; ++j)
             if (keep & (1u << j)) {
-                ring[pos % kRingN] = sets[j];
-                ring_bsum[pos % kRingN] = bsums[j];
+                ring[pos % kTreeRing] = sets[j];
+                ring_bsum[pos % kTreeRing] = bsums[j];
                 ++pos;
             }
         tail += total;
         wave_sync_lds();
-        while (tail - head >= 64u * kTreeSetsPerLane) {
-            uint32_t s[kTreeSetsPerLane], r[kTreeSetsPerLane];
-#pragma unroll
-            for (int j = 0; j < kTreeSetsPerLane; ++j) {
-                s[j] = ring[(head + 64u * j + lane) % kRingN];
-                r[j] = ring_bsum[(head + 64u * j + lane) % kRingN];
-            }
+        while (tail - head >= 64u) {
+            const uint32_t s = ring[(head + lane) % kTreeRing], r = ring_bsum[(head + lane) % kTreeRing];
             if (kUnfused) sink.slot[0] = take_slots(uo.slots, 64u, lane);
             if constexpr (kFlat)
-                eval_flat_sets<CM, kTreeSetsPerLane, kPairBatch, kUnfused>(L, M, s, r, k, off_k, cost_km1, card_km1,
-                                                                           sink);
+                eval_flat_sets<CM, 1, kPairBatch, kUnfused>(L, M, &s, &r, k, off_k, cost_km1, card_km1, sink);
             else
-                eval_tree_sets<CM, kTreeSetsPerLane, kPairBatch, kUnfused, kBatchKeys>(L, M, s, r, k, off_k, cost_km1,
-                                                                                       card_km1, sink);
-            head += 64u * kTreeSetsPerLane;
+                eval_tree_sets<CM, 1, kPairBatch, kUnfused>(L, M, &s, &r, k, off_k, cost_km1, card_km1, sink);
+            head += 64u;
         }
         wave_sync_lds();
-    }
-    while (tail - head >= 64) {
-        const uint32_t s = ring[(head + lane) % kRingN], r = ring_bsum[(head + lane) % kRingN];
-        if (kUnfused) sink.slot[0] = take_slots(uo.slots, 64u, lane);
-        if constexpr (kFlat)
-            eval_flat_sets<CM, 1, kPairBatch, kUnfused>(L, M, &s, &r, k, off_k, cost_km1, card_km1, sink);
-        else
-            eval_tree_sets<CM, 1, kPairBatch, kUnfused, kBatchKeys>(L, M, &s, &r, k, off_k, cost_km1, card_km1, sink);
-        head += 64;
     }
     if (tail != head) {
         if (kUnfused) sink.slot[0] = take_slots(uo.slots, tail - head, lane);
         if (lane < tail - head) {
-            const uint32_t s = ring[(head + lane) % kRingN], r = ring_bsum[(head + lane) % kRingN];
+            const uint32_t s = ring[(head + lane) % kTreeRing], r = ring_bsum[(head + lane) % kTreeRing];
             if constexpr (kFlat)
                 eval_flat_sets<CM, 1, kPairBatch, kUnfused>(L, M, &s, &r, k, off_k, cost_km1, card_km1, sink);
             else
-                eval_tree_sets<CM, 1, kPairBatch, kUnfused, kBatchKeys>(L, M, &s, &r, k, off_k, cost_km1, card_km1,
-                                                                        sink);
+                eval_tree_sets<CM, 1, kPairBatch, kUnfused>(L, M, &s, &r, k, off_k, cost_km1, card_km1, sink);
         }
     }
     wave_sync_lds();
@@ -1845,86 +1595,55 @@ __device__ uint32_t level_tree_split_wave(const LdsGraph &L, const MemoPtrs &M, 
     return found;
 }
 
-// One wave's share of the unrank + filter step for the block-based path:
-// kFilterChunk consecutive colex ranks per lane.  The connected sets that
-// induce a tree are appended at the front of `list` (count in *ntree), the
-// others at its back, from list[cap - 1] downwards (count in *ngen); each
-// lane's counts are prefixed across the wave with one ballot per count bit
-// and one atomic per list and wave (global or LDS) reserves the range.
+// One wave's share of the unrank + filter step (DPSUB): kFilterChunk
+// consecutive colex ranks per lane; the connected sets are appended to
+// `list` (count in *count).  Each lane's count is prefixed across the wave
+// with one ballot per count bit, and one atomic per wave reserves the range.
 __device__ void filter_wave(const LdsGraph &L, int n, uint32_t k, uint64_t ncand, uint64_t w0, uint64_t wstride,
-                            uint32_t *list, uint32_t cap, uint32_t *ntree, uint32_t *ngen, uint32_t lane,
-                            bool split = true) {
+                            uint32_t *list, uint32_t *count, uint32_t lane) {
     const unsigned long long below_me = (1ull << lane) - 1ull;
     const uint64_t per_wave = 64ull * kFilterChunk;
     for (uint64_t w = w0; w * per_wave < ncand; w += wstride) {
         const uint64_t r0 = w * per_wave + (uint64_t)lane * kFilterChunk;
         uint32_t S = r0 < ncand ? colex_unrank(L.binom, n, (int)k, (uint32_t)r0) : 0u;
         uint32_t sets[kFilterChunk];
-        uint32_t keep_t = 0, keep_g = 0;
+        uint32_t keep = 0;
 #pragma unroll
         for (int j = 0; j < kFilterChunk; ++j) {
             sets[j] = S;
             if (r0 + (uint64_t)j < ncand) {
-                if (grow(L.nb, lowbit(S), S) == S) {
-                    if (split && induces_tree(L, S)) keep_t |= 1u << j;
-                    else keep_g |= 1u << j;
-                }
+                if (grow(L.nb, lowbit(S), S) == S) keep |= 1u << j;
                 S = next_subset(S);
             }
         }
-        const uint32_t mt = (uint32_t)popc32(keep_t), mg = (uint32_t)popc32(keep_g);
-        uint32_t bt = 0, bg = 0;
+        const uint32_t mine = (uint32_t)popc32(keep);
+        uint32_t before = 0;
 #pragma unroll
-        for (int b = 0; b < 5; ++b) {  // exclusive prefixes (counts <= 16) across the wave
-            bt += (uint32_t)__popcll(__ballot((mt >> b) & 1u) & below_me) << b;
-            bg += (uint32_t)__popcll(__ballot((mg >> b) & 1u) & below_me) << b;
-        }
-        const uint32_t tot_t = (uint32_t)__shfl((int)(bt + mt), 63);
-        const uint32_t tot_g = (uint32_t)__shfl((int)(bg + mg), 63);
-        if (tot_t) {
+        for (int b = 0; b < 5; ++b)  // exclusive prefix (counts <= 16) across the wave
+            before += (uint32_t)__popcll(__ballot((mine >> b) & 1u) & below_me) << b;
+        const uint32_t total = (uint32_t)__shfl((int)(before + mine), 63);
+        if (total) {
             uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(ntree, tot_t);
-            base = (uint32_t)__shfl((int)base, 0) + bt;
+            if (lane == 0) base = atomicAdd(count, total);
+            base = (uint32_t)__shfl((int)base, 0) + before;
 #pragma unroll
             for (int j = 0; j < kFilterChunk; ++j)
-                if (keep_t & (1u << j)) list[base++] = sets[j];
-        }
-        if (tot_g) {
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(ngen, tot_g);
-            base = (uint32_t)__shfl((int)base, 0) + bg;
-#pragma unroll
-            for (int j = 0; j < kFilterChunk; ++j)
-                if (keep_g & (1u << j)) list[cap - 1u - base++] = sets[j];
+                if (keep & (1u << j)) list[base++] = sets[j];
         }
     }
 }
 
-// One wave's share of the light work of a block-based level.  Work item i
-// (i = w0, w0 + wstride, ...) is either a group of 64 tree-inducing sets
-// from the front of `list`, one per lane (Alg. 2 on G[S]), or, past the
-// groups, one other set from the back of `list`, taken by the whole wave
-// (Alg. 3 over its blocks).  A set with more than kHeavyChunks 16-candidate
-// chunks is appended to `heavy` for a whole workgroup instead.
-template <int CM, bool kChunkTables = true>
-__device__ void light_sets(const LdsGraph &L, const MemoPtrs &M, const uint32_t *list, uint32_t cap, uint32_t ntree,
-                           uint32_t ngen, uint32_t w0, uint32_t wstride, WaveScratch &W, uint32_t *heavy,
-                           uint32_t *nheavy, uint32_t lane, unsigned long long &ccp, unsigned long long &evaluated,
-                           bool dpsub = false, uint32_t heavy_chunks = kHeavyChunks, uint2 *sv = nullptr) {
-    const uint32_t groups = (ntree + 63u) >> 6;
-    for (uint32_t i = w0; i < groups + ngen; i += wstride) {
-        if (i < groups) {
-            const uint32_t idx = (i << 6) + lane;
-            if (idx < ntree) {
-                const uint32_t S = list[idx];
-                eval_treelike_set<CM>(L, M, S, ccp);
-                evaluated += 2ull * (unsigned long long)(popc32(S) - 1);
-            }
-            continue;
-        }
-        const uint32_t S = list[cap - 1u - (i - groups)];
-        const SetBlocks sb = dpsub ? whole_set(S, W, (int)lane, 64u) : analyze_set(L, S, W, (int)lane, 64u);
-        if ((kChunkTables ? sb.work16 : sb.chunks16) > heavy_chunks) {
+// One wave's share of a level's light sets (DPSUB): sets w0, w0 + wstride, ...
+// of `list`, each taken by the whole wave.  A set with more than kHeavyChunks
+// 16-candidate chunks is appended to `heavy` for a whole workgroup instead.
+template <int CM>
+__device__ void light_sets(const LdsGraph &L, const MemoPtrs &M, const uint32_t *list, uint32_t count, uint32_t w0,
+                           uint32_t wstride, WaveScratch &W, uint32_t *heavy, uint32_t *nheavy, uint32_t lane,
+                           unsigned long long &ccp, unsigned long long &evaluated, uint2 *sv) {
+    for (uint32_t i = w0; i < count; i += wstride) {
+        const uint32_t S = list[i];
+        const SetBlocks sb = whole_set(S, W, (int)lane, 64u);
+        if (sb.chunks16 > kHeavyChunks) {
             if (lane == 0) heavy[atomicAdd(nheavy, 1u)] = S;
             wave_sync_lds();
             continue;
@@ -1933,7 +1652,7 @@ __device__ void light_sets(const LdsGraph &L, const MemoPtrs &M, const uint32_t 
         wave_sync_lds();
         const double cardS = card_of_wave(L, S, lane);
         Key best = worst_key();
-        eval_chunks<CM, kChunkTables>(L, M, W, S, sb, lane, 64u, cardS, best, ccp, sv);
+        eval_chunks<CM>(L, M, W, S, sb, lane, 64u, cardS, best, ccp, sv);
         best = wave_min(best);
         const uint64_t at = memo_index_wave(L, S, lane);
         if (lane == 0) store_best(M, at, best, cardS);

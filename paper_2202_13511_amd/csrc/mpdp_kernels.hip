@@ -1,10 +1,10 @@
 // gfx950 kernels of the MPDP level loop (Section 5, Alg. 5):
 //   k_init          memo init + base-relation fill
-//   k_level_tree    one level of Alg. 2 (tree join graphs): unrank, filter
-//                   and evaluate fused, one lane per connected set
-//   k_filter        unrank the k-subsets and keep the connected ones
-//   k_eval_general  Alg. 3 (block-based enumeration): one wave64 per set
+//   k_level_flat    one level of a star around relation 0 (Alg. 2)
 //   k_extract       rebuild the plan tree from the memo
+// and the ablations (no compaction, prune unfused, DPSUB): k_level_tree,
+// k_level_tree_unfused, k_prune, k_filter, k_eval_general, k_eval_heavy.
+// Levels of other queries: mpdp_small.hip, mpdp_bits.hip, mpdp_lists.hip.
 //
 // Everything is integer bitmap work plus a few IEEE binary64 operations per
 // join pair; nothing here is a dense contraction, so no MFMA.  Compiled with
@@ -81,13 +81,12 @@ __device__ __forceinline__ void wave_ranges(uint64_t nw, uint64_t &w0, uint64_t 
     }
 }
 
-// One DP level of a tree join graph, Alg. 5's unrank, filter, evaluate,
-// prune and scatter fused.  Each wave walks ranges of 64 * kTreeChunk colex
-// ranks (kTreeChunk consecutive ranks per lane: unrank the first, then the
-// same-popcount successor), appends the connected sets to its LDS ring in
-// rank order, and evaluates 64 of them at a time, one per lane, so no lane
-// idles on a disconnected candidate.
-template <int CM, int kTreeChunk, bool kCompact, bool kFlat>
+// One DP level of a tree join graph without compaction (ablation), Alg. 5's
+// unrank, filter, evaluate, prune and scatter fused.  Each wave walks ranges
+// of 64 * kTreeChunk colex ranks (kTreeChunk consecutive ranks per lane:
+// unrank the first, then the same-popcount successor); a lane whose candidate
+// is not connected idles.
+template <int CM, int kTreeChunk, bool kFlat>
 __global__ __launch_bounds__(kBlock) void k_level_tree(const DevGraph *g, uint32_t k, uint64_t ncand,
                                                        Counters *cnt, MemoPtrs M) {
     __shared__ __align__(16) LdsGraph L;
@@ -98,8 +97,7 @@ __global__ __launch_bounds__(kBlock) void k_level_tree(const DevGraph *g, uint32
     const uint64_t per_wave = 64ull * kTreeChunk;
     uint64_t w0, ws, we;
     wave_ranges((ncand + per_wave - 1) / per_wave, w0, ws, we);
-    const uint32_t found = level_tree_wave<CM, kTreeChunk, kCompact, kTreeRing, tree_sets_per_lane<CM>(),
-                                           MPDP_TREE_PAIR_BATCH, false, kFlat, true>(
+    const uint32_t found = level_tree_wave<CM, kTreeChunk, false, false, kFlat>(
         L, M, (int)g->n, k, ncand, w0, ws, we, ring_all[threadIdx.x >> 6], ring_bsum_all[threadIdx.x >> 6], lane);
     if (lane == 0 && found) atomicAdd(&cnt->level_count[k], found);
 }
@@ -148,7 +146,7 @@ __global__ __launch_bounds__(kBlock) void k_level_tree_unfused(const DevGraph *g
     const uint64_t per_wave = 64ull * kTreeChunk;
     uint64_t w0, ws, we;
     wave_ranges((ncand + per_wave - 1) / per_wave, w0, ws, we);
-    const uint32_t found = level_tree_wave<CM, kTreeChunk, true, kTreeRing, 1, MPDP_TREE_PAIR_BATCH, true, kFlat>(
+    const uint32_t found = level_tree_wave<CM, kTreeChunk, true, true, kFlat>(
         L, M, (int)g->n, k, ncand, w0, ws, we, ring_all[threadIdx.x >> 6], ring_bsum_all[threadIdx.x >> 6], lane,
         UnfusedOut{keys, recs, &cnt->prune_slots[k]});
     if (lane == 0 && found) atomicAdd(&cnt->level_count[k], found);
@@ -179,22 +177,19 @@ __global__ __launch_bounds__(kBlock) void k_level_tree_split(const DevGraph *g, 
     if (lane == 0 && found) atomicAdd(&cnt->level_count[k], found);
 }
 
-// Unrank + filter of a block-based level: kFilterChunk consecutive colex
-// ranks per lane; sets that induce a tree go to the front of the list, the
-// other connected sets to its back.
+// Unrank + filter of a level (DPSUB): kFilterChunk consecutive colex ranks
+// per lane.
 __global__ __launch_bounds__(kBlock) void k_filter(const DevGraph *g, uint32_t k, uint64_t ncand,
                                                    uint32_t *list, Counters *cnt) {
     __shared__ __align__(16) LdsGraph L;
     stage_graph(g, L);
-    const uint32_t n = g->n;
-    filter_wave(L, (int)n, k, ncand, (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6),
-                (uint64_t)gridDim.x * kWaves, list, L.binom[n * 33 + n / 2], &cnt->level_count[k],
-                &cnt->general_count[k], threadIdx.x & 63u, (g->ablate & kAblateDpsub) == 0);
+    filter_wave(L, (int)g->n, k, ncand, (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6),
+                (uint64_t)gridDim.x * kWaves, list, &cnt->general_count[k], threadIdx.x & 63u);
 }
 
-// Light work of a block-based level: groups of 64 tree-inducing sets, one
-// per lane, then one wave64 per other set.  A set with more than
-// kHeavyChunks 16-candidate chunks is handed to k_eval_heavy instead.
+// DPSUB (ablation), one wave64 per set: every subset of the set that holds
+// its lowest relation is a candidate.  A set with more than kHeavyChunks
+// 16-candidate chunks is handed to k_eval_heavy instead.
 template <int CM>
 __global__ __launch_bounds__(kBlock) void k_eval_general(const DevGraph *g, uint32_t k, const uint32_t *list,
                                                          uint32_t *heavy, Counters *cnt, MemoPtrs M) {
@@ -202,12 +197,10 @@ __global__ __launch_bounds__(kBlock) void k_eval_general(const DevGraph *g, uint
     __shared__ WaveScratch WS[kWaves];
     __shared__ uint2 SV[kWaves][3 * kSurvCap];
     stage_graph(g, L);
-    const uint32_t lane = threadIdx.x & 63u, n = g->n;
+    const uint32_t lane = threadIdx.x & 63u;
     unsigned long long my_ccp = 0, my_eval = 0;
-    light_sets<CM>(L, M, list, L.binom[n * 33 + n / 2], cnt->level_count[k], cnt->general_count[k],
-                   blockIdx.x * kWaves + (threadIdx.x >> 6), gridDim.x * kWaves, WS[threadIdx.x >> 6], heavy,
-                   &cnt->heavy_count[k], lane, my_ccp, my_eval, (g->ablate & kAblateDpsub) != 0, kHeavyChunks,
-                   SV[threadIdx.x >> 6]);
+    light_sets<CM>(L, M, list, cnt->general_count[k], blockIdx.x * kWaves + (threadIdx.x >> 6), gridDim.x * kWaves,
+                   WS[threadIdx.x >> 6], heavy, &cnt->heavy_count[k], lane, my_ccp, my_eval, SV[threadIdx.x >> 6]);
 
     // one atomic per wave for the counters
     for (int off = 32; off >= 1; off >>= 1) {
@@ -220,13 +213,13 @@ __global__ __launch_bounds__(kBlock) void k_eval_general(const DevGraph *g, uint
     }
 }
 
-// Alg. 3, heavy sets: one 512-thread workgroup per set, or, when a level
-// has fewer heavy sets than workgroups (the top levels of a large cyclic
-// query: one set of all relations, then n, ...), `parts` workgroups per
+// DPSUB, heavy sets: one 512-thread workgroup per set, or, when a level has
+// fewer heavy sets than workgroups (the top levels: one set of all
+// relations, then n, ...), `parts` workgroups per
 // set, each taking every parts-th run of 512 candidate chunks; their keys
-// then go to HeavyPart records for k_heavy_reduce.  Wave 0 of each
-// workgroup finds the blocks, all 8 waves share the candidate chunks, and
-// the plan keys are reduced through LDS.
+// then go to HeavyPart records for k_heavy_reduce.  All 8 waves of a
+// workgroup share the candidate chunks, and the plan keys are reduced
+// through LDS.
 template <int CM>
 __global__ __launch_bounds__(kHeavyBlock) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_eval_heavy(const DevGraph *g, uint32_t k, const uint32_t *heavy,
                                                             Counters *cnt, MemoPtrs M, HeavyPart *partrec) {
@@ -246,8 +239,7 @@ __global__ __launch_bounds__(kHeavyBlock) __attribute__((amdgpu_waves_per_eu(6, 
         const uint32_t h = t / parts, part = t - h * parts;
         const uint32_t S = heavy[h];
         if (wave == 0) {
-            const SetBlocks sb = (g->ablate & kAblateDpsub) ? whole_set(S, W, lane, kHeavyBlock)
-                                                            : analyze_set(L, S, W, lane, kHeavyBlock);
+            const SetBlocks sb = whole_set(S, W, lane, kHeavyBlock);
             if (lane == 0) { sbs = sb; if (part == 0) my_eval += sb.evaluated; }
         }
         __syncthreads();
@@ -402,16 +394,13 @@ hipError_t launch_level_tree(const DevGraph *g, int cost_model, uint32_t n, uint
     uint64_t blocks = (ncand + (uint64_t)kBlock * chunk - 1) / ((uint64_t)kBlock * chunk);
     const uint32_t cap = cost_model == MPDP_COST_COUT ? kPersistGridCout : kPersistGrid;
     const uint32_t grid = (uint32_t)(blocks < 1 ? 1 : (blocks > cap ? cap : blocks));
-    // (a compacted depth-one level went to k_level_flat above; without
-    // compaction, the ablation, it keeps the depth-one evaluation)
+    // without compaction (the ablation; other levels come here for stars alone)
 #define MPDP_LEVEL_TREE(CMV, CH)                                                                        \
     do {                                                                                                \
-        if (compact)                                                                                    \
-            hipLaunchKernelGGL((k_level_tree<CMV, CH, true, false>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
-        else if (flat)                                                                                  \
-            hipLaunchKernelGGL((k_level_tree<CMV, CH, false, true>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
+        if (flat)                                                                                       \
+            hipLaunchKernelGGL((k_level_tree<CMV, CH, true>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
         else                                                                                            \
-            hipLaunchKernelGGL((k_level_tree<CMV, CH, false, false>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
+            hipLaunchKernelGGL((k_level_tree<CMV, CH, false>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
     } while (0)
     if (cost_model == MPDP_COST_COUT) {
         if (chunk == 8) MPDP_LEVEL_TREE(MPDP_COST_COUT, 8);
