@@ -315,9 +315,9 @@ def host_cpu():
 PROFILE_WORKLOADS = {
     "star25": "star 25, seeds 0-1 (tree level kernels)",
     "snowflake25": "snowflake 25, seeds 0-3 (tree level kernels, sparse levels)",
-    "cycle_p99": "cycle30+12-s15, the slowest C3a seed (filter, general and heavy kernels)",
+    "cycle_p99": "cycle30+12-s15, the slowest C3a seed (pair search kernels)",
     "cycle_median": "cycle27+8-s8, a median C3a seed",
-    "clique18": "clique 18, seed 0 (general and heavy kernels)",
+    "clique18": "clique 18, seed 0 (bitmap kernels)",
     "batch": "the 4096-query mixed batch, one persistent launch",
 }
 

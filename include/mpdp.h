@@ -84,23 +84,25 @@ typedef struct {
     uint64_t evaluated_pairs;  /* Alg. 3 EvaluatedCounter: sum over sets and blocks of 2^b - 2 */
     uint64_t ccp_pairs;        /* csg-cmp pairs, unordered ((L,R) and (R,L) count once)        */
     double ms_total;           /* host wall time of the call                                  */
-    double ms_filter;          /* device time of the unrank/filter kernels (MPDP_FLAG_TIMING) */
-    double ms_eval;            /* device time of the evaluate kernels      (MPDP_FLAG_TIMING) */
+    double ms_filter;          /* device time before the levels' own kernels: the connectivity
+                                  of all sets of a cyclic query of up to 18 relations, the
+                                  filter of DPSUB (MPDP_FLAG_TIMING)                          */
+    double ms_eval;            /* device time of the level kernels         (MPDP_FLAG_TIMING) */
     uint32_t levels;           /* number of DP levels run (n - 1)                             */
-    uint32_t eval_launches;    /* evaluate-kernel launches                                    */
+    uint32_t eval_launches;    /* levels evaluated, a launch each with MPDP_FLAG_TIMING
+                                  (without it runs of small levels share one)                 */
 } mpdp_stats;
 
 /* Flags for mpdp_optimize_ws. */
-#define MPDP_FLAG_TIMING 1u   /* time the filter and evaluate kernels with HIP events */
+#define MPDP_FLAG_TIMING 1u   /* time the level kernels with HIP events */
 /* Ablations (measurement only; plans, costs and ccp counts are unchanged):
  * DPSUB      every connected set takes DPSUB's vertex-based candidates (Alg. 1:
  *            every subset holding its lowest relation, CCP-checked) instead of
  *            Alg. 2/3's block-local ones; evaluated_pairs counts 2^|S| - 2 per set
- * NO_COMPACTION  tree joins: each lane evaluates the connected candidates it
- *            unranked instead of compacting them through the wave's LDS ring;
- *            a tree of depth one from relation 0 (a star around it), whose
- *            connected sets are otherwise enumerated directly, is then
- *            unranked and filtered over every k-subset as well
+ * NO_COMPACTION  tree joins: every k-subset is unranked and filtered, and
+ *            each lane evaluates the connected ones it unranked, instead of
+ *            lists that hold connected sets alone (or, for a star around
+ *            relation 0, their direct enumeration)
  * UNFUSED_PRUNE  tree joins: prune is not fused into evaluate (Section 5,
  *            "Enhancements"): the evaluate kernel writes the key of every
  *            pair to global memory and a separate prune kernel reduces each
@@ -116,7 +118,8 @@ const char *mpdp_status_str(mpdp_status s);
 
 /* Bytes of device workspace mpdp_optimize_ws needs for n relations
  * (0 if n is 0 or above 32): a memo entry of 21 bytes for every subset of
- * the relations (2^n entries) plus one level of candidate sets. */
+ * the relations (2^n entries) plus two levels of connected sets and, up to
+ * 18 relations, 24 bytes and a bit for every subset. */
 size_t mpdp_workspace_bytes(uint32_t n, mpdp_cost_model cost_model);
 
 /* Byte offsets of the memo arrays inside the workspace, for callers that

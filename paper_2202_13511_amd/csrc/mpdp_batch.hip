@@ -230,7 +230,7 @@ constexpr uint32_t kBatchPer = 16;
 // Two workgroups a CU: 16 waves, 128 registers a lane (some 50 spilled, in the
 // set-up and the plan).  4096 mixed queries of 8-20 relations, C_out, took
 // 14.7 ms while every level unranked and tested all C(n, k) subsets and every
-// block's subsets were walked, and take 5.1; per query on one workgroup a
+// block's subsets were walked, and take 4.8; per query on one workgroup a
 // chain of 20 went from 1.42 to 0.16 ms, a cycle of 20 with up to two chords
 // from 2.89 to 0.87, a 20-relation tree with one to three extra edges from
 // more than 3.4 to 1.15.
