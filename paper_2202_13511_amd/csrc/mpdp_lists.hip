@@ -108,8 +108,10 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
     __shared__ __align__(16) uint32_t ranks[kRankWords];
     __shared__ uint32_t buf[kSpanExpand];
     __shared__ ExpandEnds ends;
+    __shared__ uint32_t counts[36];  // sets of level k, while the span lasts
     const uint32_t t = threadIdx.x;
     const LdsGraph &L = G.lds;
+    if (t < 36u) counts[t] = t != k0 || kStar ? 0u : k0 == 2u ? n - 1u : cnt->level_count[k0];
     bring_graph(k0 == 2u ? src : nullptr, g, G);
     stage_ranks(ranks, n);
     if (k0 == 2u) {
@@ -129,16 +131,17 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
     __syncthreads();
     for (uint32_t k = k0; k <= k1; ++k) {
         uint32_t *list = (k & 1u) ? odd : even;
-        const uint32_t count = kStar ? L.binom[(n - 1u) * 33u + k - 1u]
-                                     : __hip_atomic_load(&cnt->level_count[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t count = kStar ? L.binom[(n - 1u) * 33u + k - 1u] : counts[k];
         if (kStar) {
             if (t == 0) cnt->level_count[k] = count;
             for (uint32_t i = t; i < count; i += kSpanBlock)
                 list[i] = (colex_unrank(L.binom, (int)n - 1, (int)k - 1, i) << 1) | 1u;
             __syncthreads();
-        } else if (k < n)
-            expand_sets<true, true>(L, list, count, (k & 1u) ? even : odd, &cnt->level_count[k + 1], t >> 6,
-                              kSpanBlock / 64, 1u, buf, kSpanExpand, ends, t & 63u);
+        } else if (k < n) {
+            expand_sets<true, true>(L, list, count, (k & 1u) ? even : odd, &counts[k + 1], t >> 6, kSpanBlock / 64, 1u,
+                                    buf, kSpanExpand, ends, t & 63u);
+            if (t == 0) cnt->level_count[k + 1] = counts[k + 1];
+        }
         eval_tree_list<CM>(L, ColexMemo{ranks, L.loff, n > 24u}, M, list, count, k, tree_group(count, kSpanBlock), t, kSpanBlock);
         __syncthreads();
     }
