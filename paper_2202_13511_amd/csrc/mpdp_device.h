@@ -41,10 +41,16 @@ constexpr int kHeavyBlock = 512;         // threads per heavy set
 constexpr uint32_t kMaxGrid = 8192; // workgroups per launch (grid-stride beyond)
 constexpr uint32_t kGeneralGrid = 1024;  // workgroups of a block-based level's light sets
 
-// per-wave ring of the ablations: room for the sets a drain leaves (fewer
-// than 64) and one pass of appends (at most 64 * chunk)
-constexpr int kTreeRing = 640;
-static_assert(kTreeRing >= 63 + 64 * kTreeChunkMax, "ring too small");
+// Sets a lane evaluates at once in k_level_tree (independent chains,
+// interleaved): two under C_out, one under PG-like, whose gathers and
+// costs of two sets at once need more registers than pay off.
+template <int CM>
+constexpr int tree_sets_per_lane() { return CM == MPDP_COST_COUT ? 2 : 1; }  // (one: star of 25 1.36 -> 1.50 ms)
+// words of a wave's ring in k_level_tree: room for the sets a drain leaves
+// (fewer than 64 per lane's set) and one pass of appends (at most 64 * chunk).
+// No more: PG-like's four workgroups per CU share the LDS (with 640 words
+// three fit, and a star of 25 takes 2.22 ms for 1.83).
+constexpr int tree_ring(int chunk, int sets_per_lane) { return 64 * (chunk + sets_per_lane); }
 // members per batch of the tree pair loop (gathers in flight per lane) and of
 // the card(S) pass (LDS reads in flight)
 // depth-one tree levels (k_level_flat): sets per lane and grid caps.  On
@@ -482,10 +488,12 @@ __device__ __forceinline__ void eval_tree_sets(const LdsGraph &L, const MemoPtrs
     // C_out offers carry one operator, so the running best starts with it
     // and the operator never decides
     Key best[R];
+    double bc[R];  // C_out: running smallest cost, +inf before the first pair
     uint32_t pa[R], pb[R], T[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         best[r] = worst_key();
+        bc[r] = __builtin_inf();
         if (CM == MPDP_COST_COUT) best[r].op = MPDP_OP_JOIN;
         pa[r] = pb[r] = 0;
         T[r] = S[r];
@@ -582,6 +590,32 @@ __device__ __forceinline__ void eval_tree_sets(const LdsGraph &L, const MemoPtrs
                     if (CM != MPDP_COST_COUT) kA[r][u] = single ? L.card[m] : hA[r][u];
                 }
         }
+        if (CM == MPDP_COST_COUT && !kUnfused) {
+            // the batch's keys without per-pair branches: the smallest cost
+            // of the batch and the running best, then the smallest left set
+            // among the pairs that reach it (the key order); a slot without
+            // a pair offers +inf with the largest left set, so that a pair of
+            // infinite cost still comes before it
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                double c[kPairBatch];
+                uint32_t l[kPairBatch];
+                double mn = bc[r];
+#pragma unroll
+                for (int u = 0; u < kPairBatch; ++u) {
+                    const uint32_t A = Av[r][u], B = S[r] ^ A;
+                    c[u] = A != 0 ? (cA[r][u] + cB[r][u]) + cardS[r] : __builtin_inf();
+                    l[u] = A != 0 ? (A < B ? A : B) : ~0u;
+                    mn = __builtin_fmin(mn, c[u]);
+                }
+                uint32_t nl = bc[r] == mn ? best[r].l : ~0u;
+#pragma unroll
+                for (int u = 0; u < kPairBatch; ++u) nl = min(nl, c[u] == mn ? l[u] : ~0u);
+                bc[r] = mn;
+                best[r].l = nl;
+            }
+            continue;
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -609,22 +643,19 @@ __device__ __forceinline__ void eval_tree_sets(const LdsGraph &L, const MemoPtrs
                         sink.keys[(uint64_t)sink.slot[r] * k + i0 + (uint32_t)u] = PairKey{one.c, one.l, one.op};
                     continue;
                 }
-                if (CM == MPDP_COST_COUT) {
-                    offer_if<CM>(on, best[r], base + cardS[r], A < B ? A : B, MPDP_OP_JOIN);
-                } else {
-                    const double out = 0.01 * cardS[r];
-                    const double hjA = ((base + 0.0125 * kB[r][u]) + 0.0025 * kA[r][u]) + out;  // A outer, B hashed
-                    const double nlA = (base + (0.0025 * kA[r][u]) * kB[r][u]) + out;
-                    const double hjB = ((base + 0.0125 * kA[r][u]) + 0.0025 * kB[r][u]) + out;  // B outer, A hashed
-                    const double nlB = (base + (0.0025 * kB[r][u]) * kA[r][u]) + out;
-                    const bool hA = hjA <= nlA, hB = hjB <= nlB;
-                    offer_if<CM>(on, best[r], hA ? hjA : nlA, A, hA ? MPDP_OP_HASH : MPDP_OP_NESTLOOP);
-                    offer_if<CM>(on, best[r], hB ? hjB : nlB, B, hB ? MPDP_OP_HASH : MPDP_OP_NESTLOOP);
-                }
+                const double out = 0.01 * cardS[r];
+                const double hjA = ((base + 0.0125 * kB[r][u]) + 0.0025 * kA[r][u]) + out;  // A outer, B hashed
+                const double nlA = (base + (0.0025 * kA[r][u]) * kB[r][u]) + out;
+                const double hjB = ((base + 0.0125 * kA[r][u]) + 0.0025 * kB[r][u]) + out;  // B outer, A hashed
+                const double nlB = (base + (0.0025 * kB[r][u]) * kA[r][u]) + out;
+                const bool hA = hjA <= nlA, hB = hjB <= nlB;
+                offer_if<CM>(on, best[r], hA ? hjA : nlA, A, hA ? MPDP_OP_HASH : MPDP_OP_NESTLOOP);
+                offer_if<CM>(on, best[r], hB ? hjB : nlB, B, hB ? MPDP_OP_HASH : MPDP_OP_NESTLOOP);
             }
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
+        if (CM == MPDP_COST_COUT && !kUnfused) best[r].c = (unsigned long long)__double_as_longlong(bc[r]);
         if (kUnfused) sink.recs[sink.slot[r]] = PruneRec{pa[r], S[r], cardS[r]};
         else store_best(M, off_k + pa[r], best[r], cardS[r]);
     }
@@ -1459,9 +1490,10 @@ __device__ void level_flat_wave(const LdsGraph &L, const MemoPtrs &M, int n, uin
 // scatter fused): it walks the ranges w0, w0 + wstride, ... (below wend) of
 // 64 * kTreeChunk colex ranks (kTreeChunk consecutive ranks per lane: unrank the
 // first, then the same-popcount successor), appends the connected sets to
-// its LDS ring (kTreeRing entries) in rank order, each with its sum of
-// C(s_i, i), and evaluates 64 of them at a time, so no lane idles on a
-// disconnected candidate; without kCompact each lane evaluates its own.
+// its LDS ring (tree_ring words) in rank order, each with its sum of
+// C(s_i, i), and evaluates 64 * kSets of them at a time, kSets per lane, so no
+// lane idles on a disconnected candidate; without kCompact each lane evaluates
+// its own.
 // Returns the number of connected sets it found (uniform across the wave).
 // Outputs of the unfused-prune ablation (see TreeSink): the pair keys, the
 // set records and the counter that hands out their slots.
@@ -1478,13 +1510,15 @@ __device__ __forceinline__ uint32_t take_slots(uint32_t *slots, uint32_t count, 
     return (uint32_t)__shfl((int)base, 0) + lane;
 }
 
-template <int CM, int kTreeChunk, bool kCompact, bool kUnfused, bool kFlat>
+template <int CM, int kTreeChunk, int kSets, bool kCompact, bool kUnfused, bool kFlat>
 __device__ uint32_t level_tree_wave(const LdsGraph &L, const MemoPtrs &M, int n, uint32_t k, uint64_t ncand,
                                     uint64_t w0, uint64_t wstride, uint64_t wend, uint32_t *ring,
                                     uint32_t *ring_bsum, uint32_t lane,
                                     UnfusedOut uo = UnfusedOut{nullptr, nullptr, nullptr}) {
     constexpr int kPairBatch = MPDP_TREE_PAIR_BATCH;
-    static_assert(!kUnfused || kCompact, "the unfused ablation takes the sets from the ring");
+    constexpr int kTreeRing = tree_ring(kTreeChunk, kSets);
+    static_assert(!kUnfused || (kCompact && kSets == 1), "the unfused ablation takes single sets from the ring");
+    static_assert(!kFlat || kSets == 1, "one set of a star per lane");
     TreeSink sink;
     sink.keys = uo.keys;
     sink.recs = uo.recs;
@@ -1545,17 +1579,28 @@ __device__ uint32_t level_tree_wave(const LdsGraph &L, const MemoPtrs &M, int n,
             }
         tail += total;
         wave_sync_lds();
-        while (tail - head >= 64u) {
-            const uint32_t s = ring[(head + lane) % kTreeRing], r = ring_bsum[(head + lane) % kTreeRing];
+        while (tail - head >= 64u * kSets) {
+            uint32_t s[kSets], r[kSets];
+#pragma unroll
+            for (int j = 0; j < kSets; ++j) {
+                s[j] = ring[(head + 64u * j + lane) % kTreeRing];
+                r[j] = ring_bsum[(head + 64u * j + lane) % kTreeRing];
+            }
             if (kUnfused) sink.slot[0] = take_slots(uo.slots, 64u, lane);
             if constexpr (kFlat)
-                eval_flat_sets<CM, 1, kPairBatch, kUnfused>(L, M, &s, &r, k, off_k, cost_km1, card_km1, sink);
+                eval_flat_sets<CM, 1, kPairBatch, kUnfused>(L, M, s, r, k, off_k, cost_km1, card_km1, sink);
             else
-                eval_tree_sets<CM, 1, kPairBatch, kUnfused>(L, M, &s, &r, k, off_k, cost_km1, card_km1, sink);
-            head += 64u;
+                eval_tree_sets<CM, kSets, kPairBatch, kUnfused>(L, M, s, r, k, off_k, cost_km1, card_km1, sink);
+            head += 64u * kSets;
         }
         wave_sync_lds();
     }
+    if constexpr (kSets > 1 && !kFlat)
+        while (tail - head >= 64u) {
+            const uint32_t s = ring[(head + lane) % kTreeRing], r = ring_bsum[(head + lane) % kTreeRing];
+            eval_tree_sets<CM, 1, kPairBatch>(L, M, &s, &r, k, off_k, cost_km1, card_km1);
+            head += 64u;
+        }
     if (tail != head) {
         if (kUnfused) sink.slot[0] = take_slots(uo.slots, tail - head, lane);
         if (lane < tail - head) {

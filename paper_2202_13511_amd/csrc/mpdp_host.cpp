@@ -445,6 +445,26 @@ mpdp_status run_small(const Query &q, const Layout &L, char *base, hipStream_t s
 #endif
 constexpr uint64_t kSpanLevelPairs = MPDP_SPAN_LEVEL_PAIRS;
 
+// Tree joins with so many connected sets that unranking every k-subset takes
+// less time than lists of the connected ones: a level unranked in rank order
+// gathers and stores neighbouring entries and gets its sets' ranks with them
+// (4 to 6 ps a pair, PG-like 5 to 8, and 5 to 9 ps a subset), a list's sets look
+// theirs up and lie scattered (10 to 17 ps a pair, PG-like 20 to 33).  Lists
+// and unranked levels, us, with the pairs and subsets in millions:
+//   C_out: star of 22 around relation 11 (22, 4) 412 / 458, of 23 (46, 8)
+//     708 / 608, of 25 (201, 34) 3294 / 1355; two hubs of 1 and 20 leaves
+//     (35, 8) 526 / 586, 11 and 11 (50, 17) 722 / 975, 6 and 17 (106, 34)
+//     1624 / 1346; star of 20 on a chain of 4 (48, 17) 894 / 902
+//   PG-like: star of 21 (10, 2) 334 / 419, of 22 542 / 510, of 25 5987 / 1830;
+//     two hubs of 10 and 10 (12, 4) 365 / 507, 1 and 20 805 / 697, 11 and 11
+//     1164 / 1032; star of 18 on a chain of 8 (26, 67) 1002 / 1328
+bool many_sets(const Query &q) {
+    double pairs = 0.0;
+    for (uint32_t k = 2; k <= q.n; ++k) pairs += (double)(k - 1) * (double)q.sets[k];
+    const double subsets = std::ldexp(1.0, (int)q.n);
+    return q.cost_model == MPDP_COST_COUT ? pairs > 2.0 * subsets + 25e6 : pairs > subsets + 12e6;
+}
+
 // One exact optimization in the workspace d_ws on stream s.  With
 // no_alloc, nothing is allocated on the host or the device: the query
 // information goes up and the plan comes back through pageable memory (the
@@ -520,12 +540,13 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
                                 reinterpret_cast<double *>(bat + (cout_model ? 8 * N : 8)), cout_model ? 1u : 2u,
                                 reinterpret_cast<uint32_t *>(bat + 16 * N),
                                 reinterpret_cast<uint32_t *>(bat + 20 * N)};
-    // tree joins: lists of connected sets, but for stars around relation 0
-    // (every set that holds it is connected: 13 relations 98 us without lists
-    // and 104 with, 19 relations 155 and 187, C_out) and the ablations
-    const bool tree_lists = !general && !unfused && (flags & MPDP_FLAG_ABLATE_NO_COMPACTION) == 0 &&
-                            q.g.flat == 0;
-    const bool star = !general && !unfused && (flags & MPDP_FLAG_ABLATE_NO_COMPACTION) == 0 && !tree_lists;
+    // tree joins: lists of connected sets, but for those of many sets
+    // (many_sets), stars around relation 0 (every set that holds it is
+    // connected: 13 relations 98 us without lists and 104 with, 19 relations
+    // 155 and 187, C_out) and the ablations
+    const bool fused_tree = !general && !unfused && (flags & MPDP_FLAG_ABLATE_NO_COMPACTION) == 0;
+    const bool tree_lists = fused_tree && q.g.flat == 0 && !many_sets(q);
+    const bool star = fused_tree && q.g.flat != 0;
     auto in_span = [&](uint32_t k) { return (k - 1) * q.sets[k] <= kSpanLevelPairs; };
     // the whole call on one stream: upload, init, every level, plan, readback
     auto enqueue = [&](hipStream_t st) -> hipError_t {
@@ -587,7 +608,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
             else if (unfused)  // ablation: evaluate writes every pair's key, prune reduces
                 e = mpdp::launch_level_tree_unfused(dg, q.cost_model, k, nc, q.g.flat != 0, cnt, memo, ukeys, urecs,
                                                     st);
-            else  // tree joins: unrank, filter and evaluate in one kernel per level
+            else  // tree joins of many sets, ablation: unrank, filter and evaluate in one kernel per level
                 e = mpdp::launch_level_tree(dg, q.cost_model, n, k, nc, (flags & MPDP_FLAG_ABLATE_NO_COMPACTION) == 0,
                                             q.g.flat != 0, cnt, memo, st);
             if (e == hipSuccess && timing) e = hipEventRecord(ev.ev[4 * k - 6], st);

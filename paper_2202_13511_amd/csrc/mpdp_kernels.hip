@@ -1,6 +1,8 @@
 // gfx950 kernels of the MPDP level loop (Section 5, Alg. 5):
 //   k_init          memo init + base-relation fill
 //   k_level_flat    one level of a star around relation 0 (Alg. 2)
+//   k_level_tree    one level of another tree join of many connected sets
+//                   (k_level_tree_split: a small one)
 //   k_extract       rebuild the plan tree from the memo
 // and the ablations (no compaction, prune unfused, DPSUB): k_level_tree,
 // k_level_tree_unfused, k_prune, k_filter, k_eval_general, k_eval_heavy.
@@ -81,23 +83,29 @@ __device__ __forceinline__ void wave_ranges(uint64_t nw, uint64_t &w0, uint64_t 
     }
 }
 
-// One DP level of a tree join graph without compaction (ablation), Alg. 5's
-// unrank, filter, evaluate, prune and scatter fused.  Each wave walks ranges
-// of 64 * kTreeChunk colex ranks (kTreeChunk consecutive ranks per lane:
-// unrank the first, then the same-popcount successor); a lane whose candidate
-// is not connected idles.
-template <int CM, int kTreeChunk, bool kFlat>
+// One DP level of a tree join graph of many connected sets, Alg. 5's unrank,
+// filter, evaluate, prune and scatter fused.  Each wave walks ranges of
+// 64 * kTreeChunk colex ranks (kTreeChunk consecutive ranks per lane: unrank
+// the first, then the same-popcount successor), appends the connected sets to
+// its LDS ring in rank order, and evaluates 64 or 128 of them at a time, so
+// that no lane idles on a disconnected candidate and neighbouring lanes gather
+// neighbouring entries.  Without kCompact (ablation) it does idle.  Bound by
+// gather latency and issue, as k_level_flat: a star of 25 around relation 12
+// takes 1.36 ms, PG-like 1.83, where lists of its sets (k_tree_level) take 3.3
+// and 6.0.
+template <int CM, int kTreeChunk, bool kCompact, bool kFlat>
 __global__ __launch_bounds__(kBlock) void k_level_tree(const DevGraph *g, uint32_t k, uint64_t ncand,
                                                        Counters *cnt, MemoPtrs M) {
     __shared__ __align__(16) LdsGraph L;
-    __shared__ uint32_t ring_all[kWaves][kTreeRing];
-    __shared__ uint32_t ring_bsum_all[kWaves][kTreeRing];
+    constexpr int kSets = kCompact && !kFlat ? tree_sets_per_lane<CM>() : 1;
+    __shared__ uint32_t ring_all[kWaves][tree_ring(kTreeChunk, kSets)];
+    __shared__ uint32_t ring_bsum_all[kWaves][tree_ring(kTreeChunk, kSets)];
     stage_graph_tree(g, L);
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t per_wave = 64ull * kTreeChunk;
     uint64_t w0, ws, we;
     wave_ranges((ncand + per_wave - 1) / per_wave, w0, ws, we);
-    const uint32_t found = level_tree_wave<CM, kTreeChunk, false, false, kFlat>(
+    const uint32_t found = level_tree_wave<CM, kTreeChunk, kSets, kCompact, false, kFlat>(
         L, M, (int)g->n, k, ncand, w0, ws, we, ring_all[threadIdx.x >> 6], ring_bsum_all[threadIdx.x >> 6], lane);
     if (lane == 0 && found) atomicAdd(&cnt->level_count[k], found);
 }
@@ -139,14 +147,14 @@ __global__ __launch_bounds__(kBlock) void k_level_tree_unfused(const DevGraph *g
                                                                Counters *cnt, MemoPtrs M, PairKey *keys,
                                                                PruneRec *recs) {
     __shared__ __align__(16) LdsGraph L;
-    __shared__ uint32_t ring_all[kWaves][kTreeRing];
-    __shared__ uint32_t ring_bsum_all[kWaves][kTreeRing];
+    __shared__ uint32_t ring_all[kWaves][tree_ring(kTreeChunk, 1)];
+    __shared__ uint32_t ring_bsum_all[kWaves][tree_ring(kTreeChunk, 1)];
     stage_graph_tree(g, L);
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t per_wave = 64ull * kTreeChunk;
     uint64_t w0, ws, we;
     wave_ranges((ncand + per_wave - 1) / per_wave, w0, ws, we);
-    const uint32_t found = level_tree_wave<CM, kTreeChunk, true, true, kFlat>(
+    const uint32_t found = level_tree_wave<CM, kTreeChunk, 1, true, true, kFlat>(
         L, M, (int)g->n, k, ncand, w0, ws, we, ring_all[threadIdx.x >> 6], ring_bsum_all[threadIdx.x >> 6], lane,
         UnfusedOut{keys, recs, &cnt->prune_slots[k]});
     if (lane == 0 && found) atomicAdd(&cnt->level_count[k], found);
@@ -397,10 +405,12 @@ hipError_t launch_level_tree(const DevGraph *g, int cost_model, uint32_t n, uint
     // without compaction (the ablation; other levels come here for stars alone)
 #define MPDP_LEVEL_TREE(CMV, CH)                                                                        \
     do {                                                                                                \
-        if (flat)                                                                                       \
-            hipLaunchKernelGGL((k_level_tree<CMV, CH, true>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
+        if (compact)                                                                                    \
+            hipLaunchKernelGGL((k_level_tree<CMV, CH, true, false>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
+        else if (flat)                                                                                  \
+            hipLaunchKernelGGL((k_level_tree<CMV, CH, false, true>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
         else                                                                                            \
-            hipLaunchKernelGGL((k_level_tree<CMV, CH, false>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
+            hipLaunchKernelGGL((k_level_tree<CMV, CH, false, false>), dim3(grid), dim3(kBlock), 0, s, g, k, ncand, cnt, memo); \
     } while (0)
     if (cost_model == MPDP_COST_COUT) {
         if (chunk == 8) MPDP_LEVEL_TREE(MPDP_COST_COUT, 8);

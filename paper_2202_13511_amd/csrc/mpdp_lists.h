@@ -592,12 +592,16 @@ __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M
 // kTree: sets of a tree join in preorder numbers, for which the sets that
 // add a child numbered above every member are all there is to list (a set's
 // last relation in preorder has no child in it), without any search.
-// The waves of a workgroup collect their sets in LDS (`buf`, `cap` words) and
-// append them with one atomic on the list's end: some 30 ns each when all workgroups add to one word, an atomic per 64
-// sets or per wave made that word the bound of the smaller levels.  Starts
-// and ends with the workgroup in step.
+// The waves of a workgroup collect their sets in LDS (`buf`, `cap` words, 64 or
+// more) and append them with one atomic on the list's end: some 30 ns each when
+// all workgroups add to one word, an atomic per 64 sets or per wave made that
+// word the bound of the smaller levels.  A wave that finds the buffer full
+// keeps its place and goes on once the workgroup has emptied it (straight to
+// the list from there on, an atomic per step, made a star of 25 around another
+// relation than 0 take 8.7 ms).  Starts and ends with the workgroup in step.
 struct ExpandEnds {
     uint32_t fill, end, start;  // words taken, first word not used, place in the list
+    uint32_t more;              // a wave waits for room
 };
 
 template <bool kTree, bool kWide>
@@ -606,16 +610,21 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
                             uint32_t lane) {
     const unsigned long long below = (1ull << lane) - 1ull;
     const uint32_t each = 64u / group, sub = lane & (group - 1u);
-    if (threadIdx.x == 0) ends = ExpandEnds{0u, cap, 0u};
+    uint32_t base = w * each, S = 0, N = 0;  // the wave's next sets; this lane's set and its neighbours still to add
+    if (threadIdx.x == 0) ends = ExpandEnds{0u, cap, 0u, 0u};
     __syncthreads();
-    for (uint32_t base = w * each; base < count; base += nw * each) {
-        const uint32_t i = base + lane / group;
-        const uint32_t S = i < count ? list[i] : 0u;
-        uint32_t N = kTree ? nbrs_of<kWide>(L.pch, S) & ~(0xffffffffu >> __builtin_clz(S | 1u)) : nbrs_of<kWide>(L.nb, S) & ~S;
-        for (uint32_t j = 0; j < sub; ++j) N &= N - 1u;
-        while (__ballot(N != 0u) != 0ull) {
+    for (;;) {
+        for (;;) {
+            if (__ballot(N != 0u) == 0ull) {
+                if (base >= count) break;
+                const uint32_t i = base + lane / group;
+                base += nw * each;
+                S = i < count ? list[i] : 0u;
+                N = kTree ? nbrs_of<kWide>(L.pch, S) & ~(0xffffffffu >> __builtin_clz(S | 1u)) : nbrs_of<kWide>(L.nb, S) & ~S;
+                for (uint32_t j = 0; j < sub; ++j) N &= N - 1u;
+                continue;
+            }
             const uint32_t v = lowbit(N), S1 = S | v;
-            for (uint32_t j = 0; j < group; ++j) N &= N - 1u;
             bool keep = kTree && v != 0u;
             if (!kTree && v != 0u) {
                 uint32_t seen = lowbit(S1), fr = seen;
@@ -627,28 +636,31 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
             }
             const unsigned long long m = __ballot(keep);
             const uint32_t add = (uint32_t)__popcll(m);
-            if (add == 0u) continue;
-            uint32_t at = 0;
-            if (lane == 0) at = atomicAdd(&ends.fill, add);
-            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-            if (at + add <= cap) {
-                if (keep) buf[at + (uint32_t)__popcll(m & below)] = S1;
-            } else {  // the buffer is full: straight to the list
-                if (lane == 0) {
-                    atomicMin(&ends.end, at);
-                    at = atomicAdd(out_count, add);
-                }
+            if (add != 0u) {
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&ends.fill, add);
                 at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-                if (keep) out[at + (uint32_t)__popcll(m & below)] = S1;
+                if (at + add > cap) {  // full; so is it for whoever comes next
+                    if (lane == 0) {
+                        atomicMin(&ends.end, at);
+                        ends.more = 1u;
+                    }
+                    break;
+                }
+                if (keep) buf[at + (uint32_t)__popcll(m & below)] = S1;
             }
+            for (uint32_t j = 0; j < group; ++j) N &= N - 1u;
         }
+        __syncthreads();
+        const uint32_t have = min(ends.fill, ends.end), more = ends.more;
+        if (threadIdx.x == 0 && have != 0u) ends.start = atomicAdd(out_count, have);
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < have; i += blockDim.x) out[ends.start + i] = buf[i];
+        __syncthreads();
+        if (more == 0u) return;
+        if (threadIdx.x == 0) ends = ExpandEnds{0u, cap, 0u, 0u};
+        __syncthreads();
     }
-    __syncthreads();
-    const uint32_t have = min(ends.fill, ends.end);
-    if (threadIdx.x == 0 && have != 0u) ends.start = atomicAdd(out_count, have);
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < have; i += blockDim.x) out[ends.start + i] = buf[i];
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------- best keys of lane groups
