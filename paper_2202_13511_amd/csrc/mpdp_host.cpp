@@ -294,11 +294,16 @@ void *ablation_buffer(size_t bytes) {
     return buf[dev];
 }
 
-// A call's launch sequence (upload, init, every level, plan, readback) is
-// recorded once per workspace, staging buffer, device and shape into a HIP
-// graph and replayed, which takes the host's per-launch work out of the
-// call (star 12: 0.122 -> 0.112 ms; the rest is the levels' own latency).
-// Calls with timing events or ablation flags launch directly.
+// The launch sequence of a cyclic query or a star around relation 0 (first
+// kernel, every level, plan) follows from its size, cost model and a few flags
+// alone.  It is recorded once per workspace, staging buffer and device into a
+// HIP graph and replayed, which takes the host's per-launch work out of the
+// call.  Other tree joins launch directly: their spans and grids follow from
+// each level's number of sets, so that every new tree would be recorded anew
+// (16 relations, each call another tree: 146 us, 118 launched directly; 20:
+// 207 and 159), and a replay of the same one saves nothing (16: 105 and 104 us,
+// 25: 237 and 235), as their kernels take longer than their launches.
+// Calls with timing events or ablation flags launch directly as well.
 #ifndef MPDP_GRAPH_MAX_REL
 #define MPDP_GRAPH_MAX_REL 32
 #endif
@@ -308,11 +313,10 @@ constexpr size_t kGraphCacheSize = 32;  // recorded graphs kept per thread
 struct GraphKey {
     void *ws, *pin;
     uint32_t n, cost_model;
-    bool general, flat, lazy;  // the level kernels recorded depend on them
-    uint64_t sets[33];   // tree joins: and their grids on the levels' sizes
+    bool general, lazy;  // the level kernels recorded depend on them
     bool operator==(const GraphKey &o) const {
         return ws == o.ws && pin == o.pin && n == o.n && cost_model == o.cost_model && general == o.general &&
-               flat == o.flat && lazy == o.lazy && std::memcmp(sets, o.sets, sizeof(sets)) == 0;
+               lazy == o.lazy;
     }
 };
 
@@ -616,14 +620,12 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
         return e == hipSuccess ? finish(counted ? tally : nullptr) : e;
     };
     if (pin) std::memcpy(pin, &q.g, sizeof(DevGraph));
-    const bool graphed = pin && !timing && flags == 0 && n <= kGraphMaxRel;
+    const bool graphed = pin && !timing && flags == 0 && (general || star) && n <= kGraphMaxRel;
     if (graphed) {
         // replay the sequence recorded once for this workspace, staging
-        // buffer and shape (the upload reads the staging buffer at replay)
+        // buffer and shape (its first kernel reads the staging buffer)
         hipGraphExec_t exec = nullptr;
-        GraphKey key{d_ws, pin, n, (uint32_t)q.cost_model, general, q.g.flat != 0, lazy, {0}};
-        if (tree_lists) std::memcpy(key.sets, q.sets, sizeof(key.sets));
-        HIPCHK(cached_graph(key, enqueue, exec));
+        HIPCHK(cached_graph(GraphKey{d_ws, pin, n, (uint32_t)q.cost_model, general, lazy}, enqueue, exec));
         HIPCHK(hipGraphLaunch(exec, s));
     } else {
         HIPCHK(enqueue(s));
