@@ -119,7 +119,8 @@ const char *mpdp_status_str(mpdp_status s);
 /* Bytes of device workspace mpdp_optimize_ws needs for n relations
  * (0 if n is 0 or above 32): a memo entry of 21 bytes for every subset of
  * the relations (2^n entries) plus two levels of connected sets and, up to
- * 18 relations, 24 bytes and a bit for every subset. */
+ * 18 relations, 24 bytes and a bit for every subset.  Never less than for
+ * fewer relations, so that one workspace serves queries of up to n. */
 size_t mpdp_workspace_bytes(uint32_t n, mpdp_cost_model cost_model);
 
 /* Byte offsets of the memo arrays inside the workspace, for callers that
