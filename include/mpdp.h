@@ -90,7 +90,7 @@ typedef struct {
     double ms_eval;            /* device time of the level kernels         (MPDP_FLAG_TIMING) */
     uint32_t levels;           /* number of DP levels run (n - 1)                             */
     uint32_t eval_launches;    /* levels evaluated, a launch each with MPDP_FLAG_TIMING
-                                  (without it runs of small levels share one)                 */
+                                  (without it levels may share one)                           */
 } mpdp_stats;
 
 /* Flags for mpdp_optimize_ws. */

@@ -433,7 +433,7 @@ mpdp_status run_small(const Query &q, const Layout &L, char *base, hipStream_t s
         st.ccp_pairs = r.ccp;
         st.evaluated_pairs = r.evaluated;
         st.levels = n - 1;
-        st.eval_launches = 1;
+        st.eval_launches = n - 1;  // (levels evaluated)
         st.ms_total = now_ms() - t0;
         *stats_out = st;
     }

@@ -53,3 +53,11 @@ def test_infinite_costs(n, make, cm):
     assert np.isinf(ref.root_cost)
     check_memo(q, gm, ref)
     check_plan(q, res, ref)
+
+
+@pytest.mark.parametrize("n", [2, 12, 13])
+def test_levels_evaluated(n):
+    """eval_launches counts the levels, however many share a launch."""
+    for q in (W.star(n, 1), W.random_tree(n, 2)):
+        for st in (run_ws(q, mpdp.MPDP_COST_COUT)[0].stats, mpdp.mpdp_optimize_noalloc(q, mpdp.MPDP_COST_COUT).stats):
+            assert st["levels"] == st["eval_launches"] == n - 1
