@@ -73,22 +73,25 @@ __device__ bool team_barrier(TeamRec *R, uint32_t team, bool spread, uint32_t &p
 __device__ __forceinline__ uint32_t xcd_id() { return (uint32_t)__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 7u; }
 
 // The next queue entry: of the XCD's own share, of the common rest, of the
-// other shares; bc->entries when there is none.  One thread.
-__device__ uint32_t take_entry(BatchCounters *bc, uint32_t xcd, bool &own) {
+// other shares; bc->entries when there is none.  `end`: share_end.  A batch
+// without teams has no shares and reads no counter but `next` (with every
+// workgroup looking through the shares as it came and went, 500 queries of
+// two relations took 106 us; they take 30).  One thread.
+__device__ uint32_t take_entry(BatchCounters *bc, const uint32_t *end, uint32_t entries, uint32_t xcd, bool &own) {
     for (uint32_t y = 0; y < 9u; ++y) {
         if (y == 1u) {  // after the own share
             own = false;
             const uint32_t i = atomicAdd(&bc->next, 1u);
-            if (i < bc->entries) return i;
+            if (i < entries) return i;
         }
-        if (y == 0u && !own) continue;
+        if ((y == 0u && !own) || end[7] == 0u) continue;
         const uint32_t x = (xcd + y) & 7u;
-        const uint32_t first = x ? bc->share_end[x - 1u] : 0u, end = bc->share_end[x];
-        if (load_shared_count(&bc->share_taken[x]) >= end - first) continue;
+        const uint32_t first = x ? end[x - 1u] : 0u;
+        if (end[x] == first || load_shared_count(&bc->share_taken[x]) >= end[x] - first) continue;
         const uint32_t i = first + atomicAdd(&bc->share_taken[x], 1u);
-        if (i < end) return i;
+        if (i < end[x]) return i;
     }
-    return bc->entries;
+    return entries;
 }
 
 
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
     __shared__ __align__(16) HeavyPart parts_rec[kBW];
     __shared__ uint32_t parts_arrived[kBW];
     __shared__ ExpandEnds ends;
-    __shared__ uint32_t s_q, s_ok;
+    __shared__ uint32_t s_q, s_ok, s_end[8];  // (s_end: by wave 0 alone)
     __shared__ uint32_t s_count[24];  // connected sets per level k
     __shared__ uint32_t s_num[kMaxRel], s_kids[kMaxRel];
     __shared__ unsigned long long s_conn, s_ccp, s_eval, s_t0;
@@ -255,6 +258,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
     // the entry count travels with the uploaded data, so a recorded launch
     // serves any run with the same layout
     const uint32_t nq = bc->entries;
+    if (t < 8) s_end[t] = bc->share_end[t];
     for (uint32_t i = t; i < 33 * 33; i += blockDim.x) L.binom[i] = binom_g[i];
     stage_ranks(ranks, kBatchMaxRel);
     if (t < kBW) parts_arrived[t] = 0;
@@ -271,8 +275,9 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
 
     const uint32_t xcd = xcd_id();
     bool own = true;
+    if (t < 64u) wave_sync_lds();
     for (;;) {
-        if (t == 0) s_q = take_entry(bc, xcd, own);
+        if (t == 0) s_q = take_entry(bc, s_end, nq, xcd, own);
         __syncthreads();
         const uint32_t q = s_q;
         if (q >= nq) break;

@@ -153,12 +153,14 @@ struct BatchOut {
 // The queue: the teams in a share for each XCD, entries share_end[x - 1] ..
 // share_end[x] - 1 (from 0 for the first), then the others for all.  The
 // workgroups of an XCD start with its share, so that a team's members,
-// neighbours there, run on one XCD.
+// neighbours there, run on one XCD.  What the workgroups count in lies on
+// lines of its own: accesses to one line take turns, some 30 ns each.
 struct BatchCounters {
-    uint32_t next;           // next entry to take after the shares
     uint32_t entries;        // queue entries of this launch
-    unsigned long long t0;   // earliest workgroup start (device wall clock)
-    uint32_t share_taken[8], share_end[8];
+    uint32_t share_end[8];
+    alignas(128) uint32_t next;            // next entry to take after the shares
+    alignas(128) unsigned long long t0;    // earliest workgroup start (device wall clock)
+    alignas(128) uint32_t share_taken[8];
 };
 
 constexpr uint32_t kBatchMaxRel = 20;      // largest query the batched path takes
