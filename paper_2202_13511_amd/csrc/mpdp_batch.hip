@@ -27,6 +27,9 @@ namespace {
 
 constexpr int kBatchBlock = 512;
 constexpr int kBW = kBatchBlock / 64;
+// members per gather batch of an unranked tree set: three keeps the kernel
+// (every path of a query inlined, 128 registers per lane) from more spilling
+constexpr int kBatchPairBatch = 3;
 constexpr unsigned long long kTeamWaitTicks = 200000000ull;  // 2 s of the 100 MHz device clock
 
 __device__ __forceinline__ uint32_t load_shared_count(const uint32_t *p) {
@@ -107,6 +110,9 @@ union BatchScratch {
     struct {
         uint32_t set[kBW][flat_block_words(kTreeChunkMax)], bsum[kBW][flat_block_words(kTreeChunkMax)];
     } flat;
+    struct {
+        uint32_t set[kBW][tree_ring(4, 1)], bsum[kBW][tree_ring(4, 1)];
+    } ring;
     uint32_t grow[sizeof(BatchBuf) * kBW / 4];  // expand_sets
     PlanScratch plan;
 };
@@ -220,6 +226,11 @@ __device__ void build_image(LdsGraph &L, const BatchQueryDev &Q, const uint32_t 
             }
             L.pch[byte][x] = c;
             L.perm[byte][x] = p;
+            if (Q.sched & kSchedUnrank) {
+                uint32_t own = 0;  // children in the query's own numbers
+                for (uint32_t v = 1; v < n; ++v) own |= (L.pd[v][0] & (x << (8u * byte))) ? 1u << v : 0u;
+                L.ch[byte][x] = own;
+            }
         }
     }
     __syncthreads();
@@ -288,6 +299,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         build_image(L, Q, edges, cards, sels, bcosts, s_num, s_kids);
         const uint32_t n = Q.n;
         const bool star = Q.is_tree && L.adj[0] == (1u << n) - 2u;
+        const bool unrank = (Q.sched & kSchedUnrank) != 0u;
         if (t == 0) {
             s_t0 = (unsigned long long)wall_clock64();
             s_conn = 0;
@@ -351,11 +363,11 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         // this workgroup's waves among the team's, neighbours in other members
         const uint32_t nw = Q.team * kBW, w = wave * Q.team + Q.member;
         uint32_t *counts = team ? R->count : s_count;
-        unsigned long long my_ccp = 0, my_eval = 0;
+        unsigned long long my_sets = 0, my_ccp = 0, my_eval = 0;
         for (uint32_t k = 2; k <= n && !failed; ++k) {
             const uint32_t *list = (k & 1u) ? odd : even;
             uint32_t *next = (k & 1u) ? even : odd;
-            const uint32_t count = star ? L.binom[(n - 1) * 33 + k - 1] : team ? load_shared_count(&counts[k]) : counts[k];
+            const uint32_t count = star ? L.binom[(n - 1) * 33 + k - 1] : unrank ? 0u : team ? load_shared_count(&counts[k]) : counts[k];
             if (star) {
                 constexpr int kR = flat_sets_per_lane<CM>();
                 switch (Q.sched & kSchedChunkMask) {  // consecutive ranks per lane
@@ -368,6 +380,15 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                     default:
                         level_flat_wave<CM, 4, kR>(L, M, (int)n, k, 0, count, w, nw, W.flat.set[wave], W.flat.bsum[wave], lane);
                         break;
+                }
+            } else if (unrank) {
+                const uint32_t subsets = L.binom[n * 33 + k];
+                const uint32_t found = level_tree_wave<CM, 4, 1, true, false, false, kBatchPairBatch>(
+                    L, M, (int)n, k, subsets, w, nw, (subsets + 255u) / 256u, W.ring.set[wave], W.ring.bsum[wave], lane);
+                if (lane == 0) {
+                    my_sets += found;
+                    my_ccp += (unsigned long long)(k - 1) * found;
+                    my_eval += 2ull * (k - 1) * found;
                 }
             } else if (Q.is_tree) {
                 if (k < n)
@@ -395,24 +416,27 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 }
             }
         }
-        // counters of the cyclic queries
+        // counters of the cyclic queries and unranked tree joins
         for (int off = 32; off >= 1; off >>= 1) {
             my_ccp += (unsigned long long)__shfl_xor((long long)my_ccp, off);
             my_eval += (unsigned long long)__shfl_xor((long long)my_eval, off);
         }
         if (lane == 0 && (my_ccp || my_eval)) {
+            atomicAdd(&s_conn, my_sets);  // (found by lane 0 alone)
             atomicAdd(&s_ccp, my_ccp);
             atomicAdd(&s_eval, my_eval);
         }
         __syncthreads();
         if (team) {  // the team's counters meet in its record; the first member finishes the query
             if (t == 0) {
+                __hip_atomic_fetch_add(&R->connected, s_conn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_fetch_add(&R->ccp, s_ccp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_fetch_add(&R->evaluated, s_eval, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             if (!failed) failed = !team_barrier(R, Q.team, spread, phase, s_ok);
             if (Q.member != 0) continue;
             if (t == 0) {
+                s_conn = __hip_atomic_load(&R->connected, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 s_ccp = __hip_atomic_load(&R->ccp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 s_eval = __hip_atomic_load(&R->evaluated, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }

@@ -1510,12 +1510,12 @@ __device__ __forceinline__ uint32_t take_slots(uint32_t *slots, uint32_t count, 
     return (uint32_t)__shfl((int)base, 0) + lane;
 }
 
-template <int CM, int kTreeChunk, int kSets, bool kCompact, bool kUnfused, bool kFlat>
+template <int CM, int kTreeChunk, int kSets, bool kCompact, bool kUnfused, bool kFlat,
+          int kPairBatch = MPDP_TREE_PAIR_BATCH>
 __device__ uint32_t level_tree_wave(const LdsGraph &L, const MemoPtrs &M, int n, uint32_t k, uint64_t ncand,
                                     uint64_t w0, uint64_t wstride, uint64_t wend, uint32_t *ring,
                                     uint32_t *ring_bsum, uint32_t lane,
                                     UnfusedOut uo = UnfusedOut{nullptr, nullptr, nullptr}) {
-    constexpr int kPairBatch = MPDP_TREE_PAIR_BATCH;
     constexpr int kTreeRing = tree_ring(kTreeChunk, kSets);
     static_assert(!kUnfused || (kCompact && kSets == 1), "the unfused ablation takes single sets from the ring");
     static_assert(!kFlat || kSets == 1, "one set of a star per lane");

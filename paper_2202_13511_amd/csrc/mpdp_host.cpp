@@ -804,8 +804,15 @@ mpdp_status check_batch_args(uint32_t nq, const mpdp_batch_query *queries, const
 // Queries of up to 12 relations end the queue and are told apart by their
 // relations and extra edges alone: the logarithms and searches for all of
 // 4096 queries took 0.5 ms.
-double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges) {
+// `how`: kSchedUnrank where the query's levels take that path, as in
+// many_sets; the workgroups' memos are small, so that only subsets and pairs
+// count (us, lists / unranked, pairs and subsets in thousands; 600 stars of 14
+// (53, 16) 434 / 434, PG-like 520 / 552, of 16 (246, 66) 1243 / 1075, of 18
+// (1114, 262) 6843 / 3613; 500 double stars of 7 and 7 leaves (131, 66) 645 /
+// 687, PG-like 935 / 846; 1000 random trees of 10-20 1133 / 2846).
+double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges, uint32_t &how) {
     const uint32_t n = Q.n;
+    how = 0;
     if (n <= 12) {
         const double more = (double)(Q.m - (n - 1));
         return 1e-3 * (Q.m == n - 1 ? 10.0 + 5.0 * n : 30.0 + 1.4 * n * n * (1.0 + 0.1 * more));
@@ -843,6 +850,11 @@ double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges) {
     if (extra == 0) {
         const bool star = n >= 2 && adj[0] == (1u << n) - 2u;
         const double pairs = members - subtrees;
+        const double subsets = std::ldexp(1.0, (int)n);
+        if (!star && pairs > subsets + 60e3) {
+            how = mpdp::kSchedUnrank;
+            return 1e-3 * (10.0 + 5.0 * n + 1.5e-3 * pairs + 0.3e-3 * subsets);
+        }
         return 1e-3 * (star ? 5.1 + 3.2 * n + 0.86e-3 * pairs : 10.0 + 5.0 * n + 2.7e-3 * pairs);
     }
     uint32_t alive = (n == 32) ? ~0u : (1u << n) - 1u;
@@ -881,10 +893,11 @@ uint32_t team_size(const mpdp_batch_query &Q, double ms, double batch_ms) {
 // each query's first plan node in input order.
 void batch_order(uint32_t nq, const mpdp_batch_query *queries, const mpdp_edge *edges,
                  std::vector<uint32_t> &order, std::vector<uint32_t> &team, std::vector<double> &ms,
-                 std::vector<uint64_t> &plan_at, bool all_teams = false) {
+                 std::vector<uint32_t> &how, std::vector<uint64_t> &plan_at, bool all_teams = false) {
     ms.resize(nq);
+    how.resize(nq);
     double total = 0.0;
-    for (uint32_t i = 0; i < nq; ++i) total += ms[i] = predicted_ms(queries[i], edges);
+    for (uint32_t i = 0; i < nq; ++i) total += ms[i] = predicted_ms(queries[i], edges, how[i]);
     // by falling time, then by place: the bits of a positive float ascend with it
     std::vector<uint64_t> by(nq);
     for (uint32_t i = 0; i < nq; ++i) {
@@ -916,7 +929,7 @@ void batch_order(uint32_t nq, const mpdp_batch_query *queries, const mpdp_edge *
 // uploaded to the workspace in one copy.
 void fill_batch_upload(char *up, const BatchLayout &B, uint32_t nq, const mpdp_batch_query *queries,
                        const std::vector<uint32_t> &order, const std::vector<uint32_t> &team_of,
-                       const std::vector<double> &ms,
+                       const std::vector<double> &ms, const std::vector<uint32_t> &how,
                        const std::vector<uint64_t> &plan_at,
                        const mpdp_edge *edges, const double *cardinalities, const double *selectivities,
                        const double *base_costs, mpdp_cost_model cost_model, const mpdp_batch_schedule *sched) {
@@ -964,6 +977,7 @@ void fill_batch_upload(char *up, const BatchLayout &B, uint32_t nq, const mpdp_b
         const mpdp_batch_query &Q = queries[i];
         uint32_t packed = mpdp::kSchedDefault;
         if (sched) (void)encode_schedule(sched[i], packed);  // checked by check_batch_args
+        packed |= how[i];
         const uint32_t team = team_of[j];
         for (uint32_t member = 0; member < team; ++member)
             dq[entry_of[j] + member] = mpdp::BatchQueryDev{Q.n, Q.m, Q.m == Q.n - 1 ? 1u : 0u, (uint32_t)cost_model,
@@ -1042,12 +1056,12 @@ mpdp_status batch_core(uint32_t nq, const mpdp_batch_query *queries, const mpdp_
     if (ws_bytes < B.total) return MPDP_ENOMEM;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     char *base = static_cast<char *>(d_workspace);
-    std::vector<uint32_t> order, team;
+    std::vector<uint32_t> order, team, how;
     std::vector<uint64_t> plan_at;
     std::vector<double> ms;
-    batch_order(nq, queries, edges, order, team, ms, plan_at, (flags & kFlagBatchAllTeams) != 0);
+    batch_order(nq, queries, edges, order, team, ms, how, plan_at, (flags & kFlagBatchAllTeams) != 0);
     std::vector<char> up(B.plans);
-    fill_batch_upload(up.data(), B, nq, queries, order, team, ms, plan_at, edges, cardinalities, selectivities, base_costs,
+    fill_batch_upload(up.data(), B, nq, queries, order, team, ms, how, plan_at, edges, cardinalities, selectivities, base_costs,
                       cost_model, sched);
     const int rate_khz = wall_clock_khz();
     const bool timing = (flags & MPDP_FLAG_TIMING) != 0;
@@ -1181,7 +1195,7 @@ struct mpdp_batch_graph {
     mpdp_cost_model cm = MPDP_COST_COUT;
     std::vector<mpdp_batch_query> shape;  // n and m per query, offsets as given at creation
     BatchLayout B{};
-    std::vector<uint32_t> order, team;    // queue order and team sizes of the current run
+    std::vector<uint32_t> order, team, how;  // queue order, team sizes and paths of the current run
     std::vector<double> ms;               // predicted times, by query
     std::vector<uint64_t> plan_at;
     char *base = nullptr;                 // device workspace
@@ -1394,8 +1408,8 @@ mpdp_status mpdp_batch_graph_run(mpdp_batch_graph *g, const mpdp_batch_query *qu
     if (st0 != MPDP_OK) return st0;
     // order and teams follow this run's edges; the layout, fixed by the
     // shapes, has room for any choice of teams
-    batch_order(g->nq, queries, edges, g->order, g->team, g->ms, g->plan_at);
-    fill_batch_upload(g->h_up, g->B, g->nq, queries, g->order, g->team, g->ms, g->plan_at, edges, cardinalities, selectivities,
+    batch_order(g->nq, queries, edges, g->order, g->team, g->ms, g->how, g->plan_at);
+    fill_batch_upload(g->h_up, g->B, g->nq, queries, g->order, g->team, g->ms, g->how, g->plan_at, edges, cardinalities, selectivities,
                       nullptr, g->cm, schedules);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     HIPCHK(hipGraphLaunch(g->exec, s));

@@ -129,7 +129,7 @@ struct TeamRec {
     uint32_t error;                  // a barrier wait ran out of time
     uint32_t xcds;                   // bit x: a member runs on XCD x
     uint32_t count[24];              // connected sets per level k
-    unsigned long long ccp, evaluated;
+    unsigned long long connected, ccp, evaluated;
 };
 
 constexpr uint32_t kTeamSize = 8;     // largest team
@@ -138,8 +138,10 @@ constexpr uint32_t kTeamMinRel = 17;  // only queries of at least this many rela
 // Schedule of one query in the batched kernel: bits 0-1 hold log2 of the
 // consecutive ranks per lane of a star's levels (1, 2 or 4), bits 8-23 the
 // number of 16-subset chunks from which a cyclic query's sets may be shared
-// by several waves.
+// by several waves.  Bit 2, set by the host from the query's shape: a tree
+// join's levels are unranked.
 constexpr uint32_t kSchedChunkMask = 3u;
+constexpr uint32_t kSchedUnrank = 4u;
 constexpr uint32_t kSchedHeavyShift = 8;
 constexpr uint32_t kSchedDefault = 2u | (256u << kSchedHeavyShift);
 
