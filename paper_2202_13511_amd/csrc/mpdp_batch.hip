@@ -7,8 +7,10 @@
 // levels 2..n, rebuilds the plan and records the device wall clock at the
 // query's start and end.  A level is its list of connected sets, grown from
 // the level before (see mpdp_lists.h): tree joins cost their edges (Alg. 2),
-// the others search their csg-cmp pairs; of a star around relation 0 every
-// set of relation 0 and others is connected, so it needs no lists.  Memo and
+// the others search their csg-cmp pairs or, in dense graphs, walk the subsets
+// of their sets; of a star around relation 0 every set of relation 0 and
+// others is connected, so it needs no lists, and trees of many connected sets
+// are unranked.  Memo and
 // scratch live in a per-workgroup slot that is reused from query to query,
 // so the workspace does not grow with the batch.  A large query may be
 // taken by a team of workgroups (consecutive queue entries): they split the
@@ -299,7 +301,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         build_image(L, Q, edges, cards, sels, bcosts, s_num, s_kids);
         const uint32_t n = Q.n;
         const bool star = Q.is_tree && L.adj[0] == (1u << n) - 2u;
-        const bool unrank = (Q.sched & kSchedUnrank) != 0u;
+        const bool unrank = (Q.sched & kSchedUnrank) != 0u, walk = (Q.sched & kSchedWalk) != 0u;
         if (t == 0) {
             s_t0 = (unsigned long long)wall_clock64();
             s_conn = 0;
@@ -355,6 +357,12 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         } else {
             __syncthreads();
         }
+        if (walk && !failed) {  // no plan yet for sets of two or more relations (base relations: the first member)
+            for (uint32_t S = Q.member * kBatchBlock + t; S < (1u << n); S += Q.team * kBatchBlock)
+                if ((S & (S - 1u)) != 0u || S == 0u) M.cost[S] = -1.0;
+            if (team) failed = !team_barrier(R, Q.team, spread, phase, s_ok);
+            else __syncthreads();
+        }
         // (a record and a counter for each of the team's waves: a team has
         // kTeamMinRel relations or more, and its slot room for a third list)
         const PairParts pp = team ? PairParts{reinterpret_cast<HeavyPart *>(slot + parts_off),
@@ -402,7 +410,11 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 const uint32_t per = max(pair_sets(count, nw), min(count, kBatchPer));
                 const bool heavy = (1u << k) / 16u >= ((Q.sched >> kSchedHeavyShift) & 0xffffu);
                 const uint32_t parts = heavy && 2u * count <= nw ? nw / count : 1u;
-                eval_pairs<CM, false, false>(L, BitMemo{}, M, list, count, k, w, nw, per, parts, W.pairs[wave], pp, lane, my_ccp,
+                if (walk)
+                    eval_subsets<CM>(L, M, list, count, k, w, nw, pair_sets(count, nw), parts, W.pairs[wave].p0, pp, lane,
+                                     my_ccp, my_eval);
+                else
+                    eval_pairs<CM, false, false>(L, BitMemo{}, M, list, count, k, w, nw, per, parts, W.pairs[wave], pp, lane, my_ccp,
                                my_eval);
             }
             // the level's memo is complete before the next level reads it

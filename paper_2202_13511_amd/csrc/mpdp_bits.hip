@@ -174,37 +174,7 @@ __global__ __launch_bounds__(kBitsBlock) void k_bits_level(const DevGraph *g, ui
             }
         }
         bool store = live && sub == 0u;
-        if (parts > 1u) {
-            HeavyPart *r = rec + (size_t)s0 * parts;
-            uint32_t n_here = 0;
-            if (lane == 0) {
-                unsigned long long *r64 = reinterpret_cast<unsigned long long *>(&r[part]);
-                __hip_atomic_store(&r64[0], (unsigned long long)__double_as_longlong(best.c), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&r64[1], ((unsigned long long)best.op << 32) | best.l, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                // (device-wide stores, complete before the arrival)
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_s_waitcnt(0);
-                n_here = __hip_atomic_fetch_add(&arrived[s0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            n_here = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_here);
-            store = false;
-            if (n_here == parts - 1u) {  // the last part takes the best of all
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                SetBest o{__builtin_inf(), ~0u, ~0u};
-                if (lane < parts) {
-                    unsigned long long *r64 = reinterpret_cast<unsigned long long *>(&r[lane]);
-                    const unsigned long long c = __hip_atomic_load(&r64[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const unsigned long long l = __hip_atomic_load(&r64[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    o = SetBest{__longlong_as_double((long long)c), (uint32_t)l, (uint32_t)(l >> 32)};
-                }
-                group_best(o, 64u);
-                best = o;
-                store = lane == 0;
-                if (store) __hip_atomic_store(&arrived[s0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        if (parts > 1u) store = meet_parts(PairParts{rec, arrived}, s0, part, parts, best, lane);
         if (store) {
             Q.cost[(size_t)S * kStride] = best.c;
             store_best(M, off + colex_rank(kRankTable.v, S, false),

@@ -789,6 +789,52 @@ mpdp_status check_batch_args(uint32_t nq, const mpdp_batch_query *queries, const
     return MPDP_OK;
 }
 
+// True if a fifth or more of a query's candidates (its disjoint pairs of
+// relation sets), a tenth from 18 relations on, are csg-cmp pairs: from 96
+// random ones, the same for all queries, of which 20 (10) pairs decide, and none
+// among the first 32.  Graphs with so many have nearly two edges a relation (all
+// relations on two hubs have 2 n - 4); most others end there.
+bool many_pairs(uint32_t n, uint32_t m, const uint32_t *adj) {
+    if (n < 15 || m + 4 < 2 * n) return false;
+    constexpr uint32_t kTries = 96;
+    struct Tries {
+        uint32_t a[kTries], b[kTries];
+    };
+    static const Tries tries = [] {
+        Tries t{};
+        uint64_t state = 0x9e3779b97f4a7c15ull;
+        for (uint32_t i = 0; i < kTries; ++i)
+            for (uint32_t v = 0; v < 32; ++v) {  // each relation in one, in the other or in neither
+                state = state * 6364136223846793005ull + 1442695040888963407ull;
+                const uint32_t third = (uint32_t)(((state >> 32) * 3u) >> 32);
+                t.a[i] |= third == 0 ? 1u << v : 0u;
+                t.b[i] |= third == 1 ? 1u << v : 0u;
+            }
+        return t;
+    }();
+    const auto neighbours = [&](uint32_t S) {
+        uint32_t nb = 0;
+        for (uint32_t T = S; T; T &= T - 1) nb |= adj[__builtin_ctz(T)];
+        return nb;
+    };
+    const auto connected = [&](uint32_t S) {
+        uint32_t seen = S & (0u - S), fr = seen;
+        while (fr) {
+            fr = neighbours(fr) & S & ~seen;
+            seen |= fr;
+        }
+        return S != 0u && seen == S;
+    };
+    const uint32_t full = (n == 32) ? ~0u : (1u << n) - 1u;
+    const uint32_t want = n >= 18 ? 10 : 20;
+    uint32_t pairs = 0;
+    for (uint32_t i = 0; i < kTries && pairs < want && (i < 32 || pairs > 0); ++i) {
+        const uint32_t A = tries.a[i] & full, B = tries.b[i] & full;
+        if (connected(A) && connected(B) && (neighbours(A) & B)) ++pairs;
+    }
+    return pairs >= want;
+}
+
 // Predicted device time (ms) of a query alone on one workgroup of the
 // batched kernel, for scheduling only.  A tree query's time is close to
 // linear in its pairs (the connected sets, weighted by their size less one:
@@ -804,12 +850,19 @@ mpdp_status check_batch_args(uint32_t nq, const mpdp_batch_query *queries, const
 // Queries of up to 12 relations end the queue and are told apart by their
 // relations and extra edges alone: the logarithms and searches for all of
 // 4096 queries took 0.5 ms.
-// `how`: kSchedUnrank where the query's levels take that path, as in
-// many_sets; the workgroups' memos are small, so that only subsets and pairs
-// count (us, lists / unranked, pairs and subsets in thousands; 600 stars of 14
-// (53, 16) 434 / 434, PG-like 520 / 552, of 16 (246, 66) 1243 / 1075, of 18
-// (1114, 262) 6843 / 3613; 500 double stars of 7 and 7 leaves (131, 66) 645 /
-// 687, PG-like 935 / 846; 1000 random trees of 10-20 1133 / 2846).
+// `how`: kSchedUnrank or kSchedWalk where the query's levels take that path.
+// Unranking, as in many_sets; the workgroups' memos are small, so that only
+// subsets and pairs count (us, lists / unranked, pairs and subsets in
+// thousands; 600 stars of 14 (53, 16) 434 / 434, PG-like 520 / 552, of 16 (246,
+// 66) 1243 / 1075, of 18 (1114, 262) 6843 / 3613; 500 double stars of 7 and 7
+// leaves (131, 66) 645 / 687, PG-like 935 / 846; 1000 random trees of 10-20 1133
+// / 2846).  Walking subset by subset where many of them are pairs (kernel, ms,
+// searched / walked, and the share of pairs; graphs with random edges, PG-like
+// behind the stroke; 100 of 16 14.0 / 11.6, 14.8 / 19.1, 0.018, 105 / 19.9, 112 /
+// 40, 0.27; 200 of 17 from a tenth on 37 / 45, 42 / 52, from a fifth on 37 / 34,
+// 43 / 41; 20 of 19 29 / 43, 32 / 54, 0.013, 612 / 67, 653 / 122, 0.29; 100
+// cliques of 13 3.4 / 1.3, 4 of 17 65 / 5.8, 73 / 10.9; one of 19 in a team 788 /
+// 41, 894 / 114).
 double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges, uint32_t &how) {
     const uint32_t n = Q.n;
     how = 0;
@@ -856,6 +909,10 @@ double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges, uint32_t 
             return 1e-3 * (10.0 + 5.0 * n + 1.5e-3 * pairs + 0.3e-3 * subsets);
         }
         return 1e-3 * (star ? 5.1 + 3.2 * n + 0.86e-3 * pairs : 10.0 + 5.0 * n + 2.7e-3 * pairs);
+    }
+    if (many_pairs(n, Q.m, adj)) {
+        how = mpdp::kSchedWalk;
+        return 0.5e-6 * std::pow(3.0, (double)n);
     }
     uint32_t alive = (n == 32) ? ~0u : (1u << n) - 1u;
     for (bool changed = true; changed;) {

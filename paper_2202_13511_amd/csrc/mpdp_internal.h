@@ -138,10 +138,11 @@ constexpr uint32_t kTeamMinRel = 17;  // only queries of at least this many rela
 // Schedule of one query in the batched kernel: bits 0-1 hold log2 of the
 // consecutive ranks per lane of a star's levels (1, 2 or 4), bits 8-23 the
 // number of 16-subset chunks from which a cyclic query's sets may be shared
-// by several waves.  Bit 2, set by the host from the query's shape: a tree
-// join's levels are unranked.
+// by several waves.  Bits 2 and 3, set by the host from the query's shape: a
+// tree join's levels are unranked (kSchedUnrank), a cyclic query's sets are
+// walked subset by subset (kSchedWalk).
 constexpr uint32_t kSchedChunkMask = 3u;
-constexpr uint32_t kSchedUnrank = 4u;
+constexpr uint32_t kSchedUnrank = 4u, kSchedWalk = 8u;
 constexpr uint32_t kSchedHeavyShift = 8;
 constexpr uint32_t kSchedDefault = 2u | (256u << kSchedHeavyShift);
 

@@ -734,6 +734,113 @@ __device__ __forceinline__ SetBest pair_best(uint32_t A, uint32_t B, double cA, 
     return o;
 }
 
+// The keys of one set's `parts` parts meet in pp.rec: true, with the best of all
+// in `best`, in lane 0 of the part that comes last.
+__device__ __forceinline__ bool meet_parts(const PairParts &pp, uint32_t set, uint32_t part, uint32_t parts, SetBest &best,
+                                           uint32_t lane) {
+    HeavyPart *rec = pp.rec + (size_t)set * parts;
+    uint32_t n_here = 0;
+    if (lane == 0) {
+        unsigned long long *r64 = reinterpret_cast<unsigned long long *>(&rec[part]);
+        __hip_atomic_store(&r64[0], (unsigned long long)__double_as_longlong(best.c), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&r64[1], ((unsigned long long)best.op << 32) | best.l, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        // (device-wide stores, complete before the arrival)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        n_here = __hip_atomic_fetch_add(&pp.arrived[set], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    n_here = (uint32_t)__builtin_amdgcn_readfirstlane((int)n_here);
+    if (n_here != parts - 1u) return false;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    SetBest o{__builtin_inf(), ~0u, ~0u};
+    if (lane < parts) {
+        unsigned long long *r64 = reinterpret_cast<unsigned long long *>(&rec[lane]);
+        const unsigned long long c = __hip_atomic_load(&r64[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long l = __hip_atomic_load(&r64[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        o = SetBest{__longlong_as_double((long long)c), (uint32_t)l, (uint32_t)(l >> 32)};
+    }
+    group_best(o, 64u);
+    best = o;
+    if (lane == 0) __hip_atomic_store(&pp.arrived[set], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return lane == 0;
+}
+
+// ---------------------------------------------------------------- subsets of sets, dense graphs
+
+// The csg-cmp pairs of the sets list[0 .. count) where most subsets are
+// connected: every subset that holds the set's lowest relation, A = lowest +
+// x, and the rest of the set.  The memo is the kernel's own, indexed by the
+// set, with a cost below zero where there is no plan, so that the two gathers
+// that a pair's cost takes are its test as well; neighbouring lanes take
+// neighbouring subsets.  Up to six relations 2^(k-1) lanes take a set, from
+// seven on a wave does, or `parts` waves.  PG-like reads the cards of pairs
+// whose costs leave them a chance (see pass_pair).  Bound by the gathers; the
+// search (eval_pairs) takes a chain of dependent steps for each pair, here
+// the next subset waits for nothing.
+template <int CM>
+__device__ void eval_subsets(const LdsGraph &L, const MemoPtrs &M, const uint32_t *list, uint32_t count, uint32_t k,
+                             uint32_t w, uint32_t nw, uint32_t per, uint32_t parts, uint32_t *todo, PairParts pp,
+                             uint32_t lane, unsigned long long &ccp, unsigned long long &evaluated) {
+    // subsets of a lane in flight (PG-like, four cost the batched kernel
+    // registers that all its paths then miss, 5 to 10 %)
+    constexpr int kEach = CM == MPDP_COST_COUT ? 4 : 2;
+    const uint32_t chunks = (count + per - 1u) / per, items = parts > 1u ? count * parts : chunks;
+    const uint32_t lgP = k < 7u ? k - 1u : 6u, P = 1u << lgP, sub = lane & (P - 1u), sets = 64u >> lgP;
+    const uint32_t all = k < 7u ? 1u : 1u << (k - 7u);  // rounds of P subsets
+    for (uint32_t item = w; item < items; item += nw) {
+        const uint32_t s0 = parts > 1u ? item / parts : item, part = parts > 1u ? item - s0 * parts : 0u;
+        const uint32_t ns = parts > 1u ? 1u : (count - s0 + chunks - 1u) / chunks;
+        const uint32_t rounds = part < all ? (all - part + parts - 1u) / parts : 0u;
+        uint32_t myset = 0;
+        double mycard = 0.0;
+        if (lane < ns) {
+            myset = list[s0 + lane * chunks];
+            if (part == 0u) evaluated += block_candidates<false>(L, myset, todo + lane);
+            tree_card_n<1>(L, &myset, k, &mycard);
+        }
+        for (uint32_t j = 0; j < ns; j += sets) {
+            const int from = (int)(j + (lane >> lgP));
+            const uint32_t S = (uint32_t)__shfl((int)myset, from, 64), lo = lowbit(S), rest = S ^ lo;
+            const double cS = __shfl(mycard, from, 64);
+            const uint32_t step = all > parts ? deposit(64u * parts, rest) : 0u;
+            uint32_t x = deposit(part * 64u + sub, rest);
+            SetBest best{__builtin_inf(), ~0u, ~0u};
+            for (uint32_t r = 0; r < rounds; r += kEach) {
+                uint32_t A[kEach];
+                double cA[kEach], cB[kEach];
+#pragma unroll
+                for (int u = 0; u < kEach; ++u) {
+                    const bool in = r + (uint32_t)u < rounds && x != rest;
+                    A[u] = in ? lo | x : 0u;  // (the empty set has no plan)
+                    x = ((x | ~rest) + step) & rest;  // (the masked add carries through the holes)
+                    cA[u] = M.cost[A[u]];
+                    cB[u] = M.cost[in ? S ^ A[u] : 0u];
+                }
+#pragma unroll
+                for (int u = 0; u < kEach; ++u) {
+                    const bool on = cA[u] >= 0.0 && cB[u] >= 0.0;
+                    ccp += on ? 1u : 0u;
+                    const uint32_t B = S ^ A[u];
+                    if (CM == MPDP_COST_COUT) {
+                        SetBest o = pair_best<CM>(A[u], B, cA[u], cB[u], 0.0, 0.0, cS);
+                        o.l = on ? o.l : ~0u;
+                        o.c = on ? o.c : __builtin_inf();
+                        take_best(best, o);
+                    } else if (on && (cA[u] + cB[u]) + 0.01 * cS <= best.c) {
+                        take_best(best, pair_best<CM>(A[u], B, cA[u], cB[u], M.card[A[u]], M.card[B], cS));
+                    }
+                }
+            }
+            group_best(best, P);
+            bool store = S != 0u && sub == 0u;
+            if (parts > 1u) store = meet_parts(pp, s0, part, parts, best, lane);
+            if (store) store_best(M, S, Key{(unsigned long long)__double_as_longlong(best.c), best.l, best.op}, cS);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- tree joins
 
 // Alg. 2 for the sets list[0 .. count) of a tree join (in preorder numbers),
