@@ -313,10 +313,10 @@ constexpr size_t kGraphCacheSize = 32;  // recorded graphs kept per thread
 struct GraphKey {
     void *ws, *pin;
     uint32_t n, cost_model;
-    bool general, lazy;  // the level kernels recorded depend on them
+    bool general, dense;  // the level kernels recorded depend on them
     bool operator==(const GraphKey &o) const {
         return ws == o.ws && pin == o.pin && n == o.n && cost_model == o.cost_model && general == o.general &&
-               lazy == o.lazy;
+               dense == o.dense;
     }
 };
 
@@ -536,7 +536,6 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     std::vector<char> down_pageable((pin || no_alloc) ? 0 : down_bytes);
     char *down = pin ? pin : (no_alloc ? down_stack : down_pageable.data());
     const bool bits = general && !dpsub && n <= mpdp::kBitsMaxRel;
-    const bool lazy = general && mpdp::lazy_cards((uint32_t)q.cost_model, n, q.m);
     const size_t N = size_t(1) << n;
     char *const bat = base + L.bits;
     const bool cout_model = q.cost_model == MPDP_COST_COUT;
@@ -605,8 +604,8 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
             if (bits)
                 e = mpdp::launch_bits_level(dg, q.cost_model, n, k, nc, cnt, space, memo, parts, arrived, tally, st);
             else if (counted)  // lists of connected sets: odd levels in one buffer, even ones in the other
-                e = mpdp::launch_level_pairs(dg, q.cost_model, lazy, n, k, (k & 1u) ? heavy : list, (k & 1u) ? list : heavy,
-                                             cnt, memo, parts, arrived, tally, st);
+                e = mpdp::launch_level_pairs(dg, q.cost_model, n, q.m, k, (k & 1u) ? heavy : list,
+                                             (k & 1u) ? list : heavy, cnt, memo, parts, arrived, tally, st);
             else if (dpsub)
                 e = mpdp::launch_eval_general(dg, q.cost_model, k, nc, list, heavy, cnt, memo, parts, st);
             else if (unfused)  // ablation: evaluate writes every pair's key, prune reduces
@@ -625,7 +624,8 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
         // replay the sequence recorded once for this workspace, staging
         // buffer and shape (its first kernel reads the staging buffer)
         hipGraphExec_t exec = nullptr;
-        HIPCHK(cached_graph(GraphKey{d_ws, pin, n, (uint32_t)q.cost_model, general, lazy}, enqueue, exec));
+        HIPCHK(cached_graph(GraphKey{d_ws, pin, n, (uint32_t)q.cost_model, general,
+                                     mpdp::many_edges(n, q.m)}, enqueue, exec));
         HIPCHK(hipGraphLaunch(exec, s));
     } else {
         HIPCHK(enqueue(s));
@@ -795,7 +795,7 @@ mpdp_status check_batch_args(uint32_t nq, const mpdp_batch_query *queries, const
 // among the first 32.  Graphs with so many have nearly two edges a relation (all
 // relations on two hubs have 2 n - 4); most others end there.
 bool many_pairs(uint32_t n, uint32_t m, const uint32_t *adj) {
-    if (n < 15 || m + 4 < 2 * n) return false;
+    if (n < 15 || !mpdp::many_edges(n, m)) return false;
     constexpr uint32_t kTries = 96;
     struct Tries {
         uint32_t a[kTries], b[kTries];

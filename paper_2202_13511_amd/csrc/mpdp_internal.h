@@ -219,19 +219,12 @@ hipError_t launch_tree_level(const DevGraph *g, int cost_model, uint32_t n, uint
                              const uint32_t *list, uint32_t *next, Counters *cnt, MemoPtrs memo, hipStream_t s);
 hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, bool star, uint32_t n, uint32_t k0,
                             uint32_t k1, uint32_t *even, uint32_t *odd, Counters *cnt, MemoPtrs memo, hipStream_t s);
-// PG-like queries whose relations and edges beyond a spanning tree come to
-// this many (and that have more than 24 relations) read a pair's cards only if
-// its costs leave it a chance: their gathers, most of them past every cache,
-// bound them, while smaller ones wait for each step.  39 (28 relations, 10
-// chords on a cycle): 6.08 -> 5.10 ms; 36 (26, 9): 1.94 -> 1.98; 35 (25, 9):
-// 1.82 -> 1.89; 34 (27, 6): 1.90 -> 1.96.
-constexpr uint32_t kLazyMin = 38;
-inline bool lazy_cards(uint32_t cost_model, uint32_t n, uint32_t m) {
-    return cost_model == MPDP_COST_PGLIKE && n > 24 && m + 1 >= kLazyMin;  // n + (m - (n - 1))
-}
-// One level of the block-based path: the sets of k relations in `list`
+// Nearly two edges a relation: only such graphs have many connected subsets
+// that make pairs.
+inline bool many_edges(uint32_t n, uint32_t m) { return m + 4 >= 2 * n; }
+// One level of a cyclic query: the sets of k relations in `list`
 // (cnt->level_count[k] of them) evaluated, the sets of k + 1 into `next`.
-hipError_t launch_level_pairs(const DevGraph *g, int cost_model, bool lazy, uint32_t n, uint32_t k, const uint32_t *list,
+hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t m, uint32_t k, const uint32_t *list,
                               uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
                               unsigned long long *tally, hipStream_t s);
 hipError_t launch_filter(const DevGraph *g, uint32_t k, uint64_t ncand, uint32_t *list, Counters *cnt,

@@ -16,6 +16,23 @@ namespace {
 // to divide.
 constexpr uint32_t kShareMinK = 10;
 
+// PG-like levels whose pairs' cards are read only where the costs leave a
+// chance (see pass_pair): those bound by their gathers, of many sets or of which
+// most subsets are connected and make pairs.  Other levels wait for each step of
+// the search, and a pair takes one more with its cards read later (2 to 6 %).
+// Asked only (lazy_query) where a memo's costs are more than the L2s hold (8 B <<
+// n: 32 MB at 22 relations) or the graph has many edges: a smaller star's sets
+// have one pair a member.  Always later / always along with the costs / by this
+// rule, ms: cliques of 19 4.7 / 8.2 / 5.0, of 22 245 / 604 / 257; two hubs of 20
+// relations 69 / 160 / 74; cycles with chords, of 24 (8) 1.77 / 1.68 / 1.69, 24 (14)
+// 3.47 / 4.14 / 3.43, 28 (10) 5.08 / 6.13 / 5.06, 30 (11) 10.9 / 15.4 / 10.9; star
+// of 22 with two more edges 1.20 / 1.12 / 1.12, of 24 with three 4.07 / 4.40 / 4.07;
+// chain of 16 on a clique of 14 3.66 / 3.35 / 3.42.
+__device__ __forceinline__ bool lazy_level(uint32_t count, uint64_t subsets) {
+    return count >= 65536u || (count >= 2048u && 4ull * count >= subsets);
+}
+bool lazy_query(uint32_t n, uint32_t m) { return n >= 23 || many_edges(n, m); }
+
 // One workgroup of 16 waves per CU (the waves' pools, the rank table and the
 // query fill 160 KB of LDS).  The next level's list first, which the
 // workgroup does in step, then each wave its own sets.  `tally` holds two
@@ -49,8 +66,12 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
         expand_sets<false, kWide>(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, reinterpret_cast<uint32_t *>(buf),
                     sizeof(buf) / 4, ends, lane);
     unsigned long long ccp = 0, evaluated = 0;
-    eval_pairs<CM, kWide, kLazy>(L, ColexMemo{ranks, L.loff, kWide}, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6],
-                   PairParts{rec, arrived}, lane, ccp, evaluated);
+    const ColexMemo at{ranks, L.loff, kWide};
+    const PairParts pp{rec, arrived};
+    if (kLazy && lazy_level(count, L.loff[k + 1] - L.loff[k]))
+        eval_pairs<CM, kWide, true>(L, at, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6], pp, lane, ccp, evaluated);
+    else
+        eval_pairs<CM, kWide, false>(L, at, M, list, count, k, w, nw, per, parts, buf[threadIdx.x >> 6], pp, lane, ccp, evaluated);
     for (int off = 32; off >= 1; off >>= 1) {
         ccp += (unsigned long long)__shfl_xor((long long)ccp, off);
         evaluated += (unsigned long long)__shfl_xor((long long)evaluated, off);
@@ -149,7 +170,7 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
 
 }  // namespace
 
-hipError_t launch_level_pairs(const DevGraph *g, int cost_model, bool lazy, uint32_t n, uint32_t k, const uint32_t *list,
+hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t m, uint32_t k, const uint32_t *list,
                               uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
                               unsigned long long *tally, hipStream_t s) {
     const auto go = [&](auto kernel) {
@@ -158,10 +179,10 @@ hipError_t launch_level_pairs(const DevGraph *g, int cost_model, bool lazy, uint
     };
     if (cost_model == MPDP_COST_COUT)
         n > 24 ? go(k_level_pairs<MPDP_COST_COUT, true, false>) : go(k_level_pairs<MPDP_COST_COUT, false, false>);
-    else if (lazy)
-        go(k_level_pairs<MPDP_COST_PGLIKE, true, true>);
+    else if (lazy_query(n, m))
+        n > 24 ? go(k_level_pairs<MPDP_COST_PGLIKE, true, true>) : go(k_level_pairs<MPDP_COST_PGLIKE, false, true>);
     else
-        n > 24 ? go(k_level_pairs<MPDP_COST_PGLIKE, true, false>) : go(k_level_pairs<MPDP_COST_PGLIKE, false, false>);
+        go(k_level_pairs<MPDP_COST_PGLIKE, false, false>);
     return hipGetLastError();
 }
 

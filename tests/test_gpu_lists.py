@@ -153,3 +153,30 @@ def test_cards_read_only_where_needed(q):
            [(p["relset"], p["left"], p["right"], p["op"]) for p in want]
     assert (got.stats["connected_sets"], got.stats["ccp_pairs"], got.stats["evaluated_pairs"]) == \
            (ref.connected_sets, ref.ccp_ordered // 2, ref.evaluated)
+
+
+@pytest.mark.parametrize("card,sel", [(None, None), (1000.0, 0.001), (1e308, 1.0)], ids=["drawn", "ties", "infinite"])
+def test_cards_read_late_on_dense_levels(card, sel):
+    """PG-like: levels of which a quarter or more of the subsets are connected
+    (and levels of many sets) read a pair's cards after its costs, others along
+    with them; a query has levels of both kinds."""
+    q = W.random_connected(19, 3, 0.15)
+    if card is not None:
+        q.card[:] = card
+        q.sel[:] = sel
+    cm = mpdp.MPDP_COST_PGLIKE
+    res, gm = run_ws(q, cm)
+    ref = oracle.mpdp(q, cm)
+    check_memo(q, gm, ref)
+    check_plan(q, res, ref)
+    check_stats(q, res, ref, general=True)
+
+
+def test_dense_query_under_both_models():
+    """A clique of 20 takes 17 ms under PG-like and 14 under C_out; with every
+    pair's cards read it took 31."""
+    def median_ms(cm):
+        q, ws = W.clique(20, 1), mpdp.workspace(20, cm)
+        return sorted(mpdp.mpdp_optimize_ws(q, cm, ws).stats["ms_total"] for _ in range(5))[2]
+
+    assert median_ms(mpdp.MPDP_COST_PGLIKE) < 1.8 * median_ms(mpdp.MPDP_COST_COUT)
