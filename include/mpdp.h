@@ -332,7 +332,10 @@ typedef struct {
  * times, acyclic and cyclic candidates sharing launches; every query's
  * device time comes from the kernel's clock at its start and end, and each
  * class gets the candidate with the smallest median time over its queries
- * and repetitions (ties to the default).  schedules_out: host, nq entries in
+ * and repetitions (ties to the default).  Of an acyclic class only the stars
+ * around relation 0 count, which tree_chunk has an effect on; a class without
+ * any keeps the default, and est_tuned_ms equals est_default_ms for the others.
+ * schedules_out: host, nq entries in
  * input order.  reps in 1..16; other arguments and errors as in
  * mpdp_optimize_batch (the workspace is sized by mpdp_batch_workspace_bytes).
  */

@@ -1154,6 +1154,15 @@ mpdp_status batch_core(uint32_t nq, const mpdp_batch_query *queries, const mpdp_
 
 // ---------------------------------------------------------------- batch schedule autotuner
 
+// A star around relation 0, the only acyclic shape whose time tree_chunk
+// changes: its edges are all of relation 0.
+bool star_at_0(const mpdp_batch_query &Q, const mpdp_edge *edges) {
+    if (Q.m != Q.n - 1) return false;
+    for (uint32_t e = 0; e < Q.m; ++e)
+        if (edges[Q.edge_offset + e].u != 0 && edges[Q.edge_offset + e].v != 0) return false;
+    return true;
+}
+
 // Class of a query for the autotuner: n, acyclic or not, band of the number
 // of edges beyond a spanning tree.
 uint32_t tune_class(const mpdp_batch_query &Q) {
@@ -1215,23 +1224,34 @@ mpdp_status batch_autotune(uint32_t nq, const mpdp_batch_query *queries, const m
             if (cls[i] == key) members.push_back(i);
         const bool tree = queries[members[0]].m == queries[members[0]].n - 1;
         const uint32_t ncand = tree ? nT : nH;
-        double med[5] = {0, 0, 0, 0, 0};
-        for (uint32_t c = 0; c < ncand; ++c) {
+        // the members that the candidates differ for: of an acyclic class, its stars
+        std::vector<uint32_t> tuned, others;
+        for (uint32_t i : members) (!tree || star_at_0(queries[i], edges) ? tuned : others).push_back(i);
+        const auto median = [&](const std::vector<uint32_t> &of, uint32_t c) {
             std::vector<double> v;
-            for (uint32_t i : members) v.insert(v.end(), times[(size_t)i * 5 + c].begin(), times[(size_t)i * 5 + c].end());
+            for (uint32_t i : of) v.insert(v.end(), times[(size_t)i * 5 + c].begin(), times[(size_t)i * 5 + c].end());
             std::nth_element(v.begin(), v.begin() + v.size() / 2, v.end());
-            med[c] = v[v.size() / 2];
-        }
+            return v[v.size() / 2];
+        };
         uint32_t best = 0;  // candidate 0 is the default; a later one must be strictly faster
-        for (uint32_t c = 1; c < ncand; ++c)
-            if (med[c] < med[best]) best = c;
+        if (!tuned.empty()) {
+            double med[5] = {0, 0, 0, 0, 0};
+            for (uint32_t c = 0; c < ncand; ++c) med[c] = median(tuned, c);
+            for (uint32_t c = 1; c < ncand; ++c)
+                if (med[c] < med[best]) best = c;
+            est_default += med[0] * (double)tuned.size() * 1e-3;
+            est_tuned += med[best] * (double)tuned.size() * 1e-3;
+        }
+        if (!others.empty()) {
+            const double ms = median(others, 0) * (double)others.size() * 1e-3;
+            est_default += ms;
+            est_tuned += ms;
+        }
         for (uint32_t i : members) {
             out[i] = dflt;
             if (tree) out[i].tree_chunk = kTreeCand[best];
             else out[i].heavy_chunks = kHeavyCand[best];
         }
-        est_default += med[0] * (double)members.size() * 1e-3;
-        est_tuned += med[best] * (double)members.size() * 1e-3;
     }
     if (stats) {
         stats->classes = (uint32_t)keys.size();

@@ -104,3 +104,16 @@ def test_graph_replays_match_eager_launches(cm):
             g.run(base[:-1] + [W.chain(base[-1].n, 1) if base[-1].m != base[-1].n - 1 else W.clique(5, 1)])
     finally:
         g.close()
+
+
+def test_autotune_leaves_trees_without_a_choice():
+    """Ranks per lane are the stars' alone: other acyclic queries keep the default
+    (three runs of the same code used to decide by noise), and no gain is
+    estimated for them; a class's schedule is that of its stars."""
+    trees = [t for n in range(8, 16) for t in (W.chain(n, n), W.snowflake(n, n), W.random_tree(n, n + 1))]
+    sched, st = mpdp.mpdp_batch_autotune(trees, mpdp.MPDP_COST_COUT, mpdp.batch_workspace(trees), reps=1)
+    assert set(sched) == {(4, 256)} and st["est_tuned_ms"] == st["est_default_ms"] > 0
+    mixed = trees + [W.star(n, n) for n in range(8, 16)]
+    sched, st = mpdp.mpdp_batch_autotune(mixed, mpdp.MPDP_COST_COUT, mpdp.batch_workspace(mixed), reps=1)
+    assert st["est_tuned_ms"] <= st["est_default_ms"]
+    assert len({(q.n, s) for q, s in zip(mixed, sched)}) == 8
