@@ -264,10 +264,11 @@ size_t mpdp_batch_workspace_bytes(uint32_t nq, const mpdp_batch_query *queries);
  * workgroup takes the next query, runs all its DP levels with workgroup
  * barriers between levels, and writes its plan.  A query of 17 or more
  * relations that is predicted to take a large part of the batch's time is
- * taken by a team of 2, 4 or 8 workgroups, which split every level and meet
- * at device-wide barriers (each wait bounded; a team that times out reports
- * MPDP_EDEVICE); there are at most as many teams as cyclic queries of 17 or
- * more relations.
+ * shared by a team of up to 2, 4 or 8 workgroups, which split every level and
+ * meet at device-wide barriers (each wait bounded; a team that times out
+ * reports MPDP_EDEVICE); there are at most as many teams as cyclic queries of
+ * 17 or more relations.  A team works with those of its workgroups that have
+ * come within 2 ms, so the launch needs no number of them to run at once.
  * Results equal those of mpdp_optimize on each query alone.
  *   plans_out      host, sum over q of (2 n_q - 1) nodes; query q's plan
  *                  (layout of mpdp_plan_node) starts after those of 0..q-1

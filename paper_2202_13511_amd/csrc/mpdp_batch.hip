@@ -33,6 +33,10 @@ constexpr int kBW = kBatchBlock / 64;
 // (every path of a query inlined, 128 registers per lane) from more spilling
 constexpr int kBatchPairBatch = 3;
 constexpr unsigned long long kTeamWaitTicks = 200000000ull;  // 2 s of the 100 MHz device clock
+// 2 ms: longer than the members of a team take to come where the device has
+// room for them (0.5, 2 and 10 ms give the same times on batches of all sizes),
+// and little to wait for each team where it has not
+constexpr unsigned long long kTeamFormTicks = 200000ull;
 
 __device__ __forceinline__ uint32_t load_shared_count(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -72,6 +76,53 @@ __device__ bool team_barrier(TeamRec *R, uint32_t team, bool spread, uint32_t &p
     ++phase;
     __syncthreads();
     return s_ok != 0u;
+}
+
+// This workgroup's place in the team (kTeamClosed set: it came too late).  Its
+// XCD is in the record before it counts.  One thread.
+__device__ __forceinline__ uint32_t join_team(TeamRec *R, uint32_t xcd) {
+    __hip_atomic_fetch_or(&R->xcds, 1u << xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);
+    return __hip_atomic_fetch_add(&R->joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The team is formed: its leader (member 0), whose memo slot is set up, closes
+// it when `most` workgroups have joined or kTeamFormTicks have passed, and
+// publishes slot and size; the others wait for that, and see the slot's
+// contents afterwards.  Returns TeamRec::formed, 0 if it did not come (the wait
+// is bounded; the leader's is shorter).
+__device__ uint32_t form_team(TeamRec *R, uint32_t most, uint32_t member, uint32_t slot, uint32_t &s_ok) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned long long start = wall_clock64();
+        uint32_t formed;
+        if (member == 0u) {
+            while (load_shared_count(&R->joined) < most && (unsigned long long)wall_clock64() - start < kTeamFormTicks)
+                __builtin_amdgcn_s_sleep(2);
+            formed = __hip_atomic_fetch_or(&R->joined, kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t xcds = load_shared_count(&R->xcds);
+            if (xcds & (xcds - 1u)) {
+                formed |= kTeamSpread;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            }
+            __hip_atomic_store(&R->slot, slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_s_waitcnt(0);
+            __hip_atomic_store(&R->formed, formed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            while ((formed = load_shared_count(&R->formed)) == 0u) {
+                __builtin_amdgcn_s_sleep(2);
+                if ((unsigned long long)wall_clock64() - start > kTeamWaitTicks) {
+                    __hip_atomic_store(&R->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        s_ok = formed;
+    }
+    __syncthreads();
+    return s_ok;
 }
 
 // The XCD this workgroup runs on (hardware register XCC_ID).
@@ -309,10 +360,15 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
             s_eval = 0;
         }
         // a team works in its first member's slot, published through the team record
-        uint32_t slot_id = blockIdx.x;
-        if (team && t == 0) {
-            if (Q.member == 0) __hip_atomic_store(&R->slot, slot_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_or(&R->xcds, 1u << xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t slot_id = blockIdx.x, member = 0, size = 1;
+        if (team) {
+            if (t == 0) s_q = join_team(R, xcd);
+            __syncthreads();
+            member = s_q;
+            if (member & kTeamClosed) {  // too late
+                __syncthreads();
+                continue;
+            }
         }
         char *slot = slots + (uint64_t)slot_id * slot_bytes;
         MemoPtrs M{reinterpret_cast<double *>(slot), reinterpret_cast<double *>(slot + 8 * N),
@@ -320,7 +376,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         uint32_t *even = reinterpret_cast<uint32_t *>(slot + list_off), *odd = even + cap;
         const uint64_t parts_off = (list_off + 8ull * cap + 15) & ~15ull;
         if (t < 24) s_count[t] = t == 2u ? Q.m : 0u;
-        if (Q.member == 0) {
+        if (member == 0) {
             if (t < n) {
                 const uint64_t at = Q.is_tree ? L.loff[1] + t : 1u << t;
                 M.cost[at] = L.bcost[t];
@@ -342,12 +398,10 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
         }
         bool failed = false, spread = false;
         if (team) {
-            // the first meeting is for the record alone, unless it shows that
-            // the first member's stores have yet to leave its XCD
-            failed = !team_barrier(R, Q.team, false, phase, s_ok);
-            const uint32_t xcds = load_shared_count(&R->xcds);
-            spread = (xcds & (xcds - 1u)) != 0u;
-            if (spread && !failed) failed = !team_barrier(R, Q.team, true, phase, s_ok);
+            const uint32_t formed = form_team(R, Q.team, member, slot_id, s_ok);
+            failed = formed == 0u;
+            spread = (formed & kTeamSpread) != 0u;
+            size = formed & ~kTeamSpread;
             slot_id = load_shared_count(&R->slot);
             slot = slots + (uint64_t)slot_id * slot_bytes;
             M = MemoPtrs{reinterpret_cast<double *>(slot), reinterpret_cast<double *>(slot + 8 * N),
@@ -358,9 +412,9 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
             __syncthreads();
         }
         if (walk && !failed) {  // no plan yet for sets of two or more relations (base relations: the first member)
-            for (uint32_t S = Q.member * kBatchBlock + t; S < (1u << n); S += Q.team * kBatchBlock)
+            for (uint32_t S = member * kBatchBlock + t; S < (1u << n); S += size * kBatchBlock)
                 if ((S & (S - 1u)) != 0u || S == 0u) M.cost[S] = -1.0;
-            if (team) failed = !team_barrier(R, Q.team, spread, phase, s_ok);
+            if (team) failed = !team_barrier(R, size, spread, phase, s_ok);
             else __syncthreads();
         }
         // (a record and a counter for each of the team's waves: a team has
@@ -369,7 +423,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                                               reinterpret_cast<uint32_t *>(slot + parts_off + sizeof(HeavyPart) * kTeamSize * kBW)}
                                   : PairParts{parts_rec, parts_arrived};
         // this workgroup's waves among the team's, neighbours in other members
-        const uint32_t nw = Q.team * kBW, w = wave * Q.team + Q.member;
+        const uint32_t nw = size * kBW, w = wave * size + member;
         uint32_t *counts = team ? R->count : s_count;
         unsigned long long my_sets = 0, my_ccp = 0, my_eval = 0;
         for (uint32_t k = 2; k <= n && !failed; ++k) {
@@ -418,9 +472,9 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                                my_eval);
             }
             // the level's memo is complete before the next level reads it
-            if (team) failed = !team_barrier(R, Q.team, spread, phase, s_ok);
+            if (team) failed = !team_barrier(R, size, spread, phase, s_ok);
             else __syncthreads();
-            if (t == 0 && Q.member == 0) {
+            if (t == 0 && member == 0) {
                 s_conn += count;
                 if (Q.is_tree) {
                     s_ccp += (unsigned long long)(k - 1) * count;
@@ -445,8 +499,8 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 __hip_atomic_fetch_add(&R->ccp, s_ccp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_fetch_add(&R->evaluated, s_eval, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (!failed) failed = !team_barrier(R, Q.team, spread, phase, s_ok);
-            if (Q.member != 0) continue;
+            if (!failed) failed = !team_barrier(R, size, spread, phase, s_ok);
+            if (member != 0) continue;
             if (t == 0) {
                 s_conn = __hip_atomic_load(&R->connected, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 s_ccp = __hip_atomic_load(&R->ccp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

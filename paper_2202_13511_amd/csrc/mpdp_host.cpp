@@ -675,6 +675,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
 // Internal flag for tests: run Alg. 3 (the general kernel) on tree joins too.
 constexpr uint32_t kFlagForceGeneral = 0x100u;
 constexpr uint32_t kFlagBatchAllTeams = 0x200u;  // test aid: every query that may take a team takes the largest
+constexpr uint32_t kFlagBatchFew = 0x400u;       // test aid: three workgroups, as if the device had room for no more
 
 // ---------------------------------------------------------------- batch
 
@@ -1038,7 +1039,7 @@ void fill_batch_upload(char *up, const BatchLayout &B, uint32_t nq, const mpdp_b
         const uint32_t team = team_of[j];
         for (uint32_t member = 0; member < team; ++member)
             dq[entry_of[j] + member] = mpdp::BatchQueryDev{Q.n, Q.m, Q.m == Q.n - 1 ? 1u : 0u, (uint32_t)cost_model,
-                                              co, eo, plan_at[i], packed, j, team, member,
+                                              co, eo, plan_at[i], packed, j, team, 0u,
                                               team > 1 ? team_rec : 0u, 0u};
         if (team > 1) ++team_rec;
         for (uint32_t v = 0; v < Q.n; ++v) {
@@ -1111,6 +1112,7 @@ mpdp_status batch_core(uint32_t nq, const mpdp_batch_query *queries, const mpdp_
     if (!d_workspace) return MPDP_EINVAL;
     if (reinterpret_cast<uintptr_t>(d_workspace) % kAlign) return MPDP_EINVAL;
     if (ws_bytes < B.total) return MPDP_ENOMEM;
+    if (flags & kFlagBatchFew) B.workgroups = std::min(B.workgroups, 3u);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     char *base = static_cast<char *>(d_workspace);
     std::vector<uint32_t> order, team, how;

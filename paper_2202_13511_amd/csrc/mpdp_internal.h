@@ -116,14 +116,17 @@ struct BatchQueryDev {
     uint32_t n, m, is_tree, cost_model;
     uint64_t card_off, edge_off, plan_off;
     uint32_t sched, out;       // the query's schedule (packed as below); index of its BatchOut
-    uint32_t team, member;     // workgroups sharing the query (1: alone); this entry's place among them
+    uint32_t team, pad0;       // entries, and so most workgroups, of the query (1: no team)
     uint32_t team_rec, pad;    // the team's TeamRec (team > 1)
 };
 
 // Shared state of one team, zero at the start of a launch.  The first
-// member publishes its memo slot, which the whole team uses; the level's
-// list counts live here instead of in LDS.
+// workgroup that joins leads: it publishes its memo slot, which the whole team
+// uses, and closes the team when all have joined or some time has passed; the
+// level's list counts live here instead of in LDS.
 struct TeamRec {
+    uint32_t joined;                 // workgroups that have joined; kTeamClosed once no more may
+    uint32_t formed;                 // set by the leader: the team's workgroups, kTeamSpread if on several XCDs
     uint32_t arrive;                 // barrier arrivals so far
     uint32_t slot;                   // workgroup whose slot holds the memo and lists
     uint32_t error;                  // a barrier wait ran out of time
@@ -131,6 +134,7 @@ struct TeamRec {
     uint32_t count[24];              // connected sets per level k
     unsigned long long connected, ccp, evaluated;
 };
+constexpr uint32_t kTeamClosed = 1u << 31, kTeamSpread = 1u << 31;
 
 constexpr uint32_t kTeamSize = 8;     // largest team
 constexpr uint32_t kTeamMinRel = 17;  // only queries of at least this many relations may get a team

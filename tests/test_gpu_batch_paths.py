@@ -101,3 +101,20 @@ def test_dense_queries_time(cm):
     ws = mpdp.workspace(16, cm)
     one = statistics.median(mpdp.mpdp_optimize_ws(q, cm, ws).stats["ms_total"] for _ in range(9))
     assert kernel_ms([W.clique(16, i) for i in range(8)], cm) < 200.0 * one
+
+
+@pytest.mark.parametrize("flags", [0x200, 0x400, 0x600])  # (internal: largest teams, three workgroups, both)
+@pytest.mark.parametrize("cm", [COUT, PG])
+def test_teams_with_room_for_few_workgroups(cm, flags):
+    """A team goes on with the workgroups that have come after a while: with
+    three in all, the members that eight entries wait for never come (the launch
+    used to end in MPDP_EDEVICE after two seconds), and the entries that are
+    taken later are dropped."""
+    queries = [W.cycle_chords(70 + i, n=17 + i % 3, chords=i % 4) for i in range(9)] + [W.random_connected(17, 3, 0.4)]
+    queries += [star_around(17, 5, 1), W.star(18, 2), W.random_tree(18, 3), W.chain(6, 4), W.clique(9, 5)]
+    ws = mpdp.batch_workspace(queries)
+    want = mpdp.mpdp_optimize_batch(queries, cm, ws)
+    got = mpdp.mpdp_optimize_batch(queries, cm, ws, flags=flags)
+    assert got.costs == want.costs and got.plans == want.plans
+    for key in ("connected_sets", "ccp_pairs", "evaluated_pairs"):
+        assert got.stats[key] == want.stats[key]
