@@ -180,3 +180,55 @@ def test_dense_query_under_both_models():
         return sorted(mpdp.mpdp_optimize_ws(q, cm, ws).stats["ms_total"] for _ in range(5))[2]
 
     assert median_ms(mpdp.MPDP_COST_PGLIKE) < 1.8 * median_ms(mpdp.MPDP_COST_COUT)
+
+
+def triangles(k):
+    """k triangles strung along a path, one edge between neighbours."""
+    edges = []
+    for i in range(k):
+        c = 3 * i
+        edges += [[c, c + 1], [c + 1, c + 2], [c, c + 2]] + ([[c + 2, c + 3]] if i + 1 < k else [])
+    return 3 * k, edges
+
+
+def joined_cliques(sizes):
+    """Cliques in a row, neighbours sharing a relation."""
+    edges, at = [], 0
+    for s in sizes:
+        edges += [[at + i, at + j] for i in range(s) for j in range(i)]
+        at += s - 1
+    return at + 1, edges
+
+
+# from 19 relations on: smaller cyclic queries walk their subsets (up to 18)
+LARGER = [friendship(9), barbell(6, 9, 6), barbell(10, 0, 9), necklace(6), necklace(7), triangles(7),
+          joined_cliques((4, 5, 6, 7)), joined_cliques((3, 9, 3, 9)), necklace(8), barbell(7, 12, 7)]
+
+
+@pytest.mark.parametrize("cm", CMS)
+@pytest.mark.parametrize("n,edges", LARGER)
+def test_block_structures_of_larger_queries(n, edges, cm):
+    """The pair search and Alg. 3's counter on graphs of many blocks; the last two
+    with more than 24 relations."""
+    assert n > 18
+    q = W.from_edges(n, edges, n, f"blocks{n}")
+    res, gm = run_ws(q, cm)
+    ref = oracle.mpdp(q, cm)
+    check_memo(q, gm, ref)
+    check_plan(q, res, ref)
+    check_stats(q, res, ref, general=True)
+
+
+@pytest.mark.parametrize("cm", CMS)
+@pytest.mark.parametrize("q", [chain_and_clique(9, 12), chain_and_clique(12, 10), chain_and_clique(6, 13),
+                               chain_and_clique(8, 12, 1000.0, 0.001), W.cycle_chords(5, n=19, chords=8)],
+                         ids=lambda q: f"{q.name}-{q.card[0]:.0e}")
+def test_full_pools_and_shared_sets_of_larger_queries(q, cm):
+    """Sets of up to 8191 pairs, whose search states overflow a wave's pool, and
+    top levels whose few sets are shared between waves."""
+    assert q.n > 18
+    res, gm = run_ws(q, cm)
+    ref = oracle.mpdp(q, cm)
+    check_memo(q, gm, ref)
+    check_plan(q, res, ref)
+    check_stats(q, res, ref, general=True)
