@@ -454,11 +454,11 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 }
             } else if (Q.is_tree) {
                 if (k < n)
-                    expand_sets<true, false>(L, list, count, next, &counts[k + 1], w, nw, 1u, W.grow, sizeof(W.grow) / 4, ends, lane);
+                    expand_tree(L, list, count, next, &counts[k + 1], w, nw, W.grow, sizeof(W.grow) / 4, ends, lane);
                 eval_tree_list<CM>(L, ColexMemo{ranks, L.loff, false}, M, list, count, k, tree_group(count, 64u * nw), 64u * w + lane, 64u * nw);
             } else {
                 if (k < n)
-                    expand_sets<false, false>(L, list, count, next, &counts[k + 1], w, nw, expand_group(count, 64u * nw),
+                    expand_sets<false>(L, list, count, next, &counts[k + 1], w, nw, expand_group(count, 64u * nw),
                                        W.grow, sizeof(W.grow) / 4, ends, lane);
                 // sets per wave at a time, and waves per set, as in the per-level kernel
                 const uint32_t per = max(pair_sets(count, nw), min(count, kBatchPer));

@@ -582,6 +582,15 @@ __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M
 
 // ---------------------------------------------------------------- the next level's sets
 
+// The waves of a workgroup collect the sets that they find in LDS (`buf`, `cap`
+// words, 64 or more) and append them with one atomic on the list's end: some 30
+// ns each when all workgroups add to one word, an atomic per 64 sets or per wave
+// made that word the bound of the smaller levels.
+struct ExpandEnds {
+    uint32_t fill, end, start;  // words taken, first word not used, place in the list
+    uint32_t more;              // (expand_tree) a wave waits for room
+};
+
 // The connected sets of k + 1 relations from the `count` of k relations in
 // `list`: S + v for every neighbour v of S.  Such a set arises once per
 // relation whose removal leaves it connected; it is kept where v is the
@@ -589,44 +598,26 @@ __device__ void eval_pairs(const LdsGraph &L, const At &at_of, const MemoPtrs &M
 // lowest relation (which can always be removed), so that every set is listed
 // once.  One search per neighbour, against C(n, k + 1) subsets to unrank and
 // search; `group` lanes (a power of two) divide the neighbours of one set.
-// kTree: sets of a tree join in preorder numbers, for which the sets that
-// add a child numbered above every member are all there is to list (a set's
-// last relation in preorder has no child in it), without any search.
-// The waves of a workgroup collect their sets in LDS (`buf`, `cap` words, 64 or
-// more) and append them with one atomic on the list's end: some 30 ns each when
-// all workgroups add to one word, an atomic per 64 sets or per wave made that
-// word the bound of the smaller levels.  A wave that finds the buffer full
-// keeps its place and goes on once the workgroup has emptied it (straight to
-// the list from there on, an atomic per step, made a star of 25 around another
-// relation than 0 take 8.7 ms).  Starts and ends with the workgroup in step.
-struct ExpandEnds {
-    uint32_t fill, end, start;  // words taken, first word not used, place in the list
-    uint32_t more;              // a wave waits for room
-};
-
-template <bool kTree, bool kWide>
+// Sets that the workgroup's buffer has no room for go straight to the list,
+// an atomic per step.  Starts and ends with the workgroup in step.
+template <bool kWide>
 __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t count, uint32_t *out, uint32_t *out_count,
                             uint32_t w, uint32_t nw, uint32_t group, uint32_t *buf, uint32_t cap, ExpandEnds &ends,
                             uint32_t lane) {
     const unsigned long long below = (1ull << lane) - 1ull;
     const uint32_t each = 64u / group, sub = lane & (group - 1u);
-    uint32_t base = w * each, S = 0, N = 0;  // the wave's next sets; this lane's set and its neighbours still to add
     if (threadIdx.x == 0) ends = ExpandEnds{0u, cap, 0u, 0u};
     __syncthreads();
-    for (;;) {
-        for (;;) {
-            if (__ballot(N != 0u) == 0ull) {
-                if (base >= count) break;
-                const uint32_t i = base + lane / group;
-                base += nw * each;
-                S = i < count ? list[i] : 0u;
-                N = kTree ? nbrs_of<kWide>(L.pch, S) & ~(0xffffffffu >> __builtin_clz(S | 1u)) : nbrs_of<kWide>(L.nb, S) & ~S;
-                for (uint32_t j = 0; j < sub; ++j) N &= N - 1u;
-                continue;
-            }
+    for (uint32_t base = w * each; base < count; base += nw * each) {
+        const uint32_t i = base + lane / group;
+        const uint32_t S = i < count ? list[i] : 0u;
+        uint32_t N = nbrs_of<kWide>(L.nb, S) & ~S;
+        for (uint32_t j = 0; j < sub; ++j) N &= N - 1u;
+        while (__ballot(N != 0u) != 0ull) {
             const uint32_t v = lowbit(N), S1 = S | v;
-            bool keep = kTree && v != 0u;
-            if (!kTree && v != 0u) {
+            for (uint32_t j = 0; j < group; ++j) N &= N - 1u;
+            bool keep = false;
+            if (v != 0u) {
                 uint32_t seen = lowbit(S1), fr = seen;
                 while (seen != S1) {  // S1 is connected
                     fr = nbrs_of<kWide>(L.nb, fr) & S1 & ~seen;
@@ -636,20 +627,66 @@ __device__ void expand_sets(const LdsGraph &L, const uint32_t *list, uint32_t co
             }
             const unsigned long long m = __ballot(keep);
             const uint32_t add = (uint32_t)__popcll(m);
-            if (add != 0u) {
-                uint32_t at = 0;
-                if (lane == 0) at = atomicAdd(&ends.fill, add);
-                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-                if (at + add > cap) {  // full; so is it for whoever comes next
-                    if (lane == 0) {
-                        atomicMin(&ends.end, at);
-                        ends.more = 1u;
-                    }
-                    break;
-                }
+            if (add == 0u) continue;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&ends.fill, add);
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+            if (at + add <= cap) {
                 if (keep) buf[at + (uint32_t)__popcll(m & below)] = S1;
+            } else {  // the buffer is full: straight to the list
+                if (lane == 0) {
+                    atomicMin(&ends.end, at);
+                    at = atomicAdd(out_count, add);
+                }
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+                if (keep) out[at + (uint32_t)__popcll(m & below)] = S1;
             }
-            for (uint32_t j = 0; j < group; ++j) N &= N - 1u;
+        }
+    }
+    __syncthreads();
+    const uint32_t have = min(ends.fill, ends.end);
+    if (threadIdx.x == 0 && have != 0u) ends.start = atomicAdd(out_count, have);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < have; i += blockDim.x) out[ends.start + i] = buf[i];
+    __syncthreads();
+}
+
+// The same for a tree join's sets in preorder numbers, for which the sets that
+// add a child numbered above every member are all there is to list (a set's
+// last relation in preorder has no child in it), without any search.  A wave
+// that finds the buffer full keeps its place and goes on once the workgroup has
+// emptied it: finding sets is so quick here that their atomics bound the level
+// (straight to the list, a star of 25 around relation 12 took 8.7 ms).
+__device__ __forceinline__ void expand_tree(const LdsGraph &L, const uint32_t *list, uint32_t count, uint32_t *out,
+                                            uint32_t *out_count, uint32_t w, uint32_t nw, uint32_t *buf, uint32_t cap,
+                                            ExpandEnds &ends, uint32_t lane) {
+    const unsigned long long below = (1ull << lane) - 1ull;
+    uint32_t base = w * 64u, S = 0, N = 0;  // the wave's next sets; this lane's set and its children still to add
+    if (threadIdx.x == 0) ends = ExpandEnds{0u, cap, 0u, 0u};
+    __syncthreads();
+    for (;;) {
+        for (;;) {
+            const unsigned long long m = __ballot(N != 0u);
+            if (m == 0ull) {
+                if (base >= count) break;
+                S = base + lane < count ? list[base + lane] : 0u;
+                N = nbrs(L.pch, S) & ~(0xffffffffu >> __builtin_clz(S | 1u));
+                base += nw * 64u;
+                continue;
+            }
+            const uint32_t add = (uint32_t)__popcll(m);
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&ends.fill, add);
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+            if (at + add > cap) {  // full; so is it for whoever comes next
+                if (lane == 0) {
+                    atomicMin(&ends.end, at);
+                    ends.more = 1u;
+                }
+                break;
+            }
+            if (N) buf[at + (uint32_t)__popcll(m & below)] = S | lowbit(N);
+            N &= N - 1u;
         }
         __syncthreads();
         const uint32_t have = min(ends.fill, ends.end), more = ends.more;

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
     if (threadIdx.x < 2) sums[threadIdx.x] = 0ull;
     __syncthreads();
     if (k < n)
-        expand_sets<false, kWide>(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, reinterpret_cast<uint32_t *>(buf),
+        expand_sets<kWide>(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, reinterpret_cast<uint32_t *>(buf),
                     sizeof(buf) / 4, ends, lane);
     unsigned long long ccp = 0, evaluated = 0;
     const ColexMemo at{ranks, L.loff, kWide};
@@ -107,8 +107,8 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_level(const DevGraph *g, ui
                            (wave * eval + blockIdx.x) * 64u + lane, threads);
     } else {
         const uint32_t blocks = gridDim.x - eval, threads = blocks * kTreeBlock;
-        expand_sets<true, true>(L, list, count, next, &cnt->level_count[k + 1], wave * blocks + blockIdx.x - eval,
-                          threads / 64, 1u, ranks, kTreeExpand, ends, lane);
+        expand_tree(L, list, count, next, &cnt->level_count[k + 1], wave * blocks + blockIdx.x - eval, threads / 64,
+                    ranks, kTreeExpand, ends, lane);
     }
 }
 
@@ -159,8 +159,8 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
                 list[i] = (colex_unrank(L.binom, (int)n - 1, (int)k - 1, i) << 1) | 1u;
             __syncthreads();
         } else if (k < n) {
-            expand_sets<true, true>(L, list, count, (k & 1u) ? even : odd, &counts[k + 1], t >> 6, kSpanBlock / 64, 1u,
-                                    buf, kSpanExpand, ends, t & 63u);
+            expand_tree(L, list, count, (k & 1u) ? even : odd, &counts[k + 1], t >> 6, kSpanBlock / 64, buf, kSpanExpand,
+                        ends, t & 63u);
             if (t == 0) cnt->level_count[k + 1] = counts[k + 1];
         }
         eval_tree_list<CM>(L, ColexMemo{ranks, L.loff, n > 24u}, M, list, count, k, tree_group(count, kSpanBlock), t, kSpanBlock);
