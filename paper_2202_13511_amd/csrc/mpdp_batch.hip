@@ -465,7 +465,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(4, 
                 const bool heavy = (1u << k) / 16u >= ((Q.sched >> kSchedHeavyShift) & 0xffffu);
                 const uint32_t parts = heavy && 2u * count <= nw ? nw / count : 1u;
                 if (walk)
-                    eval_subsets<CM>(L, M, list, count, k, w, nw, pair_sets(count, nw), parts, W.pairs[wave].p0, pp, lane,
+                    eval_subsets<CM>(L, BitMemo{}, M, list, count, k, w, nw, pair_sets(count, nw), parts, W.pairs[wave].p0, pp, lane,
                                      my_ccp, my_eval);
                 else
                     eval_pairs<CM, false, false>(L, BitMemo{}, M, list, count, k, w, nw, per, parts, W.pairs[wave], pp, lane, my_ccp,

@@ -313,10 +313,10 @@ constexpr size_t kGraphCacheSize = 32;  // recorded graphs kept per thread
 struct GraphKey {
     void *ws, *pin;
     uint32_t n, cost_model;
-    bool general, dense;  // the level kernels recorded depend on them
+    bool general, dense, walk;  // the level kernels recorded depend on them
     bool operator==(const GraphKey &o) const {
         return ws == o.ws && pin == o.pin && n == o.n && cost_model == o.cost_model && general == o.general &&
-               dense == o.dense;
+               dense == o.dense && walk == o.walk;
     }
 };
 
@@ -469,6 +469,51 @@ bool many_sets(const Query &q) {
     return q.cost_model == MPDP_COST_COUT ? pairs > 2.0 * subsets + 25e6 : pairs > subsets + 12e6;
 }
 
+// True if about `want` of 96 candidates of a query (disjoint pairs of relation
+// sets) or more are csg-cmp pairs: random ones, the same for all queries, of
+// which `want` pairs decide, and none among the first 32.  Graphs with so many
+// have nearly two edges a relation (all relations on two hubs have 2 n - 4);
+// most others end there.
+bool many_pairs(uint32_t n, uint32_t m, const uint32_t *adj, uint32_t want) {
+    if (!mpdp::many_edges(n, m)) return false;
+    constexpr uint32_t kTries = 96;
+    struct Tries {
+        uint32_t a[kTries], b[kTries];
+    };
+    static const Tries tries = [] {
+        Tries t{};
+        uint64_t state = 0x9e3779b97f4a7c15ull;
+        for (uint32_t i = 0; i < kTries; ++i)
+            for (uint32_t v = 0; v < 32; ++v) {  // each relation in one, in the other or in neither
+                state = state * 6364136223846793005ull + 1442695040888963407ull;
+                const uint32_t third = (uint32_t)(((state >> 32) * 3u) >> 32);
+                t.a[i] |= third == 0 ? 1u << v : 0u;
+                t.b[i] |= third == 1 ? 1u << v : 0u;
+            }
+        return t;
+    }();
+    const auto neighbours = [&](uint32_t S) {
+        uint32_t nb = 0;
+        for (uint32_t T = S; T; T &= T - 1) nb |= adj[__builtin_ctz(T)];
+        return nb;
+    };
+    const auto connected = [&](uint32_t S) {
+        uint32_t seen = S & (0u - S), fr = seen;
+        while (fr) {
+            fr = neighbours(fr) & S & ~seen;
+            seen |= fr;
+        }
+        return S != 0u && seen == S;
+    };
+    const uint32_t full = (n == 32) ? ~0u : (1u << n) - 1u;
+    uint32_t pairs = 0;
+    for (uint32_t i = 0; i < kTries && pairs < want && (i < 32 || pairs > 0); ++i) {
+        const uint32_t A = tries.a[i] & full, B = tries.b[i] & full;
+        if (connected(A) && connected(B) && (neighbours(A) & B)) ++pairs;
+    }
+    return pairs >= want;
+}
+
 // One exact optimization in the workspace d_ws on stream s.  With
 // no_alloc, nothing is allocated on the host or the device: the query
 // information goes up and the plan comes back through pageable memory (the
@@ -536,6 +581,12 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     std::vector<char> down_pageable((pin || no_alloc) ? 0 : down_bytes);
     char *down = pin ? pin : (no_alloc ? down_stack : down_pageable.data());
     const bool bits = general && !dpsub && n <= mpdp::kBitsMaxRel;
+    // dense queries walk their sets' subsets, from two fifths of them pairs on
+    // (ms, searched / walked, and that share; PG-like behind the stroke: two hubs
+    // of 20 relations 67 / 100, 75 / 120, 0.22; three of 18 32 / 28, 36 / 34, 0.45;
+    // random graph of 20 3.7 / 6.8, 0.2; cliques of 19 4.4 / 3.0, 5.0 / 4.4, of 22
+    // 239 / 113, 258 / 178)
+    const bool walk = general && !dpsub && !bits && n <= mpdp::kWalkMaxRel && many_pairs(n, q.m, q.g.lds.adj, 38);
     const size_t N = size_t(1) << n;
     char *const bat = base + L.bits;
     const bool cout_model = q.cost_model == MPDP_COST_COUT;
@@ -591,6 +642,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
             return e == hipSuccess ? finish(nullptr) : e;
         }
         const bool counted = general && !dpsub;  // per workgroup
+        if (e == hipSuccess && walk) e = mpdp::launch_no_plans(memo, n, st);
         if (e == hipSuccess)
             e = mpdp::launch_init(src, dg, n, memo, counted && !bits ? list : nullptr, counted ? arrived : nullptr, tally,
                                   false, cnt, st);
@@ -603,6 +655,9 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
             if (e != hipSuccess) break;
             if (bits)
                 e = mpdp::launch_bits_level(dg, q.cost_model, n, k, nc, cnt, space, memo, parts, arrived, tally, st);
+            else if (walk)
+                e = mpdp::launch_level_walk(dg, q.cost_model, n, k, (k & 1u) ? heavy : list, (k & 1u) ? list : heavy, cnt,
+                                            memo, parts, arrived, tally, st);
             else if (counted)  // lists of connected sets: odd levels in one buffer, even ones in the other
                 e = mpdp::launch_level_pairs(dg, q.cost_model, n, q.m, k, (k & 1u) ? heavy : list,
                                              (k & 1u) ? list : heavy, cnt, memo, parts, arrived, tally, st);
@@ -625,7 +680,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
         // buffer and shape (its first kernel reads the staging buffer)
         hipGraphExec_t exec = nullptr;
         HIPCHK(cached_graph(GraphKey{d_ws, pin, n, (uint32_t)q.cost_model, general,
-                                     mpdp::many_edges(n, q.m)}, enqueue, exec));
+                                     mpdp::many_edges(n, q.m), walk}, enqueue, exec));
         HIPCHK(hipGraphLaunch(exec, s));
     } else {
         HIPCHK(enqueue(s));
@@ -790,52 +845,6 @@ mpdp_status check_batch_args(uint32_t nq, const mpdp_batch_query *queries, const
     return MPDP_OK;
 }
 
-// True if a fifth or more of a query's candidates (its disjoint pairs of
-// relation sets), a tenth from 18 relations on, are csg-cmp pairs: from 96
-// random ones, the same for all queries, of which 20 (10) pairs decide, and none
-// among the first 32.  Graphs with so many have nearly two edges a relation (all
-// relations on two hubs have 2 n - 4); most others end there.
-bool many_pairs(uint32_t n, uint32_t m, const uint32_t *adj) {
-    if (n < 15 || !mpdp::many_edges(n, m)) return false;
-    constexpr uint32_t kTries = 96;
-    struct Tries {
-        uint32_t a[kTries], b[kTries];
-    };
-    static const Tries tries = [] {
-        Tries t{};
-        uint64_t state = 0x9e3779b97f4a7c15ull;
-        for (uint32_t i = 0; i < kTries; ++i)
-            for (uint32_t v = 0; v < 32; ++v) {  // each relation in one, in the other or in neither
-                state = state * 6364136223846793005ull + 1442695040888963407ull;
-                const uint32_t third = (uint32_t)(((state >> 32) * 3u) >> 32);
-                t.a[i] |= third == 0 ? 1u << v : 0u;
-                t.b[i] |= third == 1 ? 1u << v : 0u;
-            }
-        return t;
-    }();
-    const auto neighbours = [&](uint32_t S) {
-        uint32_t nb = 0;
-        for (uint32_t T = S; T; T &= T - 1) nb |= adj[__builtin_ctz(T)];
-        return nb;
-    };
-    const auto connected = [&](uint32_t S) {
-        uint32_t seen = S & (0u - S), fr = seen;
-        while (fr) {
-            fr = neighbours(fr) & S & ~seen;
-            seen |= fr;
-        }
-        return S != 0u && seen == S;
-    };
-    const uint32_t full = (n == 32) ? ~0u : (1u << n) - 1u;
-    const uint32_t want = n >= 18 ? 10 : 20;
-    uint32_t pairs = 0;
-    for (uint32_t i = 0; i < kTries && pairs < want && (i < 32 || pairs > 0); ++i) {
-        const uint32_t A = tries.a[i] & full, B = tries.b[i] & full;
-        if (connected(A) && connected(B) && (neighbours(A) & B)) ++pairs;
-    }
-    return pairs >= want;
-}
-
 // Predicted device time (ms) of a query alone on one workgroup of the
 // batched kernel, for scheduling only.  A tree query's time is close to
 // linear in its pairs (the connected sets, weighted by their size less one:
@@ -857,7 +866,8 @@ bool many_pairs(uint32_t n, uint32_t m, const uint32_t *adj) {
 // thousands; 600 stars of 14 (53, 16) 434 / 434, PG-like 520 / 552, of 16 (246,
 // 66) 1243 / 1075, of 18 (1114, 262) 6843 / 3613; 500 double stars of 7 and 7
 // leaves (131, 66) 645 / 687, PG-like 935 / 846; 1000 random trees of 10-20 1133
-// / 2846).  Walking subset by subset where many of them are pairs (kernel, ms,
+// / 2846).  Walking subset by subset where a fifth of them, a tenth from 18
+// relations on, are pairs (kernel, ms,
 // searched / walked, and the share of pairs; graphs with random edges, PG-like
 // behind the stroke; 100 of 16 14.0 / 11.6, 14.8 / 19.1, 0.018, 105 / 19.9, 112 /
 // 40, 0.27; 200 of 17 from a tenth on 37 / 45, 42 / 52, from a fifth on 37 / 34,
@@ -911,7 +921,7 @@ double predicted_ms(const mpdp_batch_query &Q, const mpdp_edge *edges, uint32_t 
         }
         return 1e-3 * (star ? 5.1 + 3.2 * n + 0.86e-3 * pairs : 10.0 + 5.0 * n + 2.7e-3 * pairs);
     }
-    if (many_pairs(n, Q.m, adj)) {
+    if (n >= 15 && many_pairs(n, Q.m, adj, n >= 18 ? 10 : 20)) {
         how = mpdp::kSchedWalk;
         return 0.5e-6 * std::pow(3.0, (double)n);
     }

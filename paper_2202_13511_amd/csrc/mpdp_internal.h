@@ -231,6 +231,13 @@ inline bool many_edges(uint32_t n, uint32_t m) { return m + 4 >= 2 * n; }
 hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t m, uint32_t k, const uint32_t *list,
                               uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
                               unsigned long long *tally, hipStream_t s);
+// The same for dense queries of up to kWalkMaxRel relations, subset by subset,
+// after launch_no_plans (before launch_init).
+constexpr uint32_t kWalkMaxRel = 24;
+hipError_t launch_no_plans(MemoPtrs memo, uint32_t n, hipStream_t s);
+hipError_t launch_level_walk(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,
+                             uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
+                             unsigned long long *tally, hipStream_t s);
 hipError_t launch_filter(const DevGraph *g, uint32_t k, uint64_t ncand, uint32_t *list, Counters *cnt,
                          hipStream_t s);
 constexpr uint32_t kAblateDpsub = 1u;

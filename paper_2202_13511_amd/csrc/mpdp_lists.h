@@ -808,16 +808,15 @@ __device__ __forceinline__ bool meet_parts(const PairParts &pp, uint32_t set, ui
 
 // The csg-cmp pairs of the sets list[0 .. count) where most subsets are
 // connected: every subset that holds the set's lowest relation, A = lowest +
-// x, and the rest of the set.  The memo is the kernel's own, indexed by the
-// set, with a cost below zero where there is no plan, so that the two gathers
-// that a pair's cost takes are its test as well; neighbouring lanes take
-// neighbouring subsets.  Up to six relations 2^(k-1) lanes take a set, from
-// seven on a wave does, or `parts` waves.  PG-like reads the cards of pairs
-// whose costs leave them a chance (see pass_pair).  Bound by the gathers; the
-// search (eval_pairs) takes a chain of dependent steps for each pair, here
-// the next subset waits for nothing.
-template <int CM>
-__device__ void eval_subsets(const LdsGraph &L, const MemoPtrs &M, const uint32_t *list, uint32_t count, uint32_t k,
+// x, and the rest of the set.  The memo holds a cost below zero where there is
+// no plan, so that the two gathers that a pair's cost takes are its test as
+// well; neighbouring lanes take neighbouring subsets.  Up to six relations
+// 2^(k-1) lanes take a set, from seven on a wave does, or `parts` waves.
+// PG-like reads the cards of pairs whose costs leave them a chance (see
+// pass_pair).  Bound by the gathers; the search (eval_pairs) takes a chain of
+// dependent steps for each pair, here the next subset waits for nothing.
+template <int CM, class At>
+__device__ void eval_subsets(const LdsGraph &L, const At &at_of, const MemoPtrs &M, const uint32_t *list, uint32_t count, uint32_t k,
                              uint32_t w, uint32_t nw, uint32_t per, uint32_t parts, uint32_t *todo, PairParts pp,
                              uint32_t lane, unsigned long long &ccp, unsigned long long &evaluated) {
     // subsets of a lane in flight (PG-like, four cost the batched kernel
@@ -846,14 +845,18 @@ __device__ void eval_subsets(const LdsGraph &L, const MemoPtrs &M, const uint32_
             SetBest best{__builtin_inf(), ~0u, ~0u};
             for (uint32_t r = 0; r < rounds; r += kEach) {
                 uint32_t A[kEach];
+                uint64_t ia[kEach], ib[kEach];
                 double cA[kEach], cB[kEach];
 #pragma unroll
                 for (int u = 0; u < kEach; ++u) {
                     const bool in = r + (uint32_t)u < rounds && x != rest;
                     A[u] = in ? lo | x : 0u;  // (the empty set has no plan)
                     x = ((x | ~rest) + step) & rest;  // (the masked add carries through the holes)
-                    cA[u] = M.cost[A[u]];
-                    cB[u] = M.cost[in ? S ^ A[u] : 0u];
+                    const uint32_t ka = (uint32_t)popc32(A[u]);
+                    ia[u] = in ? at_of(A[u], ka) : 0ull;
+                    ib[u] = in ? at_of(S ^ A[u], k - ka) : 0ull;
+                    cA[u] = M.cost[ia[u]];
+                    cB[u] = M.cost[ib[u]];
                 }
 #pragma unroll
                 for (int u = 0; u < kEach; ++u) {
@@ -866,14 +869,15 @@ __device__ void eval_subsets(const LdsGraph &L, const MemoPtrs &M, const uint32_
                         o.c = on ? o.c : __builtin_inf();
                         take_best(best, o);
                     } else if (on && (cA[u] + cB[u]) + 0.01 * cS <= best.c) {
-                        take_best(best, pair_best<CM>(A[u], B, cA[u], cB[u], M.card[A[u]], M.card[B], cS));
+                        take_best(best, pair_best<CM>(A[u], B, cA[u], cB[u], M.card[ia[u]], M.card[ib[u]], cS));
                     }
                 }
             }
             group_best(best, P);
             bool store = S != 0u && sub == 0u;
             if (parts > 1u) store = meet_parts(pp, s0, part, parts, best, lane);
-            if (store) store_best(M, S, Key{(unsigned long long)__double_as_longlong(best.c), best.l, best.op}, cS);
+            if (store)
+                store_best(M, at_of(S, k), Key{(unsigned long long)__double_as_longlong(best.c), best.l, best.op}, cS);
         }
     }
 }

@@ -84,6 +84,58 @@ __global__ __launch_bounds__(kPairBlock) void k_level_pairs(const DevGraph *g, u
     if (threadIdx.x < 2) tally[2 * blockIdx.x + threadIdx.x] += sums[threadIdx.x];
 }
 
+// Dense queries of up to 24 relations: no plan yet for any set.
+__global__ __launch_bounds__(256) void k_no_plans(double *cost, uint64_t sets) {
+    double2 *c = reinterpret_cast<double2 *>(cost);
+    for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < sets / 2; i += gridDim.x * 256ull) c[i] = make_double2(-1.0, -1.0);
+}
+
+// One level of them: the next level's list, then every set's subsets.  Two
+// workgroups of 16 waves per CU (their rank tables and queries fill its LDS).
+// Bound by the gathers past the L2 and the eight table lookups of a candidate's
+// two ranks: a clique of 22 takes 113 ms, 138 G pairs a second (searched 239, and
+// 222 when each block's subsets were walked).
+constexpr int kWalkBlock = 1024;
+constexpr uint32_t kWalkGrid = 512;
+template <int CM>
+__global__ __launch_bounds__(kWalkBlock) void k_level_walk(const DevGraph *g, uint32_t n, uint32_t k,
+                                                           const uint32_t *list, uint32_t *next, Counters *cnt,
+                                                           MemoPtrs M, HeavyPart *rec, uint32_t *arrived,
+                                                           unsigned long long *tally) {
+    __shared__ __align__(16) unsigned char image[kListLdsBytes];
+    __shared__ __align__(16) uint32_t ranks[kRankWords24];
+    __shared__ __align__(16) uint32_t todo[kWalkBlock / 64][64 * 12];  // (block_candidates: 24 relations, 12 pieces)
+    __shared__ ExpandEnds ends;
+    __shared__ unsigned long long sums[2];
+    const uint32_t count = cnt->level_count[k];
+    const uint32_t nw = gridDim.x * (kWalkBlock / 64);
+    const uint32_t per = pair_sets(count, nw), group = expand_group(count, 64u * nw);
+    const uint32_t most = min(nw, kPairWaves), parts = k >= kShareMinK && 2u * count <= most ? min(64u, most / count) : 1u;
+    const uint32_t lane = threadIdx.x & 63u, w = (threadIdx.x >> 6) * gridDim.x + blockIdx.x;
+    const uint32_t items = parts > 1u ? count * parts : (count + per - 1u) / per;
+    if (blockIdx.x >= items && blockIdx.x * (64u / group) >= count) return;  // the whole workgroup
+    LdsGraph &L = *reinterpret_cast<LdsGraph *>(image);
+    stage_graph_prefix(g, L, kListLdsBytes);
+    stage_ranks(ranks, 24u);
+    if (threadIdx.x < 2) sums[threadIdx.x] = 0ull;
+    __syncthreads();
+    if (k < n)
+        expand_sets<false>(L, list, count, next, &cnt->level_count[k + 1], w, nw, group, &todo[0][0], sizeof(todo) / 4, ends, lane);
+    unsigned long long ccp = 0, evaluated = 0;
+    eval_subsets<CM>(L, ColexMemo{ranks, L.loff, false}, M, list, count, k, w, nw, per, parts, todo[threadIdx.x >> 6],
+                     PairParts{rec, arrived}, lane, ccp, evaluated);
+    for (int off = 32; off >= 1; off >>= 1) {
+        ccp += (unsigned long long)__shfl_xor((long long)ccp, off);
+        evaluated += (unsigned long long)__shfl_xor((long long)evaluated, off);
+    }
+    if (lane == 0) {
+        atomicAdd(&sums[0], ccp);
+        atomicAdd(&sums[1], evaluated);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) atomicAdd(&tally[2u * (blockIdx.x % kPairGrid) + threadIdx.x], sums[threadIdx.x]);
+}
+
 // One level of a tree join: the first `eval` workgroups cost the level's
 // sets, the others grow the next level's list, so that neither waits for the
 // other's reads.
@@ -183,6 +235,22 @@ hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uin
         n > 24 ? go(k_level_pairs<MPDP_COST_PGLIKE, true, true>) : go(k_level_pairs<MPDP_COST_PGLIKE, false, true>);
     else
         go(k_level_pairs<MPDP_COST_PGLIKE, false, false>);
+    return hipGetLastError();
+}
+
+hipError_t launch_no_plans(MemoPtrs memo, uint32_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_no_plans, dim3(1024), dim3(256), 0, s, memo.cost, 1ull << n);
+    return hipGetLastError();
+}
+
+hipError_t launch_level_walk(const DevGraph *g, int cost_model, uint32_t n, uint32_t k, const uint32_t *list,
+                             uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
+                             unsigned long long *tally, hipStream_t s) {
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(kWalkGrid), dim3(kWalkBlock), 0, s, g, n, k, list, next, cnt, memo, rec, arrived,
+                           tally);
+    };
+    cost_model == MPDP_COST_COUT ? go(k_level_walk<MPDP_COST_COUT>) : go(k_level_walk<MPDP_COST_PGLIKE>);
     return hipGetLastError();
 }
 

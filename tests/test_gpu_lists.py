@@ -232,3 +232,40 @@ def test_full_pools_and_shared_sets_of_larger_queries(q, cm):
     check_memo(q, gm, ref)
     check_plan(q, res, ref)
     check_stats(q, res, ref, general=True)
+
+
+def with_stats(q, card, sel):
+    q.card[:] = card
+    q.sel[:] = sel
+    return q
+
+
+@pytest.mark.parametrize("cm", CMS)
+@pytest.mark.parametrize("q", [W.clique(19, 1), W.clique(21, 2), W.random_connected(20, 4, 0.9), W.random_connected(19, 3, 0.4),
+                               with_stats(W.random_connected(19, 3, 0.4), 1000.0, 0.001),
+                               with_stats(W.clique(20, 5), 1e308, 1.0)], ids=lambda q: f"{q.name}-{q.card[0]:.0e}")
+def test_dense_queries_against_dpsub(q, cm):
+    """Dense queries walk their sets' subsets.  The oracle takes minutes here: Alg.
+    1's kernels, which are compared with it on smaller queries and share no
+    level code, leave the same memo; ties and infinite costs among them."""
+    res, gm = run_ws(q, cm)
+    ref, rm = run_ws(q, cm, flags=mpdp.MPDP_FLAG_ABLATE_DPSUB)
+    planned = gm["cost"] >= 0
+    planned[0] = False
+    assert planned.sum() == ref.stats["connected_sets"] + q.n
+    for name in ("cost", "card", "left", "op"):
+        assert np.array_equal(gm[name][planned], rm[name][planned]), name
+    assert res.plan == ref.plan and res.cost == ref.cost
+    for key in ("connected_sets", "ccp_pairs"):
+        assert res.stats[key] == ref.stats[key]
+
+
+def test_dense_query_time():
+    """A clique of 22 took 222 ms while each block's subsets were walked, 239 with
+    a search for each pair, next to a clique of 19 in 7.3 and 4.4: 31 and 54
+    times as long; 113 and 3.0 ms (38 times)."""
+    def median_ms(n):
+        q, ws = W.clique(n, 1), mpdp.workspace(n, mpdp.MPDP_COST_COUT)
+        return sorted(mpdp.mpdp_optimize_ws(q, mpdp.MPDP_COST_COUT, ws).stats["ms_total"] for _ in range(3))[1]
+
+    assert median_ms(22) < 47.0 * median_ms(19)
