@@ -1,8 +1,8 @@
 // Device-side building blocks of the MPDP kernels (shared by the per-level
 // kernels in mpdp_kernels.hip and the batched kernel in mpdp_batch.hip).
 // Bitmap set algebra, grow, colex ranks, card(S), the plan key, the Alg. 2
-// pair evaluation of one set and the Alg. 3 block analysis and candidate
-// loop.  Internal; every function is inlined into its kernels.
+// pair evaluation of one set, DPSUB's candidate loop and the plan walk.
+// Internal; every function is inlined into its kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -1,7 +1,7 @@
-// Host side of the C-ABI in include/mpdp.h: input validation, the query
-// information upload, the level loop of Alg. 5 (unrank+filter, evaluate per
-// level, all enqueued on one stream with no host round trip between levels)
-// and the plan readback.
+// Host side of the C-ABI in include/mpdp.h: input validation, the choice of a
+// query's path (one launch, bitmap, lists, subsets, unranked levels), the level
+// loop of Alg. 5 (all levels enqueued on one stream with no host round trip
+// between them) and the plan readback.
 #include <hip/hip_runtime.h>
 
 #include <chrono>
@@ -774,7 +774,7 @@ bool batch_layout(uint32_t nq, const mpdp_batch_query *qs, BatchLayout &B) {
     B.plans = o;    o = align_up(o + sizeof(mpdp_plan_node) * B.sum_nodes);
     B.out = o;      o = align_up(o + sizeof(mpdp::BatchOut) * nq);
     const uint64_t N = 1ull << maxn;
-    B.slot_bytes = align_up(21 * N) + align_up(12 * binom64(maxn, maxn / 2));  // memo, two set lists, heavy list
+    B.slot_bytes = align_up(21 * N) + align_up(12 * binom64(maxn, maxn / 2));  // memo, two set lists, a team's parts
     B.slots = o;    o += B.slot_bytes * B.workgroups;
     B.total = align_up(o);
     return true;

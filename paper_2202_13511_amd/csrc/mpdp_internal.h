@@ -201,7 +201,10 @@ struct HeavyPart;
 // launch_bits_level a level.  sets: C(n, k), the most the level can have.
 // At 18 relations, C_out, a clique takes 1074 us here and 1742 with lists and
 // pair search, a cycle with 4 chords 331 and 530; each relation more triples
-// the candidates.
+// the candidates.  At 19 (limit 19 against 18) this path still takes 330 us
+// for a bare cycle against 414, but 1080 against 628 with 8 chords, 1870
+// against 525 for a star with one edge more, and 3869 for a clique against
+// the subset walk's 2841.
 constexpr uint32_t kBitsMaxRel = 18;
 struct BitsSpace {
     uint32_t *conn;       // bit S: S is connected

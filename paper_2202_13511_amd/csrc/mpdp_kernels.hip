@@ -402,7 +402,7 @@ hipError_t launch_level_tree(const DevGraph *g, int cost_model, uint32_t n, uint
     uint64_t blocks = (ncand + (uint64_t)kBlock * chunk - 1) / ((uint64_t)kBlock * chunk);
     const uint32_t cap = cost_model == MPDP_COST_COUT ? kPersistGridCout : kPersistGrid;
     const uint32_t grid = (uint32_t)(blocks < 1 ? 1 : (blocks > cap ? cap : blocks));
-    // without compaction (the ablation; other levels come here for stars alone)
+    // (a compacted level of a star went to k_level_flat above)
 #define MPDP_LEVEL_TREE(CMV, CH)                                                                        \
     do {                                                                                                \
         if (compact)                                                                                    \

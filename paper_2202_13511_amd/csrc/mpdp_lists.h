@@ -2,8 +2,9 @@
 // this one's (expand_sets), and a set's csg-cmp pairs are enumerated
 // directly (eval_pairs: one search step per pair, whatever the block
 // structure of the set), instead of unranking every k-subset and testing
-// every subset of every block.  Shared by the per-level kernels and the
-// batched kernel.  Internal; every function is inlined into its kernels.
+// every subset of every block; where most subsets are connected, by a walk
+// over the set's subsets (eval_subsets).  Shared by the per-level kernels and
+// the batched kernel.  Internal; every function is inlined into its kernels.
 #pragma once
 
 #include "mpdp_device.h"

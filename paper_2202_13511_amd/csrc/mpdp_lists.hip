@@ -1,6 +1,6 @@
-// The levels of the block-based path as lists of connected sets (see
-// mpdp_lists.h): one launch per level evaluates the level's sets and grows
-// the next level's list.
+// Levels as lists of connected sets (see mpdp_lists.h), of cyclic queries from
+// 19 relations on and of tree joins: one launch per level evaluates the level's
+// sets and grows the next level's list.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
