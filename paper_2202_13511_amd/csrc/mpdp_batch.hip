@@ -10,14 +10,15 @@
 // the others search their csg-cmp pairs or, in dense graphs, walk the subsets
 // of their sets; of a star around relation 0 every set of relation 0 and
 // others is connected, so it needs no lists, and trees of many connected sets
-// are unranked.  Memo and
-// scratch live in a per-workgroup slot that is reused from query to query,
-// so the workspace does not grow with the batch.  A large query may be
-// taken by a team of workgroups (consecutive queue entries): they split the
-// sets of every level and meet at barriers, in the slot of the team's first
-// member.  Entries are taken in queue order within their share, so of each
-// share at most one team waits for members, and those come: every workgroup
-// that does not wait takes entries, of all shares in the end.
+// are unranked.  Memo and scratch live in a per-workgroup slot that is reused
+// from query to query, so the workspace does not grow with the batch.  A large
+// query may be taken by a team of workgroups (consecutive queue entries): they
+// split the sets of every level and meet at barriers, in the slot of the team's
+// first member.  Entries are taken in queue order within their share, so of
+// each share at most one team waits for members, for kTeamFormTicks at most:
+// those that have come by then are the team, and a workgroup that takes an entry
+// of it later passes it by.  So a launch ends however few of its workgroups the
+// device runs at a time.
 #include <hip/hip_runtime.h>
 
 #include "mpdp_device.h"
