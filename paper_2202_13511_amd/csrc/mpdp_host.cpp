@@ -1536,10 +1536,9 @@ size_t mpdp_workspace_bytes(uint32_t n, mpdp_cost_model cost_model) {
     (void)cost_model;
     if (n == 0 || n > 32) return 0;
     // a workspace serves every smaller query as well, also where the smaller
-    // one needs more (the bitmap path's arrays end at kBitsMaxRel relations)
-    size_t most = 0;
-    for (uint32_t j = 1; j <= n; ++j) most = std::max(most, make_layout(j).total);
-    return most;
+    // one needs more: the bitmap path's arrays end at kBitsMaxRel relations, and
+    // nothing else shrinks
+    return std::max(make_layout(n).total, make_layout(std::min(n, mpdp::kBitsMaxRel)).total);
 }
 
 mpdp_status mpdp_memo_layout(uint32_t n, size_t *off_cost, size_t *off_card, size_t *off_left, size_t *off_op) {
