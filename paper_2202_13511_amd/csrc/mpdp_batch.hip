@@ -167,7 +167,7 @@ union BatchScratch {
     struct {
         uint32_t set[kBW][tree_ring(4, 1)], bsum[kBW][tree_ring(4, 1)];
     } ring;
-    uint32_t grow[sizeof(BatchBuf) * kBW / 4];  // expand_sets
+    uint32_t grow[sizeof(BatchBuf) * kBW / 4];  // expand_sets, expand_tree
     PlanScratch plan;
 };
 
