@@ -313,10 +313,10 @@ constexpr size_t kGraphCacheSize = 32;  // recorded graphs kept per thread
 struct GraphKey {
     void *ws, *pin;
     uint32_t n, cost_model;
-    bool general, dense, walk;  // the level kernels recorded depend on them
+    bool general, lazy, walk;  // the level kernels recorded depend on them
     bool operator==(const GraphKey &o) const {
         return ws == o.ws && pin == o.pin && n == o.n && cost_model == o.cost_model && general == o.general &&
-               dense == o.dense && walk == o.walk;
+               lazy == o.lazy && walk == o.walk;
     }
 };
 
@@ -587,6 +587,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
     // random graph of 20 3.7 / 6.8, 0.2; cliques of 19 4.4 / 3.0, 5.0 / 4.4, of 22
     // 239 / 113, 258 / 178)
     const bool walk = general && !dpsub && !bits && n <= mpdp::kWalkMaxRel && many_pairs(n, q.m, q.g.lds.adj, 38);
+    const bool lazy = general && q.cost_model == MPDP_COST_PGLIKE && mpdp::lazy_query(n, q.m, q.g.lds.adj);
     const size_t N = size_t(1) << n;
     char *const bat = base + L.bits;
     const bool cout_model = q.cost_model == MPDP_COST_COUT;
@@ -659,7 +660,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
                 e = mpdp::launch_level_walk(dg, q.cost_model, n, k, (k & 1u) ? heavy : list, (k & 1u) ? list : heavy, cnt,
                                             memo, parts, arrived, tally, st);
             else if (counted)  // lists of connected sets: odd levels in one buffer, even ones in the other
-                e = mpdp::launch_level_pairs(dg, q.cost_model, n, q.m, k, (k & 1u) ? heavy : list,
+                e = mpdp::launch_level_pairs(dg, q.cost_model, lazy, n, k, (k & 1u) ? heavy : list,
                                              (k & 1u) ? list : heavy, cnt, memo, parts, arrived, tally, st);
             else if (dpsub)
                 e = mpdp::launch_eval_general(dg, q.cost_model, k, nc, list, heavy, cnt, memo, parts, st);
@@ -679,8 +680,7 @@ mpdp_status run(const Query &q, void *d_ws, size_t ws_bytes, hipStream_t s, uint
         // replay the sequence recorded once for this workspace, staging
         // buffer and shape (its first kernel reads the staging buffer)
         hipGraphExec_t exec = nullptr;
-        HIPCHK(cached_graph(GraphKey{d_ws, pin, n, (uint32_t)q.cost_model, general,
-                                     mpdp::many_edges(n, q.m), walk}, enqueue, exec));
+        HIPCHK(cached_graph(GraphKey{d_ws, pin, n, (uint32_t)q.cost_model, general, lazy, walk}, enqueue, exec));
         HIPCHK(hipGraphLaunch(exec, s));
     } else {
         HIPCHK(enqueue(s));

@@ -231,9 +231,11 @@ hipError_t launch_tree_span(const DevGraph *src, DevGraph *g, int cost_model, bo
 inline bool many_edges(uint32_t n, uint32_t m) { return m + 4 >= 2 * n; }
 // One level of a cyclic query: the sets of k relations in `list`
 // (cnt->level_count[k] of them) evaluated, the sets of k + 1 into `next`.
-hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t m, uint32_t k, const uint32_t *list,
-                              uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
-                              unsigned long long *tally, hipStream_t s);
+// lazy (PG-like): levels of many sets read cards late, see lazy_level.
+bool lazy_query(uint32_t n, uint32_t m, const uint32_t *adj);
+hipError_t launch_level_pairs(const DevGraph *g, int cost_model, bool lazy, uint32_t n, uint32_t k,
+                              const uint32_t *list, uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec,
+                              uint32_t *arrived, unsigned long long *tally, hipStream_t s);
 // The same for dense queries of up to kWalkMaxRel relations, subset by subset,
 // after launch_no_plans (before launch_init).
 constexpr uint32_t kWalkMaxRel = 24;

@@ -31,7 +31,6 @@ constexpr uint32_t kShareMinK = 10;
 __device__ __forceinline__ bool lazy_level(uint32_t count, uint64_t subsets) {
     return count >= 65536u || (count >= 2048u && 4ull * count >= subsets);
 }
-bool lazy_query(uint32_t n, uint32_t m) { return n >= 23 || many_edges(n, m); }
 
 // One workgroup of 16 waves per CU (the waves' pools, the rank table and the
 // query fill 160 KB of LDS).  The next level's list first, which the
@@ -222,19 +221,30 @@ __global__ __launch_bounds__(kSpanBlock) void k_tree_span(const DevGraph *src, D
 
 }  // namespace
 
-hipError_t launch_level_pairs(const DevGraph *g, int cost_model, uint32_t n, uint32_t m, uint32_t k, const uint32_t *list,
-                              uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec, uint32_t *arrived,
-                              unsigned long long *tally, hipStream_t s) {
+// Which queries take the kernel that holds both forms of the search: it costs
+// 1 to 1.7 % where no level gains (cycle of 28 912 us / 923, of 28 with two chords
+// 1138 / 1158), as where up to three edges more than a tree's meet no relation of
+// five or more (star of 24 with one more edge 4152 / 3907).
+bool lazy_query(uint32_t n, uint32_t m, const uint32_t *adj) {
+    if (many_edges(n, m)) return true;
+    if (n < 23) return false;
+    const auto hub = [](uint32_t a) { return __builtin_popcount(a) > 4; };
+    return m >= n + 3 || std::any_of(adj, adj + n, hub);
+}
+
+hipError_t launch_level_pairs(const DevGraph *g, int cost_model, bool lazy, uint32_t n, uint32_t k,
+                              const uint32_t *list, uint32_t *next, Counters *cnt, MemoPtrs memo, HeavyPart *rec,
+                              uint32_t *arrived, unsigned long long *tally, hipStream_t s) {
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(kPairGrid), dim3(kPairBlock), 0, s, g, n, k, list, next, cnt, memo, rec,
                            arrived, tally);
     };
     if (cost_model == MPDP_COST_COUT)
         n > 24 ? go(k_level_pairs<MPDP_COST_COUT, true, false>) : go(k_level_pairs<MPDP_COST_COUT, false, false>);
-    else if (lazy_query(n, m))
+    else if (lazy)
         n > 24 ? go(k_level_pairs<MPDP_COST_PGLIKE, true, true>) : go(k_level_pairs<MPDP_COST_PGLIKE, false, true>);
     else
-        go(k_level_pairs<MPDP_COST_PGLIKE, false, false>);
+        n > 24 ? go(k_level_pairs<MPDP_COST_PGLIKE, true, false>) : go(k_level_pairs<MPDP_COST_PGLIKE, false, false>);
     return hipGetLastError();
 }
 
